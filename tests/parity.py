@@ -80,7 +80,10 @@ def compare_head(gpu: dict, b: int, h: int, ref: dict, Qb, Kb, Vb, *, p: float =
         k = int(rmask[0].sum()) if (p == 0.0 and forced is None) else None
         for n in diff_rows:
             d = np.nonzero(gmask[n] != rmask[n])[0]
-            kept_sorted = np.sort(logA[n][rmask[n] & ~(forced[n] if forced is not None else False)])
+            # (a boolean mask in either case: `~False` is the integer -1, and `& -1` would turn the mask into
+            # the indices 0 and 1)
+            unforced = rmask[n] if forced is None else rmask[n] & ~forced[n]
+            kept_sorted = np.sort(logA[n][unforced])
             tau = kept_sorted[0]
             assert np.all(np.abs(logA[n][d] - tau) <= MASK_BAND), \
                 f"mask differs outside the threshold band at row {n}: blocks {d}, dist {np.abs(logA[n][d] - tau)}"
