@@ -1,6 +1,6 @@
 // The small kernels that run before the persistent attention kernel (paper Alg. 1 step 21 for the pooled
 // compensation; the launch order and the schedule are this library's own): compensation_kernel,
-// row_order_kernel, schedule_kernel, and compensation_schedule_kernel = the first and the third in one launch.
+// row_rank_kernel, schedule_kernel, and compensation_schedule_kernel = the first and the third in one launch.
 #include "attn_sched.hpp"
 
 namespace rsa {
@@ -111,42 +111,41 @@ __global__ __launch_bounds__(256) void compensation_kernel(Dims dm, AttnArgs a) 
 }
 
 // Launch order of the video query blocks of one (batch, head): sorted by their first three
-// kept key blocks (ties: block index). Workgroups that are resident on an XCD at the same time
+// kept key blocks (ties: block index). Groups of waves that are resident on an XCD at the same time
 // then walk similar lists and find each other's K/V tiles in that XCD's L2 (on the benchmark
 // inputs the traffic that crosses the fabric drops by 40 %). A heuristic: any permutation gives
-// the same results. One workgroup per (batch, head), bitonic sort of 64-bit keys in LDS.
-__global__ __launch_bounds__(1024) void row_order_kernel(Dims dm, AttnArgs a) {
-  __shared__ uint64_t keys[RSA_MAX_BLOCKS];
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  int P = 1;
-  while (P < dm.n) P <<= 1;
-  for (int i = tid; i < P; i += 1024) {
-    uint64_t k = ~0ull;                                    // padding sorts to the end
-    if (i < dm.n) {
-      const size_t row = (size_t)bh * dm.n + i;
-      const int cnt = a.count[row];
-      const int32_t* lst = a.block_idx + row * dm.m;
-      const uint64_t i0 = cnt > 0 ? lst[0] : 4095, i1 = cnt > 1 ? lst[1] : 4095, i2 = cnt > 2 ? lst[2] : 4095;
-      k = (i0 << 36) | (i1 << 24) | (i2 << 12) | (uint64_t)i;     // every index < RSA_MAX_BLOCKS = 2^12
-    }
-    keys[i] = k;
+// the same results. The keys are distinct (the block index is part of them), so the place of a row is the
+// number of smaller keys: a workgroup gathers the keys of a head in LDS and counts for 64 of its rows, four
+// threads to a row. One workgroup per head sorting the keys took 21 us at 929 rows (24 heads) and 12 us at 159,
+// most of it barriers of a chip that stood still; counting takes 11 and 5 us, the gathering of the keys (a cache
+// line per row, in every workgroup) being most of it.
+constexpr int kRankRows = 64;
+__global__ __launch_bounds__(256) void row_rank_kernel(Dims dm, AttnArgs a) {
+  __shared__ uint64_t keys[RSA_MAX_BLOCKS + 32];
+  const int bh = blockIdx.y, tid = threadIdx.x;
+  const int padded = (dm.n + 31) & ~31;                     // the counting loop takes 32 keys at a time
+  const int e1 = min(1, dm.m - 1), e2 = min(2, dm.m - 1);
+#pragma unroll 4
+  for (int i = tid; i < padded; i += 256) {
+    const int r = min(i, dm.n - 1);
+    const size_t row = (size_t)bh * dm.n + r;
+    const int cnt = a.count[row];
+    const int32_t* lst = a.block_idx + row * dm.m;          // (all loads at once: what lies past the count is not used)
+    const int l0 = lst[0], l1 = lst[e1], l2 = lst[e2];
+    const uint64_t i0 = cnt > 0 ? (uint32_t)l0 & 4095 : 4095, i1 = cnt > 1 ? (uint32_t)l1 & 4095 : 4095, i2 = cnt > 2 ? (uint32_t)l2 & 4095 : 4095;
+    keys[i] = i < dm.n ? (i0 << 36) | (i1 << 24) | (i2 << 12) | (uint64_t)i : ~0ull;     // every index < RSA_MAX_BLOCKS = 2^12
   }
   __syncthreads();
-  for (int k2 = 2; k2 <= P; k2 <<= 1)
-    for (int j = k2 >> 1; j > 0; j >>= 1) {
-      for (int i = tid; i < P; i += 1024) {
-        const int o = i ^ j;
-        if (o > i) {
-          const uint64_t x = keys[i], y = keys[o];
-          if ((x > y) == ((i & k2) == 0)) {
-            keys[i] = y;
-            keys[o] = x;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  for (int i = tid; i < dm.n; i += 1024) a.row_order[(size_t)bh * dm.n + i] = (int32_t)(keys[i] & 4095u);
+  const int r = blockIdx.x * kRankRows + tid / 4;
+  const uint64_t mine = keys[min(r, dm.n - 1)];
+  int below = 0;
+  for (int i = tid % 4; i < padded; i += 32) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) below += keys[i + 4 * k] < mine ? 1 : 0;
+  }
+  below += __shfl_xor(below, 1);
+  below += __shfl_xor(below, 2);
+  if (r < dm.n && tid % 4 == 0) a.row_order[(size_t)bh * dm.n + below] = r;
 }
 
 // Deals the items of one launch to the slots of the persistent attention kernel. One workgroup per
@@ -269,7 +268,7 @@ hipError_t launch_attn_side_t(const Dims& dm, const AttnArgs& a, const DealArgs&
   const dim3 comp_grid((dm.n + 31) / 32, bh);
   const unsigned comp_lds = comp_lds_bytes<D>();
   const unsigned deal_lds = 2u * kDealSegment * 4u;
-  if (sort_rows) hipLaunchKernelGGL(row_order_kernel, dim3(bh), dim3(1024), 0, s, dm, a);
+  if (sort_rows) hipLaunchKernelGGL(row_rank_kernel, dim3((dm.n + kRankRows - 1) / kRankRows, bh), dim3(256), 0, s, dm, a);
   if (deal && compensate && da.n_queues <= (int)comp_grid.x) {
     hipLaunchKernelGGL((compensation_schedule_kernel<D, SPB>), dim3(comp_grid.x, bh + 1), dim3(256),
                        comp_lds > deal_lds ? comp_lds : deal_lds, s, dm, a, da);
