@@ -190,10 +190,13 @@ int rsa_adjacency_mask(const rsa_shape* shape, const int32_t* grid, const int32_
  * ws / ws_bytes: device scratch of at least attn_ws_bytes, 256-byte aligned (RSA_E_WORKSPACE
  * otherwise). It receives the pooled compensation term C_n (fp32 [b][h][N][d], Alg. 1 step 21),
  * an order of the video query blocks (rows with similar lists next to each other, so that they
- * share K/V tiles in the L2 of their XCD) and the schedule that deals the query blocks, in that
+ * share K/V tiles in the L2 of their XCD), the schedule that deals the query blocks, in that
  * order and balanced by the length of their lists, to the resident workgroups of the attention
- * kernel; the results do not depend on the order or the schedule. Required with RSA_COMPENSATE
- * (RSA_E_NULL); without that flag it may be NULL, and the query blocks are then dealt in index
+ * kernel, and fp32 buffers for the query blocks that the schedule cuts into pieces (where a few long rows
+ * or an uneven last round would leave part of the chip idle). A query block that is cut adds the same terms in
+ * another order, so that with and without a workspace the last bits may differ; for the same arguments and
+ * workspace size the results are always the same. Required with RSA_COMPENSATE
+ * (RSA_E_NULL); without that flag it may be NULL, and the query blocks are then dealt whole in index
  * order. With RSA_DENSE a workspace that is too small or misaligned is ignored (index order).
  * The caller owns it; its contents afterwards are unspecified.
  */
@@ -210,10 +213,11 @@ int rsa_sparse_attn_rectified(const rsa_shape* shape, const void* Q, const void*
  * order of the query blocks and their schedule) lives in a device array of RSA_STATIC_SCRATCH_BYTES (16 MiB) that is part of the
  * library image, one copy per GPU, held until the process ends. The call allocates and frees nothing.
  * Its first call on a device looks up that device's copy (hipGetSymbolAddress; RSA_E_LAUNCH if that
- * fails). Shapes whose attn_ws_bytes (rsa_workspace_bytes) exceed RSA_STATIC_SCRATCH_BYTES are
- * refused with RSA_E_WORKSPACE before anything is enqueued: 4 * batch * heads * N * (head_dim + 1)
- * bytes plus the schedule tables and padding, e.g. 11.7 MB for 24 heads of 118 800 + 256 tokens at
- * block 128, head_dim 128.
+ * fails). Shapes whose C_n and query block order, 4 * batch * heads * N * (head_dim + 1) bytes plus padding,
+ * exceed RSA_STATIC_SCRATCH_BYTES are refused with RSA_E_WORKSPACE before anything is enqueued. The schedule
+ * (together with the former 11.9 MB for 24 heads of 118 800 + 256 tokens at block 128, head_dim 128) and the
+ * buffers of query blocks that are cut take what is left, as far as they fit: where rsa_workspace_bytes asks for
+ * more than RSA_STATIC_SCRATCH_BYTES no query block is cut.
  * Every call on a GPU uses that GPU's one array and overwrites all of it that it reads (nothing has
  * to start at zero); two calls that overlap in time on one GPU (different streams) race on it.
  * With RSA_DENSE the scratch is not touched (the query blocks are dealt in index order).

@@ -26,7 +26,7 @@
 // A^pool[n][m] v^pool_m (computed beforehand by compensation_kernel into the workspace).
 //
 // 4*B*B*d flop per (query block, key block) pair against 2*B*d*2 bytes of K/V traffic.
-// The small kernels named here are in attn_side_kernels.hip. row_rank_kernel orders the video query blocks of a head by their first kept key blocks;
+// The small kernels named here are in attn_side_kernels.hip. row_order_kernel sorts the video query blocks of a head by their first kept key blocks;
 // schedule_kernel deals that order (long dense rows first) to the groups so that each XCD
 // (workgroup id modulo 8) owns a contiguous range of it, groups resident together walk similar
 // lists and share K/V tiles in the XCD's L2, and all groups end within one item of each other.
@@ -140,13 +140,16 @@ __device__ __forceinline__ void static_for(F&& f) {
 // Work of the persistent attention kernel. An item is one query block of one (batch, head); a slot
 // is one group of waves of one resident workgroup and works through a sequence of items.
 //   table != NULL: schedule_kernel dealt the items to the slots (balanced by their number of steps,
-//                  neighbouring rows of the launch order to neighbouring slots at the same time);
+//                  neighbouring rows of the launch order to neighbouring slots at the same time; an item may be
+//                  part of a row, whose result goes to a piece buffer for merge_kernel);
 //   table == NULL: item i goes to slot i % n_slots (no workspace: index order).
 struct SchedArgs {
-  const int32_t* table;     // [slots][cap] item records: (batch*heads index) * RSA_MAX_BLOCKS + query block
+  const int2* table;        // [slots][cap] entries (attn_sched.hpp)
   const int32_t* nitems;    // [slots]
-  const int32_t* total;     // [slots] steps of all items of the slot
-  int cap;
+  const int32_t* total;     // [slots] key blocks of all items of the slot
+  const int32_t* piece0;    // [slots] the slot's first piece buffer within its queue
+  float* pieces;
+  int cap, slots_per_queue, pieces_per_queue;
   int n_items, n_dense;     // all items; the dense ones (text query blocks, or every block under RSA_DENSE) come first
   int dense_per_bh, dense_first;
 };
@@ -168,13 +171,12 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   u32x4* lds = lds_all + grp * C::GROUP;
 
   // ---- the items of this group, and how many rounds the workgroup turns -------------------
-  // Slots are numbered so that the 64 slots of one schedule queue sit on one XCD (workgroup id
+  // Slots are numbered so that the slots of one schedule queue sit on one XCD (workgroup id
   // modulo 8) and the groups of a workgroup are neighbours in it.
   const int n_wg = gridDim.x, wg = blockIdx.x;
   auto slot_of_group = [&](int g) __attribute__((always_inline)) {
     if (!sc.table) return wg * NGRP + g;
-    const int u = (wg / 8) * NGRP + g;
-    return ((wg % 8) + 8 * (u / 64)) * 64 + u % 64;
+    return (wg % 8) * sc.slots_per_queue + (wg / 8) * NGRP + g;
   };
   const int n_slots = n_wg * NGRP;                   // (index-order dealing)
   auto record_of_item = [&](int i) __attribute__((always_inline)) {       // index order: dense items, then video rows
@@ -189,10 +191,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     }
     return bhx * RSA_MAX_BLOCKS + qbx;
   };
-  auto steps_of_record = [&](int rec) __attribute__((always_inline)) {
+  auto blocks_of_record = [&](int rec) __attribute__((always_inline)) {
     const int bhx = rec / RSA_MAX_BLOCKS, qbx = rec % RSA_MAX_BLOCKS;
     const bool sp = !dense_all && qbx < dm.n;
-    return (sp ? list_length(a, dm, (size_t)bhx * dm.n + qbx) : dm.m) * C::SPB;
+    return sp ? list_length(a, dm, (size_t)bhx * dm.n + qbx) : dm.m;
   };
   const int slot = slot_of_group(grp);
   int n_my_items, wg_rounds = 0;
@@ -201,56 +203,59 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 #pragma unroll
     for (int g = 0; g < NGRP; ++g) {
       const int t = sc.total[slot_of_group(g)];
-      wg_rounds = max(wg_rounds, t > 0 ? t + 1 : 0);
+      wg_rounds = max(wg_rounds, t > 0 ? t * C::SPB + 1 : 0);
     }
   } else {
     n_my_items = slot < sc.n_items ? (sc.n_items - slot + n_slots - 1) / n_slots : 0;
 #pragma unroll
     for (int g = 0; g < NGRP; ++g) {
       int t = 0;
-      for (int i = wg * NGRP + g; i < sc.n_items; i += n_slots) t += steps_of_record(record_of_item(i));
-      wg_rounds = max(wg_rounds, t > 0 ? t + 1 : 0);
+      for (int i = wg * NGRP + g; i < sc.n_items; i += n_slots) t += blocks_of_record(record_of_item(i));
+      wg_rounds = max(wg_rounds, t > 0 ? t * C::SPB + 1 : 0);
     }
   }
   if (wg_rounds == 0) return;                        // the whole workgroup: nothing was dealt to it
-  auto my_record = [&](int k) __attribute__((always_inline)) {
-    typedef const int32_t __attribute__((address_space(4))) * const_i32_t;   // scalar loads
-    return sc.table ? ((const_i32_t)(uintptr_t)sc.table)[(size_t)slot * sc.cap + k] : record_of_item(slot + k * n_slots);
+  // k-th entry of this group: record and span. Scalar loads (one with a table), so that it can be asked for well ahead of make_item.
+  struct Entry { int rec, span; };
+  auto my_entry = [&](int k) __attribute__((always_inline)) {
+    typedef const int32_t __attribute__((address_space(4))) * const_i32_t;
+    Entry e;
+    if (sc.table) {
+      const const_i32_t p = (const_i32_t)(uintptr_t)sc.table + ((size_t)slot * sc.cap + k) * 2;
+      e.rec = p[0];
+      e.span = p[1];
+    } else {
+      e.rec = record_of_item(slot + k * n_slots);
+      e.span = make_span(0, blocks_of_record(e.rec), false);
+    }
+    return e;
   };
 
   // What the phases need to know of an item: all wave-uniform.
   typedef const int32_t __attribute__((address_space(4))) * const_list_t;
   struct Item {
     int bh, qb;
-    int ns;                 // steps: SPB per entry of its list (all M key blocks for a dense row)
-    int nlist;
+    int ns;                 // steps: SPB per entry of its span
+    int span;               // its span of the list (a dense row: of the M key blocks)
     int has_list;
-    const_list_t list;      // its list of key blocks; a dense row: any readable address
+    const_list_t list;      // the entries of its span; a dense row: any readable address
     uint64_t Kbytes, Vtbytes;   // K rows and V^T tiles of its (batch, head)
     int64_t qo_off;         // element offset of its first query row in Q and in O
     int q_t0, q_count;      // its first token and how many it has
   };
-  // An item from its record and the raw count of its list (raw_count: one scalar load, nothing else, so
-  // that the load can be requested well ahead of make_item).
-  auto raw_count = [&](int rec) __attribute__((always_inline)) {
-    typedef const int32_t __attribute__((address_space(4))) * const_i32_t;
-    const int bh = rec / RSA_MAX_BLOCKS, qb = rec % RSA_MAX_BLOCKS;
-    const bool sp = !dense_all && qb < dm.n;
-    return sp ? ((const_i32_t)(uintptr_t)a.count)[(size_t)bh * dm.n + qb] : dm.m;
-  };
-  auto make_item = [&](int rec, int cnt) __attribute__((always_inline)) {
+  auto make_item = [&](const Entry& en) __attribute__((always_inline)) {
     Item it;
-    it.bh = rec / RSA_MAX_BLOCKS;
-    it.qb = rec % RSA_MAX_BLOCKS;
+    it.bh = en.rec / RSA_MAX_BLOCKS;
+    it.qb = en.rec % RSA_MAX_BLOCKS;
     const bool sp = !dense_all && it.qb < dm.n;
     const size_t vrow = (size_t)it.bh * dm.n + it.qb;
-    it.nlist = min(max(cnt, 1), dm.m);        // as list_length() holds it
-    it.ns = it.nlist * C::SPB;
+    it.span = en.span;
+    it.ns = span_len(en.span) * C::SPB;
     it.has_list = sp ? 1 : 0;
     const int b = it.bh / dm.heads, h = it.bh % dm.heads;
     const int64_t base = (int64_t)b * dm.sb + (int64_t)h * dm.sh;
     // (with RSA_DENSE every list pointer may be NULL: a dense row reads the first word of Q instead)
-    it.list = (const_list_t)(uintptr_t)(sp ? (const void*)(a.block_idx + vrow * dm.m) : (const void*)a.Q);
+    it.list = (const_list_t)(uintptr_t)(sp ? (const void*)(a.block_idx + vrow * dm.m + span_first(en.span)) : (const void*)a.Q);
     it.Kbytes = (uint64_t)(uintptr_t)(a.K + base);
     it.Vtbytes = (uint64_t)(uintptr_t)(a.Vt + (size_t)it.bh * dm.m * D * BLK);
     const int64_t t0 = dm.block_start(it.qb);
@@ -259,10 +264,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     it.qo_off = base + t0 * dm.st;
     return it;
   };
-  auto load_item = [&](int k) __attribute__((always_inline)) {
-    const int rec = my_record(k);
-    return make_item(rec, raw_count(rec));
-  };
+  auto load_item = [&](int k) __attribute__((always_inline)) { return make_item(my_entry(k)); };
 
   // ---- direct-to-LDS loads ---------------------------------------------------------------
   // A load fills 1 KB of LDS = RK consecutive K rows (RV consecutive V^T rows). Load ii of
@@ -380,9 +382,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // ---- the item being computed, the one after it, and the one whose output is still to be written
   Item cur = {}, nxt = {};
   int nxt_valid = 0, k_next = 0;       // k_next: the first item not yet loaded
-  int rec_ahead = 0;                   // ... and its record, read an item ahead
+  Entry ahead = {};                    // ... and its entry, read an item ahead
   // what the epilogue needs of the item that has just ended
   int done_bh = 0, done_sparse = 0, done_q_t0 = 0, done_q_count = 0;
+  int done_piece = -1, next_piece = sc.table ? sc.piece0[slot] : 0;      // piece buffer it goes to (-1: to O), and the next one free
   int64_t done_qo_off = 0;
 
   // Q as the B operand of S^T = K Q^T, resident in registers; the next item's rows replace it right
@@ -435,7 +438,21 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 #pragma unroll
     for (int j = 0; j < CV; ++j) asm volatile("" : "+v"(done_comp[j]));
   };
-  auto write_output = [&]() __attribute__((always_inline)) {
+  // A piece of a row: the accumulators as they are (1 KB per store instruction), row sum and reference.
+  auto write_piece = [&]() __attribute__((always_inline)) {
+    const float lsum = half_wave_sum(lpart);
+    const int ln = lane_now();
+    float* p = sc.pieces + (size_t)((wg % 8) * sc.pieces_per_queue + done_piece) * (BLK * D + 2 * BLK);
+    floatx4* dst = reinterpret_cast<floatx4*>(p) + wave * (C::DT * 4 * 64) + ln;
+#pragma unroll
+    for (int i = 0; i < C::DT * 4; ++i)
+      dst[i * 64] = floatx4{oacc[i / 4][4 * (i % 4)], oacc[i / 4][4 * (i % 4) + 1], oacc[i / 4][4 * (i % 4) + 2], oacc[i / 4][4 * (i % 4) + 3]};
+    if (ln < 32) {
+      p[BLK * D + wave * 32 + ln] = lsum;
+      p[BLK * D + BLK + wave * 32 + ln] = mref;
+    }
+  };
+  auto write_rows = [&]() __attribute__((always_inline)) {
     const bool do_comp = done_sparse && (a.flags & RSA_COMPENSATE);
     const int q_count = done_q_count;
     const float lsum = half_wave_sum(lpart);
@@ -476,6 +493,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     }
     if (q < q_count && a.lse && hf == 0)
       a.lse[((size_t)done_bh * dm.t) + done_q_t0 + q] = (mref + log2f(lsum)) * 0.6931471805599453f;
+  };
+  auto write_output = [&]() __attribute__((always_inline)) {
+    if (done_piece >= 0) write_piece();
+    else write_rows();
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
@@ -632,7 +653,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // entry j of an item's list; a dense row: j itself
   auto list_entry = [&](const Item& it, int j) __attribute__((always_inline)) {
     const int e = it.list[it.has_list ? j : 0];
-    return it.has_list ? e : j;
+    return it.has_list ? e : span_first(it.span) + j;
   };
 
   int fj = 0;                 // entry of the current item's list that the next even step fetches
@@ -644,15 +665,14 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     __builtin_amdgcn_s_setprio(0);
     constexpr int VLOADS = SPLIT_LOADS ? C::VPW : 0;  // requests of this phase: the V^T rows of step s+1
     // The last step of an item: what the switch to the next item and the epilogue need from memory is
-    // requested here, a whole softmax ahead of its use -- R_n and C_n of this item, the list length of
-    // the item after the next (its record came in an item ago), the record of the one after that.
-    int cnt_ahead = 0, rec_new = 0;
+    // requested here, a whole softmax ahead of its use -- R_n and C_n of this item, the entry of the item
+    // after the one after the next.
+    Entry entry_new = {};
     bool more = false;
     if constexpr (last_of_item) {
       request_epilogue(cur);
       more = k_next < n_my_items;
-      if (more) cnt_ahead = raw_count(rec_ahead);
-      if (k_next + 1 < n_my_items) rec_new = my_record(k_next + 1);
+      if (k_next + 1 < n_my_items) entry_new = my_entry(k_next + 1);
     }
     // The list entry of step s+2 (an even step opens a key block) for M(s+1): requested ahead of the
     // softmax, which hides the scalar cache miss that every sixteenth entry (and the head of every list)
@@ -660,17 +680,18 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // is settled where M(s+1) opens the block.
     if constexpr (FETCH == 1) {
       m_nxt_e = cur.list[cur.has_list ? fj : 0];
-      m_nxt_j = cur.has_list ? -1 : fj;
+      m_nxt_j = cur.has_list ? -1 : span_first(cur.span) + fj;
       fj += 1;
     } else if constexpr (FETCH == 2) {
       // it may be the first entry of the next item; past the last item, the last entry again (a valid
       // block: the tile requested for a step that does not exist is never read)
-      const bool own = fj < cur.nlist, follow = !own && nxt_valid;
+      const int nlist = span_len(cur.span);
+      const bool own = fj < nlist, follow = !own && nxt_valid;
       const_list_t lp = follow ? nxt.list : cur.list;
       const int hl = follow ? nxt.has_list : cur.has_list;
-      const int j = own ? fj : (follow ? 0 : cur.nlist - 1);
+      const int j = own ? fj : (follow ? 0 : nlist - 1);
       m_nxt_e = lp[hl ? j : 0];
-      m_nxt_j = hl ? -1 : j;
+      m_nxt_j = hl ? -1 : span_first(follow ? nxt.span : cur.span) + j;
       fj += 1;
     }
     if constexpr (SPLIT_LOADS && !first_of_item) {
@@ -778,13 +799,14 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       done_q_t0 = cur.q_t0;
       done_q_count = cur.q_count;
       done_qo_off = cur.qo_off;
+      done_piece = (cur.span & kSpanPartial) ? next_piece++ : -1;
       have_output = 1;
       if (nxt_valid) {
         cur = nxt;
         fj = 1;                          // entry 0 was fetched two steps ago
         nxt_valid = more;
-        if (more) nxt = make_item(rec_ahead, cnt_ahead);
-        rec_ahead = rec_new;
+        if (more) nxt = make_item(ahead);
+        ahead = entry_new;
         k_next += 1;
       }
     }
@@ -810,7 +832,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     nxt_valid = n_my_items > 1;
     if (nxt_valid) nxt = load_item(1);
     k_next = 2;
-    if (n_my_items > 2) rec_ahead = my_record(2);
+    if (n_my_items > 2) ahead = my_entry(2);
     load_q(cur);
     // Q must have arrived before the first direct-to-LDS load is requested: the compiler
     // does not see those loads, and would otherwise place its own wait for Q -- a wait for
@@ -898,46 +920,84 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   if (grp < NGRP / 2) group_barrier();
 }
 
+// Where the schedule's parts lie in the room it is given (bytes from its start, all 256-byte aligned).
+struct SchedLayout {
+  size_t nitems, total, piece0, cross, info, table, schedule, pieces, bytes;
+};
+SchedLayout sched_layout(const Dims& dm, const SchedShape& sh) {
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t slots = (size_t)kQueues * sh.slots, pieces = (size_t)kQueues * sh.pieces_per_queue;
+  SchedLayout l;
+  size_t off = 0;
+  l.nitems = off;  off += up(slots * sizeof(int32_t));
+  l.total = off;   off += up(slots * sizeof(int32_t));
+  l.piece0 = off;  off += up(slots * sizeof(int32_t));
+  l.cross = off;   off += up(kQueues * kQueues * sizeof(int2));
+  l.info = off;    off += up(pieces * sizeof(int2));
+  l.table = off;   off += up(slots * sh.cap * sizeof(int2));
+  l.schedule = off;
+  l.pieces = off;  off += pieces * piece_floats(dm.d, dm.blk) * sizeof(float);
+  l.bytes = off;
+  return l;
+}
+
 template <int D, int BLK>
 hipError_t launch_attn_t(const Dims& dm, const AttnArgs& a, const AttnSched& ws, hipStream_t s) {
   using C = AttnCfg<D, BLK>;
   const bool dense_all = (a.flags & RSA_DENSE) != 0;
   const int n_wg = ws.n_wg;
   if (n_wg < 8 || n_wg % 8) return hipErrorInvalidValue;
-  const SchedShape sh = sched_shape(dm, a.flags, n_wg, C::NGRP);
+  SchedShape sh = sched_shape(dm, a.flags, n_wg, C::NGRP);
   SchedArgs sc = {};
   sc.n_items = sh.n_items;
-  sc.n_dense = sh.n_dense;
-  sc.dense_per_bh = sh.dense_per_bh > 0 ? sh.dense_per_bh : 1;
-  sc.dense_first = sh.dense_first;
+  sc.n_dense = dense_all ? sh.n_items : sh.n_dense;
+  sc.dense_per_bh = dense_all ? dm.m : (dm.mt > 0 ? dm.mt : 1);
+  sc.dense_first = dense_all ? 0 : dm.n;
   const bool compensate = !dense_all && (a.flags & RSA_COMPENSATE);
-  const bool deal = ws.table && sh.n_queues * 64 <= RSA_ATTN_SCHED_SLOTS && (size_t)sh.n_queues * 64 * sh.cap <= ws.table_entries;
+  SchedLayout l = sched_layout(dm, sh);
+  if (l.bytes > ws.room_bytes) {                   // no room for pieces: nothing is cut
+    sh.pieces_per_queue = sh.n_cross = 0;
+    l = sched_layout(dm, sh);
+  }
+  const bool deal = ws.room && l.bytes <= ws.room_bytes && sh.slots <= kMaxSlots;
   DealArgs da = {};
   if (deal) {
-    da.table = ws.table; da.nitems = ws.nitems; da.total = ws.total;
-    da.cap = sh.cap; da.n_queues = sh.n_queues; da.slots_per_xcd = sh.slots_per_xcd;
-    da.n_dense = sh.n_dense; da.dense_per_bh = sc.dense_per_bh; da.dense_first = sh.dense_first;
-    sc.table = ws.table; sc.nitems = ws.nitems; sc.total = ws.total; sc.cap = sh.cap;
+    char* room = (char*)ws.room;
+    da.table = (int2*)(room + l.table);
+    da.nitems = (int32_t*)(room + l.nitems);
+    da.total = (int32_t*)(room + l.total);
+    da.piece0 = (int32_t*)(room + l.piece0);
+    da.piece_info = (int2*)(room + l.info);
+    da.cross = (int2*)(room + l.cross);
+    da.pieces = (float*)(room + l.pieces);
+    da.cap = sh.cap; da.slots = sh.slots; da.groups = C::NGRP; da.pieces_per_queue = sh.pieces_per_queue;
+    da.rows_per_bh = sh.rows_per_bh; da.n_dense = sh.n_dense; da.dense_per_bh = sh.dense_per_bh > 0 ? sh.dense_per_bh : 1;
+    da.dense_first = sh.dense_first; da.n_cross = sh.n_cross; da.min_piece = sh.min_piece; da.switch_cost = sh.switch_cost;
+    sc.table = da.table; sc.nitems = da.nitems; sc.total = da.total; sc.piece0 = da.piece0; sc.pieces = da.pieces;
+    sc.cap = sh.cap; sc.slots_per_queue = sh.slots; sc.pieces_per_queue = sh.pieces_per_queue;
   }
-  const hipError_t side = launch_attn_side(dm, a, da, !dense_all && a.row_order, compensate, deal, C::SPB, s);
+  // With no more items than slots every row starts at once: no order helps, and the launch is saved.
+  AttnArgs aa = a;
+  if (sh.n_items <= kQueues * sh.slots) aa.row_order = nullptr;
+  const hipError_t side = launch_attn_side(dm, aa, da, !dense_all && aa.row_order && deal, compensate, deal, s);
   if (side != hipSuccess) return side;
-  hipLaunchKernelGGL((attn_kernel<D, BLK>), dim3((unsigned)n_wg), dim3(C::NTHR), 0, s, dm, a, sc);
-  return hipGetLastError();
+  hipLaunchKernelGGL((attn_kernel<D, BLK>), dim3((unsigned)n_wg), dim3(C::NTHR), 0, s, dm, aa, sc);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !deal || sh.pieces_per_queue == 0) return e;
+  return launch_attn_merge(dm, aa, da, s);
 }
 
 }  // namespace
 
-// Entries of the schedule table for RSA_ATTN_MAX_WGS resident workgroups, dense launch or not. (A GPU
-// with fewer CUs forms fewer, longer queues; should its table not fit, the items go out in index order.)
-size_t attn_sched_entries(const Dims& dm) {
-  const int ngrp = dm.blk == 128 ? 2 : 4;
-  size_t need = 0;
+// The larger of what a sparse and a dense launch on RSA_ATTN_MAX_WGS resident workgroups need. (A GPU
+// with fewer CUs has fewer, longer queues; should its table not fit, the items go out in index order.)
+void attn_sched_bytes(const Dims& dm, size_t* schedule, size_t* pieces) {
+  *schedule = *pieces = 0;
   for (int flags : {0, (int)RSA_DENSE}) {
-    const SchedShape sh = sched_shape(dm, flags, RSA_ATTN_MAX_WGS, ngrp);
-    const size_t e = (size_t)sh.n_queues * 64 * (size_t)sh.cap;
-    need = e > need ? e : need;
+    const SchedLayout l = sched_layout(dm, sched_shape(dm, flags, RSA_ATTN_MAX_WGS, dm.blk == 128 ? 2 : 4));
+    *schedule = l.schedule > *schedule ? l.schedule : *schedule;
+    *pieces = l.bytes - l.schedule > *pieces ? l.bytes - l.schedule : *pieces;
   }
-  return need;
 }
 
 hipError_t launch_attn(const Dims& dm, const AttnArgs& a, const AttnSched& ws, hipStream_t s) {

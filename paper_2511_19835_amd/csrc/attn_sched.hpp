@@ -1,5 +1,5 @@
-// What the attention launch and the small kernels that run before it share: the shape of the schedule
-// (host and device agree on it), the arguments of the dealing kernel, and the one launcher of those kernels.
+// What the attention launch and the small kernels around it share: the shape of the schedule
+// (host and device agree on it), the arguments of the dealing and merging kernels, and their launchers.
 #pragma once
 #include "rsa_common.hpp"
 
@@ -13,42 +13,85 @@ __device__ __forceinline__ int list_length(const AttnArgs& a, const Dims& dm, si
   return min(max(c, 1), dm.m);
 }
 
+// A schedule entry (two int32): the query block, (batch*heads index) * RSA_MAX_BLOCKS + block, and the
+// span of its key blocks that the slot walks: first entry | (entries - 1) << 12 | partial << 24. A whole
+// row is the span of all its entries; a partial one (a row that several slots share) leaves its
+// unnormalised result in a piece buffer, and merge_kernel puts the pieces of the row together.
+constexpr int kSpanPartial = 1 << 24;
+__host__ __device__ __forceinline__ int make_span(int first, int len, bool partial) {
+  return first | (len - 1) << 12 | (partial ? kSpanPartial : 0);
+}
+__host__ __device__ __forceinline__ int span_first(int span) { return span & 4095; }
+__host__ __device__ __forceinline__ int span_len(int span) { return ((span >> 12) & 4095) + 1; }
+
+// Floats of a piece buffer: the accumulators of BLK rows as the waves hold them ([wave][16-register
+// quarter][lane][4]), then the row sums, then the softmax references (binades).
+__host__ __device__ __forceinline__ size_t piece_floats(int d, int blk) { return (size_t)blk * d + 2 * (size_t)blk; }
+
+constexpr int kQueues = 8;                     // one queue of items per XCD
+constexpr int kMaxSlots = 128;                 // slots (resident groups of waves) of an XCD: 32 CUs, at most 4 groups each
+constexpr int kMaxCross = kQueues - 1;         // dense rows cut over all queues: what is left when they do not divide by 8
+constexpr int kTailDense = 128;                // dense rows of a queue that may be cut (more: dealt whole, ahead of the others)
+// Rows are cut only where an uneven last round would cost something: below this many rounds of items. (At 24 rounds
+// it still takes 1.4 % off the layer; at 44 the most it could take off is 1.1 % of the attention, for 70 MB of buffers.)
+constexpr int kSplitRounds = 32;
+
 struct DealArgs {
-  int32_t* table;           // [queues * 64][cap]
-  int32_t* nitems;          // [queues * 64]
-  int32_t* total;           // [queues * 64]
-  int cap, n_queues, slots_per_xcd;
-  int n_dense, dense_per_bh, dense_first;
+  int2* table;              // [queues][slots][cap] entries
+  int32_t* nitems;          // [queues][slots]
+  int32_t* total;           // [queues][slots] key blocks of all entries of the slot
+  int32_t* piece0;          // [queues][slots] first piece of the slot
+  int2* piece_info;         // [queues][pieces]: query block; pieces of its row if this is the first of them, else 0
+  int2* cross;              // [queues][8]: first and last piece of this queue's part of cross row j
+  float* pieces;            // [queues][pieces][piece_floats]
+  int cap, slots, groups;   // slots = slots per queue, groups = slots per workgroup
+  int pieces_per_queue;     // 0: no row is cut
+  int rows_per_bh;          // N, or M under RSA_DENSE (every row is then walked whole, no list)
+  int n_dense, dense_per_bh, dense_first;      // text query blocks (none under RSA_DENSE)
+  int n_cross;              // the last n_cross dense rows are cut over all queues
+  int min_piece, switch_cost;                  // shortest piece and what an item costs beside its key blocks, in key blocks
 };
 
-// Sizes of the schedule for `n_wg` resident workgroups of NGRP groups (host and launcher agree on them).
+// Sizes of the schedule for `n_wg` resident workgroups of NGRP groups.
 struct SchedShape {
-  int n_queues, slots_per_xcd, cap, chunk, n_items, n_dense, dense_per_bh, dense_first;
+  int slots, cap, n_items, n_dense, dense_per_bh, dense_first, rows_per_bh, n_cross, pieces_per_queue, min_piece, switch_cost;
 };
 inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   SchedShape s;
   const bool dense_all = (flags & RSA_DENSE) != 0;
   const int bh = dm.batch * dm.heads;
-  s.slots_per_xcd = (n_wg / 8) * ngrp;
-  s.n_queues = 8 * ((s.slots_per_xcd + 63) / 64);
-  s.dense_per_bh = dense_all ? dm.m : dm.mt;
-  s.dense_first = dense_all ? 0 : dm.n;
+  s.slots = (n_wg / 8) * ngrp;
+  s.rows_per_bh = dense_all ? dm.m : dm.n;
+  s.dense_per_bh = dense_all ? 0 : dm.mt;
+  s.dense_first = dm.n;
   s.n_dense = bh * s.dense_per_bh;
-  s.n_items = s.n_dense + (dense_all ? 0 : bh * dm.n);
-  s.chunk = (dm.n + s.n_queues - 1) / s.n_queues;
-  const long long longest = (s.n_dense + s.n_queues - 1) / s.n_queues + (dense_all ? 0LL : (long long)bh * s.chunk);
-  // room for twice the average share of a slot, so that a queue of very unequal items still balances;
-  // the last queue of an XCD may have fewer than 64 slots
-  const int fewest = s.slots_per_xcd % 64 ? s.slots_per_xcd % 64 : 64;
-  s.cap = (int)(2 * ((longest + fewest - 1) / fewest) + 8);
+  s.n_items = s.n_dense + bh * s.rows_per_bh;
+  // An item costs its key blocks and the switch from one query block to the next: about 15 000 cycles where
+  // a block of 128 keys takes 6 000 (two steps of both groups) and one of 64 keys 2 600. A piece also writes and
+  // reads its accumulators in fp32; below a few blocks it is not worth either.
+  s.switch_cost = dm.blk == 128 ? 3 : 6;
+  s.min_piece = 4;
+  const long long longest = (long long)bh * ((s.rows_per_bh + kQueues - 1) / kQueues) + (s.n_dense + kQueues - 1) / kQueues;
+  s.cap = (int)(2 * ((longest + s.slots - 1) / s.slots) + 8);      // room for twice the average share of a slot
+  s.pieces_per_queue = 0;
+  s.n_cross = 0;
+  if (s.n_items <= kSplitRounds * kQueues * s.slots) {
+    if (dm.m >= kQueues * s.min_piece && s.slots >= kQueues) s.n_cross = s.n_dense % kQueues;
+    // Every cut makes two pieces (S - 1 cuts), a cross part is a piece by itself; a row of M blocks cannot become more
+    // than M / min_piece, and short problems not even that many in all.
+    const long long blocks = dm.m < 2 * s.min_piece ? s.n_cross : (longest + s.n_cross) * (dm.m / s.min_piece);
+    const long long most = 2LL * s.slots + s.n_cross;
+    s.pieces_per_queue = (int)(blocks < most ? blocks : most);
+  }
   return s;
 }
 
-// Launches, on stream s and in this order, the sort of the launch order (when `sort_rows`: writes a.row_order), the
-// pooled compensation (when `compensate`) and the dealing of the schedule (when `deal`; da filled by the
-// caller) -- the last two as one launch when both are wanted and the grid allows it. d = head dimension,
-// spb = steps per key block of the attention kernel that will read the table.
+// Launches, on stream s and in this order, the ranking of the rows (when `sort_rows`: writes a.row_order) and, in
+// one launch where both are wanted, the pooled compensation (`compensate`) and the dealing of the schedule
+// (`deal`; da filled by the caller).
 hipError_t launch_attn_side(const Dims& dm, const AttnArgs& a, const DealArgs& da, bool sort_rows, bool compensate, bool deal,
-                            int spb, hipStream_t s);
+                            hipStream_t s);
+// Puts the pieces of the rows that were cut together (after the attention kernel).
+hipError_t launch_attn_merge(const Dims& dm, const AttnArgs& a, const DealArgs& da, hipStream_t s);
 
 }  // namespace rsa

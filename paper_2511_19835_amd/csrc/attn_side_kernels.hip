@@ -1,6 +1,7 @@
-// The small kernels that run before the persistent attention kernel (paper Alg. 1 step 21 for the pooled
-// compensation; the launch order and the schedule are this library's own): compensation_kernel,
-// row_rank_kernel, schedule_kernel, and compensation_schedule_kernel = the first and the third in one launch.
+// The small kernels around the persistent attention kernel (paper Alg. 1 step 21 for the pooled
+// compensation; the launch order and the schedule are this library's own): row_rank_kernel,
+// compensation_kernel, schedule_kernel, and compensation_schedule_kernel = the second and the third in one
+// launch, before it; merge_kernel behind it when rows were cut.
 #include "attn_sched.hpp"
 
 namespace rsa {
@@ -148,14 +149,6 @@ __global__ __launch_bounds__(256) void row_rank_kernel(Dims dm, AttnArgs a) {
   if (r < dm.n && tid % 4 == 0) a.row_order[(size_t)bh * dm.n + below] = r;
 }
 
-// Deals the items of one launch to the slots of the persistent attention kernel. One workgroup per
-// queue of 64 slots (the slots of a queue run on one XCD). The queue's items, in launch order: its
-// share of the dense items (text query blocks, or every block under RSA_DENSE: the long ones first),
-// then, head by head, its contiguous range of the row order of the video query blocks. They are
-// dealt in rounds by one wave, lane = slot: in a round every slot whose load (steps so far) is within
-// one item of the lightest takes the next item, in lane order -- neighbouring items go to neighbouring
-// slots at about the same time, so that workgroups resident together walk similar lists, and the
-// loads end within one item of each other whatever the lengths of the rows.
 // Minimum over the 64 lanes of a wave with data-parallel-primitive moves (row shifts inside the rows of
 // 16 lanes, then the two row broadcasts): lane 63 ends up with it. Lanes without a source take INT_MAX.
 __device__ __forceinline__ int wave_min_i32(int v) {
@@ -168,123 +161,544 @@ __device__ __forceinline__ int wave_min_i32(int v) {
   v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
   return __builtin_amdgcn_readlane(v, 63);
 }
+__device__ __forceinline__ int wave_sum_i32(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+__device__ __forceinline__ int wave_inclusive_scan_i32(int v, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(v, o);
+    if (lane >= o) v += up;
+  }
+  return v;
+}
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
 
-constexpr int kDealSegment = 2048;   // items of a queue staged in LDS at a time: two int32 each
-template <int SPB>
+// Deals the items of one launch to the slots of the persistent attention kernel (a slot = one group of
+// waves of one resident workgroup). One workgroup per queue; the slots of a queue run on one XCD. The
+// queue's items: of every head a contiguous eighth of its row order (which eighth turns with the head, so that
+// the queues come out even when the rows do not divide by 8), and its share of the text query blocks.
+//
+// The rows go out in rounds by one wave, a lane per slot (SPL slots per lane): in a round every slot whose load
+// (key blocks so far) is within one item of the lightest takes the next item, in slot order -- neighbouring
+// items go to neighbouring slots at about the same time, so that groups resident together walk similar lists.
+//
+// What is left at the end -- fewer rows than slots when all lists are equally long, up to twice as many
+// otherwise -- and the long text rows are cut: laid end to end and divided over the slots so that every
+// slot ends at the same key block, give or take min_piece. A row that is cut is put together by merge_kernel. Cut points
+// closer than min_piece to the end of a row move there. Without that, an uneven last round
+// leaves slots idle (159 blocks of 24 heads on 512 slots: 7.45 rounds took 8; the dense layer of that shape
+// 4.25 -> 4.08 ms) and a text row, which walks all M blocks, can be longer than the whole share of a slot
+// (3 heads of 931 blocks, 6 text rows: a slot's share is 522 blocks; attention 2.79 -> 1.95 ms). In the smallest
+// calls every row is its own round (2 heads of 17 blocks: 23.6 -> 11 us and 4 us of merging). Cuts need piece buffers;
+// without them (pieces_per_queue 0: enough rounds that it does not matter, or no room) the long rows go first and the
+// last rows one at a time to the lightest slot.
+// The dealing itself takes 8-12 us up to 4000 items and 18-32 us at 22 000 to 28 000, beside the compensation that
+// shares the launch (the last 128 rows one at a time took 38 us at 3816 items).
+// One queue for all slots of an XCD: with block 64 an XCD has 128 slots, and two queues of 64 on distant ranges of
+// the row order shared less of its L2 (24 heads of 1182 blocks: attention 9.80 -> 9.03 ms).
+constexpr int kDealSegment = 2048;   // rows of a queue staged in LDS at a time
+constexpr int kTailMax = 512;        // at most kTailDense + kMaxCross + 2 kMaxSlots - 1 entries are cut
+static_assert(kTailDense + kMaxCross + 2 * kMaxSlots <= kTailMax && 2 * kMaxSlots <= kDealSegment, "the tail fits its arrays and one segment");
+constexpr int kDealLdsInts = 2 * kDealSegment + 3 * kTailMax + 1 + 2 * kMaxSlots + 2 * kQueues + 4;
+
+template <int SPL>
 __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, const DealArgs& da, int q, uint32_t* lds) {
   constexpr int SEG = kDealSegment;
-  constexpr int kStrictTail = 128;
   int32_t* rec = reinterpret_cast<int32_t*>(lds);
   int32_t* len = rec + SEG;
+  int32_t* t_rec = len + SEG;                     // the tail: row, first entry | (1 + cross row) << 16, start on the line
+  int32_t* t_fc = t_rec + kTailMax;
+  int32_t* t_pos = t_fc + kTailMax;
+  int32_t* s_load = t_pos + kTailMax + 1;         // by slot
+  int32_t* s_cnt = s_load + kMaxSlots;
+  int32_t* s_cross = s_cnt + kMaxSlots;           // [8][2]: first and last piece of this queue's part of a cross row
+  int32_t* t_cut = rec;                           // (the tail no longer needs the staged rows) pieces of an entry
+  int32_t* s_left = s_cross + 2 * kQueues;        // rows of the last segment still to be dealt: from, to; equal; number of tail entries
   const int tid = threadIdx.x, lane = tid % 64;
   const bool dense_all = (a.flags & RSA_DENSE) != 0;
-  const int bh_total = dm.batch * dm.heads;
-  // items of this queue: dense items d = q, q + n_queues, ...; then for every head the positions
-  // [q N / n_queues, (q + 1) N / n_queues) of its row order
-  const int my_dense = q < da.n_dense ? (da.n_dense - q + da.n_queues - 1) / da.n_queues : 0;
-  const int p0 = (int)((long long)q * dm.n / da.n_queues), p1 = (int)((long long)(q + 1) * dm.n / da.n_queues);
-  const int per_head = dense_all ? 0 : p1 - p0;
-  const int n_queue_items = my_dense + per_head * bh_total;
-  // lane = slot u of this queue; the XCD has slots_per_xcd of them in all
-  const bool slot_ok = (q / 8) * 64 + lane < da.slots_per_xcd;
-  const int slot = q * 64 + lane;
-  int load = 0, cnt = 0;
-  for (int seg0 = 0; seg0 < n_queue_items; seg0 += SEG) {
-    const int seg_n = min(SEG, n_queue_items - seg0);
+  const int bh_total = dm.batch * dm.heads, NR = da.rows_per_bh, S = da.slots;
+  const bool split = da.pieces_per_queue > 0;
+  const int n_whole = da.n_dense - da.n_cross;
+  const int my_dense = q < n_whole ? (n_whole - q + kQueues - 1) / kQueues : 0;
+  const int lead = (split && my_dense <= kTailDense) ? 0 : my_dense;         // text rows dealt whole, ahead of the others
+  const int tail_dense = my_dense - lead;
+  auto range_start = [&](int r) __attribute__((always_inline)) { return (int)((long long)r * NR / kQueues); };
+  int n_rows = (bh_total / kQueues) * NR;
+  for (int i = 0; i < bh_total % kQueues; ++i) {
+    const int r = (q + i) % kQueues;
+    n_rows += range_start(r + 1) - range_start(r);
+  }
+  const int n_bulk = lead + n_rows;
+  auto dense_record = [&](int d) __attribute__((always_inline)) {
+    return (d / da.dense_per_bh) * RSA_MAX_BLOCKS + da.dense_first + d % da.dense_per_bh;
+  };
+  auto row_record = [&](int v) __attribute__((always_inline)) {          // v-th row of this queue
+    const int h8 = v / NR;
+    int rem = v % NR, head = 0, pos = 0;
+    for (int i = 0; i < kQueues; ++i) {
+      const int r = (q + i) % kQueues, r0 = range_start(r), sz = range_start(r + 1) - r0;
+      if (rem < sz) {
+        head = h8 * kQueues + i;
+        pos = r0 + rem;
+        break;
+      }
+      rem -= sz;
+    }
+    const int qb = (!dense_all && a.row_order) ? a.row_order[(size_t)head * dm.n + pos] : pos;
+    return head * RSA_MAX_BLOCKS + qb;
+  };
+
+  int load[SPL], cnt[SPL];
+  bool ok[SPL];
+#pragma unroll
+  for (int j = 0; j < SPL; ++j) {
+    load[j] = cnt[j] = 0;
+    ok[j] = lane + 64 * j < S;
+  }
+  auto put = [&](int u, int at, int record, int span) __attribute__((always_inline)) {
+    da.table[((size_t)q * S + u) * da.cap + at] = make_int2(record, span);
+  };
+  // one round over rows next .. limit-1 of the staged segment; the lightest slots only when `strict`
+  auto deal_round = [&](int next, int limit, bool strict) __attribute__((always_inline)) {
+    int l = 0x7fffffff;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) l = min(l, ok[j] && cnt[j] < da.cap - 1 ? load[j] : 0x7fffffff);
+    const int lightest = wave_min_i32(l);
+    const int reach = strict ? lightest + 1 : lightest + len[next];
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      const bool take = ok[j] && cnt[j] < da.cap - 1 && load[j] < reach;
+      const unsigned long long takers = __ballot(take);
+      const int mine = next + lanes_below(takers);
+      if (take && mine < limit) {
+        put(lane + 64 * j, cnt[j], rec[mine], make_span(0, len[mine], false));
+        load[j] += len[mine];
+        cnt[j] += 1;
+      }
+      any = any || takers != 0;
+      next = min(limit, next + __popcll(takers));
+    }
+    return any ? next : limit;         // (the table has room for all rows, so some slot always takes)
+  };
+  // Segments of SEG rows, the odd one first, so that the tail lies in the last one.
+  int seg0 = 0;
+  do {
+    const int left = n_bulk - seg0;
+    const int seg_n = left <= 0 ? 0 : (left - 1) % SEG + 1;
+    const bool last = seg0 + seg_n >= n_bulk;
     __syncthreads();
     for (int i = tid; i < seg_n; i += 256) {
       const int it = seg0 + i;
-      int bhx, qbx;
-      if (it < my_dense) {
-        const int d = q + it * da.n_queues;
-        bhx = d / da.dense_per_bh;
-        qbx = da.dense_first + d % da.dense_per_bh;
-      } else {
-        const int v = it - my_dense;
-        bhx = v / per_head;
-        const int pos = p0 + v % per_head;
-        qbx = a.row_order ? a.row_order[(size_t)bhx * dm.n + pos] : pos;
-      }
-      const bool sp = !dense_all && qbx < dm.n;
-      rec[i] = bhx * RSA_MAX_BLOCKS + qbx;
-      len[i] = (sp ? list_length(a, dm, (size_t)bhx * dm.n + qbx) : dm.m) * SPB;
+      const int r = it < lead ? dense_record(q + it * kQueues) : row_record(it - lead);
+      const int qb = r % RSA_MAX_BLOCKS;
+      rec[i] = r;
+      len[i] = !dense_all && qb < dm.n ? list_length(a, dm, (size_t)(r / RSA_MAX_BLOCKS) * dm.n + qb) : dm.m;
     }
     __syncthreads();
     if (tid < 64) {
       int next = 0;
-      while (next < seg_n) {
-        const bool can = slot_ok && cnt < da.cap;
-        const int lightest = wave_min_i32(can ? load : 0x7fffffff);
-        bool take = can && load < lightest + len[next];
-        if (n_queue_items - (seg0 + next) <= kStrictTail) {
-          // the last items go one at a time to the lightest slot, so that the loads end within one item
-          const unsigned long long lightest_ones = __ballot(can && load == lightest);
-          take = lightest_ones != 0 && lane == __builtin_ctzll(lightest_ones);
+      const int bulk_end = seg_n - 2 * S;          // (of the last segment)
+      while (next < seg_n && (!last || next <= bulk_end)) next = deal_round(next, seg_n, false);
+      if (last && !split) {
+        while (next < seg_n) next = deal_round(next, seg_n, true);
+      } else if (last) {
+        int lo = 0x7fffffff, hi = 0x7fffffff, flo = 0x7fffffff, fhi = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < SPL; ++j)
+          if (ok[j]) {
+            flo = min(flo, load[j]);
+            fhi = min(fhi, -load[j]);
+          }
+        for (int i = next + lane; i < seg_n; i += 64) {
+          lo = min(lo, len[i]);
+          hi = min(hi, -len[i]);
         }
-        const unsigned long long takers = __ballot(take);
-        const int mine = next + __builtin_amdgcn_mbcnt_hi((uint32_t)(takers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)takers, 0));
-        if (take && mine < seg_n) {
-          da.table[(size_t)slot * da.cap + cnt] = rec[mine];
-          load += len[mine];
-          cnt += 1;
+        const bool equal = wave_min_i32(flo) == -wave_min_i32(fhi) && (next >= seg_n || wave_min_i32(lo) == -wave_min_i32(hi));
+        if (equal)
+          while (seg_n - next >= S) next = deal_round(next, seg_n, false);
+        if (lane == 0) {
+          s_left[0] = next;
+          s_left[1] = seg_n;
+          s_left[2] = equal ? 1 : 0;
+          s_left[3] = tail_dense + da.n_cross + seg_n - next;
         }
-        if (takers == 0) break;            // cannot happen while the table has room (the lightest slot always takes)
-        next += __popcll(takers);
+      }
+    }
+    seg0 += seg_n;
+  } while (seg0 < n_bulk);
+
+  if (!split) {
+    if (tid < 64) {
+#pragma unroll
+      for (int j = 0; j < SPL; ++j)
+        if (ok[j]) {
+          const int slot = q * S + lane + 64 * j;
+          da.nitems[slot] = cnt[j];
+          da.total[slot] = load[j];
+          da.piece0[slot] = 0;
+        }
+    }
+    return;
+  }
+
+  // ---- the tail: text rows, this queue's parts of the cross rows, the rows left ----------------------
+  if (tid < 64) {
+#pragma unroll
+    for (int j = 0; j < SPL; ++j)
+      if (ok[j]) {
+        s_load[lane + 64 * j] = load[j];
+        s_cnt[lane + 64 * j] = cnt[j];
+      }
+    if (lane < 2 * kQueues) s_cross[lane] = lane % 2 ? -1 : 0;      // (no pieces: first 0, last -1)
+  }
+  __syncthreads();
+  const int left0 = s_left[0], TN = s_left[3];
+  const bool equal = s_left[2] != 0;
+  for (int i = tid; i < TN; i += 256) {
+    int r, first = 0, l, cross = 0;
+    if (i < tail_dense) {
+      r = dense_record(q + i * kQueues);
+      l = dm.m;
+    } else if (i < tail_dense + da.n_cross) {
+      const int j = i - tail_dense;
+      r = dense_record(n_whole + j);
+      first = (int)((long long)q * dm.m / kQueues);
+      l = (int)((long long)(q + 1) * dm.m / kQueues) - first;
+      cross = j + 1;
+    } else {
+      const int k = left0 + i - tail_dense - da.n_cross;
+      r = rec[k];
+      l = len[k];
+    }
+    t_rec[i] = r;
+    t_fc[i] = first | cross << 16;
+    t_pos[i] = l;
+  }
+  __syncthreads();
+  for (int i = tid; i < TN; i += 256) t_cut[i] = 0;
+  __syncthreads();
+  if (tid >= 64) return;                           // one wave from here on
+  int line = 0;                                    // the tail laid end to end: entry i from t_pos[i] to t_pos[i + 1]
+  const int len0 = TN > 0 ? t_pos[TN - 1] : 0;     // (the length of a row, when all are equal)
+  for (int c = 0; c < TN; c += 64) {
+    const int v = c + lane < TN ? t_pos[c + lane] : 0;
+    const int incl = wave_inclusive_scan_i32(v, lane);
+    asm volatile("" ::: "memory");
+    if (c + lane < TN) t_pos[c + lane] = line + incl - v;
+    line += __shfl(incl, 63);
+  }
+  if (lane == 0) t_pos[TN] = line;
+  asm volatile("" ::: "memory");
+  // Slots in the order in which they take the line: one group of every workgroup first, so that a short line
+  // spreads over the CUs.
+  const int W = S / da.groups;
+  int u[SPL], base[SPL];
+#pragma unroll
+  for (int j = 0; j < SPL; ++j) {
+    const int sp = lane + 64 * j;
+    u[j] = ok[j] ? (sp % W) * da.groups + sp / W : 0;
+    base[j] = ok[j] ? s_load[u[j]] : 0x3fffffff;
+    cnt[j] = ok[j] ? s_cnt[u[j]] : 0;
+  }
+  // The level at which the line is used up: slots above it take nothing, and leaving them out of the average
+  // lowers it, so a few steps from the average over all slots reach it from above.
+  int level = 0x3ffffffe;
+  for (int step = 0; step < 4; ++step) {
+    int sum = 0, act = 0;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j)
+      if (base[j] < level) {
+        sum += base[j];
+        act += 1;
+      }
+    sum = wave_sum_i32(sum);
+    act = wave_sum_i32(act);
+    if (act == 0) break;                           // (nothing left, all loads equal)
+    level = (sum + line + act - 1) / act;
+  }
+  int lo = 0x7fffffff;
+#pragma unroll
+  for (int j = 0; j < SPL; ++j) lo = min(lo, base[j]);
+  lo = wave_min_i32(lo);
+  level = max(level, lo + da.min_piece);
+  // equal rows with nothing long among them: cutting them saves (S - rows) / S of a row and costs a switch
+  if (equal && tail_dense + da.n_cross == 0 && (long long)S * len0 - line < (long long)S * da.switch_cost) level = lo + len0;
+  int from[SPL], to[SPL];
+  {
+    int at = 0;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      const int room = max(0, level - base[j]);                  // (slots that do not exist: none)
+      const int incl = wave_inclusive_scan_i32(room, lane);
+      from[j] = at + incl - room;
+      to[j] = at + incl;
+      at += __shfl(incl, 63);
+    }
+  }
+  auto entry_at = [&](int x) __attribute__((always_inline)) {     // the entry that x lies in (x < line)
+    int l = 0, h = TN - 1;
+    while (l < h) {
+      const int mid = (l + h + 1) / 2;
+      if (t_pos[mid] <= x) l = mid;
+      else h = mid - 1;
+    }
+    return l;
+  };
+  auto cut_at = [&](int x) __attribute__((always_inline)) {
+    if (x >= line) return line;
+    const int i = entry_at(x);
+    const int p = t_pos[i], e = t_pos[i + 1], h = min(da.min_piece, (e - p + 1) / 2);
+    return x - p < h ? p : (e - x < h ? e : x);
+  };
+  int n_new[SPL], n_part[SPL], id0[SPL], pieces = 0;
+  bool fits = true;
+#pragma unroll
+  for (int j = 0; j < SPL; ++j) {
+    n_new[j] = n_part[j] = 0;
+    if (ok[j]) {
+      from[j] = cut_at(from[j]);
+      to[j] = cut_at(to[j]);
+      int pos = from[j];
+      for (int i = pos < to[j] ? entry_at(pos) : TN; i < TN && pos < to[j]; ++i) {
+        const int e = min(t_pos[i + 1], to[j]);
+        if (e <= pos) continue;
+        n_new[j] += 1;
+        n_part[j] += (pos != t_pos[i] || e != t_pos[i + 1] || (t_fc[i] >> 16)) ? 1 : 0;
+        atomicAdd(&t_cut[i], 1);                 // (LDS; a count, whatever the order)
+        pos = e;
+      }
+      fits = fits && cnt[j] + n_new[j] <= da.cap;
+    }
+    const int incl = wave_inclusive_scan_i32(n_part[j], lane);
+    id0[j] = pieces + incl - n_part[j];
+    pieces += __shfl(incl, 63);
+  }
+  fits = __ballot(!fits) == 0 && pieces <= da.pieces_per_queue;
+  int total[SPL];
+#pragma unroll
+  for (int j = 0; j < SPL; ++j) total[j] = ok[j] ? base[j] : 0;
+  int2* info = da.piece_info + (size_t)q * da.pieces_per_queue;
+  if (fits) {
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      if (!ok[j]) continue;
+      int pos = from[j], id = id0[j];
+      for (int i = pos < to[j] ? entry_at(pos) : TN; i < TN && pos < to[j]; ++i) {
+        const int p = t_pos[i], pe = t_pos[i + 1], e = min(pe, to[j]);
+        if (e <= pos) continue;
+        const int cross = t_fc[i] >> 16;
+        const bool partial = pos != p || e != pe || cross;
+        put(u[j], cnt[j], t_rec[i], make_span((t_fc[i] & 0xffff) + pos - p, e - pos, partial));
+        cnt[j] += 1;
+        total[j] += e - pos;
+        if (partial) {
+          info[id] = make_int2(t_rec[i], pos == p && !cross ? t_cut[i] : 0);
+          if (cross && pos == p) s_cross[2 * (cross - 1)] = id;
+          if (cross && e == pe) s_cross[2 * (cross - 1) + 1] = id;
+          id += 1;
+        }
+        pos = e;
+      }
+    }
+  } else {
+    // (the table has no room for the cuts: very unequal rows) whole entries, one at a time to the lightest slot
+    pieces = da.n_cross;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) id0[j] = j == 0 && lane < da.n_cross ? lane : 0;
+    for (int i = 0; i < TN; ++i) {
+      const int l = t_pos[i + 1] - t_pos[i], cross = t_fc[i] >> 16;
+      if (l <= 0) continue;
+      int best = 0x7fffffff;
+#pragma unroll
+      for (int j = 0; j < SPL; ++j) best = min(best, ok[j] && cnt[j] < da.cap - 1 ? total[j] : 0x7fffffff);
+      best = wave_min_i32(best);
+      bool given = false;
+#pragma unroll
+      for (int j = 0; j < SPL; ++j) {
+        // a cross part goes to the slot of its number: one piece per slot
+        const unsigned long long light = __ballot(ok[j] && cnt[j] < da.cap - 1 && total[j] == best);
+        const bool mine = cross ? (j == 0 && lane == cross - 1) : (!given && light && lane == __builtin_ctzll(light));
+        given = given || light != 0;
+        if (mine) {
+          put(u[j], cnt[j], t_rec[i], make_span(t_fc[i] & 0xffff, l, cross != 0));
+          cnt[j] += 1;
+          total[j] += l;
+          if (cross) {
+            info[cross - 1] = make_int2(t_rec[i], 0);
+            s_cross[2 * (cross - 1)] = s_cross[2 * (cross - 1) + 1] = cross - 1;
+          }
+        }
       }
     }
   }
-  if (tid < 64) {
-    da.nitems[slot] = cnt;
-    da.total[slot] = load;
-  }
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int j = 0; j < SPL; ++j)
+    if (ok[j]) {
+      const int slot = q * S + u[j];
+      da.nitems[slot] = cnt[j];
+      da.total[slot] = total[j];
+      da.piece0[slot] = id0[j];
+    }
+  for (int i = pieces + lane; i < da.pieces_per_queue; i += 64) info[i] = make_int2(-1, 0);
+  if (lane < kQueues) da.cross[q * kQueues + lane] = make_int2(s_cross[2 * lane], s_cross[2 * lane + 1]);
 }
 
-template <int SPB>
+__device__ __forceinline__ void deal_queue_any(const Dims& dm, const AttnArgs& a, const DealArgs& da, int q, uint32_t* lds) {
+  if (da.slots <= 64) deal_queue<1>(dm, a, da, q, lds);
+  else deal_queue<2>(dm, a, da, q, lds);
+}
 __global__ __launch_bounds__(256) void schedule_kernel(Dims dm, AttnArgs a, DealArgs da) {
   extern __shared__ uint32_t side_lds[];
-  deal_queue<SPB>(dm, a, da, blockIdx.x, side_lds);
+  deal_queue_any(dm, a, da, blockIdx.x, side_lds);
 }
 
 // Both of the above in one launch (neither needs the other's result, and the few workgroups that deal
 // the queues would otherwise have the chip to themselves): plane 0 of the grid deals queue blockIdx.x,
 // plane 1 + bh compensates the rows of (batch, head) bh. The dealing workgroups are dispatched first.
-template <int D, int SPB>
+template <int D>
 __global__ __launch_bounds__(256) void compensation_schedule_kernel(Dims dm, AttnArgs a, DealArgs da) {
   extern __shared__ uint32_t side_lds[];
   if (blockIdx.y == 0) {
-    if ((int)blockIdx.x < da.n_queues) deal_queue<SPB>(dm, a, da, blockIdx.x, side_lds);   // uniform over the workgroup
+    if ((int)blockIdx.x < kQueues) deal_queue_any(dm, a, da, blockIdx.x, side_lds);   // uniform over the workgroup
     return;
   }
-  compensate_tile<D>(dm, a, blockIdx.x * 32, (int)blockIdx.y - 1, side_lds);
+  if ((int)blockIdx.x * 32 < dm.n) compensate_tile<D>(dm, a, blockIdx.x * 32, (int)blockIdx.y - 1, side_lds);
 }
 
-}  // namespace
+// The rows that were cut: O = R_n * (sum over pieces of 2^(m_p - m) acc_p) / (sum of 2^(m_p - m) l_p) + C_n with
+// m the largest reference of the pieces (text rows: neither R_n nor C_n), always in the order of the key blocks.
+// Latency is all there is to it (a few dozen megabytes at most, out of the L2 or the Infinity Cache): one
+// workgroup per piece buffer and 32 channels, of which those with the first piece of a row do its work (the
+// pieces of a row are consecutive) and one per cross row and 32 channels (a run of pieces in every queue); four
+// pieces are on their way at a time. A wave holds 32 query rows in the layout of the attention kernel's
+// accumulators, so that pieces are read as they were written, 1 KB per instruction.
+template <int D, int BLK>
+__global__ __launch_bounds__(64 * (BLK / 32)) void merge_kernel(Dims dm, AttnArgs a, DealArgs da) {
+  constexpr int NT = 64 * (BLK / 32);
+  __shared__ int32_t ids[kQueues * (2 * kMaxSlots + kMaxCross)];       // the row's piece buffers, in the order of its key blocks
+  const int P = da.pieces_per_queue, dt = blockIdx.y;
+  int n_run = 0;
+  if ((int)blockIdx.x < kQueues * P) {
+    n_run = da.piece_info[blockIdx.x].y;
+    if (n_run == 0) return;                        // not the first piece of a row
+    for (int i = threadIdx.x; i < n_run; i += NT) ids[i] = blockIdx.x + i;
+  } else {
+    const int j = (int)blockIdx.x - kQueues * P;
+    int2 run[kQueues];
+#pragma unroll
+    for (int r = 0; r < kQueues; ++r) run[r] = da.cross[r * kQueues + j];
+#pragma unroll
+    for (int r = 0; r < kQueues; ++r) {
+      const int n = run[r].y - run[r].x + 1;
+      for (int i = threadIdx.x; i < n; i += NT) ids[n_run + i] = r * P + run[r].x + i;
+      n_run += n;
+    }
+    if (n_run == 0) return;                        // (a cross row without pieces: cannot be)
+  }
+  __syncthreads();
+  const int rec = da.piece_info[ids[0]].x;
+  const int bh = rec / RSA_MAX_BLOCKS, qb = rec % RSA_MAX_BLOCKS;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, l32 = lane % 32, hf = lane / 32;
+  const int row = wave * 32 + l32;
+  const bool sparse = !(a.flags & RSA_DENSE) && qb < dm.n;
+  const size_t vrow = (size_t)bh * dm.n + qb;
+  const float rfac = (sparse && (a.flags & RSA_RECTIFY_CRITICAL)) ? a.R[vrow] : 1.0f;
+  floatx4 c[4], acc[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    acc[g] = c[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (sparse && (a.flags & RSA_COMPENSATE)) c[g] = *reinterpret_cast<const floatx4*>(a.comp + vrow * D + 32 * dt + 8 * g + 4 * hf);
+  }
+  float m = -INFINITY, l = 0.f;
+  for (int i = 0; i < n_run; i += 4) {
+    float mp[4], lp[4];
+    floatx4 v[4][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float* p = da.pieces + (size_t)ids[min(i + k, n_run - 1)] * piece_floats(D, BLK);
+      lp[k] = p[BLK * D + row];
+      mp[k] = i + k < n_run ? p[BLK * D + BLK + row] : -INFINITY;      // (a piece past the end: the last one, weight 0)
+      const floatx4* src = reinterpret_cast<const floatx4*>(p) + (size_t)((wave * (D / 32) + dt) * 4) * 64 + lane;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) v[k][g] = src[g * 64];
+    }
+    const float mnew = fmaxf(fmaxf(m, fmaxf(mp[0], mp[1])), fmaxf(mp[2], mp[3]));
+    const float old = __builtin_amdgcn_exp2f(m - mnew);
+    m = mnew;
+    l *= old;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[g][e] *= old;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float w = __builtin_amdgcn_exp2f(mp[k] - mnew);
+      l = fmaf(w, lp[k], l);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[g][e] = fmaf(w, v[k][g][e], acc[g][e]);
+    }
+  }
+  if (row >= dm.block_count(qb)) return;
+  const float f = rfac / l;
+  const int64_t t = dm.block_start(qb) + row;
+  uint16_t* orow = a.O + (int64_t)(bh / dm.heads) * dm.sb + (int64_t)(bh % dm.heads) * dm.sh + t * dm.st + 32 * dt + 4 * hf;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    float o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = fmaf(acc[g][e], f, c[g][e]);
+    uint2 w;
+    w.x = pack_bf16x2(o[0], o[1]);
+    w.y = pack_bf16x2(o[2], o[3]);
+    *reinterpret_cast<uint2*>(orow + 8 * g) = w;
+  }
+  if (a.lse && hf == 0 && dt == 0) a.lse[(size_t)bh * dm.t + t] = (m + log2f(l)) * 0.6931471805599453f;
+}
 
-namespace {
-template <int D, int SPB>
+template <int D>
 hipError_t launch_attn_side_t(const Dims& dm, const AttnArgs& a, const DealArgs& da, bool sort_rows, bool compensate, bool deal,
                               hipStream_t s) {
-  const int bh = dm.batch * dm.heads;
-  const dim3 comp_grid((dm.n + 31) / 32, bh);
-  const unsigned comp_lds = comp_lds_bytes<D>();
-  const unsigned deal_lds = 2u * kDealSegment * 4u;
+  const unsigned bh = (unsigned)(dm.batch * dm.heads), tiles = (unsigned)((dm.n + 31) / 32);
+  const unsigned comp_lds = comp_lds_bytes<D>(), deal_lds = kDealLdsInts * 4u;
   if (sort_rows) hipLaunchKernelGGL(row_rank_kernel, dim3((dm.n + kRankRows - 1) / kRankRows, bh), dim3(256), 0, s, dm, a);
-  if (deal && compensate && da.n_queues <= (int)comp_grid.x) {
-    hipLaunchKernelGGL((compensation_schedule_kernel<D, SPB>), dim3(comp_grid.x, bh + 1), dim3(256),
+  if (deal && compensate && bh < 65535u) {
+    hipLaunchKernelGGL((compensation_schedule_kernel<D>), dim3(tiles > (unsigned)kQueues ? tiles : (unsigned)kQueues, bh + 1), dim3(256),
                        comp_lds > deal_lds ? comp_lds : deal_lds, s, dm, a, da);
   } else {
-    if (compensate) hipLaunchKernelGGL((compensation_kernel<D>), comp_grid, dim3(256), comp_lds, s, dm, a);
-    if (deal) hipLaunchKernelGGL((schedule_kernel<SPB>), dim3(da.n_queues), dim3(256), deal_lds, s, dm, a, da);
+    if (compensate) hipLaunchKernelGGL((compensation_kernel<D>), dim3(tiles, bh), dim3(256), comp_lds, s, dm, a);
+    if (deal) hipLaunchKernelGGL(schedule_kernel, dim3(kQueues), dim3(256), deal_lds, s, dm, a, da);
   }
   return hipGetLastError();
 }
+
+template <int D, int BLK>
+hipError_t launch_attn_merge_t(const Dims& dm, const AttnArgs& a, const DealArgs& da, hipStream_t s) {
+  hipLaunchKernelGGL((merge_kernel<D, BLK>), dim3((unsigned)(kQueues * da.pieces_per_queue + da.n_cross), D / 32), dim3(64 * (BLK / 32)), 0, s, dm, a, da);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_attn_side(const Dims& dm, const AttnArgs& a, const DealArgs& da, bool sort_rows, bool compensate, bool deal,
-                            int spb, hipStream_t s) {
-  if (spb != 2) return hipErrorInvalidValue;      // every attention template takes two steps per key block
-  if (dm.d == 128) return launch_attn_side_t<128, 2>(dm, a, da, sort_rows, compensate, deal, s);
-  return launch_attn_side_t<64, 2>(dm, a, da, sort_rows, compensate, deal, s);
+                            hipStream_t s) {
+  if (dm.d == 128) return launch_attn_side_t<128>(dm, a, da, sort_rows, compensate, deal, s);
+  return launch_attn_side_t<64>(dm, a, da, sort_rows, compensate, deal, s);
+}
+
+hipError_t launch_attn_merge(const Dims& dm, const AttnArgs& a, const DealArgs& da, hipStream_t s) {
+  if (dm.d == 128 && dm.blk == 128) return launch_attn_merge_t<128, 128>(dm, a, da, s);
+  if (dm.d == 128 && dm.blk == 64) return launch_attn_merge_t<128, 64>(dm, a, da, s);
+  if (dm.d == 64 && dm.blk == 128) return launch_attn_merge_t<64, 128>(dm, a, da, s);
+  return launch_attn_merge_t<64, 64>(dm, a, da, s);
 }
 
 }  // namespace rsa

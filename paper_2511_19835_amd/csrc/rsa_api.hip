@@ -61,21 +61,18 @@ PoolWs pool_ws_layout(const Dims& d) {
 }
 
 // rsa_sparse_attn_rectified scratch: the pooled compensation term C_n, fp32 [b][h][N][d]; the launch
-// order of the video query blocks, int32 [b][h][N]; the schedule of the persistent kernel (item
-// table, items and steps per slot).
+// order of the video query blocks, int32 [b][h][N]; the schedule of the persistent kernel and the
+// buffers of the rows that it cuts.
 struct AttnWs {
-  size_t comp, order, table, nitems, total, bytes;
-  size_t table_entries;
+  size_t comp, order, sched, bytes;
 };
 AttnWs attn_ws_layout(const Dims& d) {
   AttnWs w;
-  size_t off = 0;
+  size_t off = 0, schedule = 0, pieces = 0;
   w.comp = off;   off += align256((size_t)d.batch * d.heads * d.n * d.d * sizeof(float));
   w.order = off;  off += align256((size_t)d.batch * d.heads * d.n * sizeof(int32_t));
-  w.table_entries = rsa::attn_sched_entries(d);
-  w.table = off;  off += align256(w.table_entries * sizeof(int32_t));
-  w.nitems = off; off += align256(RSA_ATTN_SCHED_SLOTS * sizeof(int32_t));
-  w.total = off;  off += align256(RSA_ATTN_SCHED_SLOTS * sizeof(int32_t));
+  rsa::attn_sched_bytes(d, &schedule, &pieces);
+  w.sched = off;  off += align256(schedule) + align256(pieces);
   w.bytes = off;
   return w;
 }
@@ -113,10 +110,11 @@ int check_attn_args(const Dims&, const void* Q, const void* K, const void* Vt, c
   return RSA_OK;
 }
 
-// `ws` (may be NULL without RSA_COMPENSATE): C_n, then the launch order of the video query blocks.
+// `ws` (may be NULL without RSA_COMPENSATE): C_n, the launch order of the video query blocks, then whatever
+// of the schedule and its piece buffers fits `ws_bytes`.
 int enqueue_attn(const Dims& d, const void* Q, const void* K, const void* Vt, const int32_t* block_idx,
                  const int32_t* count, const uint32_t* mask_bits, const float* R, const float* Apool,
-                 const uint32_t* Mc_bits, const float* Vp, int flags, void* O, float* lse, void* ws, void* stream) {
+                 const uint32_t* Mc_bits, const float* Vp, int flags, void* O, float* lse, void* ws, size_t ws_bytes, void* stream) {
   rsa::AttnArgs aa;
   aa.Q = (const uint16_t*)Q; aa.K = (const uint16_t*)K; aa.Vt = (const uint16_t*)Vt;
   aa.block_idx = block_idx; aa.count = count; aa.mask_bits = mask_bits; aa.Mc_bits = Mc_bits;
@@ -130,10 +128,8 @@ int enqueue_attn(const Dims& d, const void* Q, const void* K, const void* Vt, co
   aa.comp = ws ? (float*)(wsb + wl.comp) : nullptr;
   aa.row_order = (ws && !(flags & RSA_DENSE)) ? (int32_t*)(wsb + wl.order) : nullptr;
   if (ws) {
-    sch.table = (int32_t*)(wsb + wl.table);
-    sch.nitems = (int32_t*)(wsb + wl.nitems);
-    sch.total = (int32_t*)(wsb + wl.total);
-    sch.table_entries = wl.table_entries;
+    sch.room = wsb + wl.sched;
+    sch.room_bytes = ws_bytes > wl.sched ? ws_bytes - wl.sched : 0;
   }
   if (rsa::launch_attn(d, aa, sch, (hipStream_t)stream) != hipSuccess) return RSA_E_LAUNCH;
   return RSA_OK;
@@ -321,7 +317,7 @@ int rsa_sparse_attn_rectified(const rsa_shape* shape, const void* Q, const void*
   } else if (ws && (ws_bytes < attn_ws_size(d) || ((uintptr_t)ws & 255))) {
     ws = nullptr;            // a dense launch never needed a workspace: without a usable one it runs in index order
   }
-  return enqueue_attn(d, Q, K, Vt, block_idx, count, mask_bits, R, Apool, Mc_bits, Vp, flags, O, lse, ws, stream);
+  return enqueue_attn(d, Q, K, Vt, block_idx, count, mask_bits, R, Apool, Mc_bits, Vp, flags, O, lse, ws, ws_bytes, stream);
 }
 
 int rsa_sparse_attn_rectified_static(const rsa_shape* shape, const void* Q, const void* K, const void* Vt,
@@ -336,11 +332,13 @@ int rsa_sparse_attn_rectified_static(const rsa_shape* shape, const void* Q, cons
   if (rc != RSA_OK) return rc;
   void* ws = nullptr;
   if (!(flags & RSA_DENSE)) {
-    if (attn_ws_size(d) > (size_t)RSA_STATIC_SCRATCH_BYTES) return RSA_E_WORKSPACE;
+    // what has to fit is C_n and the launch order; the schedule is dealt, and rows are cut, as far as the rest allows
+    if (attn_ws_layout(d).sched > (size_t)RSA_STATIC_SCRATCH_BYTES) return RSA_E_WORKSPACE;
     ws = static_scratch_of_current_device();
     if (!ws) return RSA_E_LAUNCH;
   }
-  return enqueue_attn(d, Q, K, Vt, block_idx, count, mask_bits, R, Apool, Mc_bits, Vp, flags, O, lse, ws, stream);
+  return enqueue_attn(d, Q, K, Vt, block_idx, count, mask_bits, R, Apool, Mc_bits, Vp, flags, O, lse, ws,
+                      RSA_STATIC_SCRATCH_BYTES, stream);
 }
 
 const char* rsa_status_string(int status) {

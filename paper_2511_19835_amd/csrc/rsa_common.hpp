@@ -147,12 +147,13 @@ struct AttnArgs {
 #define RSA_ATTN_MAX_WGS 256
 struct AttnSched {
   int n_wg;                 // workgroups to launch: a multiple of 8, at most RSA_ATTN_MAX_WGS
-  int32_t* table;           // NULL: items are dealt in index order
-  int32_t *nitems, *total;  // [RSA_ATTN_SCHED_SLOTS] each
-  size_t table_entries;     // room in `table`
+  void* room;               // NULL: items are dealt in index order
+  size_t room_bytes;
 };
-#define RSA_ATTN_SCHED_SLOTS 4096
-size_t attn_sched_entries(const Dims& dm);   // table entries that rsa_workspace_bytes sets aside
+// Bytes of `room` for the schedule and for the buffers of rows that are cut (0 where none is), as
+// rsa_workspace_bytes sets them aside. With less, no row is cut; with less than the schedule itself, the items
+// are dealt in index order.
+void attn_sched_bytes(const Dims& dm, size_t* schedule, size_t* pieces);
 hipError_t launch_attn(const Dims& dm, const AttnArgs& a, const AttnSched& ws, hipStream_t s);
 
 }  // namespace rsa

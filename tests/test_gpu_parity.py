@@ -285,6 +285,49 @@ def _blockwise_constant_bits(rng, cfg, amp):
     return synth.f32_to_bf16_bits(X).reshape(1, 1, cfg.t_total, cfg.head_dim).copy()
 
 
+CUT = {
+    # text rows over all XCDs (their number does not divide by 8 and M >= 32) and ragged ends
+    "cross_rows": LayerConfig("cross_rows", 1, 3, 128, (9, 24, 40), 200, 128, 0.8),
+    "cross_rows_d64_b64": LayerConfig("cross_rows_d64_b64", 1, 5, 64, (5, 16, 30), 70, 64, 0.7),
+    # text rows whole or cut inside one XCD's queue, a batch, fewer rows than XCDs
+    "short_rows_d64": LayerConfig("short_rows_d64", 2, 2, 64, (10, 16, 20), 129, 128, 0.5),
+    "few_rows_b64": LayerConfig("few_rows_b64", 1, 1, 128, (2, 9, 11), 64 * 9 + 1, 64, 0.85),
+    # more rows than slots: full rounds, then an uneven last one
+    "uneven_rounds": LayerConfig("uneven_rounds", 1, 26, 64, (8, 16, 40), 0, 128, 0.6),
+}
+
+
+@pytest.mark.parametrize("unequal", [False, True])
+@pytest.mark.parametrize("name", sorted(CUT))
+def test_rows_cut_over_several_slots(gpu, name, unequal):
+    """With a workspace, rows are cut into pieces that several groups of waves walk and a merge kernel puts
+    together; without one every row is walked whole. Both attend to the same keys, so outputs may differ by
+    the order of fp32 sums only: at most 1e-5 relative before rounding, i.e. a last bf16 bit (2^-8 of the
+    value) in fewer than 1 of 200 elements, a relative L2 distance below 2^-8 / sqrt(200) = 2.8e-4. Head 0 is
+    also compared with the oracle, compensation and factor included."""
+    import parity
+    from oracle import rsa_oracle as ro
+    cfg = CUT[name]
+    Qb, Kb, Vb = synth.make_inputs(cfg, 41)
+    forced = None
+    if unequal:                                    # rows of very different length, some of them full
+        rng = np.random.default_rng(42)
+        density = rng.choice([0.0, 0.1, 0.5, 1.0], size=(cfg.batch, cfg.heads, cfg.n_video_blocks, 1))
+        forced = rng.random((cfg.batch, cfg.heads, cfg.n_video_blocks, cfg.n_blocks)) < density
+    kw = dict(gapr_mode=1, forced=forced)
+    args = (Qb, Kb, Vb, cfg.t_video, cfg.t_text, cfg.block, cfg.sparsity)
+    whole = gpu.run_layer(*args, flags=1, attn_workspace=False, **kw)
+    cut = gpu.run_layer(*args, flags=1, **kw)
+    a, b = (ro.bf16_bits_to_f64(x["O_bits"]) for x in (whole, cut))
+    assert np.isfinite(b).all()
+    assert np.linalg.norm(a - b) / np.linalg.norm(a) <= 2.8e-4
+    np.testing.assert_allclose(cut["lse"], whole["lse"], atol=2e-5, rtol=2e-6)
+    full = gpu.run_layer(*args, flags=3, **kw)
+    f0 = None if forced is None else forced[0, 0]
+    ref = parity.oracle_head(Qb[0, 0], Kb[0, 0], Vb[0, 0], *args[3:], gapr_mode=1, forced=f0)
+    parity.compare_head(full, 0, 0, ref, Qb[0, 0], Kb[0, 0], Vb[0, 0], forced=f0)
+
+
 @pytest.mark.parametrize("sparsity", [0.5, 0.9])
 @pytest.mark.parametrize("name", ["ragged_d64_b128", "d128_b64_text"])
 def test_identical_tokens_per_block_recover_dense_attention(gpu, name, sparsity):
