@@ -135,14 +135,14 @@ __global__ __launch_bounds__(256) void pool_v_kernel(Dims dm, PoolArgs a) {
 }
 
 // The same launch with the text log-masses on board: the first `text_wgs` workgroups of every
-// (batch, head) take eight pooled queries each against the text keys (vector-ALU work, no traffic to
+// (batch, head) take 32 pooled queries each against 128 text keys (fp32 matrix work, no traffic to
 // speak of), the others pool a block of V (HBM-bound) -- the one hides under the other.
 template <int D, int BLK>
 __global__ __launch_bounds__(256) void pool_v_text_kernel(Dims dm, PoolArgs a, ScoreArgs sa, int text_wgs) {
-  constexpr int WORDS = PoolVLds<D, BLK>::WORDS > text_mass_lds_floats<D>() ? PoolVLds<D, BLK>::WORDS : text_mass_lds_floats<D>();
+  constexpr int WORDS = PoolVLds<D, BLK>::WORDS > kTextMassLdsFloats ? PoolVLds<D, BLK>::WORDS : kTextMassLdsFloats;
   __shared__ uint32_t lds[WORDS];
   if ((int)blockIdx.x < text_wgs) {          // the whole workgroup
-    text_mass_block<D, BLK>(dm, sa, blockIdx.x * kTextMassQueries, blockIdx.y, reinterpret_cast<float*>(lds));
+    text_mass_block<D, BLK>(dm, sa, blockIdx.x, blockIdx.y, reinterpret_cast<float*>(lds));
     return;
   }
   pool_v_block<D, BLK>(dm, a, (int)blockIdx.x - text_wgs, blockIdx.y, lds);
@@ -156,7 +156,7 @@ hipError_t launch_pool_t(const Dims& dm, const PoolArgs& a, hipStream_t s) {
   if (a.text_K && a.text_Lmass && a.Q && dm.tt > 0) {   // Qp is written by the launch above
     ScoreArgs sa = {};
     sa.K = a.text_K; sa.Qp = a.Qp; sa.Lmass = a.text_Lmass;
-    const int text_wgs = (dm.n + kTextMassQueries - 1) / kTextMassQueries;
+    const int text_wgs = text_mass_workgroups(dm);
     hipLaunchKernelGGL((pool_v_text_kernel<D, BLK>), dim3(dm.m + text_wgs, dm.batch * dm.heads, 1), block, 0, s, dm, a, sa, text_wgs);
   } else {
     hipLaunchKernelGGL((pool_v_kernel<D, BLK>), dim3(dm.m, dm.batch * dm.heads, 1), block, 0, s, dm, a);

@@ -92,8 +92,8 @@ __global__ __launch_bounds__(256) void pooled_scores_kernel(Dims dm, ScoreArgs a
 // The text log-masses by themselves (text_mass.hpp has the work).
 template <int D, int BLK>
 __global__ __launch_bounds__(256) void text_mass_kernel(Dims dm, ScoreArgs a) {
-  __shared__ float lds[text_mass_lds_floats<D>()];
-  text_mass_block<D, BLK>(dm, a, blockIdx.x * kTextMassQueries, blockIdx.y, lds);
+  __shared__ float lds[kTextMassLdsFloats];
+  text_mass_block<D, BLK>(dm, a, blockIdx.x, blockIdx.y, lds);
 }
 
 // One wave per row, the row held in registers (rows of at most 64 * NI blocks), so every value
@@ -401,7 +401,7 @@ hipError_t launch_scores_t(const Dims& dm, const ScoreArgs& a, hipStream_t s) {
   if (dm.m <= 1024) {
     // rows short enough for the registers of a workgroup: the text log-masses first, then one pass
     if (dm.tt > 0 && !a.text_done)
-      hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3((dm.n + 7) / 8, bh), dim3(256), 0, s, dm, a);
+      hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3(text_mass_workgroups(dm), bh), dim3(256), 0, s, dm, a);
     const dim3 fgrid(8 * ((bh + 7) / 8) * ((dm.n + 31) / 32));
     if (dm.m <= 256)
       hipLaunchKernelGGL((ipar_fused_kernel<D, 2>), fgrid, dim3(256), 0, s, dm, a);
@@ -413,7 +413,7 @@ hipError_t launch_scores_t(const Dims& dm, const ScoreArgs& a, hipStream_t s) {
   }
   hipLaunchKernelGGL((pooled_scores_kernel<D>), dim3((dm.m + 63) / 64, (dm.n + 63) / 64, bh), dim3(256), 0, s, dm, a);
   if (dm.tt > 0 && !a.text_done)
-    hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3((dm.n + 7) / 8, bh), dim3(256), 0, s, dm, a);
+    hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3(text_mass_workgroups(dm), bh), dim3(256), 0, s, dm, a);
   const dim3 rgrid((dm.n + 3) / 4, bh);
   if (dm.m <= 64 * 4)
     hipLaunchKernelGGL(ipar_softmax_rows_kernel<4>, rgrid, dim3(256), 0, s, dm, a);

@@ -1,87 +1,84 @@
 // Log-masses of the text key blocks (paper Sec. 3.2, Sec. 4.1; Alg. 1 steps 5-7):
 //   Lmass[n][N+i] = log sum_{t in text block i} exp(scale * q^pool_n . k_t)
 // as a device function, because two launches carry it: text_mass_kernel by itself, and the launch
-// that pools V (the streaming of V is bound by HBM, this by the vector ALU).
+// that pools V (the streaming of V is bound by HBM, this by latency and the fp32 matrix rate).
 #pragma once
 #include "rsa_common.hpp"
 
 namespace rsa {
 
-constexpr int kTextMassQueries = 8;                                   // pooled queries per workgroup
-template <int D>
-constexpr int text_mass_lds_floats() { return kTextMassQueries * D + kTextMassQueries * 256; }
-
-__device__ inline float text_wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ inline float text_wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+constexpr int kTextQueries = 32;                                      // pooled queries per workgroup
+constexpr int kTextTokens = 128;                                      // ... and text tokens: one block of 128 or two of 64
+constexpr int kTextMassLdsFloats = 2 * (kTextTokens / 32) * kTextQueries;
+__host__ __device__ inline int text_mass_workgroups(const Dims& dm) {  // of one (batch, head)
+  return (dm.n + kTextQueries - 1) / kTextQueries * (int)((dm.tt + kTextTokens - 1) / kTextTokens);
 }
 
-// Eight pooled queries (n0 .. n0 + 7 of (batch, head) bh) against the individual text keys, 256 tokens
-// at a time (a multiple of the block size), then one log-sum-exp per (query, text block). 256 threads;
-// `lds`: text_mass_lds_floats<D>() floats.
+// Workgroup `wg` of the text_mass_workgroups() of (batch, head) bh: 32 pooled queries against 128 text tokens, a
+// wave per 32 tokens, v_mfma_f32_32x32x2_f32 (fp32 operands, products and sums; a bf16 key is exact in fp32), then
+// one log-sum-exp per query and text block. A lane holds 16 scores of one query, so the block's maximum and sum go
+// across the two half-waves and, through LDS, across the waves of the block. Bound by latency: one pass of loads, a
+// chain of D/2 matrix instructions (2 us at d = 128) and two barriers. (A token per thread and eight queries on the
+// vector ALU, the block sums then taken one query at a time by a wave, was 11 us in the smallest call, now 5; with 512
+// text tokens it reached out from under the pooling of V: 165 us for the launch at 24 heads of 65 536 tokens, now 145.)
+// `lds`: kTextMassLdsFloats floats.
 template <int D, int BLK>
-__device__ __forceinline__ void text_mass_block(const Dims& dm, const ScoreArgs& a, int n0, int bh, float* lds) {
-  constexpr int NQ = kTextMassQueries;
-  float (*qs)[D] = reinterpret_cast<float (*)[D]>(lds);
-  float (*u)[256] = reinterpret_cast<float (*)[256]>(lds + NQ * D);
+__device__ __forceinline__ void text_mass_block(const Dims& dm, const ScoreArgs& a, int wg, int bh, float* lds) {
+  constexpr int KH = D / 2;                      // channels per half-wave: k-step s takes channel s from the lower half, KH + s from the upper
+  constexpr int TB = BLK / 32;                   // token tiles (waves) of a text block
+  float (*mxs)[kTextQueries] = reinterpret_cast<float (*)[kTextQueries]>(lds);
+  float (*sums)[kTextQueries] = mxs + kTextTokens / 32;
   const int b = bh / dm.heads, h = bh % dm.heads;
-  const float* Qp = a.Qp + (size_t)bh * dm.n * D;
-  for (int idx = threadIdx.x; idx < NQ * D; idx += 256) {
-    const int r = idx / D, c = idx % D;
-    qs[r][c] = (n0 + r < dm.n) ? Qp[(size_t)(n0 + r) * D + c] : 0.f;
-  }
-  __syncthreads();
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, l32 = lane % 32, hf = lane / 32;
+  const int query_tiles = (dm.n + kTextQueries - 1) / kTextQueries;
+  const int n = (wg % query_tiles) * kTextQueries + l32;
+  const int t0 = (wg / query_tiles) * kTextTokens + 32 * wave;       // this wave's first text token
+  const int last = (int)dm.tt - 1;
   const uint16_t* Kt = a.K + (int64_t)b * dm.sb + (int64_t)h * dm.sh + dm.tv * dm.st;
-  float* L = a.Lmass + (size_t)bh * dm.n * dm.m;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-
-  for (int64_t c0 = 0; c0 < dm.tt; c0 += 256) {
-    const int64_t tok = c0 + threadIdx.x;
-    float acc[NQ];
+  const uint4* krow = reinterpret_cast<const uint4*>(Kt + (int64_t)(t0 + l32 < last ? t0 + l32 : last) * dm.st + hf * KH);
+  const floatx4* qrow = reinterpret_cast<const floatx4*>(a.Qp + ((size_t)bh * dm.n + (n < dm.n ? n : dm.n - 1)) * D + hf * KH);
+  floatx16 acc;
 #pragma unroll
-    for (int r = 0; r < NQ; ++r) acc[r] = 0.f;
-    if (tok < dm.tt) {
-      const uint4* row = reinterpret_cast<const uint4*>(Kt + tok * dm.st);
-#pragma unroll 4
-      for (int cc = 0; cc < D / 8; ++cc) {
-        const uint4 v = row[cc];
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  // A = text keys (M = token), B = pooled queries (N = query); rows past the end repeat the last one and are masked
+  uint4 kv[KH / 8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float k0 = bf16_bits_to_float(w[i] & 0xffffu), k1 = bf16_bits_to_float(w[i] >> 16);
+  for (int i = 0; i < KH / 8; ++i) kv[i] = krow[i];
 #pragma unroll
-          for (int r = 0; r < NQ; ++r) {
-            acc[r] = fmaf(qs[r][cc * 8 + 2 * i], k0, acc[r]);
-            acc[r] = fmaf(qs[r][cc * 8 + 2 * i + 1], k1, acc[r]);
-          }
-        }
-      }
+  for (int i = 0; i < KH / 8; ++i) {
+    const floatx4 q0 = qrow[2 * i], q1 = qrow[2 * i + 1];
+    const uint32_t w[4] = {kv[i].x, kv[i].y, kv[i].z, kv[i].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float qa = e < 2 ? q0[2 * e] : q1[2 * e - 4], qb = e < 2 ? q0[2 * e + 1] : q1[2 * e - 3];
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_bits_to_float(w[e] & 0xffffu), qa, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_bits_to_float(w[e] >> 16), qb, acc, 0, 0, 0);
     }
+  }
+  // accumulator register r: token t0 + 8(r/4) + 4*hf + r%4, query n
+  float mx = -INFINITY;
 #pragma unroll
-    for (int r = 0; r < NQ; ++r) u[r][threadIdx.x] = acc[r] * dm.scale;
-    __syncthreads();
-    // tasks: (query r, block j of this chunk); one wave per task
-    constexpr int BPC = 256 / BLK;
-    for (int task = wave; task < NQ * BPC; task += 4) {
-      const int r = task / BPC, j = task % BPC;
-      const int64_t first = c0 + (int64_t)j * BLK;
-      if (first >= dm.tt || n0 + r >= dm.n) continue;
-      const int cnt = (int)((dm.tt - first) < BLK ? (dm.tt - first) : BLK);
-      float mx = -INFINITY;
-      for (int i = lane; i < cnt; i += 64) mx = fmaxf(mx, u[r][j * BLK + i]);
-      mx = text_wave_max(mx);
-      float sum = 0.f;
-      for (int i = lane; i < cnt; i += 64) sum += expf(u[r][j * BLK + i] - mx);
-      sum = text_wave_sum(sum);
-      if (lane == 0) L[(size_t)(n0 + r) * dm.m + dm.n + (int)(first / BLK)] = mx + logf(sum);
-    }
-    __syncthreads();
+  for (int r = 0; r < 16; ++r) {
+    acc[r] = t0 + 8 * (r / 4) + 4 * hf + (r % 4) <= last ? acc[r] * dm.scale : -INFINITY;
+    mx = fmaxf(mx, acc[r]);
+  }
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  if (hf == 0) mxs[wave][l32] = mx;
+  __syncthreads();
+  const int w0 = wave / TB * TB;                 // first wave of this text block
+#pragma unroll
+  for (int w = 0; w < TB; ++w) mx = fmaxf(mx, mxs[w0 + w][l32]);
+  float sum = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sum += expf(acc[r] - mx);             // exp(-inf) = 0 past the end
+  sum += __shfl_xor(sum, 32);
+  if (hf == 0) sums[wave][l32] = sum;
+  __syncthreads();
+  if (wave == w0 && hf == 0 && n < dm.n && t0 <= last) {
+    float total = 0.f;
+#pragma unroll
+    for (int w = 0; w < TB; ++w) total += sums[w0 + w][l32];
+    a.Lmass[((size_t)bh * dm.n + n) * dm.m + dm.n + t0 / BLK] = mx + logf(total);
   }
 }
 

@@ -692,6 +692,50 @@ def test_implicit_attention_alone(gpu):
         assert torch.equal(got, ref)
 
 
+@pytest.mark.parametrize("d,block,blocks,t_text", [
+    (64, 64, 1, 1), (128, 128, 3, 31), (128, 64, 15, 33), (64, 128, 17, 127), (128, 64, 126, 129), (64, 64, 127, 65),
+    (64, 64, 250, 300), (128, 64, 254, 257), (64, 64, 509, 190), (64, 64, 1022, 128), (64, 64, 1022, 129), (64, 64, 2046, 70),
+    (64, 64, 2047, 70)])
+def test_implicit_attention_at_the_edges_of_its_tiles(gpu, d, block, blocks, t_text):
+    """Pooled scores, log-masses (text log-masses among them) and A^pool against fp64 from the same pooled vectors,
+    at row lengths around the ends of a tile, of a wave's band and of every kernel variant (128, 256, 512, 1024, 2048
+    blocks) and text lengths around a tile and a block. Bounds: a product of d fp32 terms is off by at most
+    (d + 2) u sum|q k| (u = 2^-24, any order of the sum); a logarithm of a sum of c exponentials adds the largest
+    error of its scores and a few u (c of the sum, 8 of exp and log, 4 |L| of the result); a softmax weight doubles that."""
+    import torch
+    from paper_2511_19835_amd import binding as rb
+    u = 2.0 ** -24
+    tv = blocks * block - (block // 2 + 1)                 # a ragged last video block
+    g = torch.Generator(device="cuda").manual_seed(blocks)
+    q, k, v = ((torch.randn(1, 2, tv + t_text, d, generator=g, device="cuda") * 1.5).to(torch.bfloat16) for _ in range(3))
+    buf = rb.allocate(q, tv, t_text, block)
+    for t in (buf.Spool, buf.Lmass, buf.Apool):
+        t.fill_(float("nan"))
+    rb.rsa_pool(buf.shape, q, k, v, buf.Qp, buf.Kp, buf.Vp, buf.Vt, buf.Spool, buf.Apool, buf.Lmass, buf.Mc_bits, 0,
+                buf.pool_ws)
+    torch.cuda.synchronize()
+    N, M, scale = buf.N, buf.M, d ** -0.5
+    qp, kp, kt = (x.double().cpu() for x in (buf.Qp[0], buf.Kp[0], k[0, :, tv:]))
+    S = qp @ kp.transpose(1, 2).contiguous() * scale
+    eS = qp.abs() @ kp.abs().transpose(1, 2).contiguous() * (scale * (d + 2) * u)
+    T = qp @ kt.transpose(1, 2).contiguous() * scale
+    eT = qp.abs() @ kt.abs().transpose(1, 2).contiguous() * (scale * (d + 2) * u)
+    counts = torch.full((N,), float(block), dtype=torch.float64)
+    counts[-1] = tv - (N - 1) * block
+    L, eL = S.clone(), eS.clone()
+    L[:, :, :N] += counts.log()
+    for i in range(M - N):
+        t = slice(i * block, min((i + 1) * block, t_text))
+        L[:, :, N + i] = torch.logsumexp(T[:, :, t], dim=2)
+        eL[:, :, N + i] = eT[:, :, t].max(dim=2).values + (t.stop - t.start + 8) * u
+    eL = eL + (4 * L.abs() + 8) * u
+    A = torch.softmax(L, dim=2)
+    eA = A * (2 * eL.max(dim=2, keepdim=True).values + (M + 16) * u)
+    for name, got, ref, err in (("Spool", buf.Spool, S, eS), ("Lmass", buf.Lmass, L, eL), ("Apool", buf.Apool, A, eA)):
+        bad = (got[0].double().cpu() - ref).abs() > err + 1e-37
+        assert not bad.any(), (name, int(bad.sum()), bad.nonzero()[0].tolist())
+
+
 def test_pooled_tensors_do_not_depend_on_the_gate_mode(gpu):
     """With the gate on, k^pool comes from the key-side deviation launch instead of the pooling kernel:
     every pooled tensor and the implicit attention must be bit for bit what gapr_mode 0 (no gate GEMMs,
