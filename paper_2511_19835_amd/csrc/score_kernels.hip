@@ -5,7 +5,7 @@
 //   pooled_scores_kernel   Spool[n][m] = scale * q^pool_n . k^pool_m       (N x M x d, tiny)
 //   text_mass_kernel       Lmass[n][N+i] = log sum_{t in text block i} exp(scale * q^pool_n . k_t)
 //   ipar_softmax_rows_kernel  Lmass[n][m<N] = Spool + ln c_m ; Apool = row-softmax(Lmass)
-//   ipar_fused_kernel      the first and the third in one pass (rows of at most 1024 blocks)
+//   ipar_fused_kernel      the first and the third in one pass (rows of at most 2048 blocks)
 //
 // softmax(Lmass) is the paper's reallocation written in log space: the mixed softmax
 // over [pooled video keys ; text tokens] gives weights proportional to exp(score); a video
@@ -140,198 +140,207 @@ __global__ __launch_bounds__(256) void ipar_softmax_rows_kernel(Dims dm, ScoreAr
   }
 }
 
-// Reduction over the 32 lanes of each half-wave with data-parallel-primitive moves (row shifts inside
-// the rows of 16 lanes, then a row broadcast): lanes 31 and 63 end up with the result of their half.
+// Reduction over the 16 lanes of each row of lanes with data-parallel-primitive moves: lane 15 of every
+// row ends up with the result.
 template <bool MAX>
-__device__ __forceinline__ float half_wave_reduce(float v) {
+__device__ __forceinline__ float lane_row_reduce(float v) {
   constexpr int kIdentity = MAX ? (int)0xff800000u : 0;       // -inf or 0 for lanes without a source
-  auto step = [&](auto ctrl, auto row_mask) __attribute__((always_inline)) {
-    const int o = __builtin_amdgcn_update_dpp(kIdentity, __builtin_bit_cast(int, v), decltype(ctrl)::value,
-                                              decltype(row_mask)::value, 0xf, false);
+  auto step = [&](auto ctrl) __attribute__((always_inline)) {
+    const int o = __builtin_amdgcn_update_dpp(kIdentity, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, false);
     const float f = __builtin_bit_cast(float, o);
     v = MAX ? fmaxf(v, f) : v + f;
   };
-  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr:1
-  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});   // row_shr:2
-  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});   // row_shr:4
-  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});   // row_shr:8
-  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1 and 3
+  step(std::integral_constant<int, 0x111>{});   // row_shr:1
+  step(std::integral_constant<int, 0x112>{});   // row_shr:2
+  step(std::integral_constant<int, 0x114>{});   // row_shr:4
+  step(std::integral_constant<int, 0x118>{});   // row_shr:8
   return v;
 }
 
-// Alg. 1 steps 5-7 in one pass over the N x M tensors (rows of at most 128 * NT blocks): a workgroup
-// owns 32 pooled queries and all M key blocks. Wave w takes the key tiles NT w .. NT w + NT - 1 (32
-// blocks each: a band of consecutive columns). The product is v_mfma_f32_32x32x2_f32 as in
-// pooled_scores_kernel, and every score of the wave's band stays in registers. Scores are written once
-// (Spool), turned into log-masses (video blocks: + ln c_m; text blocks: what text_mass_kernel left in
-// Lmass), and the row softmax is taken across the registers, the half-waves and the four waves, so
-// that Lmass and Apool are written once too and nothing is read back. The text columns of Lmass must
-// be in place before this kernel runs.
+// Alg. 1 steps 5-7 in one pass over the N x M tensors (rows of at most 64 * NT blocks): a workgroup
+// owns 16 pooled queries and all M key blocks, which its waves share out evenly (a band of consecutive
+// columns, 16-block tiles, at most NT of them). The product is v_mfma_f32_16x16x4_f32 (fp32 operands,
+// products and sums, at the rate of the 32x32x2 form), and every score of the wave's band stays in
+// registers. Scores are written once (Spool), turned into log-masses (video blocks: + ln c_m; text blocks:
+// what text_mass left in Lmass), and the row softmax is taken across the registers, the lanes and the four
+// waves, so that Lmass and Apool are written once too and nothing is read back. The text columns of Lmass
+// must be in place before this kernel runs.
 //
-// Each wave has 16 KB of LDS to itself (two workgroups fit a CU, so that the epilogue of one runs
-// beside the matrix work of the other):
+// Sixteen rows rather than 32: four workgroups fit a CU (two for rows of 1025 to 2048 blocks), so that the
+// stores of one run beside the matrix work of another and the last round of workgroups is shorter, a few
+// heads fill the chip, and the scores of 2048 columns still fit the registers. Bound by the stores and the fp32
+// matrix work about equally, one after the other within a round. Against 32 rows (and against a scores kernel and a
+// softmax kernel for rows above 1024): 2 heads of 17 blocks 12.5 -> 4.7 us, 24 heads of 159 blocks 17 -> 10, of 516
+// 72 -> 50, of 931 143 -> 110, of 1182 266 -> 205; 3 heads of 931 51 -> 32. Three or four buffers instead of two: no
+// gain at any of these (latency is covered), and fewer workgroups per CU.
+//
+// Each wave has a piece of LDS to itself:
 //  - in the product, two buffers of half a key tile: the pooled keys come in with direct-to-LDS loads,
-//    the contraction index in two halves (each half-wave's D/4 channels of the half), the half after the
-//    one being multiplied always on its way. A buffer row is one key block: PPR 16-byte positions, the
-//    lower half of them the channels of the lower half-wave; position p of row r holds logical chunk
-//    p ^ (r mod PPR), so that lanes reading one logical chunk of different rows hit different banks;
-//  - in the epilogue, a [32][32 * HT] tile of floats through which the accumulators (a lane holds one
-//    column of 16 rows) are turned into rows, so that a store instruction writes two runs of 128 * HT
-//    bytes instead of two of 128: a wave may have 63 stores in flight, and with narrow ones that bound,
-//    not the memory, sets the pace.
+//    the contraction index in two halves, the half after the one being multiplied always on its way. Lane
+//    row g (16 lanes) works on channels g*D/4 .. of the contraction, so a half is D/8 consecutive channels of
+//    every lane row. A buffer row is one key block: PPR 16-byte positions; position p of row r holds logical
+//    chunk p ^ key(r), so that lanes reading one logical chunk of 16 rows hit 16 different positions;
+//  - in the epilogue, a [16][16 * HT] tile of floats (rows padded by 16 bytes) through which the accumulators
+//    (a lane holds one column of 4 rows) are turned into rows, so that a store instruction writes runs of
+//    64 * HT bytes: a wave may have 63 stores in flight, and with narrow ones that bound, not the memory,
+//    sets the pace.
 typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
 template <int D, int NT>
-__global__ __launch_bounds__(256, 2) void ipar_fused_kernel(Dims dm, ScoreArgs a) {
-  constexpr int KH = D / 2;                     // k-steps; channels per half-wave
+__global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims dm, ScoreArgs a) {
+  constexpr int KQ = D / 4;                     // k-steps; channels per lane row
   constexpr int PPR = D / 8;                    // 16-byte positions per buffer row (half the channels of a key block)
-  constexpr int HALF = 32 * PPR * 4;            // floats per buffer
+  constexpr int CPG = PPR / 4;                  // ... of one lane row
+  constexpr int HALF = 16 * PPR * 4;            // floats per buffer
   constexpr int RPL = 64 / PPR;                 // rows per load
-  constexpr int LOADS = 32 / RPL;               // direct-to-LDS loads per half tile
-  constexpr int HT = NT < 4 ? NT : 4;           // tiles per epilogue pass (HT * 4 KB <= the wave's LDS)
-  static_assert(2 * HALF * 4 == 16384 || D == 64, "a wave's LDS: two half tiles");
-  static_assert(32 * 32 * HT * 4 <= 2 * HALF * 4 || D == 64, "the epilogue tile fits the wave's LDS");
-  constexpr int WAVE_LDS = (2 * HALF > 32 * 32 * HT) ? 2 * HALF : 32 * 32 * HT;   // floats
+  constexpr int LOADS = 16 / RPL;               // direct-to-LDS loads per half tile
+  constexpr int HT = NT < 8 ? NT : 8;           // tiles per epilogue pass
+  constexpr int TW = 16 * HT, TS = TW + 4;      // epilogue tile: columns, row stride in floats
+  constexpr int WAVE_LDS = ((2 * HALF > 16 * TS ? 2 * HALF : 16 * TS) + 255) / 256 * 256;   // floats
   __shared__ __attribute__((aligned(1024))) float wlds[4][WAVE_LDS];
-  __shared__ float red[2][4][32];               // row maxima, then row sums, of each wave
-  // Workgroups go round the 8 XCDs by their index; XCD x takes the (batch, head) pairs x, x + 8, ... one
-  // after the other, so that the pooled keys its L2 serves at any time are those of a head or two.
-  const int row_tiles = (dm.n + 31) / 32;
-  const int xcd = blockIdx.x % 8, k = blockIdx.x / 8;
-  const int bh = xcd + 8 * (k / row_tiles);
-  if (bh >= dm.batch * dm.heads) return;        // the whole workgroup, before any barrier
+  __shared__ __attribute__((aligned(16))) float red[2][4][16];               // row maxima, then row sums, of each wave
+  // Workgroups go round the 8 XCDs by their index; XCD x takes a contiguous eighth of the row tiles of all
+  // (batch, head) pairs, so that the pooled keys its L2 serves at any time are those of a head or two and
+  // few heads still use all XCDs.
+  const int row_tiles = (dm.n + 15) / 16;
+  const int total = row_tiles * dm.batch * dm.heads, q8 = total / 8, r8 = total % 8;
+  const int xcd = blockIdx.x % 8;
+  const int item = xcd * q8 + (xcd < r8 ? xcd : r8) + (int)blockIdx.x / 8;
+  const int bh = item / row_tiles;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int l32 = lane % 32, hf = lane / 32;
-  const int n0 = (k % row_tiles) * 32;
+  const int l16 = lane % 16, g = lane / 16;
+  const int n0 = (item % row_tiles) * 16;
   const int M = dm.m, N = dm.n;
   float* mine = wlds[wave];
 
-  // this lane's pooled query (row n0 + l32, clamped: rows past the end are computed and not stored)
-  floatx4 qv[KH / 4];
+  // this lane's pooled query (row n0 + l16, clamped: rows past the end are computed and not stored)
+  floatx4 qv[KQ / 4];
   {
-    const int n = n0 + l32 < N ? n0 + l32 : N - 1;
-    const floatx4* qrow = reinterpret_cast<const floatx4*>(a.Qp + ((size_t)bh * N + n) * D + hf * KH);
+    const int n = n0 + l16 < N ? n0 + l16 : N - 1;
+    const floatx4* qrow = reinterpret_cast<const floatx4*>(a.Qp + ((size_t)bh * N + n) * D + g * KQ);
 #pragma unroll
-    for (int i = 0; i < KH / 4; ++i) qv[i] = qrow[i];
+    for (int i = 0; i < KQ / 4; ++i) qv[i] = qrow[i];
   }
   // the query must be in before the first direct-to-LDS load goes out: the compiler does not see those
   // loads and would wait for them together with the query at its first use
   __builtin_amdgcn_s_waitcnt(0x0F70);           // vmcnt(0)
-  floatx16 acc[NT];
+  floatx4 acc[NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+  for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  const int n_tiles = (M + 31) / 32;
+  const int n_tiles = (M + 15) / 16;
+  const int per_wave = (n_tiles + 3) / 4;       // tiles of a band (at most NT)
+  const int ct0 = wave * per_wave;
+  const int my_tiles = max(0, min(per_wave, n_tiles - ct0));
   const float* Kp = a.Kp + (size_t)bh * M * D;
   const int lrow = lane / PPR, lpos = lane % PPR;
-  // half c of key tile ct into buffer `buf`
-  auto request_half = [&](int ct, int c, int buf) __attribute__((always_inline)) {
-    const int m0 = ct * 32;
-    const uint32_t dst = (uint32_t)(uintptr_t)(mine + buf * HALF);
+  auto swz = [](int r) __attribute__((always_inline)) { return (r / (16 / PPR)) & (PPR - 1); };
+  // half u % 2 of the band's key tile u / 2 into buffer u % 2
+  auto request_half = [&](int u) __attribute__((always_inline)) {
+    const int m0 = (ct0 + u / 2) * 16, c = u % 2;
+    const uint32_t dst = (uint32_t)(uintptr_t)(mine + (u % 2) * HALF);
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
       const int r = j * RPL + lrow;
       const int m = m0 + r < M ? m0 + r : M - 1;     // rows past the end repeat the last one (not stored)
-      const int q = lpos ^ (r % PPR);                // logical chunk: half-wave q / (PPR/2), chunk q % (PPR/2) of this half
-      const int ch = (q / (PPR / 2)) * KH + c * (KH / 2) + 4 * (q % (PPR / 2));
+      const int q = lpos ^ swz(r);                   // logical chunk: lane row q / CPG, chunk q % CPG of this half
+      const int ch = (q / CPG) * KQ + c * (KQ / 2) + 4 * (q % CPG);
       dma16_v(dst + j * 1024, Kp + (size_t)m * D + ch, &wlds[0][0]);
     }
   };
-  const int ct0 = wave * NT;
-  if (ct0 < n_tiles) request_half(ct0, 0, 0);
+  const int halves = 2 * my_tiles;
+  if (halves > 0) request_half(0);
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int ct = ct0 + t;
-    if (ct < n_tiles) {                          // wave-uniform
+  for (int u = 0; u < 2 * NT; ++u) {
+    if (u < halves) {                            // wave-uniform
+      // the buffer of the next half was last read in the step before: those reads fed MFMAs that have been issued
+      if (u + 1 < halves) {
+        request_half(u + 1);
+        wait_loads_leaving<LOADS>();
+      } else {
+        wait_loads_leaving<0>();
+      }
+      asm volatile("" ::: "memory");             // no read of the buffer may move above the wait
+      const floatx4* kb = reinterpret_cast<const floatx4*>(mine + (u % 2) * HALF) + l16 * PPR;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        // the buffer of the next half was last read two halves ago: those reads fed MFMAs that have been issued
-        const bool more = c == 0 || (t + 1 < NT && ct + 1 < n_tiles);
-        if (more) {
-          request_half(c == 0 ? ct : ct + 1, 1 - c, 1 - c);
-          wait_loads_leaving<LOADS>();
-        } else {
-          wait_loads_leaving<0>();
-        }
-        asm volatile("" ::: "memory");           // no read of the buffer may move above the wait
-        const floatx4* kb = reinterpret_cast<const floatx4*>(mine + c * HALF) + l32 * PPR;
+      for (int i = 0; i < CPG; ++i) {
+        const floatx4 kq = kb[(g * CPG + i) ^ swz(l16)];
 #pragma unroll
-        for (int i = 0; i < KH / 8; ++i) {
-          const floatx4 kq = kb[(hf * (PPR / 2) + i) ^ (l32 % PPR)];
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(qv[c * (KH / 8) + i][e], kq[e], acc[t], 0, 0, 0);
-        }
+        for (int e = 0; e < 4; ++e)
+          acc[u / 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[(u % 2) * CPG + i][e], kq[e], acc[u / 2], 0, 0, 0);
       }
     }
   }
 
-  // accumulator register r of tile t: query row n0 + 8(r/4) + 4*hf + r%4, key block 32*(NT*wave + t) + l32.
+  // accumulator register r of tile t: query row n0 + 4*g + r, key block 16*(ct0 + t) + l16.
   const size_t row0 = (size_t)bh * N * M;
   float* S = a.Spool + row0;
   float* L = a.Lmass + row0;
   float* A = a.Apool + row0;
   const float ln_full = logf((float)dm.blk), ln_last = logf((float)dm.block_count(N - 1));
-  const int band0 = ct0 * 32;                    // first column of the wave's band
-  const int mcol = band0 + l32;                  // this lane's column in tile 0 of the band
-  // Writes f(t, r) for every accumulator to rows n0 .. n0+31 of `out`, columns [band0, band0 + 32 NT) cut at
-  // `col_end`, through the wave's LDS tile: HT tiles at a time, whole rows of the tile per store.
+  const int band0 = ct0 * 16, band1 = band0 + 16 * my_tiles;      // the wave's columns
+  // Writes f(t, r) for every accumulator to rows n0 .. n0+15 of `out`, the band's columns below `col_end`, through
+  // the wave's LDS tile: HT tiles at a time, whole rows of the tile per store.
   auto store_band = [&](float* out, int col_end, auto f) __attribute__((always_inline)) {
-    constexpr int TW = 32 * HT;                  // floats per tile row
+    const int end = col_end < band1 ? col_end : band1;
 #pragma unroll
     for (int p0 = 0; p0 < NT; p0 += HT) {
-      asm volatile("" ::: "memory");
+      if (band0 + 16 * p0 < end) {               // wave-uniform
+        asm volatile("" ::: "memory");
 #pragma unroll
-      for (int tt = 0; tt < HT; ++tt)
+        for (int tt = 0; tt < HT; ++tt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(8 * (r / 4) + 4 * hf + (r % 4)) * TW + 32 * tt + l32] = f(p0 + tt, r);
-      asm volatile("" ::: "memory");
-      // a tile row is TW / 4 lanes of four floats: 64 lanes take RPI rows per store instruction.
-      // The loop stays rolled: unrolled, all its addresses would be worked out ahead and spill.
-      constexpr int LPR = TW / 4, RPI = 64 / LPR;
-      const int rsub = lane / LPR, cl = 4 * (lane % LPR);
-      const float* src = &mine[rsub * TW + cl];
-      const int m = band0 + 32 * p0 + cl;
-      float* dst = out + (size_t)(n0 + rsub) * M + m;
+          for (int r = 0; r < 4; ++r) mine[(4 * g + r) * TS + 16 * tt + l16] = f(p0 + tt, r);
+        asm volatile("" ::: "memory");
+        // a tile row is TW / 4 lanes of four floats: 64 lanes take RPI rows per store instruction, U instructions
+        // at a time (all 16 / RPI unrolled: their addresses would be worked out ahead and spill)
+        constexpr int LPR = TW / 4, RPI = 64 / LPR < 16 ? 64 / LPR : 16, U = 16 / RPI < 4 ? 16 / RPI : 4;
+        const int rsub = lane / LPR, cl = 4 * (lane % LPR);
+        const int m = band0 + 16 * p0 + cl;
+        const float* src = &mine[rsub * TS + cl];
+        float* dst = out + (size_t)(n0 + rsub) * M + m;
 #pragma clang loop unroll(disable)
-      for (int i = 0; i < 32 / RPI; ++i) {
-        const int n = n0 + RPI * i + rsub;
-        const floatx4 v = *reinterpret_cast<const floatx4*>(src);
-        if (n < N) {
-          if (m + 3 < col_end) {
-            *reinterpret_cast<floatx4_u*>(dst) = v;
-          } else {
+        for (int i = 0; i < 16; i += U * RPI) {
+          floatx4 v[U];
 #pragma unroll
-            for (int e = 0; e < 3; ++e)
-              if (m + e < col_end) dst[e] = v[e];
+          for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const floatx4*>(src + u * RPI * TS);
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            float* d = dst + (size_t)(u * RPI) * M;
+            if (n0 + i + u * RPI + rsub < N) {
+              if (m + 3 < end) {
+                *reinterpret_cast<floatx4_u*>(d) = v[u];
+              } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                  if (m + e < end) d[e] = v[u][e];
+              }
+            }
           }
+          src += U * RPI * TS;
+          dst += (size_t)(U * RPI) * M;
         }
-        src += RPI * TW;
-        dst += RPI * (size_t)M;
       }
     }
   };
   // (the scores first, with nothing but stores in flight: a load in between would be waited for together
   // with every store before it)
   store_band(S, M, [&](int t, int r) __attribute__((always_inline)) { return acc[t][r] * dm.scale; });
-  float pm[16];
+  float pm[4];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) pm[r] = -INFINITY;
+  for (int r = 0; r < 4; ++r) pm[r] = -INFINITY;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const int m = mcol + 32 * t;
-    const int tile_first = (ct0 + t) * 32;
-    if (tile_first + 32 <= N) {                  // wave-uniform: video blocks only, none of them the last
+    const int tile_first = band0 + 16 * t, m = tile_first + l16;
+    if (t < my_tiles && tile_first + 16 < N) {   // wave-uniform: video blocks only, none of them the last
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
+      for (int r = 0; r < 4; ++r) {
         acc[t][r] = acc[t][r] * dm.scale + ln_full;
         pm[r] = fmaxf(pm[r], acc[t][r]);
       }
-    } else {
+    } else if (t < my_tiles) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int n = n0 + 8 * (r / 4) + 4 * hf + (r % 4);
+      for (int r = 0; r < 4; ++r) {
+        const int n = n0 + 4 * g + r;
         float l = -INFINITY;
         if (m < N) l = acc[t][r] * dm.scale + (m == N - 1 ? ln_last : ln_full);
         else if (m < M) l = L[(size_t)(n < N ? n : N - 1) * M + m];
@@ -342,87 +351,74 @@ __global__ __launch_bounds__(256, 2) void ipar_fused_kernel(Dims dm, ScoreArgs a
   }
   // the log-masses of the video blocks (the text columns already hold theirs)
   store_band(L, N, [&](int t, int r) __attribute__((always_inline)) { return acc[t][r]; });
-  // row maxima: over the lanes of the half-wave, then over the waves through LDS
+  // row maxima: over the lanes of the lane row, then over the waves through LDS
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float v = half_wave_reduce<true>(pm[r]);
-    if (l32 == 31) red[0][wave][8 * (r / 4) + 4 * hf + (r % 4)] = v;
+  for (int r = 0; r < 4; ++r) {
+    const float v = lane_row_reduce<true>(pm[r]);
+    if (l16 == 15) red[0][wave][4 * g + r] = v;
   }
   __syncthreads();
-  float mx[16];
+  floatx4 mx = *reinterpret_cast<const floatx4*>(&red[0][0][4 * g]);
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    floatx4 v = *reinterpret_cast<const floatx4*>(&red[0][0][8 * g + 4 * hf]);
+  for (int w = 1; w < 4; ++w) {
+    const floatx4 u = *reinterpret_cast<const floatx4*>(&red[0][w][4 * g]);
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      const floatx4 u = *reinterpret_cast<const floatx4*>(&red[0][w][8 * g + 4 * hf]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], u[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) mx[4 * g + e] = v[e];
+    for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], u[e]);
   }
-  float ps[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) ps[r] = 0.f;
+  float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int t = 0; t < NT; ++t)
+    if (t < my_tiles) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float e = expf(acc[t][r] - mx[r]);    // exp(-inf) = 0 for the slots past the row end
-      acc[t][r] = e;
-      ps[r] += e;
+      for (int r = 0; r < 4; ++r) {
+        const float e = expf(acc[t][r] - mx[r]);    // exp(-inf) = 0 for the columns past the row end
+        acc[t][r] = e;
+        ps[r] += e;
+      }
     }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float v = half_wave_reduce<false>(ps[r]);
-    if (l32 == 31) red[1][wave][8 * (r / 4) + 4 * hf + (r % 4)] = v;
+  for (int r = 0; r < 4; ++r) {
+    const float v = lane_row_reduce<false>(ps[r]);
+    if (l16 == 15) red[1][wave][4 * g + r] = v;
   }
   __syncthreads();
-  float inv[16];
+  floatx4 inv = *reinterpret_cast<const floatx4*>(&red[1][0][4 * g]);
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    floatx4 v = *reinterpret_cast<const floatx4*>(&red[1][0][8 * g + 4 * hf]);
+  for (int w = 1; w < 4; ++w) {
+    const floatx4 u = *reinterpret_cast<const floatx4*>(&red[1][w][4 * g]);
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      const floatx4 u = *reinterpret_cast<const floatx4*>(&red[1][w][8 * g + 4 * hf]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] += u[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) inv[4 * g + e] = 1.0f / v[e];
+    for (int e = 0; e < 4; ++e) inv[e] += u[e];
   }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) inv[e] = 1.0f / inv[e];
   store_band(A, M, [&](int t, int r) __attribute__((always_inline)) { return acc[t][r] * inv[r]; });
 }
 
 template <int D, int BLK>
 hipError_t launch_scores_t(const Dims& dm, const ScoreArgs& a, hipStream_t s) {
   const int bh = dm.batch * dm.heads;
-  if (dm.m <= 1024) {
+  if (dm.m <= 2048) {
     // rows short enough for the registers of a workgroup: the text log-masses first, then one pass
     if (dm.tt > 0 && !a.text_done)
       hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3(text_mass_workgroups(dm), bh), dim3(256), 0, s, dm, a);
-    const dim3 fgrid(8 * ((bh + 7) / 8) * ((dm.n + 31) / 32));
-    if (dm.m <= 256)
+    const dim3 fgrid(bh * ((dm.n + 15) / 16));
+    if (dm.m <= 128)
       hipLaunchKernelGGL((ipar_fused_kernel<D, 2>), fgrid, dim3(256), 0, s, dm, a);
-    else if (dm.m <= 512)
+    else if (dm.m <= 256)
       hipLaunchKernelGGL((ipar_fused_kernel<D, 4>), fgrid, dim3(256), 0, s, dm, a);
-    else
+    else if (dm.m <= 512)
       hipLaunchKernelGGL((ipar_fused_kernel<D, 8>), fgrid, dim3(256), 0, s, dm, a);
+    else if (dm.m <= 1024)
+      hipLaunchKernelGGL((ipar_fused_kernel<D, 16>), fgrid, dim3(256), 0, s, dm, a);
+    else
+      hipLaunchKernelGGL((ipar_fused_kernel<D, 32>), fgrid, dim3(256), 0, s, dm, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((pooled_scores_kernel<D>), dim3((dm.m + 63) / 64, (dm.n + 63) / 64, bh), dim3(256), 0, s, dm, a);
   if (dm.tt > 0 && !a.text_done)
     hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3(text_mass_workgroups(dm), bh), dim3(256), 0, s, dm, a);
   const dim3 rgrid((dm.n + 3) / 4, bh);
-  if (dm.m <= 64 * 4)
-    hipLaunchKernelGGL(ipar_softmax_rows_kernel<4>, rgrid, dim3(256), 0, s, dm, a);
-  else if (dm.m <= 64 * 16)
-    hipLaunchKernelGGL(ipar_softmax_rows_kernel<16>, rgrid, dim3(256), 0, s, dm, a);
-  else if (dm.m <= 64 * 32)
-    hipLaunchKernelGGL(ipar_softmax_rows_kernel<32>, rgrid, dim3(256), 0, s, dm, a);
-  else
-    hipLaunchKernelGGL(ipar_softmax_rows_kernel<RSA_MAX_BLOCKS / 64>, rgrid, dim3(256), 0, s, dm, a);
+  hipLaunchKernelGGL(ipar_softmax_rows_kernel<RSA_MAX_BLOCKS / 64>, rgrid, dim3(256), 0, s, dm, a);
   return hipGetLastError();
 }
 
