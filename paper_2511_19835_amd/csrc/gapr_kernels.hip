@@ -25,6 +25,8 @@
 // quantities whose 2^-12 relative rounding leaves DA / DB within 2e-4 relative of fp64
 // arithmetic (bf16 operands: up to 1.5e-3, wider than the 1e-3 band in which the gate may
 // differ); the MFMA rate is the same. Conversions saturate at the largest finite half.
+#include <type_traits>
+
 #include "rsa_common.hpp"
 
 namespace rsa {
@@ -47,11 +49,11 @@ __device__ __forceinline__ int swizzled(int r, int c) { return r * CPR + (c ^ ((
 // with the pooled score S[n][m] and the key-side deviation DBt[m][n] of the first launch (one word each
 // per lane and iteration, asked for at the start of the iteration) the lane decides its bit of M_c, and
 // a ballot makes the mask word of the iteration.
-// POOL (key side only): the launch also makes the pooled vector of its block -- it holds the whole block in
+// The key side also makes the pooled vector of its block -- it holds the whole block in
 // registers before it centres it -- and writes it (fp32, and the fp16 operand copy) for the kernels that
 // follow, with the arithmetic of pool_qk_kernel (same thread-to-row mapping, same order of additions), so
 // the separate pooling pass over K is not needed.
-template <int D, int BLK, int NT, bool GATE, bool POOL>
+template <int D, int BLK, int NT, bool GATE>
 __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, const uint16_t* __restrict__ X,
                                                            const float* __restrict__ Xpool, float* __restrict__ Xpool_out,
                                                            uint16_t* __restrict__ Xpool_f16_out, int n_blocks_x,
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, con
       raw[i] = *reinterpret_cast<const u32x4*>(Xb + (t0 + rr) * dm.st + 8 * cc);
     }
     floatx4 m0, m1;
-    if constexpr (POOL) {
+    if constexpr (!GATE) {
       static_assert(NT == 256 && RPP * D * 4 <= BLK * CPR * 16, "the mapping of pool_qk_kernel; its partial sums fit the tile");
       __shared__ __align__(16) float mean_lds[D];
       float (*red)[D] = reinterpret_cast<float (*)[D]>(atile);   // the tile is written after the sums have been read
@@ -207,6 +209,290 @@ __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, con
   }
 }
 
+constexpr int kDevRows = 128;                    // token rows of a workgroup: one block of 128 or two of 64
+constexpr int kDevThreads = 256;
+constexpr int kDevWaves = kDevThreads / 64;
+constexpr int kDevCols = 32 * kDevWaves;         // pooled vectors of an iteration: 32 per wave
+
+// The same two launches for long rows (use_long_rows below). What bounds the gate is its matrix work (fp16, at the clock the power
+// limit leaves), so less of it is done: DA is >= 0 and rounding is monotone, so a pair with |S| <= DB has its bit
+// clear whatever DA is. The query side (GATE) lists the key blocks with |S| > DB first (44 to 63 % of them on smooth
+// clips) and multiplies those only, gathering their vectors out of the operand layout; the bits are the same. For
+// that the key side leaves DB as [N][M], rows that the query side reads whole, ahead of its product. A workgroup
+// takes 128 token rows (two blocks of 64: half the operand traffic per row, one list for both), two row tiles at a
+// time and one register set for the other operand, reloaded as it is used up: four waves per SIMD on the key side,
+// three on the query side.
+// Both launches together, against the pair of launches above (us): 24 heads of 931 blocks 1256 -> 1129, 40 heads of
+// 591 916 -> 836, 24 heads of 1182 blocks of 64 1306 -> 1093, 3 heads of 931 174 -> 158. Building the list costs a
+// workgroup about 3 us, which short rows do not earn back (24 heads of 516 blocks 437 -> 466, 2 of 17 7.2 -> 10.0) and
+// a single round of workgroups cannot hide (3 heads of 636 blocks of 64: no gain): hence the two conditions.
+inline bool use_long_rows(const Dims& dm) {
+  const int groups = (dm.n + kDevRows / dm.blk - 1) / (kDevRows / dm.blk);
+  return dm.m > 544 && (long long)groups * dm.batch * dm.heads > 1024;
+}
+// On the key side the launch also makes the pooled vector of its block, as in deviation_kernel.
+template <int D, int BLK, bool GATE>
+__global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kernel(Dims dm, const uint16_t* __restrict__ X,
+                                                          const float* __restrict__ Xpool, float* __restrict__ Xpool_out,
+                                                          uint16_t* __restrict__ Xpool_f16_out, int n_blocks_x,
+                                                          const uint16_t* __restrict__ PB,
+                                                          int n_other, float* __restrict__ out,
+                                                          const float* __restrict__ Spool,
+                                                          const float* __restrict__ DB,
+                                                          uint32_t* __restrict__ Mc_bits) {
+  constexpr int NT = kDevThreads, NW = kDevWaves;
+  constexpr int MT = kDevRows / 32, KS = D / 16, CPR = D / 8;
+  constexpr int RB = kDevRows / BLK;             // token blocks of the workgroup
+  constexpr int TB = BLK / 32;                   // row tiles of a token block
+  constexpr int TP = 2;                          // row tiles of a pass over the k-steps (a block has 2 or 4)
+  constexpr int RPP = NT / CPR;                  // rows staged per pass of the workgroup
+  constexpr int NP = kDevRows / RPP, PB_ = BLK / RPP;   // passes in all and of one token block
+  constexpr int LU = 4 / RB;                     // chunks of 64 key blocks whose scores and deviations a wave asks for at a time
+  __shared__ u32x4 atile[kDevRows * CPR];
+  // Workgroup i runs on XCD i % 8. Each XCD takes a contiguous eighth of the (batch, head, block)
+  // range, so that token blocks that are neighbours run on the same XCD at about the same time: the
+  // query side reads DBt[m][n] for a fixed n, 32 neighbouring n to a 128-byte line, which then
+  // comes into one L2 once instead of into all eight.
+  const int groups_x = (n_blocks_x + RB - 1) / RB;
+  const int total = groups_x * dm.batch * dm.heads;
+  const int xcd = blockIdx.x % 8, q8 = total / 8, r8 = total % 8;
+  const int item = xcd * q8 + (xcd < r8 ? xcd : r8) + (int)blockIdx.x / 8;
+  const int xb0 = (item % groups_x) * RB, bh = item / groups_x;
+  const int b = bh / dm.heads, h = bh % dm.heads;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int l32 = lane % 32, hf = lane / 32;
+  const uint16_t* Xb = X + (int64_t)b * dm.sb + (int64_t)h * dm.sh;
+  int count[RB];                                 // rows of each token block (0: the block does not exist)
+#pragma unroll
+  for (int k = 0; k < RB; ++k) count[k] = xb0 + k < n_blocks_x ? dm.block_count(xb0 + k) : 0;
+
+  // Pooled vectors of the other side: fp16, in the layout of gate_operand_offset: of 32 consecutive vectors
+  // one k-step is 1 KB in a row, 16 bytes per lane
+  const uint16_t* PBh = PB + (size_t)bh * gate_operand_vectors(n_other) * D + 256 * hf;
+
+  // ---- stage the centred block: thread -> chunk column tid % CPR, rows tid / CPR + RPP*i ----
+  const int cc = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
+  u32x4 raw[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int k = i / PB_, r = r0 + RPP * (i % PB_);
+    const int xb = count[k] > 0 ? xb0 + k : xb0, cnt = count[k] > 0 ? count[k] : count[0];
+    const int rr = r < cnt ? r : cnt - 1;                        // stay inside the tensor; zeroed below
+    raw[i] = *reinterpret_cast<const u32x4*>(Xb + (dm.block_start(xb) + rr) * dm.st + 8 * cc);
+  }
+  // ---- query side: the key blocks whose bit is still open, each wave from a range of its own --------
+  constexpr int LM = GATE ? RSA_MAX_BLOCKS : 1;
+  __shared__ uint16_t list[LM];                                  // wave w's from w * range on
+  __shared__ uint32_t words[RB][LM / 32 + 1];                    // the mask words of the token blocks
+  __shared__ int list_n[NW];
+  const int range = (n_other + 64 * NW - 1) / (64 * NW) * 64;       // key blocks a wave looks at
+  const float* Srow = Spool + ((size_t)bh * n_blocks_x + xb0) * n_other;       // (of the first token block, like DBcol)
+  const float* DBrow = DB + ((size_t)bh * n_blocks_x + xb0) * n_other;
+  if constexpr (GATE) {
+    for (int i = threadIdx.x; i < RB * (LM / 32 + 1); i += NT) (&words[0][0])[i] = 0u;
+    const int base = wave * range;
+    int n = 0;
+    for (int c0 = 0; c0 < range; c0 += 64 * LU) {
+      float s[LU][RB], db[LU][RB];
+#pragma unroll
+      for (int u = 0; u < LU; ++u) {
+        const int m = base + c0 + 64 * u + lane, mm = m < n_other ? m : n_other - 1;
+#pragma unroll
+        for (int k = 0; k < RB; ++k) {
+          const int kk = count[k] > 0 ? k : 0;
+          s[u][k] = fabsf(Srow[(size_t)kk * n_other + mm]);
+          db[u][k] = DBrow[(size_t)kk * n_other + mm];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < LU; ++u) {
+        const int c = c0 + 64 * u + lane, m = base + c;
+        bool open = false;
+#pragma unroll
+        for (int k = 0; k < RB; ++k) open = open || s[u][k] > db[u][k];
+        open = open && c < range && m < n_other;
+        const unsigned long long set = __ballot(open);
+        if (open) list[base + n + __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0u))] = (uint16_t)m;
+        n += __popcll(set);
+      }
+    }
+    if (lane == 0) list_n[wave] = n;
+  }
+  {
+    floatx4 m0[RB], m1[RB];
+    if constexpr (!GATE) {
+      static_assert(RB * RPP * D * 4 <= kDevRows * CPR * 16 && RB * D <= NT, "the partial sums fit the tile");
+      __shared__ __align__(16) float mean_lds[RB][D];
+      float (*red)[RPP][D] = reinterpret_cast<float (*)[RPP][D]>(atile);   // the tile is written after the sums have been read
+#pragma unroll
+      for (int k = 0; k < RB; ++k) {
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < PB_; ++i) {
+          const u32x4 x = raw[k * PB_ + i];
+          uint4 v = make_uint4(0, 0, 0, 0);
+          if (r0 + RPP * i < count[k]) v = make_uint4(x.x, x.y, x.z, x.w);
+          accumulate8(acc, v);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red[k][r0][cc * 8 + e] = acc[e];
+      }
+      __syncthreads();
+      if (threadIdx.x < RB * D) {
+        const int k = threadIdx.x / D, c = threadIdx.x % D;
+        const int cnt = k == 0 ? count[0] : count[RB - 1];
+        if (cnt > 0) {
+          float sum = 0.f;
+#pragma unroll
+          for (int r = 0; r < RPP; ++r) sum += red[k][r][c];
+          const float mean = sum / (float)cnt;
+          mean_lds[k][c] = mean;
+          Xpool_out[((size_t)bh * n_blocks_x + xb0 + k) * D + c] = mean;
+          Xpool_f16_out[(size_t)bh * gate_operand_vectors(n_blocks_x) * D + gate_operand_offset<D>(xb0 + k, c)] = to_f16_bits_sat(mean);
+        } else {
+          mean_lds[k][c] = 0.f;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < RB; ++k) {
+        m0[k] = *reinterpret_cast<const floatx4*>(&mean_lds[k][8 * cc]);
+        m1[k] = *reinterpret_cast<const floatx4*>(&mean_lds[k][8 * cc + 4]);
+      }
+      __syncthreads();                                             // every read of the sums is done
+    } else {
+#pragma unroll
+      for (int k = 0; k < RB; ++k) {
+        const float* mp = Xpool + ((size_t)bh * n_blocks_x + (count[k] > 0 ? xb0 + k : xb0)) * D + 8 * cc;
+        m0[k] = *reinterpret_cast<const floatx4*>(mp);
+        m1[k] = *reinterpret_cast<const floatx4*>(mp + 4);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int k = i / PB_, r = r0 + RPP * (i % PB_);
+      u32x4 c;
+      c.x = pack_f16x2_sat(bf16_bits_to_float(raw[i].x & 0xffffu) - m0[k][0], bf16_bits_to_float(raw[i].x >> 16) - m0[k][1]);
+      c.y = pack_f16x2_sat(bf16_bits_to_float(raw[i].y & 0xffffu) - m0[k][2], bf16_bits_to_float(raw[i].y >> 16) - m0[k][3]);
+      c.z = pack_f16x2_sat(bf16_bits_to_float(raw[i].z & 0xffffu) - m1[k][0], bf16_bits_to_float(raw[i].z >> 16) - m1[k][1]);
+      c.w = pack_f16x2_sat(bf16_bits_to_float(raw[i].w & 0xffffu) - m1[k][2], bf16_bits_to_float(raw[i].w >> 16) - m1[k][3]);
+      if (r >= count[k]) c = u32x4{0u, 0u, 0u, 0u};              // rows past a ragged block contribute nothing
+      atile[swizzled<CPR>(k * BLK + r, cc)] = c;
+    }
+  }
+  __syncthreads();
+  const u32x4* arow = atile + l32 * CPR;
+  const int akey = (l32 / (16 / CPR)) & (CPR - 1);     // (the same for every row tile: 32 rows are whole periods of the key)
+
+  float outscale[RB];
+#pragma unroll
+  for (int k = 0; k < RB; ++k) outscale[k] = dm.scale / (float)count[k];
+  int n_cols = n_other, seg1 = 0, seg2 = 0, seg3 = 0;   // columns, and where the lists of waves 1 .. 3 start among them
+  if constexpr (GATE) {
+    seg1 = __builtin_amdgcn_readfirstlane(list_n[0]);
+    seg2 = seg1 + __builtin_amdgcn_readfirstlane(list_n[1]);
+    seg3 = seg2 + __builtin_amdgcn_readfirstlane(list_n[2]);
+    n_cols = seg3 + __builtin_amdgcn_readfirstlane(list_n[3]);
+  }
+  auto block_of = [&](int j) __attribute__((always_inline)) {        // pooled vector of column j
+    j = j < n_cols ? j : n_cols - 1;               // (columns past the end repeat the last one; their results are not used)
+    if (!GATE) return j;
+    return (int)list[j < seg1 ? j : j < seg2 ? j - seg1 + range : j < seg3 ? j - seg2 + 2 * range : j - seg3 + 3 * range];
+  };
+  // the B operand of an iteration: lane (l32, hf) supplies channels 16s + 8hf .. +7 of column o0 + l32 in k-step s
+  auto vector_of = [&](int o0) __attribute__((always_inline)) {
+    const int m = block_of(o0 + l32);
+    return PBh + (size_t)(m / 32) * (KS * 512) + (m % 32) * 8;
+  };
+  u32x4 bv[KS];
+  u32x4 av[2][TP];
+  auto load_a = [&](int set, int step) __attribute__((always_inline)) {        // step: pass * KS + k-step
+    const u32x4* p = arow + ((2 * (step % KS) + hf) ^ akey) + (step / KS) * (TP * 32 * CPR);
+#pragma unroll
+    for (int t = 0; t < TP; ++t) av[set][t] = p[t * 32 * CPR];
+  };
+  // 32 columns of the wave against the 128 rows, TP row tiles at a time. The A operand (rows) of a k-step is read
+  // from LDS a k-step ahead; a register of B is reloaded for the next iteration as soon as its last k-step is done.
+  auto iteration = [&](int o0, auto morec) __attribute__((always_inline)) {
+    constexpr bool more = decltype(morec)::value != 0;
+    constexpr int NPASS = MT / TP;
+    const uint16_t* pn = nullptr;
+    if constexpr (more) pn = vector_of(o0 + kDevCols);
+    const int j = o0 + l32;                        // this lane's column
+    int m = 0;
+    float s_val[RB], db_val[RB];
+    if constexpr (GATE) {
+      m = block_of(j);
+#pragma unroll
+      for (int k = 0; k < RB; ++k) {
+        const int kk = count[k] > 0 ? k : 0;
+        s_val[k] = Srow[(size_t)kk * n_other + m];
+        db_val[k] = DBrow[(size_t)kk * n_other + m];
+      }
+    }
+    float dv4[4];                                  // four partial sums: no long chain of dependent adds
+#pragma unroll
+    for (int pass = 0; pass < NPASS; ++pass) {
+      floatx16 acc[TP];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        asm volatile("" ::: "memory");      // the A operand is re-read every iteration: no hoisting into registers
+        load_a((pass * KS + s + 1) % 2, (pass * KS + s + 1) % (NPASS * KS));
+#pragma unroll
+        for (int t = 0; t < TP; ++t) {
+          floatx16 c0 = acc[t];
+          if (s == 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c0[r] = 0.f;
+          }
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, av[(pass * KS + s) % 2][t]),
+                                                          __builtin_bit_cast(halfx8, bv[s]), c0, 0, 0, 0);
+        }
+        if constexpr (more) {
+          if (pass == NPASS - 1) bv[s] = *reinterpret_cast<const u32x4*>(pn + 512 * s);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // every accumulator of a lane belongs to its column; its rows are spread over the registers, the row
+      // tiles of the block and the two half-waves
+#pragma unroll
+      for (int t = 0; t < TP; ++t) {
+        const int tile = pass * TP + t;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dv4[r % 4] = (tile % TB == 0 && r < 4 ? 0.f : dv4[r % 4]) + fabsf(acc[t][r]);
+        if (tile % TB == TB - 1) {
+          const int k = tile / TB;
+          float dv = (dv4[0] + dv4[1]) + (dv4[2] + dv4[3]);
+          dv += __shfl_xor(dv, 32);
+          if constexpr (GATE) {
+            if (hf == 0 && j < n_cols && fabsf(s_val[k]) > dv * outscale[k] + db_val[k]) atomicOr(&words[k][m / 32], 1u << (m % 32));
+          } else {
+            // transposed, [N][M]: the query side reads whole rows. The stores are 4 bytes each, but the key blocks of
+            // a line are neighbours and meet in the L2 of their XCD.
+            if (hf == 0 && j < n_cols && count[k] > 0) out[((size_t)bh * n_other + j) * n_blocks_x + xb0 + k] = dv * outscale[k];
+          }
+        }
+      }
+    }
+  };
+  int o0 = 32 * wave;
+  if (o0 < n_cols) {
+    const uint16_t* p = vector_of(o0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) bv[s] = *reinterpret_cast<const u32x4*>(p + 512 * s);
+    load_a(0, 0);
+    for (; o0 + kDevCols < n_cols; o0 += kDevCols) iteration(o0, std::integral_constant<int, 1>{});
+    iteration(o0, std::integral_constant<int, 0>{});
+  }
+  if constexpr (GATE) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < RB * dm.w; i += NT) {
+      const int k = i / dm.w, w = i % dm.w;
+      if (xb0 + k < n_blocks_x) Mc_bits[((size_t)bh * n_blocks_x + xb0 + k) * dm.w + w] = words[k][w];
+    }
+  }
+}
+
 __global__ void fill_bits_kernel(Dims dm, uint32_t* bits, uint32_t value) {
   const size_t total = (size_t)dm.batch * dm.heads * dm.n * dm.w;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
@@ -220,24 +506,27 @@ __global__ void fill_bits_kernel(Dims dm, uint32_t* bits, uint32_t value) {
 
 template <int D, int BLK>
 hipError_t launch_gapr_keys_t(const Dims& dm, const GaprArgs& a, hipStream_t s) {
-  const int bh = dm.batch * dm.heads;
-  constexpr int NT = RSA_DEV_NT;
-  // DBt [M][N] to the workspace
-  if (a.Kp_out)
-    hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, false, true>), dim3(dm.m * bh), dim3(NT), 0, s, dm, a.K, nullptr, a.Kp_out,
-                       a.Kpb_out, dm.m, a.Qpb, dm.n, a.DBt, nullptr, nullptr, nullptr);
+  const unsigned bh = (unsigned)(dm.batch * dm.heads);
+  constexpr unsigned NT = RSA_DEV_NT, RB = kDevRows / BLK;
+  if (use_long_rows(dm))
+    hipLaunchKernelGGL((deviation_long_kernel<D, BLK, false>), dim3((dm.m + RB - 1) / RB * bh), dim3(kDevThreads), 0, s, dm, a.K,
+                       nullptr, a.Kp_out, a.Kpb_out, dm.m, a.Qpb, dm.n, a.DB, nullptr, nullptr, nullptr);
   else
-    hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, false, false>), dim3(dm.m * bh), dim3(NT), 0, s, dm, a.K, a.Kp, nullptr,
-                       nullptr, dm.m, a.Qpb, dm.n, a.DBt, nullptr, nullptr, nullptr);
+    hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, false>), dim3(dm.m * bh), dim3(NT), 0, s, dm, a.K, nullptr, a.Kp_out,
+                       a.Kpb_out, dm.m, a.Qpb, dm.n, a.DB, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
+// turns its deviations into the bits of M_c on the spot
 template <int D, int BLK>
 hipError_t launch_gapr_queries_t(const Dims& dm, const GaprArgs& a, hipStream_t s) {
-  const int bh = dm.batch * dm.heads;
-  constexpr int NT = RSA_DEV_NT;
-  // turns its deviations into the bits of M_c on the spot
-  hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, true, false>), dim3(dm.n * bh), dim3(NT), 0, s, dm, a.Q, a.Qp, nullptr, nullptr,
-                     dm.n, a.Kpb, dm.m, nullptr, a.Spool, a.DBt, a.Mc_bits);
+  const unsigned bh = (unsigned)(dm.batch * dm.heads);
+  constexpr unsigned NT = RSA_DEV_NT, RB = kDevRows / BLK;
+  if (use_long_rows(dm))
+    hipLaunchKernelGGL((deviation_long_kernel<D, BLK, true>), dim3((dm.n + RB - 1) / RB * bh), dim3(kDevThreads), 0, s, dm, a.Q, a.Qp,
+                       nullptr, nullptr, dm.n, a.Kpb, dm.m, nullptr, a.Spool, a.DB, a.Mc_bits);
+  else
+    hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, true>), dim3(dm.n * bh), dim3(NT), 0, s, dm, a.Q, a.Qp, nullptr, nullptr,
+                       dm.n, a.Kpb, dm.m, nullptr, a.Spool, a.DB, a.Mc_bits);
   return hipGetLastError();
 }
 
@@ -257,13 +546,9 @@ hipError_t launch_gapr_queries(const Dims& dm, const GaprArgs& a, hipStream_t s)
   return launch_gapr_queries_t<64, 64>(dm, a, s);
 }
 
-hipError_t launch_gapr(const Dims& dm, const GaprArgs& a, hipStream_t s) {
-  if (a.mode != 1) {
-    hipLaunchKernelGGL(fill_bits_kernel, dim3(256), dim3(256), 0, s, dm, a.Mc_bits, a.mode == 2 ? 0xffffffffu : 0u);
-    return hipGetLastError();
-  }
-  const hipError_t e = launch_gapr_keys(dm, a, s);
-  return e != hipSuccess ? e : launch_gapr_queries(dm, a, s);
+hipError_t launch_gapr_constant(const Dims& dm, const GaprArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(fill_bits_kernel, dim3(256), dim3(256), 0, s, dm, a.Mc_bits, a.mode == 2 ? 0xffffffffu : 0u);
+  return hipGetLastError();
 }
 
 }  // namespace rsa

@@ -202,11 +202,11 @@ int rsa_pool(const rsa_shape* shape, const void* Q, const void* K, const void* V
   pa.text_K = (const uint16_t*)K; pa.text_Lmass = Lmass;     // the text log-masses ride with the pooling of V
   if (rsa::launch_pool(d, pa, s) != hipSuccess) return RSA_E_LAUNCH;
 
-  rsa::GaprArgs ga;
+  rsa::GaprArgs ga = {};
   ga.Q = (const uint16_t*)Q; ga.K = (const uint16_t*)K;
-  ga.Qp = Qp; ga.Kp = Kp;
+  ga.Qp = Qp;
   ga.Qpb = pa.Qpb; ga.Kpb = pa.Kpb; ga.Spool = Spool;
-  ga.DBt = (float*)(wsb + wl.dbt);
+  ga.DB = (float*)(wsb + wl.dbt);
   ga.Mc_bits = Mc_bits; ga.mode = gapr_mode;
   if (gapr_mode == 1) {
     ga.Kp_out = Kp; ga.Kpb_out = pa.Kpb;
@@ -223,7 +223,7 @@ int rsa_pool(const rsa_shape* shape, const void* Q, const void* K, const void* V
     if (rsa::launch_gapr_queries(d, ga, s) != hipSuccess) return RSA_E_LAUNCH;
     return RSA_OK;
   }
-  if (rsa::launch_gapr(d, ga, s) != hipSuccess) return RSA_E_LAUNCH;
+  if (rsa::launch_gapr_constant(d, ga, s) != hipSuccess) return RSA_E_LAUNCH;
   return RSA_OK;
 }
 

@@ -99,21 +99,21 @@ hipError_t launch_scores(const Dims& dm, const ScoreArgs& a, hipStream_t s);
 
 struct GaprArgs {
   const uint16_t *Q, *K;
-  const float *Qp, *Kp;    // fp32 pooled vectors (the centre of each token block)
+  const float* Qp;         // fp32 pooled queries (the centre of each query block)
   const uint16_t *Qpb, *Kpb;
   const float* Spool;
-  float* DBt;              // key-side deviations, [b][h][M][N] (workspace)
+  float* DB;               // key-side deviations (workspace): [b][h][M][N], or [b][h][N][M] for many long rows
   uint32_t* Mc_bits;
   int mode;
-  float* Kp_out = nullptr;       // launch_gapr_keys: pooled keys, written by the launch that reads the key blocks anyway
-  uint16_t* Kpb_out = nullptr;
+  float* Kp_out;           // pooled keys and their fp16 copies, written by the launch that reads the key blocks anyway
+  uint16_t* Kpb_out;
 };
-// mode 1 is two launches with the pooled scores between them: the key side (needs Qpb; writes DBt and, when
-// Kp_out is set, the pooled keys) and the query side (needs Kpb, Spool, DBt; writes Mc_bits). launch_gapr runs
-// both (pooled keys given), or fills Mc_bits for the other modes.
+// mode 1 is two launches with the pooled scores between them: the key side (needs Qpb; writes DB and the pooled
+// keys) and the query side (needs Kpb, Spool, DB; writes Mc_bits). launch_gapr_constant fills Mc_bits for the
+// other modes.
 hipError_t launch_gapr_keys(const Dims& dm, const GaprArgs& a, hipStream_t s);
 hipError_t launch_gapr_queries(const Dims& dm, const GaprArgs& a, hipStream_t s);
-hipError_t launch_gapr(const Dims& dm, const GaprArgs& a, hipStream_t s);
+hipError_t launch_gapr_constant(const Dims& dm, const GaprArgs& a, hipStream_t s);
 
 struct SelectArgs {
   const float *Lmass, *Apool;

@@ -736,6 +736,43 @@ def test_implicit_attention_at_the_edges_of_its_tiles(gpu, d, block, blocks, t_t
         assert not bad.any(), (name, int(bad.sum()), bad.nonzero()[0].tolist())
 
 
+@pytest.mark.parametrize("d,block,grid,t_text", [
+    (128, 128, (14, 88, 79), 1100), (64, 128, (14, 88, 79), 901), (128, 64, (7, 88, 79), 600), (64, 64, (7, 88, 80), 1)])
+def test_gate_bits_of_long_rows(gpu, d, block, grid, t_text):
+    """The gate of many long rows (the query side multiplies the key blocks that the key side
+    left open), a ragged last video block, an odd number of blocks and one or more text blocks, against the same
+    terms in fp64 from the kernel's own pooled vectors; bits may differ inside the band stated in parity.py."""
+    import parity
+    import torch
+    from paper_2511_19835_amd import binding as rb
+    cfg = LayerConfig("long", 1, 3, d, grid, t_text, block, 0.9)
+    assert cfg.n_blocks > 544
+    Qb, Kb, Vb = synth.make_inputs(cfg, 4)
+    Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
+    buf = rb.allocate(Q, cfg.t_video, cfg.t_text, cfg.block)
+    buf.Mc_bits.fill_(-1)
+    rb.rsa_pool(buf.shape, Q, K, V, buf.Qp, buf.Kp, buf.Vp, buf.Vt, buf.Spool, buf.Apool, buf.Lmass, buf.Mc_bits, 1,
+                buf.pool_ws)
+    torch.cuda.synchronize()
+    N, M, tv = buf.N, buf.M, cfg.t_video
+    start = [n * block for n in range(N)] + [tv + i * block for i in range(M - N)]
+    stop = [min(s + block, tv if i < N else tv + t_text) for i, s in enumerate(start)]
+    words = torch.arange(M, device="cuda")
+    assert 3 * ((N * block + 127) // 128) > 1024
+    for h in (0, 2):
+        qp, kp = buf.Qp[0, h].double(), buf.Kp[0, h].double()
+        scale = d ** -0.5
+        DA = torch.stack([((Q[0, h, start[n]:stop[n]].double() - qp[n]) @ kp.T.contiguous()).abs().mean(0) for n in range(N)])
+        DB = torch.stack([((K[0, h, start[m]:stop[m]].double() - kp[m]) @ qp.T.contiguous()).abs().mean(0) for m in range(M)], 1)
+        G, E = (qp @ kp.T.contiguous()).abs() * scale, (DA + DB) * scale
+        bits = ((buf.Mc_bits[0, h][:, words // 32] >> (words % 32)) & 1).bool()
+        wrong = (bits != (G > E)) & ((G - E).abs() > parity.GATE_BAND * torch.maximum(G, E))
+        assert not wrong.any(), (h, int(wrong.sum()), wrong.nonzero()[0].tolist())
+        assert 0.02 < float((G > E).double().mean()) < 0.98 and float((G <= DB * scale).double().mean()) > 0.02
+        if M % 32:
+            assert not ((buf.Mc_bits[0, h][:, -1].to(torch.int64) & 0xffffffff) >> (M % 32)).any()
+
+
 def test_pooled_tensors_do_not_depend_on_the_gate_mode(gpu):
     """With the gate on, k^pool comes from the key-side deviation launch instead of the pooling kernel:
     every pooled tensor and the implicit attention must be bit for bit what gapr_mode 0 (no gate GEMMs,
