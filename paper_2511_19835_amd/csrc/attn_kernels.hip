@@ -39,6 +39,7 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 #ifndef RSA_NSTAGE
 #define RSA_NSTAGE 2
 #endif
@@ -452,7 +453,22 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       p[BLK * D + BLK + wave * 32 + ln] = mref;
     }
   };
+  Tile vt_next = {};          // the tile of step s+1 as M(s) prepared it: its V^T rows are requested in V(s)
+  // The rows of O go out whole: an accumulator lane holds four channels of one row at a time, and stored like that
+  // (8 bytes of 32 rows per instruction) an item kept the address unit of the CU busy for 16 x 32 lines and wave. So
+  // half of the channels at a time is turned through LDS: the V^T stage of step s+1 is free here (its last tile was
+  // read a whole step ago, and its next is requested behind the output), and a wave uses only the 1 KB pieces that
+  // its own requests fill, so no other wave can get in the way. 16-byte chunk c of row r lies at chunk c ^ row_key(r).
+  // (24 heads of 159 blocks, lists of 16: layer 684 -> 680 us; 2 x 12 heads of 160, d = 64: 860 -> 848; 24 heads of
+  // 1182 blocks of 64: 11164 -> 11090; the longer the lists the less: 24 heads of 931, lists of 94: 17295 -> 17277.)
+  constexpr int ROWB = D;                          // bytes of half a row
+  constexpr int RCH = ROWB / 16, RPC = 1024 / ROWB;   // chunks of half a row, rows per piece
+  static_assert(VOFF == 1 && C::VPW * 1024 == 32 * ROWB, "a wave's own pieces of a V^T stage hold half of its 32 rows");
+  auto row_key = [](int r) __attribute__((always_inline)) { return (r / (256 / ROWB)) % RCH; };
   auto write_rows = [&]() __attribute__((always_inline)) {
+    typedef u32x2 __attribute__((address_space(3))) lds_u32x2;
+    typedef u32x4 __attribute__((address_space(3))) lds_u32x4;
+    typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(4)));
     const bool do_comp = done_sparse && (a.flags & RSA_COMPENSATE);
     const int q_count = done_q_count;
     const float lsum = half_wave_sum(lpart);
@@ -460,36 +476,55 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     const int hf = ln / 32;                        // (a copy of its own: see lane_now)
     const int q = wave * 32 + ln % 32;
     const float f = done_rfac / lsum;
-    uint16_t* orow = a.O + done_qo_off + (int64_t)q * dm.st;
     const int hf_lane4 = (4 * hf / CV) * 4;        // byte address of lane (4 hf)/CV for the crossbar
+    const int wrow = ln % 32, wkey = row_key(wrow);
+    const uint32_t wbase = vt_next.vdst + (wrow / RPC) * V_LDS_PASS + (wrow % RPC) * ROWB + 8 * hf;
+    const int rsub = ln / RCH;                     // row of a piece that this lane stores
+    // (rows of one block: 32-bit byte offsets from the block's first row)
+    char* obase = reinterpret_cast<char*>(a.O + done_qo_off);
+    const uint32_t row_bytes = (uint32_t)dm.st * 2u;
+    const uint32_t ooff = (uint32_t)(wave * 32 + rsub) * row_bytes;
 #pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) {
-      // the 16 elements of C_n that go with this accumulator tile, all requested before the first is used
-      // (element 32 dt + 8 g + 4 hf + e; every lane takes part: one outside the block still lends its share)
-      float cadd[16];
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) cadd[r] = 0.f;
-      if (do_comp) {
+      for (int d2 = 0; d2 < C::DT / 2; ++d2) {
+        const int dt = half * (C::DT / 2) + d2;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int dc = 32 * dt + 8 * (r / 4) + (r % 4);        // + 4 hf: a multiple of CV
-          const int c = __builtin_amdgcn_ds_bpermute(hf_lane4 + (dc / CV) * 4, __builtin_bit_cast(int, done_comp[dc % CV]));
-          cadd[r] = __builtin_bit_cast(float, c);
+        for (int g0 = 0; g0 < 4; g0 += 2) {
+          // the elements of C_n that go with these accumulators, all requested before the first is used
+          // (element 32 dt + 8 g + 4 hf + e; every lane takes part: one outside the block still lends its share)
+          float cadd[8];
+#pragma unroll
+          for (int r = 0; r < 8; ++r) cadd[r] = 0.f;
+          if (do_comp) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+              const int dc = 32 * dt + 8 * (g0 + r / 4) + (r % 4);   // + 4 hf: a multiple of CV
+              const int c = __builtin_amdgcn_ds_bpermute(hf_lane4 + (dc / CV) * 4, __builtin_bit_cast(int, done_comp[dc % CV]));
+              cadd[r] = __builtin_bit_cast(float, c);
+            }
+          }
+#pragma unroll
+          for (int g = g0; g < g0 + 2; ++g) {
+            float o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(oacc[dt][4 * g + e], f, cadd[4 * (g - g0) + e]);
+            u32x2 w;
+            w.x = pack_bf16x2(o[0], o[1]);
+            w.y = pack_bf16x2(o[2], o[3]);
+            *(lds_u32x2*)(uintptr_t)(wbase + (((4 * d2 + g) ^ wkey) * 16)) = w;
+          }
         }
       }
+      asm volatile("" ::: "memory");               // (LDS instructions of a wave run in order)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int d0 = 32 * dt + 8 * g + 4 * hf;
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = fmaf(oacc[dt][4 * g + e], f, cadd[4 * g + e]);
-        if (q < q_count) {
-          uint2 w;
-          w.x = pack_bf16x2(o[0], o[1]);
-          w.y = pack_bf16x2(o[2], o[3]);
-          *reinterpret_cast<uint2*>(orow + d0) = w;
-        }
+      for (int i = 0; i < C::VPW; ++i) {
+        const int r = i * RPC + rsub;
+        const u32x4 v = *(const lds_u32x4*)(uintptr_t)(vt_next.vdst + i * V_LDS_PASS + ln * 16);
+        if (wave * 32 + r < q_count)
+          *reinterpret_cast<u32x4_u*>(obase + (ooff + (uint32_t)(i * RPC) * row_bytes + half * ROWB + 16 * ((ln % RCH) ^ row_key(r)))) = v;
       }
+      asm volatile("" ::: "memory");
     }
     if (q < q_count && a.lse && hf == 0)
       a.lse[((size_t)done_bh * dm.t) + done_q_t0 + q] = (mref + log2f(lsum)) * 0.6931471805599453f;
@@ -548,7 +583,6 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 #pragma unroll
   for (int i = 0; i < W; ++i) ring[i] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
   int vst = 0;                // V^T ring stage of the current step (s % VSTAGES)
-  Tile vt_next = {};          // the tile of step s+1 as M(s) prepared it: its V^T rows are requested in V(s)
   const u32x4* vcur[C::PC];   // vread[] moved to the V^T stage whose P V product comes next
 #pragma unroll
   for (int pc = 0; pc < C::PC; ++pc) vcur[pc] = vread[pc];
