@@ -736,6 +736,35 @@ def test_implicit_attention_at_the_edges_of_its_tiles(gpu, d, block, blocks, t_t
         assert not bad.any(), (name, int(bad.sum()), bad.nonzero()[0].tolist())
 
 
+@pytest.mark.parametrize("blocks", [1, 256, 257, 512, 513, 768, 769, 1024, 1025, 1280, 1281, 2048, 2049])
+def test_selection_at_the_ends_of_its_row_lengths(gpu, blocks):
+    """rsa_select_blocks alone at the row lengths where the number of registers per lane changes: whole numbers, so
+    the kept blocks must be exactly those of a stable sort (ties: lower block index); half of the rows full of ties."""
+    import torch
+    from paper_2511_19835_amd import binding as rb
+    q = torch.zeros(1, 1, blocks * 64, 64, dtype=torch.bfloat16, device="cuda")
+    buf = rb.allocate(q, blocks * 64, 0, 64)
+    rng = np.random.default_rng(blocks)
+    L = rng.normal(0.0, 3.0, (blocks, blocks)).astype(np.float32)
+    L[::2] = np.round(L[::2])
+    A = rng.random((blocks, blocks), dtype=np.float32)
+    buf.Lmass.copy_(torch.from_numpy(L)[None, None])
+    buf.Apool.copy_(torch.from_numpy(A)[None, None])
+    rb.rsa_select_blocks(buf.shape, buf.Lmass, buf.Apool, 0.8, 0.0, None, buf.mask_bits, buf.block_idx, buf.count, buf.R)
+    torch.cuda.synchronize()
+    keep = max(1, blocks - int(np.floor(0.8 * blocks + 1e-6)))
+    want = np.sort(np.argsort(-L, axis=1, kind="stable")[:, :keep], axis=1)
+    assert (buf.count.cpu().numpy() == keep).all()
+    np.testing.assert_array_equal(buf.block_idx[0, 0].cpu().numpy()[:, :keep], want)
+    mask = np.zeros((blocks, blocks), dtype=bool)
+    np.put_along_axis(mask, want, True, axis=1)
+    words = buf.mask_bits[0, 0].cpu().numpy().view(np.uint32)
+    bits = (words[:, np.arange(blocks) // 32] >> (np.arange(blocks) % 32).astype(np.uint32)) & 1
+    np.testing.assert_array_equal(bits.astype(bool), mask)
+    # a sum of `keep` fp32 terms in any order: keep u relative
+    np.testing.assert_allclose(buf.R[0, 0].cpu().numpy(), (A.astype(np.float64) * mask).sum(1), rtol=(keep + 1) * 2.0 ** -24)
+
+
 @pytest.mark.parametrize("d,block,grid,t_text", [
     (128, 128, (14, 88, 79), 1100), (64, 128, (14, 88, 79), 901), (128, 64, (7, 88, 79), 600), (64, 64, (7, 88, 80), 1)])
 def test_gate_bits_of_long_rows(gpu, d, block, grid, t_text):
