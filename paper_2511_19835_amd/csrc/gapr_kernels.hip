@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "rsa_common.hpp"
+#include "text_mass.hpp"
 
 namespace rsa {
 namespace {
@@ -45,6 +46,19 @@ __device__ __forceinline__ int swizzled(int r, int c) { return r * CPR + (c ^ ((
 #ifndef RSA_DEV_OCC
 #define RSA_DEV_OCC 3
 #endif
+// The first workgroups of a key-side launch, `text_wgs` for every (batch, head), make the text log-masses (they need
+// the pooled queries, like this launch, and the implicit attention that follows needs them). Counts them off `wg`.
+template <int D, int BLK>
+__device__ __forceinline__ bool text_block(const Dims& dm, const ScoreArgs& text, int text_wgs, int& wg, float* lds) {
+  const int all = text_wgs * dm.batch * dm.heads;
+  if (wg < all) {
+    text_mass_block<D, BLK>(dm, text, wg % text_wgs, wg / text_wgs, lds);
+    return true;
+  }
+  wg -= all;
+  return false;
+}
+
 // GATE: the launch for the query side, run second. Its deviations DA[n][.] never leave the registers:
 // with the pooled score S[n][m] and the key-side deviation DBt[m][n] of the first launch (one word each
 // per lane and iteration, asked for at the start of the iteration) the lane decides its bit of M_c, and
@@ -61,7 +75,7 @@ __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, con
                                                            int n_other, float* __restrict__ out,
                                                            const float* __restrict__ Spool,
                                                            const float* __restrict__ DBt,
-                                                           uint32_t* __restrict__ Mc_bits) {
+                                                           uint32_t* __restrict__ Mc_bits, ScoreArgs text, int text_wgs) {
   constexpr int MT = BLK / 32, KS = D / 16, CPR = D / 8;
   constexpr int NW = NT / 64;                    // waves per workgroup
   constexpr int RPP = NT / CPR;                  // rows staged per pass of the workgroup
@@ -71,8 +85,12 @@ __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, con
   // query side reads DBt[m][n] for a fixed n, 32 neighbouring n to a 128-byte line, which then
   // comes into one L2 once instead of into all eight.
   const int total = n_blocks_x * dm.batch * dm.heads;
-  const int xcd = blockIdx.x % 8, q8 = total / 8, r8 = total % 8;
-  const int item = xcd * q8 + (xcd < r8 ? xcd : r8) + (int)blockIdx.x / 8;
+  int wg = blockIdx.x;
+  if constexpr (!GATE) {
+    if (text_block<D, BLK>(dm, text, text_wgs, wg, reinterpret_cast<float*>(atile))) return;
+  }
+  const int xcd = wg % 8, q8 = total / 8, r8 = total % 8;
+  const int item = xcd * q8 + (xcd < r8 ? xcd : r8) + wg / 8;
   const int xb = item % n_blocks_x, bh = item / n_blocks_x;
   const int b = bh / dm.heads, h = bh % dm.heads;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
@@ -239,7 +257,7 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
                                                           int n_other, float* __restrict__ out,
                                                           const float* __restrict__ Spool,
                                                           const float* __restrict__ DB,
-                                                          uint32_t* __restrict__ Mc_bits) {
+                                                          uint32_t* __restrict__ Mc_bits, ScoreArgs text, int text_wgs) {
   constexpr int NT = kDevThreads, NW = kDevWaves;
   constexpr int MT = kDevRows / 32, KS = D / 16, CPR = D / 8;
   constexpr int RB = kDevRows / BLK;             // token blocks of the workgroup
@@ -255,8 +273,12 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
   // comes into one L2 once instead of into all eight.
   const int groups_x = (n_blocks_x + RB - 1) / RB;
   const int total = groups_x * dm.batch * dm.heads;
-  const int xcd = blockIdx.x % 8, q8 = total / 8, r8 = total % 8;
-  const int item = xcd * q8 + (xcd < r8 ? xcd : r8) + (int)blockIdx.x / 8;
+  int wg = blockIdx.x;
+  if constexpr (!GATE) {
+    if (text_block<D, BLK>(dm, text, text_wgs, wg, reinterpret_cast<float*>(atile))) return;
+  }
+  const int xcd = wg % 8, q8 = total / 8, r8 = total % 8;
+  const int item = xcd * q8 + (xcd < r8 ? xcd : r8) + wg / 8;
   const int xb0 = (item % groups_x) * RB, bh = item / groups_x;
   const int b = bh / dm.heads, h = bh % dm.heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
@@ -508,12 +530,15 @@ template <int D, int BLK>
 hipError_t launch_gapr_keys_t(const Dims& dm, const GaprArgs& a, hipStream_t s) {
   const unsigned bh = (unsigned)(dm.batch * dm.heads);
   constexpr unsigned NT = RSA_DEV_NT, RB = kDevRows / BLK;
+  ScoreArgs text = {};
+  text.K = a.K; text.Qp = a.Qp; text.Lmass = a.text_Lmass;
+  const int text_wgs = a.text_Lmass ? text_mass_workgroups(dm) : 0;
   if (use_long_rows(dm))
-    hipLaunchKernelGGL((deviation_long_kernel<D, BLK, false>), dim3((dm.m + RB - 1) / RB * bh), dim3(kDevThreads), 0, s, dm, a.K,
-                       nullptr, a.Kp_out, a.Kpb_out, dm.m, a.Qpb, dm.n, a.DB, nullptr, nullptr, nullptr);
+    hipLaunchKernelGGL((deviation_long_kernel<D, BLK, false>), dim3(((dm.m + RB - 1) / RB + text_wgs) * bh), dim3(kDevThreads), 0, s, dm,
+                       a.K, nullptr, a.Kp_out, a.Kpb_out, dm.m, a.Qpb, dm.n, a.DB, nullptr, nullptr, nullptr, text, text_wgs);
   else
-    hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, false>), dim3(dm.m * bh), dim3(NT), 0, s, dm, a.K, nullptr, a.Kp_out,
-                       a.Kpb_out, dm.m, a.Qpb, dm.n, a.DB, nullptr, nullptr, nullptr);
+    hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, false>), dim3((dm.m + text_wgs) * bh), dim3(NT), 0, s, dm, a.K, nullptr, a.Kp_out,
+                       a.Kpb_out, dm.m, a.Qpb, dm.n, a.DB, nullptr, nullptr, nullptr, text, text_wgs);
   return hipGetLastError();
 }
 // turns its deviations into the bits of M_c on the spot
@@ -523,10 +548,10 @@ hipError_t launch_gapr_queries_t(const Dims& dm, const GaprArgs& a, hipStream_t 
   constexpr unsigned NT = RSA_DEV_NT, RB = kDevRows / BLK;
   if (use_long_rows(dm))
     hipLaunchKernelGGL((deviation_long_kernel<D, BLK, true>), dim3((dm.n + RB - 1) / RB * bh), dim3(kDevThreads), 0, s, dm, a.Q, a.Qp,
-                       nullptr, nullptr, dm.n, a.Kpb, dm.m, nullptr, a.Spool, a.DB, a.Mc_bits);
+                       nullptr, nullptr, dm.n, a.Kpb, dm.m, nullptr, a.Spool, a.DB, a.Mc_bits, ScoreArgs{}, 0);
   else
     hipLaunchKernelGGL((deviation_kernel<D, BLK, NT, true>), dim3(dm.n * bh), dim3(NT), 0, s, dm, a.Q, a.Qp, nullptr, nullptr,
-                       dm.n, a.Kpb, dm.m, nullptr, a.Spool, a.DB, a.Mc_bits);
+                       dm.n, a.Kpb, dm.m, nullptr, a.Spool, a.DB, a.Mc_bits, ScoreArgs{}, 0);
   return hipGetLastError();
 }
 

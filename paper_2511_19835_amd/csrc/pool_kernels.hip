@@ -30,14 +30,14 @@ __device__ inline void finish_mean(float (*red)[D], const float (&acc)[8], int r
   }
 }
 
+// Block m of Q (which = 0) or K (1); `lds`: 256 / (D/8) rows of D floats.
 template <int D, int BLK>
-__global__ __launch_bounds__(256) void pool_qk_kernel(Dims dm, PoolArgs a) {
+__device__ __forceinline__ void pool_qk_block(const Dims& dm, const PoolArgs& a, int m, int bh, int which, float* lds) {
   constexpr int CPR = D / 8;      // 16-byte chunks per row
   constexpr int RPP = 256 / CPR;  // rows per pass
   constexpr int NPASS = BLK / RPP;
-  __shared__ float red[RPP][D];
-  const int m = blockIdx.x, bh = blockIdx.y, which = blockIdx.z;
-  if (which == 0 && m >= dm.n) return;  // pooled queries exist for video blocks only
+  float (*red)[D] = reinterpret_cast<float (*)[D]>(lds);
+  if (which == 0 && m >= dm.n) return;  // pooled queries exist for video blocks only (the whole workgroup)
   const int b = bh / dm.heads, h = bh % dm.heads;
   const uint16_t* X = (which == 0 ? a.Q : a.K) + (int64_t)b * dm.sb + (int64_t)h * dm.sh;
   const int64_t t0 = dm.block_start(m);
@@ -64,6 +64,12 @@ __global__ __launch_bounds__(256) void pool_qk_kernel(Dims dm, PoolArgs a) {
     finish_mean<D, RPP>(red, acc, r0, cc, count, a.Kp + row * D,
                         a.Kpb ? a.Kpb + (size_t)bh * gate_operand_vectors(dm.m) * D : nullptr, m);
   }
+}
+
+template <int D, int BLK>
+__global__ __launch_bounds__(256) void pool_qk_kernel(Dims dm, PoolArgs a) {
+  __shared__ float lds[256 / (D / 8) * D];
+  pool_qk_block<D, BLK>(dm, a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
 }
 
 // V: block mean plus the channel-major tile Vt[d][BLK]. Position 16c + 8h + 4g + e of a
@@ -148,9 +154,23 @@ __global__ __launch_bounds__(256) void pool_v_text_kernel(Dims dm, PoolArgs a, S
   pool_v_block<D, BLK>(dm, a, (int)blockIdx.x - text_wgs, blockIdx.y, lds);
 }
 
+// With the gate on, K is pooled by the key-side launch of the gate: Q and V in one launch, plane 0 and 1 of the grid,
+// unless the launch for V has much text to carry (text_rides_with_keys). Two launches take about 3 us more, the start of
+// one and the last round of the other: smallest call 43.7 -> 40.1 us, 24 heads of 159 blocks 680 -> 677.
+template <int D, int BLK>
+__global__ __launch_bounds__(256) void pool_qv_kernel(Dims dm, PoolArgs a) {
+  __shared__ uint32_t lds[PoolVLds<D, BLK>::WORDS];
+  if (blockIdx.z == 0) pool_qk_block<D, BLK>(dm, a, blockIdx.x, blockIdx.y, 0, reinterpret_cast<float*>(lds));
+  else pool_v_block<D, BLK>(dm, a, blockIdx.x, blockIdx.y, lds);
+}
+
 template <int D, int BLK>
 hipError_t launch_pool_t(const Dims& dm, const PoolArgs& a, hipStream_t s) {
   const dim3 block(256);
+  if (a.Q && a.skip_k && !a.text_K) {
+    hipLaunchKernelGGL((pool_qv_kernel<D, BLK>), dim3(dm.m, dm.batch * dm.heads, 2), block, 0, s, dm, a);
+    return hipGetLastError();
+  }
   if (a.Q && a.K)    // values only: the caller keeps the pooled queries / keys of an earlier call
     hipLaunchKernelGGL((pool_qk_kernel<D, BLK>), dim3(dm.m, dm.batch * dm.heads, a.skip_k ? 1 : 2), block, 0, s, dm, a);
   if (a.text_K && a.text_Lmass && a.Q && dm.tt > 0) {   // Qp is written by the launch above

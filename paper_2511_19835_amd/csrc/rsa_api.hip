@@ -4,6 +4,7 @@
 #include <atomic>
 
 #include "rsa_common.hpp"
+#include "text_mass.hpp"
 
 namespace {
 
@@ -199,7 +200,9 @@ int rsa_pool(const rsa_shape* shape, const void* Q, const void* K, const void* V
   pa.Kpb = (uint16_t*)(wsb + wl.kpb);
   // with the gate on, the launch that reads the key blocks for their deviations pools them as well
   pa.skip_k = gapr_mode == 1;
-  pa.text_K = (const uint16_t*)K; pa.text_Lmass = Lmass;     // the text log-masses ride with the pooling of V
+  // the text log-masses ride with that launch or with the pooling of V
+  const bool text_with_keys = gapr_mode == 1 && rsa::text_rides_with_keys(d);
+  if (!text_with_keys) { pa.text_K = (const uint16_t*)K; pa.text_Lmass = Lmass; }
   if (rsa::launch_pool(d, pa, s) != hipSuccess) return RSA_E_LAUNCH;
 
   rsa::GaprArgs ga = {};
@@ -209,7 +212,7 @@ int rsa_pool(const rsa_shape* shape, const void* Q, const void* K, const void* V
   ga.DB = (float*)(wsb + wl.dbt);
   ga.Mc_bits = Mc_bits; ga.mode = gapr_mode;
   if (gapr_mode == 1) {
-    ga.Kp_out = Kp; ga.Kpb_out = pa.Kpb;
+    ga.Kp_out = Kp; ga.Kpb_out = pa.Kpb; ga.text_Lmass = text_with_keys ? Lmass : nullptr;
     if (rsa::launch_gapr_keys(d, ga, s) != hipSuccess) return RSA_E_LAUNCH;
   }
 

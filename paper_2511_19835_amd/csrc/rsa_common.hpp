@@ -82,8 +82,8 @@ struct PoolArgs {
   uint16_t* Vt;
   uint16_t *Qpb, *Kpb;     // optional fp16 copies of the pooled vectors in gate_operand_offset layout
   bool skip_k = false;     // the pooled keys come from the key-side launch of the gate (launch_gapr_keys)
-  // when both are set (and Q is pooled by this call: the pooled queries are needed), the launch that pools V also
-  // writes the text columns of Lmass from the text keys of text_K
+  // when both are set (and Q is pooled by this call: the pooled queries are needed), the launch that pools V
+  // also writes the text columns of Lmass from the text keys of text_K
   const uint16_t* text_K = nullptr;
   float* text_Lmass = nullptr;
 };
@@ -107,9 +107,10 @@ struct GaprArgs {
   int mode;
   float* Kp_out;           // pooled keys and their fp16 copies, written by the launch that reads the key blocks anyway
   uint16_t* Kpb_out;
+  float* text_Lmass;       // Lmass, when the key-side launch is also to write its text columns
 };
-// mode 1 is two launches with the pooled scores between them: the key side (needs Qpb; writes DB and the pooled
-// keys) and the query side (needs Kpb, Spool, DB; writes Mc_bits). launch_gapr_constant fills Mc_bits for the
+// mode 1 is two launches with the pooled scores between them: the key side (needs Qp and Qpb; writes DB, the pooled
+// keys and, when asked, the text log-masses) and the query side (needs Kpb, Spool, DB; writes Mc_bits). launch_gapr_constant fills Mc_bits for the
 // other modes.
 hipError_t launch_gapr_keys(const Dims& dm, const GaprArgs& a, hipStream_t s);
 hipError_t launch_gapr_queries(const Dims& dm, const GaprArgs& a, hipStream_t s);

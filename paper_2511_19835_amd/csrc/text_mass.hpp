@@ -1,7 +1,8 @@
 // Log-masses of the text key blocks (paper Sec. 3.2, Sec. 4.1; Alg. 1 steps 5-7):
 //   Lmass[n][N+i] = log sum_{t in text block i} exp(scale * q^pool_n . k_t)
-// as a device function, because two launches carry it: text_mass_kernel by itself, and the launch
-// that pools V (the streaming of V is bound by HBM, this by latency and the fp32 matrix rate).
+// as a device function, because three launches carry it: the key side of the gate, the launch that pools V when the
+// gate is off (the streaming of V is bound by HBM, this by latency and the fp32 matrix rate), and text_mass_kernel by
+// itself.
 #pragma once
 #include "rsa_common.hpp"
 
@@ -13,6 +14,12 @@ constexpr int kTextMassLdsFloats = 2 * (kTextTokens / 32) * kTextQueries;
 __host__ __device__ inline int text_mass_workgroups(const Dims& dm) {  // of one (batch, head)
   return (dm.n + kTextQueries - 1) / kTextQueries * (int)((dm.tt + kTextTokens - 1) / kTextTokens);
 }
+
+// Where rsa_pool makes the text log-masses when the gate is on: with the key side of the gate, which is what lets Q and V
+// be pooled in one launch, or, when there are more than two workgroups per CU of them, with the pooling of V, under whose
+// streaming they cost nothing (24 heads, 512 text tokens and 512 query blocks, 1536 workgroups: the key side 218 -> 253 us
+// with them, the two pooling launches 219 us against 199 as one).
+inline bool text_rides_with_keys(const Dims& dm) { return (long long)text_mass_workgroups(dm) * dm.batch * dm.heads <= 512; }
 
 // Workgroup `wg` of the text_mass_workgroups() of (batch, head) bh: 32 pooled queries against 128 text tokens, a
 // wave per 32 tokens, v_mfma_f32_32x32x2_f32 (fp32 operands, products and sums; a bf16 key is exact in fp32), then
