@@ -157,6 +157,14 @@ __device__ __forceinline__ float lane_row_reduce(float v) {
   return v;
 }
 
+// Log-mass of a video block: the score as it is stored (rounded), then the logarithm of the block's token count --
+// not one fused operation, so that it is the same number in every kernel that works it out.
+__device__ __forceinline__ float video_log_mass(float product, float scale, float ln_count) {
+#pragma clang fp contract(off)
+  const float score = product * scale;
+  return score + ln_count;
+}
+
 // Alg. 1 steps 5-7 in one pass over the N x M tensors (rows of at most 64 * NT blocks): a workgroup
 // owns 16 pooled queries and all M key blocks, which its waves share out evenly (a band of consecutive
 // columns, 16-block tiles, at most NT of them). The product is v_mfma_f32_16x16x4_f32 (fp32 operands,
@@ -176,10 +184,11 @@ __device__ __forceinline__ float lane_row_reduce(float v) {
 //
 // Each wave has a piece of LDS to itself:
 //  - in the product, two buffers of half a key tile: the pooled keys come in with direct-to-LDS loads,
-//    the contraction index in two halves, the half after the one being multiplied always on its way. Lane
-//    row g (16 lanes) works on channels g*D/4 .. of the contraction, so a half is D/8 consecutive channels of
-//    every lane row. A buffer row is one key block: PPR 16-byte positions; position p of row r holds logical
-//    chunk p ^ key(r), so that lanes reading one logical chunk of 16 rows hit 16 different positions;
+//    the contraction index in two halves, the half after the one being multiplied always on its way. The four
+//    terms of a matrix instruction, one per lane row, are channels 2s, D/2 + 2s, 2s + 1, D/2 + 2s + 1, the order in
+//    which the 32x32x2 instructions of pooled_scores_kernel take them: the scores are the same bits there and
+//    here. A buffer row is one key block: PPR 16-byte positions; position p of row r holds logical chunk
+//    p ^ key(r), so that lanes reading one logical chunk of 16 rows hit 16 different positions;
 //  - in the epilogue, a [16][16 * HT] tile of floats (rows padded by 16 bytes) through which the accumulators
 //    (a lane holds one column of 4 rows) are turned into rows, so that a store instruction writes runs of
 //    64 * HT bytes: a wave may have 63 stores in flight, and with narrow ones that bound, not the memory,
@@ -187,9 +196,9 @@ __device__ __forceinline__ float lane_row_reduce(float v) {
 typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
 template <int D, int NT>
 __global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims dm, ScoreArgs a) {
-  constexpr int KQ = D / 4;                     // k-steps; channels per lane row
+  constexpr int KH = D / 2, KQ = D / 4;         // k-steps = channels per lane row: KQ
   constexpr int PPR = D / 8;                    // 16-byte positions per buffer row (half the channels of a key block)
-  constexpr int CPG = PPR / 4;                  // ... of one lane row
+  constexpr int CPH = PPR / 2;                  // ... of the channels below D/2, and of those above
   constexpr int HALF = 16 * PPR * 4;            // floats per buffer
   constexpr int RPL = 64 / PPR;                 // rows per load
   constexpr int LOADS = 16 / RPL;               // direct-to-LDS loads per half tile
@@ -213,12 +222,16 @@ __global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims 
   float* mine = wlds[wave];
 
   // this lane's pooled query (row n0 + l16, clamped: rows past the end are computed and not stored)
-  floatx4 qv[KQ / 4];
+  float qv[KQ];
   {
     const int n = n0 + l16 < N ? n0 + l16 : N - 1;
-    const floatx4* qrow = reinterpret_cast<const floatx4*>(a.Qp + ((size_t)bh * N + n) * D + g * KQ);
+    const floatx4* qrow = reinterpret_cast<const floatx4*>(a.Qp + ((size_t)bh * N + n) * D + (g % 2) * KH);
 #pragma unroll
-    for (int i = 0; i < KQ / 4; ++i) qv[i] = qrow[i];
+    for (int i = 0; i < KH / 4; ++i) {
+      const floatx4 q = qrow[i];
+      qv[2 * i] = g < 2 ? q[0] : q[1];
+      qv[2 * i + 1] = g < 2 ? q[2] : q[3];
+    }
   }
   // the query must be in before the first direct-to-LDS load goes out: the compiler does not see those
   // loads and would wait for them together with the query at its first use
@@ -242,8 +255,8 @@ __global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims 
     for (int j = 0; j < LOADS; ++j) {
       const int r = j * RPL + lrow;
       const int m = m0 + r < M ? m0 + r : M - 1;     // rows past the end repeat the last one (not stored)
-      const int q = lpos ^ swz(r);                   // logical chunk: lane row q / CPG, chunk q % CPG of this half
-      const int ch = (q / CPG) * KQ + c * (KQ / 2) + 4 * (q % CPG);
+      const int q = lpos ^ swz(r);                   // logical chunk: q / CPH = channels below or above D/2, chunk q % CPH of this half
+      const int ch = (q / CPH) * KH + c * (KH / 2) + 4 * (q % CPH);
       dma16_v(dst + j * 1024, Kp + (size_t)m * D + ch, &wlds[0][0]);
     }
   };
@@ -260,13 +273,13 @@ __global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims 
         wait_loads_leaving<0>();
       }
       asm volatile("" ::: "memory");             // no read of the buffer may move above the wait
-      const floatx4* kb = reinterpret_cast<const floatx4*>(mine + (u % 2) * HALF) + l16 * PPR;
+      const float* kb = mine + (u % 2) * HALF + l16 * (PPR * 4) + g / 2;
 #pragma unroll
-      for (int i = 0; i < CPG; ++i) {
-        const floatx4 kq = kb[(g * CPG + i) ^ swz(l16)];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc[u / 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[(u % 2) * CPG + i][e], kq[e], acc[u / 2], 0, 0, 0);
+      for (int i = 0; i < CPH; ++i) {
+        const float* kc = kb + (((g % 2) * CPH + i) ^ swz(l16)) * 4;
+        const float k0 = kc[0], k1 = kc[2];
+        acc[u / 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[(u % 2) * (KQ / 2) + 2 * i], k0, acc[u / 2], 0, 0, 0);
+        acc[u / 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[(u % 2) * (KQ / 2) + 2 * i + 1], k1, acc[u / 2], 0, 0, 0);
       }
     }
   }
@@ -334,7 +347,7 @@ __global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims 
     if (t < my_tiles && tile_first + 16 < N) {   // wave-uniform: video blocks only, none of them the last
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        acc[t][r] = acc[t][r] * dm.scale + ln_full;
+        acc[t][r] = video_log_mass(acc[t][r], dm.scale, ln_full);
         pm[r] = fmaxf(pm[r], acc[t][r]);
       }
     } else if (t < my_tiles) {
@@ -342,7 +355,7 @@ __global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims 
       for (int r = 0; r < 4; ++r) {
         const int n = n0 + 4 * g + r;
         float l = -INFINITY;
-        if (m < N) l = acc[t][r] * dm.scale + (m == N - 1 ? ln_last : ln_full);
+        if (m < N) l = video_log_mass(acc[t][r], dm.scale, m == N - 1 ? ln_last : ln_full);
         else if (m < M) l = L[(size_t)(n < N ? n : N - 1) * M + m];
         acc[t][r] = l;
         pm[r] = fmaxf(pm[r], l);

@@ -31,7 +31,6 @@ inline bool text_rides_with_keys(const Dims& dm) { return (long long)text_mass_w
 // `lds`: kTextMassLdsFloats floats.
 template <int D, int BLK>
 __device__ __forceinline__ void text_mass_block(const Dims& dm, const ScoreArgs& a, int wg, int bh, float* lds) {
-  constexpr int KH = D / 2;                      // channels per half-wave: k-step s takes channel s from the lower half, KH + s from the upper
   constexpr int TB = BLK / 32;                   // token tiles (waves) of a text block
   float (*mxs)[kTextQueries] = reinterpret_cast<float (*)[kTextQueries]>(lds);
   float (*sums)[kTextQueries] = mxs + kTextTokens / 32;
@@ -42,25 +41,22 @@ __device__ __forceinline__ void text_mass_block(const Dims& dm, const ScoreArgs&
   const int t0 = (wg / query_tiles) * kTextTokens + 32 * wave;       // this wave's first text token
   const int last = (int)dm.tt - 1;
   const uint16_t* Kt = a.K + (int64_t)b * dm.sb + (int64_t)h * dm.sh + dm.tv * dm.st;
-  const uint4* krow = reinterpret_cast<const uint4*>(Kt + (int64_t)(t0 + l32 < last ? t0 + l32 : last) * dm.st + hf * KH);
-  const floatx4* qrow = reinterpret_cast<const floatx4*>(a.Qp + ((size_t)bh * dm.n + (n < dm.n ? n : dm.n - 1)) * D + hf * KH);
+  const uint4* krow = reinterpret_cast<const uint4*>(Kt + (int64_t)(t0 + l32 < last ? t0 + l32 : last) * dm.st);
+  const floatx4* qrow = reinterpret_cast<const floatx4*>(a.Qp + ((size_t)bh * dm.n + (n < dm.n ? n : dm.n - 1)) * D);
   floatx16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   // A = text keys (M = token), B = pooled queries (N = query); rows past the end repeat the last one and are masked
-  uint4 kv[KH / 8];
-#pragma unroll
-  for (int i = 0; i < KH / 8; ++i) kv[i] = krow[i];
-#pragma unroll
-  for (int i = 0; i < KH / 8; ++i) {
+  // (both half-waves read the whole row and take the even or the odd channels)
+#pragma unroll 4
+  for (int i = 0; i < D / 8; ++i) {
+    const uint4 kv = krow[i];
     const floatx4 q0 = qrow[2 * i], q1 = qrow[2 * i + 1];
-    const uint32_t w[4] = {kv[i].x, kv[i].y, kv[i].z, kv[i].w};
+    const uint32_t w[4] = {kv.x, kv.y, kv.z, kv.w};
+    const float q[4] = {hf ? q0[1] : q0[0], hf ? q0[3] : q0[2], hf ? q1[1] : q1[0], hf ? q1[3] : q1[2]};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float qa = e < 2 ? q0[2 * e] : q1[2 * e - 4], qb = e < 2 ? q0[2 * e + 1] : q1[2 * e - 3];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_bits_to_float(w[e] & 0xffffu), qa, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_bits_to_float(w[e] >> 16), qb, acc, 0, 0, 0);
-    }
+    for (int e = 0; e < 4; ++e)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_bits_to_float(hf ? w[e] >> 16 : w[e] & 0xffffu), q[e], acc, 0, 0, 0);
   }
   // accumulator register r: token t0 + 8(r/4) + 4*hf + r%4, query n
   float mx = -INFINITY;
