@@ -75,7 +75,12 @@ inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   s.cap = (int)(2 * ((longest + s.slots - 1) / s.slots) + 8);      // room for twice the average share of a slot
   s.pieces_per_queue = 0;
   s.n_cross = 0;
-  if (s.n_items <= kSplitRounds * kQueues * s.slots) {
+  // Under RSA_DENSE all rows are equally long and share every tile while they are in step; cutting the rows of the last
+  // round puts them out of step, which costs more than the idle slots once the rows are more than about half as many
+  // (33 rows for 64 slots: 171 us whole, 142 us cut; 36 rows: 104 and 116; 93 rows of blocks of 64 for 128: 187 and 256).
+  const int last_round = s.n_items / kQueues % s.slots;
+  const bool whole = dense_all && 20 * last_round > 11 * s.slots;
+  if (s.n_items <= kSplitRounds * kQueues * s.slots && !whole) {
     if (dm.m >= kQueues * s.min_piece && s.slots >= kQueues) s.n_cross = s.n_dense % kQueues;
     // Every cut makes two pieces (S - 1 cuts), a cross part is a piece by itself; a row of M blocks cannot become more
     // than M / min_piece, and short problems not even that many in all.
