@@ -178,8 +178,8 @@ __device__ __forceinline__ float video_log_mass(float product, float scale, floa
 // stores of one run beside the matrix work of another and the last round of workgroups is shorter, a few
 // heads fill the chip, and the scores of 2048 columns still fit the registers. Bound by the stores and the fp32
 // matrix work about equally, one after the other within a round. Against 32 rows (and against a scores kernel and a
-// softmax kernel for rows above 1024): 2 heads of 17 blocks 12.5 -> 4.7 us, 24 heads of 159 blocks 17 -> 10, of 516
-// 72 -> 50, of 931 143 -> 110, of 1182 266 -> 205; 3 heads of 931 51 -> 32. Three or four buffers instead of two: no
+// softmax kernel for rows above 1024): 2 heads of 17 blocks 12.5 -> 5.3 us, 24 heads of 159 blocks 17 -> 12, of 516
+// 72 -> 50, of 931 143 -> 111, of 1182 266 -> 222; 3 heads of 931 51 -> 36. Three or four buffers instead of two: no
 // gain at any of these (latency is covered), and fewer workgroups per CU.
 //
 // Each wave has a piece of LDS to itself:
