@@ -198,27 +198,6 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     return sp ? list_length(a, dm, (size_t)bhx * dm.n + qbx) : dm.m;
   };
   const int slot = slot_of_group(grp);
-  // k-th entry of this group: record and span. Scalar loads (one with a table), so that it can be asked for well ahead of make_item.
-  struct Entry { int rec, span; };
-  auto my_entry = [&](int k) __attribute__((always_inline)) {
-    typedef const int32_t __attribute__((address_space(4))) * const_i32_t;
-    Entry e;
-    if (sc.table) {
-      const const_i32_t p = (const_i32_t)(uintptr_t)sc.table + ((size_t)slot * sc.cap + k) * 2;
-      e.rec = p[0];
-      e.span = p[1];
-    } else {
-      e.rec = record_of_item(slot + k * n_slots);
-      e.span = make_span(0, blocks_of_record(e.rec), false);
-    }
-    return e;
-  };
-  // the first two entries are asked for together with the counts (words of the table, whether or not they were dealt)
-  Entry entry0 = {}, entry1 = {};
-  if (sc.table) {
-    entry0 = my_entry(0);
-    entry1 = my_entry(1);
-  }
   int n_my_items, wg_rounds = 0;
   if (sc.table) {
     n_my_items = sc.nitems[slot];
@@ -237,6 +216,22 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     }
   }
   if (wg_rounds == 0) return;                        // the whole workgroup: nothing was dealt to it
+  // k-th entry of this group: record and span. Scalar loads (one with a table), so that it can be asked for well ahead of make_item.
+  struct Entry { int rec, span; };
+  auto my_entry = [&](int k) __attribute__((always_inline)) {
+    typedef const int32_t __attribute__((address_space(4))) * const_i32_t;
+    Entry e;
+    if (sc.table) {
+      const const_i32_t p = (const_i32_t)(uintptr_t)sc.table + ((size_t)slot * sc.cap + k) * 2;
+      e.rec = p[0];
+      e.span = p[1];
+    } else {
+      e.rec = record_of_item(slot + k * n_slots);
+      e.span = make_span(0, blocks_of_record(e.rec), false);
+    }
+    return e;
+  };
+
   // What the phases need to know of an item: all wave-uniform.
   typedef const int32_t __attribute__((address_space(4))) * const_list_t;
   struct Item {
@@ -270,6 +265,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     it.qo_off = base + t0 * dm.st;
     return it;
   };
+  auto load_item = [&](int k) __attribute__((always_inline)) { return make_item(my_entry(k)); };
 
   // ---- direct-to-LDS loads ---------------------------------------------------------------
   // A load fills 1 KB of LDS = RK consecutive K rows (RV consecutive V^T rows). Load ii of
@@ -866,23 +862,18 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 
   const bool active = n_my_items > 0;
   if (active) {
+    cur = load_item(0);
     nxt_valid = n_my_items > 1;
-    if (!sc.table) {
-      entry0 = my_entry(0);
-      if (nxt_valid) entry1 = my_entry(1);
-    }
-    cur = make_item(entry0);
-    const int first = list_entry(cur, 0);            // (on its way together with the query rows)
-    load_q(cur);
-    if (nxt_valid) nxt = make_item(entry1);
+    if (nxt_valid) nxt = load_item(1);
     k_next = 2;
     if (n_my_items > 2) ahead = my_entry(2);
+    load_q(cur);
     // Q must have arrived before the first direct-to-LDS load is requested: the compiler
     // does not see those loads, and would otherwise place its own wait for Q -- a wait for
     // *every* outstanding load -- at the first use inside the loop.
     __builtin_amdgcn_s_waitcnt(0x0F70);
     Tile t0;
-    open_block(first, cur.Kbytes, cur.Vtbytes);
+    open_block(list_entry(cur, 0), cur.Kbytes, cur.Vtbytes);
     step_of_block(t0, 0, 0, 0);
     static_for<0, LPS>([&](auto ic) __attribute__((always_inline)) { issue_load(t0, ic); });
     kvc_cur = blk_count;
