@@ -328,6 +328,63 @@ def test_rows_cut_over_several_slots(gpu, name, unequal):
     parity.compare_head(full, 0, 0, ref, Qb[0, 0], Kb[0, 0], Vb[0, 0], forced=f0)
 
 
+def _attend_to_all(gpu, cfg, Q, K, V, workspace, lists):
+    """Every query block over every key block, as RSA_DENSE or through lists that name all blocks: O and lse."""
+    import torch
+    from paper_2511_19835_amd import binding as rb
+    buf = rb.allocate(Q, cfg.t_video, cfg.t_text, cfg.block)
+    O = torch.full_like(Q, float("nan"))
+    lse = torch.full(Q.shape[:3], float("nan"), dtype=torch.float32, device=Q.device)
+    rb.rsa_pool_values(buf.shape, V, buf.Vp, buf.Vt)
+    buf.count.fill_(buf.M)
+    buf.block_idx.copy_(torch.arange(buf.M, dtype=torch.int32, device=Q.device).expand_as(buf.block_idx))
+    idx = (buf.block_idx, buf.count) if lists else (None, None)
+    rb.rsa_sparse_attn_rectified(buf.shape, Q, K, buf.Vt, *idx, None, None, None, None, None, 0 if lists else rb.RSA_DENSE,
+                                 O, lse, buf.attn_ws if workspace else None)
+    torch.cuda.synchronize()
+    return O.double().cpu(), lse.double().cpu()
+
+
+# Few rows on many slots: with a workspace every row is cut into up to M / 4 pieces of at least four key blocks.
+ALL_CUT = {
+    "b64": LayerConfig("all_cut_b64", 1, 2, 64, (10, 16, 20), 70, 64, 0.0),          # 50 + 2 blocks
+    "b128": LayerConfig("all_cut_b128", 1, 3, 128, (10, 31, 20), 40, 128, 0.0),      # 49 + 1 blocks
+}
+
+
+@pytest.mark.parametrize("lists", [False, True])
+@pytest.mark.parametrize("workspace", [False, True])
+@pytest.mark.parametrize("first_blocks", [False, True])
+@pytest.mark.parametrize("name", sorted(ALL_CUT))
+def test_keys_that_mask_themselves(gpu, name, first_blocks, workspace, lists):
+    """Keys whose scores are -inf weigh nothing, wherever the row, or a piece of it, starts: 20 key blocks in a
+    row (whole pieces among them, and the first steps of others) and the odd token elsewhere. Probabilities are
+    rounded to bf16, as everywhere: the bounds are those of the parity tests."""
+    import parity
+    from oracle import rsa_oracle as ro
+    cfg = ALL_CUT[name]
+    Qb, Kb, Vb = (x.copy() for x in synth.make_inputs(cfg, 43))
+    Qb[..., 0] = 0x3f80                            # 1.0: the product with -inf is -inf for every query
+    off = np.zeros(cfg.t_total, dtype=bool)
+    off[::7] = True
+    first = 0 if first_blocks else 5 * cfg.block
+    off[first:first + 20 * cfg.block] = True
+    Kb[:, :, off, 0] = 0xff80                      # -inf
+    Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
+    O, lse = _attend_to_all(gpu, cfg, Q, K, V, workspace, lists)
+    scale = 1 / np.sqrt(cfg.head_dim)
+    for h in range(cfg.heads):
+        q, k, v = (ro.bf16_bits_to_f64(x[0, h]) for x in (Qb, Kb, Vb))
+        want = ro.dense_attention(q, k[~off], v[~off], scale)
+        err = O[0, h].numpy() - want
+        assert np.isfinite(err).all(), f"{(~np.isfinite(err)).any(axis=1).sum()} rows are not finite"
+        assert np.abs(err).max() <= parity.OUT_MAX_ABS
+        assert np.linalg.norm(err) / np.linalg.norm(want) <= parity.OUT_REL_L2
+        S = q @ k[~off].T * scale
+        mx = S.max(axis=1)
+        np.testing.assert_allclose(lse[0, h].numpy(), np.log(np.exp(S - mx[:, None]).sum(axis=1)) + mx, atol=2e-3)
+
+
 @pytest.mark.parametrize("sparsity", [0.5, 0.9])
 @pytest.mark.parametrize("name", ["ragged_d64_b128", "d128_b64_text"])
 def test_identical_tokens_per_block_recover_dense_attention(gpu, name, sparsity):
