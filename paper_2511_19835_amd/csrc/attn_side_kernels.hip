@@ -624,11 +624,12 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void merge_kernel(Dims dm, AttnArg
     for (int k = 0; k < 4; ++k) {
       const float* p = da.pieces + (size_t)ids[min(i + k, n_run - 1)] * piece_floats(D, BLK);
       lp[k] = p[BLK * D + row];
-      mp[k] = i + k < n_run ? p[BLK * D + BLK + row] : -INFINITY;      // (a piece past the end: the last one, weight 0)
+      mp[k] = i + k < n_run ? p[BLK * D + BLK + row] : -INFINITY;      // (a piece past the end: the last one, read and left out)
       const floatx4* src = reinterpret_cast<const floatx4*>(p) + (size_t)((wave * (D / 32) + dt) * 4) * 64 + lane;
 #pragma unroll
       for (int g = 0; g < 4; ++g) v[k][g] = src[g * 64];
     }
+    asm volatile("" ::: "memory");                 // (all four requested here, whatever is left out below)
     const float mnew = fmaxf(fmaxf(m, fmaxf(mp[0], mp[1])), fmaxf(mp[2], mp[3]));
     const float old = __builtin_amdgcn_exp2f(m - mnew);
     m = mnew;
@@ -639,6 +640,7 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void merge_kernel(Dims dm, AttnArg
       for (int e = 0; e < 4; ++e) acc[g][e] *= old;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
+      if (i + k >= n_run) break;                   // (not added with weight 0: 0 x inf is no number)
       const float w = __builtin_amdgcn_exp2f(mp[k] - mnew);
       l = fmaf(w, lp[k], l);
 #pragma unroll

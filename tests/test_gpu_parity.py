@@ -385,6 +385,23 @@ def test_keys_that_mask_themselves(gpu, name, first_blocks, workspace, lists):
         np.testing.assert_allclose(lse[0, h].numpy(), np.log(np.exp(S - mx[:, None]).sum(axis=1)) + mx, atol=2e-3)
 
 
+@pytest.mark.parametrize("name", sorted(ALL_CUT))
+def test_an_infinite_value_stays_infinite(gpu, name):
+    """One value channel of the last key is +inf: every query gives that key some weight, so the channel is +inf in
+    every row of O, whole or cut, and the other channels are what they are without it."""
+    import torch
+    cfg = ALL_CUT[name]
+    Qb, Kb, Vb = (x.copy() for x in synth.make_inputs(cfg, 44))
+    Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
+    plain, _ = _attend_to_all(gpu, cfg, Q, K, V, True, False)
+    V[:, :, -1, 3] = float("inf")
+    for workspace in (False, True):
+        O, _ = _attend_to_all(gpu, cfg, Q, K, V, workspace, False)
+        assert bool((O[..., 3] == float("inf")).all()), f"workspace {workspace}: {int(torch.isnan(O[..., 3]).sum())} rows are NaN"
+    rest = [c for c in range(cfg.head_dim) if c != 3]
+    assert torch.equal(O[..., rest], plain[..., rest])
+
+
 @pytest.mark.parametrize("sparsity", [0.5, 0.9])
 @pytest.mark.parametrize("name", ["ragged_d64_b128", "d128_b64_text"])
 def test_identical_tokens_per_block_recover_dense_attention(gpu, name, sparsity):
