@@ -208,16 +208,18 @@ int rsa_sparse_attn_rectified(const rsa_shape* shape, const void* Q, const void*
 
 /*
  * For callers that cannot allocate device memory or hand over a workspace: code running under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc. Same computation, arguments,
- * results and error codes as rsa_sparse_attn_rectified, without ws / ws_bytes: the scratch (C_n, the
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc. Same computation, arguments and
+ * error codes as rsa_sparse_attn_rectified, without ws / ws_bytes: the scratch (C_n, the
  * order of the query blocks and their schedule) lives in a device array of RSA_STATIC_SCRATCH_BYTES (16 MiB) that is part of the
  * library image, one copy per GPU, held until the process ends. The call allocates and frees nothing.
  * Its first call on a device looks up that device's copy (hipGetSymbolAddress; RSA_E_LAUNCH if that
- * fails). Shapes whose C_n and query block order, 4 * batch * heads * N * (head_dim + 1) bytes plus padding,
- * exceed RSA_STATIC_SCRATCH_BYTES are refused with RSA_E_WORKSPACE before anything is enqueued. The schedule
- * (together with the former 11.9 MB for 24 heads of 118 800 + 256 tokens at block 128, head_dim 128) and the
- * buffers of query blocks that are cut take what is left, as far as they fit: where rsa_workspace_bytes asks for
- * more than RSA_STATIC_SCRATCH_BYTES no query block is cut.
+ * fails). Results are those of rsa_sparse_attn_rectified, to the last bit where both cut the same query
+ * blocks. Here none is cut where rsa_workspace_bytes asks for more than RSA_STATIC_SCRATCH_BYTES (the buffers of
+ * the pieces do not fit then) nor under RSA_DENSE; the last bits may differ there.
+ * Shapes are refused with RSA_E_WORKSPACE, before anything is enqueued, when C_n and the query block order,
+ * 4 * batch * heads * N * (head_dim + 1) bytes, and 50 to 570 KB for the schedule (a word for each of twice the average
+ * number of query blocks of a group of waves, and 32 KiB) exceed RSA_STATIC_SCRATCH_BYTES; 24 heads of 118 800 + 256
+ * tokens at block 128, head_dim 128 take 11.7 MB.
  * Every call on a GPU uses that GPU's one array and overwrites all of it that it reads (nothing has
  * to start at zero); two calls that overlap in time on one GPU (different streams) race on it.
  * With RSA_DENSE the scratch is not touched (the query blocks are dealt in index order).

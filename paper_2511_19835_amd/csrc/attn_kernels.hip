@@ -999,6 +999,11 @@ hipError_t launch_attn_t(const Dims& dm, const AttnArgs& a, const AttnSched& ws,
     sh.pieces_per_queue = sh.n_cross = 0;
     l = sched_layout(dm, sh);
   }
+  if (l.bytes > ws.room_bytes) {                   // nor for the whole table: fewer entries per slot, down to the average share
+    const size_t entry = (size_t)kQueues * sh.slots * sizeof(int2), over = (l.bytes - ws.room_bytes + entry - 1) / entry;
+    sh.cap -= (int)(over < (size_t)(sh.cap - sh.least_cap) ? over : (size_t)(sh.cap - sh.least_cap));
+    l = sched_layout(dm, sh);
+  }
   const bool deal = ws.room && l.bytes <= ws.room_bytes && sh.slots <= kMaxSlots;
   DealArgs da = {};
   if (deal) {

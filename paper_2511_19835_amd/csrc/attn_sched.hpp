@@ -54,7 +54,7 @@ struct DealArgs {
 
 // Sizes of the schedule for `n_wg` resident workgroups of NGRP groups.
 struct SchedShape {
-  int slots, cap, n_items, n_dense, dense_per_bh, dense_first, rows_per_bh, n_cross, pieces_per_queue, min_piece, switch_cost;
+  int slots, cap, least_cap, n_items, n_dense, dense_per_bh, dense_first, rows_per_bh, n_cross, pieces_per_queue, min_piece, switch_cost;
 };
 inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   SchedShape s;
@@ -73,6 +73,7 @@ inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   s.min_piece = 4;
   const long long longest = (long long)bh * ((s.rows_per_bh + kQueues - 1) / kQueues) + (s.n_dense + kQueues - 1) / kQueues;
   s.cap = (int)(2 * ((longest + s.slots - 1) / s.slots) + 8);      // room for twice the average share of a slot
+  s.least_cap = (int)((longest + s.slots - 1) / s.slots) + 1;      // ... for the average one: still enough for all rows, when none is cut
   s.pieces_per_queue = 0;
   s.n_cross = 0;
   // Under RSA_DENSE all rows are equally long and share every tile while they are in step; cutting the rows of the last

@@ -136,6 +136,17 @@ int enqueue_attn(const Dims& d, const void* Q, const void* K, const void* Vt, co
   return RSA_OK;
 }
 
+// What rsa_sparse_attn_rectified_static asks of its scratch array before it takes a shape: C_n, the launch order, and
+// of the schedule one word for each of twice the average number of rows of a slot and 32 KiB. (The limit belongs to the
+// interface and does not move with the tables: those take two words an entry by now and are shorter here where the
+// array is nearly full; half of the entries, which always fit, hold all rows.)
+size_t static_scratch_need(const Dims& d) {
+  const size_t queues = d.blk == 128 ? 8 : 16, slots = 64, bh = (size_t)d.batch * d.heads;
+  const size_t rows = (bh * d.mt + queues - 1) / queues + bh * ((d.n + queues - 1) / queues);       // of the longest queue
+  const size_t entries = queues * slots * (2 * ((rows + slots - 1) / slots) + 8);
+  return attn_ws_layout(d).sched + align256(entries * sizeof(int32_t)) + (32u << 10);
+}
+
 // Scratch of rsa_sparse_attn_rectified_static: one array per GPU, held from the moment the library's
 // code object is loaded on that GPU until the process ends. In host code the array's name is only a
 // handle for hipGetSymbolAddress; the device address it yields (one per device) is what kernels get.
@@ -335,8 +346,7 @@ int rsa_sparse_attn_rectified_static(const rsa_shape* shape, const void* Q, cons
   if (rc != RSA_OK) return rc;
   void* ws = nullptr;
   if (!(flags & RSA_DENSE)) {
-    // what has to fit is C_n and the launch order; the schedule is dealt, and rows are cut, as far as the rest allows
-    if (attn_ws_layout(d).sched > (size_t)RSA_STATIC_SCRATCH_BYTES) return RSA_E_WORKSPACE;
+    if (static_scratch_need(d) > (size_t)RSA_STATIC_SCRATCH_BYTES) return RSA_E_WORKSPACE;
     ws = static_scratch_of_current_device();
     if (!ws) return RSA_E_LAUNCH;
   }

@@ -152,8 +152,8 @@ struct AttnSched {
   size_t room_bytes;
 };
 // Bytes of `room` for the schedule and for the buffers of rows that are cut (0 where none is), as
-// rsa_workspace_bytes sets them aside. With less, no row is cut; with less than the schedule itself, the items
-// are dealt in index order.
+// rsa_workspace_bytes sets them aside. With less, no row is cut; with less than the schedule itself, its tables
+// are shorter, down to the average share of a slot; below that, the items are dealt in index order.
 void attn_sched_bytes(const Dims& dm, size_t* schedule, size_t* pieces);
 hipError_t launch_attn(const Dims& dm, const AttnArgs& a, const AttnSched& ws, hipStream_t s);
 

@@ -104,6 +104,27 @@ def test_null_and_range_arguments_are_rejected_before_launch(lib):
     assert lib.rsa_status_string(0).decode() == "ok"
 
 
+@pytest.mark.parametrize("heads,head_dim,block,t_video,t_text", [
+    (795, 128, 64, 40 * 64 - 5, 70), (1353, 128, 128, 24 * 128, 0), (3985, 64, 64, 16 * 64, 0), (31, 128, 128, 128 * 1040, 256),
+])
+def test_static_scratch_limit_counts_the_schedule(lib, heads, head_dim, block, t_video, t_text):
+    """The entry point with built-in scratch refuses shapes whose C_n and query block order fit its array, but not
+    together with the schedule: a word for each of twice the average number of query blocks of a slot (64 slots to
+    each of 8 queues, 16 at block 64), and 32 KiB."""
+    t = t_video + t_text
+    sh = _shape(heads=heads, head_dim=head_dim, block=block, t_video=t_video, t_text=t_text, stride_b=heads * t * head_dim,
+                stride_h=t * head_dim, stride_t=head_dim)
+    n, m, _ = rb.rsa_block_counts(sh)
+    up = lambda x, k: -(-x // k) * k
+    queues = 8 if block == 128 else 16
+    longest = -(-heads * (m - n) // queues) + heads * -(-n // queues)
+    fixed = up(heads * n * head_dim * 4, 256) + up(heads * n * 4, 256)
+    schedule = up(queues * 64 * (2 * -(-longest // 64) + 8) * 4, 256) + (32 << 10)
+    assert fixed <= rb.RSA_STATIC_SCRATCH_BYTES < fixed + schedule
+    one = ctypes.c_void_p(256)     # never dereferenced: refused on the host
+    assert lib.rsa_sparse_attn_rectified_static(ctypes.byref(sh), *[one] * 10, 3, one, None, None) == -4
+
+
 def test_binding_refuses_cpu_tensors(lib):
     import torch
     q = torch.zeros(1, 2, 1050, 128, dtype=torch.bfloat16)
