@@ -352,6 +352,86 @@ ALL_CUT = {
 }
 
 
+def _same_up_to_the_order_of_sums(cut, whole):
+    """The bound of test_rows_cut_over_several_slots, for (O, lse) pairs."""
+    import torch
+    (a, la), (b, lb) = cut, whole
+    assert bool(torch.isfinite(a).all())
+    assert float((a - b).norm() / b.norm()) <= 2.8e-4
+    np.testing.assert_allclose(la.numpy(), lb.numpy(), atol=2e-5, rtol=2e-6)
+
+
+DENSE = dict(CUT, **{
+    # rows of a last round on more than 11 of 20 slots: left whole (40 rows for 64 slots, 72 for 128)
+    "whole_b128": LayerConfig("whole_b128", 1, 5, 64, (7, 32, 36), 100, 128, 0.0),
+    "whole_b64": LayerConfig("whole_b64", 1, 11, 128, (5, 21, 31), 15, 64, 0.0),
+})
+
+
+@pytest.mark.parametrize("name", sorted(DENSE))
+def test_dense_rows_with_a_workspace(gpu, name):
+    """RSA_DENSE with a workspace (its rows dealt, and cut where the last round leaves most slots idle) against the
+    same call without one, and head 0 against full attention."""
+    import parity
+    import torch
+    from oracle import rsa_oracle as ro
+    cfg = DENSE[name]
+    rows, slots = cfg.batch * cfg.heads * cfg.n_blocks, 64 if cfg.block == 128 else 128
+    assert (20 * (rows // 8 % slots) > 11 * slots) == name.startswith("whole")
+    Qb, Kb, Vb = synth.make_inputs(cfg, 45)
+    Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
+    whole = _attend_to_all(gpu, cfg, Q, K, V, False, False)
+    dealt = _attend_to_all(gpu, cfg, Q, K, V, True, False)
+    _same_up_to_the_order_of_sums(dealt, whole)
+    assert torch.equal(dealt[0], whole[0]) == name.startswith("whole"), "rows were cut where they should not be, or not where they should"
+    q, k, v = (ro.bf16_bits_to_f64(x[0, 0]) for x in (Qb, Kb, Vb))
+    want = ro.dense_attention(q, k, v, 1 / np.sqrt(cfg.head_dim))
+    err = dealt[0][0, 0].numpy() - want
+    assert np.abs(err).max() <= parity.OUT_MAX_ABS
+    assert np.linalg.norm(err) / np.linalg.norm(want) <= parity.OUT_REL_L2
+
+
+@pytest.mark.parametrize("unequal", [False, True])
+@pytest.mark.parametrize("name", ["entries_beyond_the_table", "more_dense_rows_than_the_tail"])
+def test_dealing_of_short_lists_beside_long_rows(gpu, name, unequal):
+    """Two turns of the dealing that need lists of one block beside text rows that walk all blocks. (1) Shares so
+    long that a slot would take more of the short rows than its table has entries: whole entries go to the
+    lightest slot instead, a cross part (a text row over all queues) to the slot of its number. (2) More text rows
+    than are kept for cutting: they go out ahead of the others. Against the call without a workspace."""
+    import torch
+    from paper_2511_19835_amd import binding as rb
+    if name == "entries_beyond_the_table":
+        cfg = LayerConfig(name, 1, 3, 64, (10, 60, 62), 13 * 128 - 9, 128, 1.0)
+    else:
+        cfg = LayerConfig(name, 1, 41, 64, (3, 15, 17), 26 * 128 - 40, 128, 1.0)
+    N, M, slots = cfg.n_video_blocks, cfg.n_blocks, 64
+    dense = cfg.heads * (M - N)
+    cross = dense % 8
+    per_queue = (dense - cross) // 8
+    assert M >= 32 and cross > 0
+    if name == "entries_beyond_the_table":
+        cap = 2 * -(-(cfg.heads * -(-N // 8) + -(-dense // 8)) // slots) + 8
+        left = cfg.heads * (N // 8) % slots                  # rows of one block at the end of the line
+        share = (per_queue * M + cross * (M // 8) + left) // slots
+        assert per_queue <= 128 and left > cap and share > cap
+    else:
+        assert per_queue > 128 and cfg.heads * M <= 32 * 8 * slots
+    forced = None
+    if unequal:
+        forced = np.zeros((1, cfg.heads, N, M), dtype=bool)
+        forced[:, :, ::5, :3] = True
+    Qb, Kb, Vb = synth.make_inputs(cfg, 46)
+    kw = dict(gapr_mode=0, flags=1, forced=forced)
+    args = (Qb, Kb, Vb, cfg.t_video, cfg.t_text, cfg.block, cfg.sparsity)
+    outs = []
+    for workspace in (True, False):
+        out = gpu.run_layer(*args, attn_workspace=workspace, **kw)
+        assert out["count"].min() == 1 and out["count"].max() <= (4 if unequal else 1)
+        outs.append((torch.from_numpy(out["O_bits"].astype(np.int32) << 16).view(torch.float32).double(),
+                     torch.from_numpy(out["lse"]).double()))
+    _same_up_to_the_order_of_sums(*outs)
+
+
 @pytest.mark.parametrize("lists", [False, True])
 @pytest.mark.parametrize("workspace", [False, True])
 @pytest.mark.parametrize("first_blocks", [False, True])
@@ -853,10 +933,23 @@ def test_gate_bits_of_long_rows(gpu, d, block, grid, t_text):
     Qb, Kb, Vb = synth.make_inputs(cfg, 4)
     Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
     buf = rb.allocate(Q, cfg.t_video, cfg.t_text, cfg.block)
+    for t in (buf.Qp, buf.Kp, buf.Vp, buf.Vt, buf.Spool, buf.Lmass, buf.Apool):
+        t.fill_(float("nan"))
     buf.Mc_bits.fill_(-1)
     rb.rsa_pool(buf.shape, Q, K, V, buf.Qp, buf.Kp, buf.Vp, buf.Vt, buf.Spool, buf.Apool, buf.Lmass, buf.Mc_bits, 1,
                 buf.pool_ws)
+    # what this launch pools (two token blocks to a workgroup at block 64) and carries along, against the kernels of gapr_mode 0
+    names = ("Qp", "Kp", "Vp", "Vt", "Spool", "Lmass", "Apool")
+    pooled = {name: getattr(buf, name).clone() for name in names}
+    bits_on = buf.Mc_bits.clone()
+    for name in names:
+        getattr(buf, name).fill_(float("nan"))
+    rb.rsa_pool(buf.shape, Q, K, V, buf.Qp, buf.Kp, buf.Vp, buf.Vt, buf.Spool, buf.Apool, buf.Lmass, buf.Mc_bits, 0,
+                buf.pool_ws)
     torch.cuda.synchronize()
+    for name in names:
+        assert torch.equal(pooled[name].view(torch.uint8), getattr(buf, name).view(torch.uint8)), name
+    buf.Mc_bits.copy_(bits_on)
     N, M, tv = buf.N, buf.M, cfg.t_video
     start = [n * block for n in range(N)] + [tv + i * block for i in range(M - N)]
     stop = [min(s + block, tv if i < N else tv + t_text) for i, s in enumerate(start)]
