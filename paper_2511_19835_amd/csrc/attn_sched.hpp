@@ -76,11 +76,25 @@ inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   s.least_cap = (int)((longest + s.slots - 1) / s.slots) + 1;      // ... for the average one: still enough for all rows, when none is cut
   s.pieces_per_queue = 0;
   s.n_cross = 0;
-  // Under RSA_DENSE all rows are equally long and share every tile while they are in step; cutting the rows of the last
-  // round puts them out of step, which costs more than the idle slots once the rows are more than about half as many
-  // (33 rows for 64 slots: 171 us whole, 142 us cut; 36 rows: 104 and 116; 93 rows of blocks of 64 for 128: 187 and 256).
-  const int last_round = s.n_items / kQueues % s.slots;
-  const bool whole = dense_all && 20 * last_round > 11 * s.slots;
+  // Under RSA_DENSE all rows are equally long and share every tile while they are in step. Cutting the rows of the last
+  // round puts them out of step, and their groups on CUs that others use: worth it while few slots would have a row of
+  // that round -- fewest at d = 128 with blocks of 64, where a group asks the L2 for the most bytes per product -- and,
+  // where it is the only round, while the pieces are long (a slot's share of the key blocks) or very few slots have one.
+  // Measured over last rounds of 1/16 to 9/10 of the slots, none to two rounds before, 1 to 24 heads (us, whole and cut):
+  // d = 128, blocks of 128: 3 heads of 85 blocks, 31 rows for 64 slots 213 and 190; of 106, 39 rows 279 and 317; 8 of 28,
+  // 28 rows 82 and 91; 24 of 159, 477 rows 4152 and 4070; 24 of 33, 99 rows 214 and 238. Blocks of 64: 3 of 128, 48 rows for
+  // 128 slots 181 and 138; of 149, 55 rows 207 and 237; 8 of 160, 160 rows 516 and 423; 24 of 56, 168 rows 197 and 216.
+  // d = 64, blocks of 128: 2 of 128, 32 rows 237 and 167; 24 of 33, 99 rows 143 and 148; 24 of 8, 24 rows 28 and 35; blocks of
+  // 64: 8 of 64, 64 rows 83 and 72; 24 of 66, 198 rows 165 and 185.
+  bool whole = false;
+  if (dense_all) {
+    const int rows = s.n_items / kQueues, last = rows % s.slots;
+    const bool only = rows < s.slots;
+    const int most = dm.d == 64 ? 16 : dm.blk == 128 ? 15 : only ? 12 : 8;       // thirty-seconds of the slots
+    const long long share = (long long)last * dm.m / s.slots;
+    const bool long_pieces = share >= (5 * last <= s.slots ? 3 : 20) || (10 * last <= s.slots && dm.m >= 10);
+    whole = 32 * last > most * s.slots || s.n_items % (kQueues * s.slots) == 0 || (only && !long_pieces);
+  }
   if (s.n_items <= kSplitRounds * kQueues * s.slots && !whole) {
     if (dm.m >= kQueues * s.min_piece && s.slots >= kQueues) s.n_cross = s.n_dense % kQueues;
     // Every cut makes two pieces (S - 1 cuts), a cross part is a piece by itself; a row of M blocks cannot become more
