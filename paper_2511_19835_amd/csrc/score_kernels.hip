@@ -5,7 +5,7 @@
 //   pooled_scores_kernel   Spool[n][m] = scale * q^pool_n . k^pool_m       (N x M x d, tiny)
 //   text_mass_kernel       Lmass[n][N+i] = log sum_{t in text block i} exp(scale * q^pool_n . k_t)
 //   ipar_softmax_rows_kernel  Lmass[n][m<N] = Spool + ln c_m ; Apool = row-softmax(Lmass)
-//   ipar_fused_kernel      the first and the third in one pass (rows of at most 2048 blocks)
+//   ipar_fused_kernel      the first and the third in one pass (rows of at most 1024 blocks; up to 2048 where one_pass says so)
 //
 // softmax(Lmass) is the paper's reallocation written in log space: the mixed softmax
 // over [pooled video keys ; text tokens] gives weights proportional to exp(score); a video
@@ -407,11 +407,24 @@ __global__ __launch_bounds__(256, NT <= 16 ? 4 : 2) void ipar_fused_kernel(Dims 
   store_band(A, M, [&](int t, int r) __attribute__((always_inline)) { return acc[t][r] * inv[r]; });
 }
 
+// Rows of 1025 to 2048 blocks keep 32 tiles in registers, two workgroups to a CU: a round of 512, and with few heads a
+// last round that is mostly empty costs more than the pass over the scores that is saved. In one pass at d = 128 where
+// the rounds are at least 17/20 full; at d = 64, where the product is half as long, not at all. rsa_pool without the
+// gate, us, two kernels and one pass, d = 128: 1 head of 1030 blocks of 64 37 and 58, 8 heads of 1182 227 and 259, 6 of 1182
+// (444 workgroups) 171 and 168, 24 of 1182 (1776) 654 and 611, 8 of 2040 (1024) 518 and 442, 6 of 1400 (528) 211 and 250;
+// d = 64: 24 of 1030 317 and 329, 6 of 1500 136 and 165, 24 of 1182 384 and 380.
+template <int D>
+bool one_pass(const Dims& dm) {
+  if (dm.m <= 1024) return true;
+  const long long round = 512, wgs = (long long)((dm.n + 15) / 16) * dm.batch * dm.heads, rounds = (wgs + round - 1) / round;
+  return D == 128 && dm.m <= 2048 && 20 * wgs >= 17 * rounds * round;
+}
+
 template <int D, int BLK>
 hipError_t launch_scores_t(const Dims& dm, const ScoreArgs& a, hipStream_t s) {
   const int bh = dm.batch * dm.heads;
-  if (dm.m <= 2048) {
-    // rows short enough for the registers of a workgroup: the text log-masses first, then one pass
+  if (one_pass<D>(dm)) {
+    // the text log-masses first, then one pass
     if (dm.tt > 0 && !a.text_done)
       hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3(text_mass_workgroups(dm), bh), dim3(256), 0, s, dm, a);
     const dim3 fgrid(bh * ((dm.n + 15) / 16));
@@ -423,7 +436,7 @@ hipError_t launch_scores_t(const Dims& dm, const ScoreArgs& a, hipStream_t s) {
       hipLaunchKernelGGL((ipar_fused_kernel<D, 8>), fgrid, dim3(256), 0, s, dm, a);
     else if (dm.m <= 1024)
       hipLaunchKernelGGL((ipar_fused_kernel<D, 16>), fgrid, dim3(256), 0, s, dm, a);
-    else
+    else if constexpr (D == 128)
       hipLaunchKernelGGL((ipar_fused_kernel<D, 32>), fgrid, dim3(256), 0, s, dm, a);
     return hipGetLastError();
   }
@@ -431,7 +444,10 @@ hipError_t launch_scores_t(const Dims& dm, const ScoreArgs& a, hipStream_t s) {
   if (dm.tt > 0 && !a.text_done)
     hipLaunchKernelGGL((text_mass_kernel<D, BLK>), dim3(text_mass_workgroups(dm), bh), dim3(256), 0, s, dm, a);
   const dim3 rgrid((dm.n + 3) / 4, bh);
-  hipLaunchKernelGGL(ipar_softmax_rows_kernel<RSA_MAX_BLOCKS / 64>, rgrid, dim3(256), 0, s, dm, a);
+  if (dm.m <= 2048)
+    hipLaunchKernelGGL(ipar_softmax_rows_kernel<32>, rgrid, dim3(256), 0, s, dm, a);
+  else
+    hipLaunchKernelGGL(ipar_softmax_rows_kernel<RSA_MAX_BLOCKS / 64>, rgrid, dim3(256), 0, s, dm, a);
   return hipGetLastError();
 }
 

@@ -852,11 +852,13 @@ def test_implicit_attention_alone(gpu):
         assert torch.equal(got, ref)
 
 
-@pytest.mark.parametrize("d,block,blocks,t_text", [
-    (64, 64, 1, 1), (128, 128, 3, 31), (128, 64, 15, 33), (64, 128, 17, 127), (128, 64, 126, 129), (64, 64, 127, 65),
-    (64, 64, 250, 300), (128, 64, 254, 257), (64, 64, 509, 190), (64, 64, 1022, 128), (64, 64, 1022, 129), (64, 64, 2046, 70),
-    (64, 64, 2047, 70)])
-def test_implicit_attention_at_the_edges_of_its_tiles(gpu, d, block, blocks, t_text):
+@pytest.mark.parametrize("d,block,blocks,t_text,heads", [
+    (64, 64, 1, 1, 2), (128, 128, 3, 31, 2), (128, 64, 15, 33, 2), (64, 128, 17, 127, 2), (128, 64, 126, 129, 2),
+    (64, 64, 127, 65, 2), (64, 64, 250, 300, 2), (128, 64, 254, 257, 2), (64, 64, 509, 190, 2), (64, 64, 1022, 128, 2),
+    (64, 64, 1022, 129, 2), (64, 64, 2046, 70, 2), (64, 64, 2047, 70, 2),
+    # 1025 .. 2048 blocks in one pass: enough workgroups for nearly full rounds (512, 438)
+    (128, 64, 2046, 70, 4), (128, 64, 1168, 70, 6)])
+def test_implicit_attention_at_the_edges_of_its_tiles(gpu, d, block, blocks, t_text, heads):
     """Pooled scores, log-masses (text log-masses among them) and A^pool against fp64 from the same pooled vectors,
     at row lengths around the ends of a tile, of a wave's band and of every kernel variant (128, 256, 512, 1024, 2048
     blocks) and text lengths around a tile and a block. Bounds: a product of d fp32 terms is off by at most
@@ -867,7 +869,7 @@ def test_implicit_attention_at_the_edges_of_its_tiles(gpu, d, block, blocks, t_t
     u = 2.0 ** -24
     tv = blocks * block - (block // 2 + 1)                 # a ragged last video block
     g = torch.Generator(device="cuda").manual_seed(blocks)
-    q, k, v = ((torch.randn(1, 2, tv + t_text, d, generator=g, device="cuda") * 1.5).to(torch.bfloat16) for _ in range(3))
+    q, k, v = ((torch.randn(1, heads, tv + t_text, d, generator=g, device="cuda") * 1.5).to(torch.bfloat16) for _ in range(3))
     buf = rb.allocate(q, tv, t_text, block)
     for t in (buf.Spool, buf.Lmass, buf.Apool):
         t.fill_(float("nan"))
