@@ -305,24 +305,36 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
       int next = 0;
       const int bulk_end = seg_n - 2 * S;          // (of the last segment)
       while (next < seg_n && (!last || next <= bulk_end)) next = deal_round(next, seg_n, false);
-      if (last && !split) {
-        while (next < seg_n) next = deal_round(next, seg_n, true);
-      } else if (last) {
-        int lo = 0x7fffffff, hi = 0x7fffffff, flo = 0x7fffffff, fhi = 0x7fffffff;
+      if (last) {
+        bool equal = false, cut = split;
+        if (split) {
+          int lo = 0x7fffffff, hi = 0x7fffffff, flo = 0x7fffffff, fhi = 0x7fffffff;
 #pragma unroll
-        for (int j = 0; j < SPL; ++j)
-          if (ok[j]) {
-            flo = min(flo, load[j]);
-            fhi = min(fhi, -load[j]);
+          for (int j = 0; j < SPL; ++j)
+            if (ok[j]) {
+              flo = min(flo, load[j]);
+              fhi = min(fhi, -load[j]);
+            }
+          for (int i = next + lane; i < seg_n; i += 64) {
+            lo = min(lo, len[i]);
+            hi = min(hi, -len[i]);
           }
-        for (int i = next + lane; i < seg_n; i += 64) {
-          lo = min(lo, len[i]);
-          hi = min(hi, -len[i]);
+          equal = wave_min_i32(flo) == -wave_min_i32(fhi) && (next >= seg_n || wave_min_i32(lo) == -wave_min_i32(hi));
+          // Which video rows are cut (what is left of RSA_DENSE: as the host has decided). Text rows are cut in any case, and
+          // equal rows beside them. Unequal rows are cut, but at d = 128 with blocks of 64 only when they are no more than the
+          // slots and, without text rows, for half of the slots at most and not short (us, whole and cut, lists of a tenth to
+          // a half of the blocks at random: 3 heads of 106 blocks, 39 rows for 128 slots 105 and 67; 24 of 13, 39 rows 33 and
+          // 38; 8 of 192, 192 rows 333 and 425; 3 of 362, 136 rows 487 and 608; with two text blocks 3 of 490 1016 and 1233).
+          if (!dense_all && next < seg_n) {
+            if (equal) cut = da.n_dense > 0 || cut_pays(da.rule, (seg_n - next) % S, S, len[next]);
+            else if (dm.d == 128 && dm.blk == 64)
+              cut = n_bulk <= S && (da.n_dense > 0 || (2 * n_bulk <= S && (dm.m >= 24 || 10 * n_bulk <= S)));
+          }
         }
-        const bool equal = wave_min_i32(flo) == -wave_min_i32(fhi) && (next >= seg_n || wave_min_i32(lo) == -wave_min_i32(hi));
-        if (equal)
-          while (seg_n - next >= S) next = deal_round(next, seg_n, false);
-        if (lane == 0) {
+        // whole rounds of equal rows that the rest is cut of, or all rows
+        const int stop = !cut ? 1 : equal ? S : seg_n + 1;
+        while (seg_n - next >= stop) next = deal_round(next, seg_n, true);
+        if (split && lane == 0) {
           s_left[0] = next;
           s_left[1] = seg_n;
           s_left[2] = equal ? 1 : 0;

@@ -397,6 +397,39 @@ def test_dense_rows_with_a_workspace(gpu, name):
     assert np.linalg.norm(err) / np.linalg.norm(want) <= parity.OUT_REL_L2
 
 
+@pytest.mark.parametrize("heads,d,block,blocks,sparsity,unequal,cut", [
+    (1, 128, 64, 208, 0.5, False, True),        # 26 rows of 104 key blocks for 128 slots
+    (3, 128, 64, 210, 0.5, False, False),       # 78 rows: whole
+    (8, 128, 64, 144, 0.5, False, True),        # a full round, then 16 rows
+    (8, 128, 128, 40, 0.5, False, False),       # 40 rows for 64 slots: whole
+    (3, 128, 128, 34, 0.5, False, True),        # 12 rows of 17 key blocks
+    (2, 64, 64, 40, 0.5, False, True),          # 10 rows of 20 for 128 slots
+    (8, 64, 128, 31, 0.9, False, False),        # 31 rows of 4 for 64: whole
+    (3, 128, 64, 106, 0.9, True, True),         # unequal rows for less than half of the slots
+    (8, 128, 64, 136, 0.9, True, False),        # unequal rows, more than slots: whole
+    (8, 128, 128, 68, 0.9, True, True),         # the same with blocks of 128
+])
+def test_rows_without_text_are_cut_where_it_pays(gpu, heads, d, block, blocks, sparsity, unequal, cut):
+    """Which rows are cut when no text row is among them, told from the bits: a row that stays whole adds its terms
+    in the order of the call without a workspace. Either way every row is there, up to the order of sums."""
+    import torch
+    cfg = LayerConfig("no_text", 1, heads, d, (1, blocks, block), 0, block, sparsity)
+    forced = None
+    if unequal:
+        rng = np.random.default_rng(48)
+        density = rng.choice([0.0, 0.1, 0.2, 0.5], size=(1, heads, blocks, 1))
+        forced = rng.random((1, heads, blocks, blocks)) < density
+    rng = np.random.default_rng(47)
+    Qb, Kb, Vb = (synth.f32_to_bf16_bits(rng.standard_normal((1, heads, blocks * block, d), dtype=np.float32)) for _ in range(3))
+    outs = []
+    for workspace in (True, False):
+        out = gpu.run_layer(Qb, Kb, Vb, cfg.t_video, 0, block, sparsity, gapr_mode=0, flags=1, forced=forced, attn_workspace=workspace)
+        outs.append((torch.from_numpy(out["O_bits"].astype(np.int32) << 16).view(torch.float32).double(),
+                     torch.from_numpy(out["lse"]).double()))
+    _same_up_to_the_order_of_sums(*outs)
+    assert torch.equal(outs[0][0], outs[1][0]) != cut
+
+
 @pytest.mark.parametrize("unequal", [False, True])
 @pytest.mark.parametrize("name", ["entries_beyond_the_table", "more_dense_rows_than_the_tail"])
 def test_dealing_of_short_lists_beside_long_rows(gpu, name, unequal):
