@@ -26,10 +26,12 @@
 // A^pool[n][m] v^pool_m (computed beforehand by compensation_kernel into the workspace).
 //
 // 4*B*B*d flop per (query block, key block) pair against 2*B*d*2 bytes of K/V traffic.
-// The small kernels named here are in attn_side_kernels.hip. row_order_kernel sorts the video query blocks of a head by their first kept key blocks;
-// schedule_kernel deals that order (long dense rows first) to the groups so that each XCD
-// (workgroup id modulo 8) owns a contiguous range of it, groups resident together walk similar
-// lists and share K/V tiles in the XCD's L2, and all groups end within one item of each other.
+// The small kernels around this one are in attn_side_kernels.hip. row_rank_kernel orders the video query blocks of a head by
+// their first three kept key blocks; schedule_kernel deals that order to the groups so that each XCD (workgroup id modulo 8)
+// owns a contiguous range of every head and groups resident together walk similar lists and share K/V tiles in the
+// XCD's L2. With few rounds of items the rows of the last round and the text rows are cut into pieces, where that is faster,
+// and all groups end at about the same key block (merge_kernel adds the pieces); with many, the text rows go first and the
+// groups end within one item of each other.
 #include "attn_sched.hpp"
 #include "lds_dma.hpp"
 #include "rsa_common.hpp"

@@ -188,8 +188,8 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
 // items go to neighbouring slots at about the same time, so that groups resident together walk similar lists.
 //
 // What is left at the end -- fewer rows than slots when all lists are equally long, up to twice as many
-// otherwise -- and the long text rows are cut: laid end to end and divided over the slots so that every
-// slot ends at the same key block, give or take min_piece. A row that is cut is put together by merge_kernel. Cut points
+// otherwise -- and the long text rows are cut (video rows only where that is faster, see there): laid end to end and
+// divided over the slots so that every slot ends at the same key block, give or take min_piece. A row that is cut is put together by merge_kernel. Cut points
 // closer than min_piece to the end of a row move there. Without that, an uneven last round
 // leaves slots idle (159 blocks of 24 heads on 512 slots: 7.45 rounds took 8; the dense layer of that shape
 // 4.25 -> 4.08 ms) and a text row, which walks all M blocks, can be longer than the whole share of a slot

@@ -17,10 +17,10 @@
 // block (the MFMA A operand, read from LDS just ahead of each MFMA), so the accumulators hold
 // the deviations themselves and the epilogue is one |.|-add per element. Three waves per SIMD.
 // The key side runs first and leaves DB transposed ([M][N]) in the workspace; the query side runs second
-// and never stores DA: it decides the bits of M_c from its registers, S[n][m] and DBt[m][n].
-// Measured at the benchmark shape: 0.64 ms per side, 0.52 ms with the pooled-operand loads
-// switched off (they are 8 KB from L2 per 32 MFMAs and wave), 0.36 ms of MFMA time at the
-// clock the chip holds; a resident copy of the block in registers at two waves per SIMD: 0.65. The pooled operand is rounded to
+// and never stores DA: it decides the bits of M_c from its registers, S[n][m] and DBt[m][n]. Many long rows take
+// deviation_long_kernel instead (below). Measured with 24 heads of 931 blocks, before those went there: 0.64 ms per side,
+// 0.52 ms with the pooled-operand loads switched off (they are 8 KB from L2 per 32 MFMAs and wave), 0.36 ms of MFMA time at
+// the clock the chip holds; a resident copy of the block in registers at two waves per SIMD: 0.65. The pooled operand is rounded to
 // fp16 as well; accumulation is fp32. fp16 rather than bf16 because both operands are O(1)
 // quantities whose 2^-12 relative rounding leaves DA / DB within 2e-4 relative of fp64
 // arithmetic (bf16 operands: up to 1.5e-3, wider than the 1e-3 band in which the gate may
@@ -244,6 +244,10 @@ constexpr int kDevCols = 32 * kDevWaves;         // pooled vectors of an iterati
 // 591 916 -> 836, 24 heads of 1182 blocks of 64 1306 -> 1093, 3 heads of 931 174 -> 158. Building the list costs a
 // workgroup about 3 us, which short rows do not earn back (24 heads of 516 blocks 437 -> 466, 2 of 17 7.2 -> 10.0) and
 // a single round of workgroups cannot hide (3 heads of 636 blocks of 64: no gain): hence the two conditions.
+// At d = 64, the whole of rsa_pool: 24 of 931 1030 -> 901, 40 of 591 795 -> 718, 24 of 734 blocks of 64 504 -> 397. How much is
+// skipped depends on the inputs: with every pair open (blocks of equal tokens) rsa_pool takes 1753 -> 1810 us at 24 of 931 blocks of
+// 128, d = 128, and 796 -> 809 at 24 of 556, no more than before at d = 64 or with blocks of 64 (1731 -> 1557 at 24 of 1182); with
+// none open 1799 -> 1323.
 inline bool use_long_rows(const Dims& dm) {
   const int groups = (dm.n + kDevRows / dm.blk - 1) / (kDevRows / dm.blk);
   return dm.m > 544 && (long long)groups * dm.batch * dm.heads > 1024;
@@ -267,10 +271,9 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
   constexpr int NP = kDevRows / RPP, PB_ = BLK / RPP;   // passes in all and of one token block
   constexpr int LU = 4 / RB;                     // chunks of 64 key blocks whose scores and deviations a wave asks for at a time
   __shared__ u32x4 atile[kDevRows * CPR];
-  // Workgroup i runs on XCD i % 8. Each XCD takes a contiguous eighth of the (batch, head, block)
-  // range, so that token blocks that are neighbours run on the same XCD at about the same time: the
-  // query side reads DBt[m][n] for a fixed n, 32 neighbouring n to a 128-byte line, which then
-  // comes into one L2 once instead of into all eight.
+  // Workgroup i runs on XCD i % 8. Each XCD takes a contiguous eighth of the (batch, head, block) range: the key side
+  // stores DB[n][m] word by word, 32 neighbouring m to a 128-byte line, which then comes together in one L2, and the
+  // pooled vectors that an XCD reads at any time are those of a head or two.
   const int groups_x = (n_blocks_x + RB - 1) / RB;
   const int total = groups_x * dm.batch * dm.heads;
   int wg = blockIdx.x;

@@ -93,7 +93,7 @@ struct ScoreArgs {
   const uint16_t* K;
   const float *Qp, *Kp;
   float *Spool, *Apool, *Lmass;
-  bool text_done = false;  // the text columns of Lmass are already written (by the launch that pooled V)
+  bool text_done = false;  // the text columns of Lmass are already written (by the launch that pooled V, or the key side of the gate)
 };
 hipError_t launch_scores(const Dims& dm, const ScoreArgs& a, hipStream_t s);
 
