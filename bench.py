@@ -116,13 +116,13 @@ def cpu_baseline(cfg, sparsity, Qb, Kb, Vb, gpu_O_bits, gpu_mask, gpu_Mc, budget
 # (counter KiB x 1024 x the scale the same counter shows for a plain copy kernel: 2.0 fetch, 1.0 write).
 # A counter run cannot be made from inside the timed process, so the figure is carried here for the
 # exact workload it was taken on and is null for any other. Provenance: the two runs listed in
-# profiles/attn_kernel_hunyuan_pmc.md, taken with the attention kernel of this tree (persistent
-# schedule, sum-checked softmax window): FETCH_SIZE 20.06e6 KiB (three runs: 20.01e6, 20.08e6, 20.08e6), WRITE_SIZE 714.4e3 KiB per launch.
+# profiles/attn_kernel_hunyuan_pmc.md, taken with the attention kernel named by the hash below: FETCH_SIZE 19.27e6 KiB
+# (four launches: 19.09e6 to 19.45e6), WRITE_SIZE 714.3e3 KiB per launch.
 # The figure is reported only while csrc/attn_kernels.hip is byte for byte the source the counters were
 # taken on (hash below); after any change to it, re-measure and update figure, hash and profile together.
-MEASURED_TRAFFIC_BYTES = {("hunyuan", 0.9, 0, 24, 128, 128): 20.06e6 * 2.0 * 1024 + 714.4e3 * 1024}
+MEASURED_TRAFFIC_BYTES = {("hunyuan", 0.9, 0, 24, 128, 128): 19.27e6 * 2.0 * 1024 + 714.3e3 * 1024}
 MEASURED_TRAFFIC_SOURCE = "profiles/attn_kernel_hunyuan_pmc.md"
-MEASURED_TRAFFIC_KERNEL_SHA = "9cd14123b58fd508"      # first 16 hex digits of sha256(csrc/attn_kernels.hip) at the time of the counter runs
+MEASURED_TRAFFIC_KERNEL_SHA = "5b9edbfc37766db4"      # first 16 hex digits of sha256(csrc/attn_kernels.hip) at the time of the counter runs
 
 
 def measured_traffic(cfg, sparsity, args):

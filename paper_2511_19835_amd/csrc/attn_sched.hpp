@@ -40,22 +40,25 @@ constexpr int kSplitRounds = 32;
 // call has no text rows. Cut, the round is over (1 - left / slots) len key blocks earlier. But whole rows walk the keys in step
 // and share tiles, also where lists differ; their pieces are spread over the key axis and over CUs that others use,
 // and go through fp32 buffers. That costs the time of 9 key blocks of 128, of 15 of 64, 20 at d = 128, where a group asks the
-// L2 for the most bytes per product, and more than what is saved once half of the slots, there a third, have a row.
+// L2 for the most bytes per product; twice to four times that once more than half of the slots have a row, and too much above
+// five eighths (at d = 128 with blocks of 64 above a third).
 // Measured from 0.05 to 0.9 of the slots, none to twenty rounds before, 1 to 40 heads, lists of a tenth, a fifth and half
-// of the blocks, smooth and random inputs (4700 pairs; us, whole and cut, the merging launch included). d = 128, blocks of
+// of the blocks, smooth and random inputs (5600 pairs; us, whole and cut, the merging launch included). d = 128, blocks of
 // 128: 12 rows of 17 key blocks for 64 slots 57 and 48; 13 of 39 (after a full round) 252 and 211; 20 of 14 (after one) 106
 // and 112; 57 of 77 275 and 331. Blocks of 64: 26 rows of 104 for 128 slots 156 and 85; 40 of 20 47 and 54; 78 of 105 175 and 304.
 struct CutRule {
   int most_left;            // thirty-seconds of the slots
-  int least_saved;          // quarters of a key block
+  int least_saved;          // quarters of a key block, up to that many rows
+  int least_saved_over;     // ... and for more
 };
 inline CutRule cut_rule(const Dims& dm) {
-  if (dm.blk == 128) return {17, 35};
-  if (dm.d == 64) return {17, 60};
-  return {11, 80};
+  if (dm.blk == 128) return {17, 35, dm.d == 64 ? 68 : 160};
+  if (dm.d == 64) return {17, 60, 100};
+  return {11, 80, 1 << 20};
 }
 __host__ __device__ __forceinline__ bool cut_pays(const CutRule& rule, int left, int slots, int len) {
-  return 32 * left <= rule.most_left * slots && 4LL * len * (slots - left) >= (long long)rule.least_saved * slots;
+  const int least = 32 * left <= rule.most_left * slots ? rule.least_saved : rule.least_saved_over;
+  return 8 * left <= 5 * slots && 4LL * len * (slots - left) >= (long long)least * slots;
 }
 
 struct DealArgs {

@@ -405,6 +405,8 @@ def test_dense_rows_with_a_workspace(gpu, name):
     (3, 128, 128, 34, 0.5, False, True),        # 12 rows of 17 key blocks
     (2, 64, 64, 40, 0.5, False, True),          # 10 rows of 20 for 128 slots
     (8, 64, 128, 31, 0.9, False, False),        # 31 rows of 4 for 64: whole
+    (1, 64, 64, 576, 0.5, False, True),         # 72 rows of 288 for 128
+    (3, 128, 128, 101, 0.5, False, False),      # 37 or 38 rows of 51 for 64: whole
     (3, 128, 64, 106, 0.9, True, True),         # unequal rows for less than half of the slots
     (8, 128, 64, 136, 0.9, True, False),        # unequal rows, more than slots: whole
     (8, 128, 128, 68, 0.9, True, True),         # the same with blocks of 128
