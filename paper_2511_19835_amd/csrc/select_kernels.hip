@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void select_kernel(Dims dm, SelectArgs a) {
 hipError_t launch_select(const Dims& dm, const SelectArgs& a, hipStream_t s) {
   const dim3 grid((dm.n + 3) / 4, dm.batch * dm.heads), block(256);
   // A slot costs the same whether the row reaches it or not (the kernel is bound by instruction issue): 24 heads of 1182
-  // blocks 197 us in 32 slots, 127 in 20; of 516 43 us in 16, 36 in 12; 40 of 591 66 us in 16, 56 in 12.
+  // blocks 186 us in 32 slots, 110 in 20; of 516 36 us in 16, 29 in 12; 40 of 591 57 us in 16, 46 in 12.
   if (dm.m <= 64 * 4)
     hipLaunchKernelGGL(select_kernel<4>, grid, block, 0, s, dm, a);
   else if (dm.m <= 64 * 8)
