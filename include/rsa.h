@@ -194,7 +194,8 @@ int rsa_adjacency_mask(const rsa_shape* shape, const int32_t* grid, const int32_
  * order and balanced by the length of their lists, to the resident workgroups of the attention
  * kernel, and fp32 buffers for the query blocks that the schedule cuts into pieces (where a few long rows
  * or an uneven last round would leave part of the chip idle). A query block that is cut adds the same terms in
- * another order, so that with and without a workspace the last bits may differ; for the same arguments and
+ * another order, and each piece rounds its probabilities to bf16 against its own reference where the scores ask for one
+ * other than 0, so that with and without a workspace the last bits may differ; for the same arguments and
  * workspace size the results are always the same. Required with RSA_COMPENSATE
  * (RSA_E_NULL); without that flag it may be NULL, and the query blocks are then dealt whole in index
  * order. With RSA_DENSE a workspace that is too small or misaligned is ignored (index order).
