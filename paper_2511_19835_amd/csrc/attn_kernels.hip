@@ -50,9 +50,6 @@ constexpr int VSTAGES = 3;           // ... of its V^T tiles, which are read one
 #ifndef RSA_MWIN
 #define RSA_MWIN 4
 #endif
-#ifndef RSA_DSLOT
-#define RSA_DSLOT 2
-#endif
 constexpr bool SPLIT_LOADS = true;   // K rows requested in the MFMA phase, V^T rows in the softmax phase
 constexpr int MWIN = RSA_MWIN;      // MFMA slots between the LDS read of a K operand and its use
 
@@ -320,54 +317,62 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   for (int ii = 0; ii < C::KPW; ++ii) kvo[ii] = k_voff[ii % KOFF] + (uint32_t)(ii / KOFF) * kpass_bytes;
 #pragma unroll
   for (int ii = 0; ii < C::VPW; ++ii) vvo[ii] = v_voff[ii % VOFF] + (uint32_t)((ii / VOFF) * (V_ROWS_PER_PASS * BLK * 2));
-  uint32_t kvw[C::KPW];                          // the K offsets in use: kvo, or clamped rows for a ragged block
-#pragma unroll
-  for (int ii = 0; ii < C::KPW; ++ii) kvw[ii] = kvo[ii];
-  int kvw_ragged = 0;
   struct Tile {
-    uint64_t kp;          // K rows of this step (of the whole block when it is ragged)
+    uint64_t kp;          // K rows of this step
     uint64_t vp;          // V^T rows of this step
     uint32_t kdst, vdst;  // LDS byte addresses of this wave's first load into the stage
+    uint32_t klast;       // byte offset of the block's last row from kp
+    uint32_t koff[C::KPW];   // kvo, held to the rows of the block
   };
   // The key block whose tiles are being requested: start of its K rows and V^T rows, valid keys.
   uint64_t blk_kp = 0, blk_vp = 0;
   int blk_count = BLK;
-  // A tile is prepared in short pieces of scalar work so that the caller can put one behind each
-  // of its first MFMAs: open_block for the first step of a key block, step_of_block for every step.
-  // A ragged key block (the last video block, the last text block) adds vector work: K rows past
-  // the block end re-read its last row (masked later; V^T is zero-padded in HBM), with per-lane
-  // offsets from the start of the block.
-  auto open_block = [&](int m, uint64_t Kbytes, uint64_t Vtbytes) __attribute__((always_inline)) {
-    blk_kp = Kbytes + ((uint64_t)(uint32_t)m * kblock_bytes + (uint64_t)(m >= dm.n ? text_adjust : 0));
-    blk_vp = Vtbytes + (uint64_t)(uint32_t)m * kVtBlockBytes;
-    blk_count = count_of(m);
+  const uint32_t krow_bytes = (uint32_t)dm.st * 2u;
+  // A tile is prepared in pieces of a few instructions each, so that the caller can put one behind each of its first
+  // MFMAs: a matrix instruction covers 32 cycles and a wave issues an instruction every five or so, so that with all forty
+  // (two branches among them) behind one MFMA the matrix pipe stood still (MFMA phase at d = 128, blocks of 128: 1440 cycles
+  // of the 1024 that its instructions take, now 1290; 24 heads of 931 blocks 15 310 -> 14 800 us, 40 of 591 10 280 -> 9870,
+  // where the power limit gives a part of it back in clock; d = 64, bound by its softmax, 728 -> 723). Pieces
+  // 0 .. kOpenPieces-1 open the key block m (first step of a block), the kStepPieces after them are taken for every step.
+  // In a ragged key block (the last video block, the last text block) rows past its end re-read its last row (masked
+  // later; V^T is zero-padded in HBM): the byte offset of every lane is held to that row's, without a branch.
+  constexpr int kOpenPieces = 4, kStepPieces = 3;
+  uint64_t open_base = 0;
+  auto open_piece = [&](auto pc, int m, uint64_t Kbytes, uint64_t Vtbytes) __attribute__((always_inline)) {
+    constexpr int piece = decltype(pc)::value;
+    if constexpr (piece == 0) open_base = Kbytes + (uint64_t)(m >= dm.n ? text_adjust : 0);
+    if constexpr (piece == 1) blk_kp = open_base + (uint64_t)(uint32_t)m * kblock_bytes;
+    if constexpr (piece == 2) blk_count = count_of(m);
+    if constexpr (piece == 3) blk_vp = Vtbytes + (uint64_t)(uint32_t)m * kVtBlockBytes;
   };
-  auto step_of_block = [&](Tile& t, uint32_t part, int kst, int vst) __attribute__((always_inline)) {
-    t.kp = blk_kp + part * kstep_bytes;
-    t.vp = blk_vp + part * (KVS * 2u);
-    t.kdst = ldsK_addr + kst * (KBUF * 16);
-    t.vdst = ldsV_addr + vst * (C::VBUF * 16);
-    if (kvw_ragged) {
-#pragma unroll
-      for (int ii = 0; ii < C::KPW; ++ii) kvw[ii] = kvo[ii];
-      kvw_ragged = 0;
+  auto step_piece = [&](auto pc, Tile& t, auto partc, int kst, int vst) __attribute__((always_inline)) {
+    constexpr int piece = decltype(pc)::value;
+    constexpr int part = decltype(partc)::value;
+    if constexpr (piece == 0) {
+      // (a block that ends before its second step: the step reads the rows of the first, all of them masked)
+      const uint32_t skip = part > 0 && blk_count > part * KVS ? part * kstep_bytes : 0u;
+      t.kp = blk_kp + skip;
+      t.klast = (uint32_t)(blk_count - 1) * krow_bytes - skip;
     }
-    if (blk_count < BLK) {
-      t.kp = blk_kp;
+    if constexpr (piece == 1) {
+      t.vp = blk_vp + part * (KVS * 2u);
+      t.kdst = ldsK_addr + kst * (KBUF * 16);
+      t.vdst = ldsV_addr + vst * (C::VBUF * 16);
+    }
+    if constexpr (piece == 2) {
 #pragma unroll
-      for (int ii = 0; ii < C::KPW; ++ii) {
-        int r = (int)part * KVS + (ii / KOFF) * K_ROWS_PER_PASS + k_r0[ii % KOFF];
-        r = r < blk_count ? r : blk_count - 1;
-        kvw[ii] = (uint32_t)((r * dm.st + k_col[ii % KOFF]) * 2);
+      for (int c = 0; c < KOFF; ++c) {
+        const uint32_t last = t.klast + (uint32_t)k_col[c] * 2u;
+#pragma unroll
+        for (int ii = c; ii < C::KPW; ii += KOFF) t.koff[ii] = min(kvo[ii], last);
       }
-      kvw_ragged = 1;
     }
   };
   auto issue_load = [&](const Tile& t, auto idxc) __attribute__((always_inline)) {
     constexpr int idx = decltype(idxc)::value;
     if constexpr (idx < C::KPW) {
       constexpr int ii = idx;
-      dma16_sv_imm<(ii / KOFF) * K_LDS_PASS + (ii % KOFF) * K_LDS_CLASS>(t.kdst, t.kp, kvw[ii], lds);
+      dma16_sv_imm<(ii / KOFF) * K_LDS_PASS + (ii % KOFF) * K_LDS_CLASS>(t.kdst, t.kp, t.koff[ii], lds);
     } else {
       constexpr int ii = idx - C::KPW;
       dma16_sv_imm<(ii / VOFF) * V_LDS_PASS + (ii % VOFF) * V_LDS_CLASS>(t.vdst, t.vp, vvo[ii], lds);
@@ -606,7 +611,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   auto m_phase = [&](auto stc, auto qkc, auto lastc) __attribute__((always_inline)) {
     constexpr int ST = decltype(stc)::value;          // s modulo 2: the K stage and the part of the key block
     constexpr bool do_qk = decltype(qkc)::value != 0, last_of_item = decltype(lastc)::value != 0;
-    constexpr int DSLOT = RSA_DSLOT;                  // the slot in which the requests for the next tile start
+    constexpr int PART_NEXT = (ST + 1) % C::SPB;
+    constexpr int OPEN = PART_NEXT == 0 ? kOpenPieces : 0;
+    constexpr int DSLOT = OPEN + kStepPieces;         // the slot in which the requests for the next tile start
     constexpr int MLOADS = SPLIT_LOADS ? C::KPW : LPS;   // requests of this phase: the K rows, or the whole tile
     constexpr int LAST = do_qk ? NSLOT : NPV;         // slots that hold an MFMA
     constexpr int WB = W / 2;                         // operands are waited for WB at a time
@@ -650,21 +657,16 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
           ring[slot % W] = __builtin_bit_cast(bf16x8, kread[k2][(ST % KSTAGES) * KBUF + t * 32 * C::KCPR]);
         }
       }
-      if constexpr (do_qk && i < 2) {
-        // behind the first MFMAs, so that the matrix pipe starts as soon as the barrier opens:
-        // addresses of the tile of step s+1. Whether that step opens a new key block (its list entry
-        // came in during V(s-1)) follows from the parity of s. A group whose last step this is
+      if constexpr (do_qk && i < OPEN + kStepPieces) {
+        // behind the first MFMAs, one piece each: addresses of the tile of step s+1. Whether that step opens a new key block
+        // (its list entry came in during V(s-1)) follows from the parity of s. A group whose last step this is
         // requests the tile of its last list entry once more, into a stage nobody reads again.
         __builtin_amdgcn_sched_barrier(0);
-        constexpr int PART_NEXT = (ST + 1) % C::SPB;
-        if constexpr (i == 0) {
-          if constexpr (PART_NEXT == 0) {
-            const bool in_next = last_of_item && nxt_valid;
-            open_block(m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, in_next ? nxt.Kbytes : cur.Kbytes, in_next ? nxt.Vtbytes : cur.Vtbytes);
-          }
-          kvc_nxt = blk_count;
+        if constexpr (i < OPEN) {
+          const bool in_next = last_of_item && nxt_valid;
+          open_piece(ic, m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, in_next ? nxt.Kbytes : cur.Kbytes, in_next ? nxt.Vtbytes : cur.Vtbytes);
         } else {
-          step_of_block(nt, PART_NEXT, (ST + 1) % KSTAGES, vst + 1 >= VSTAGES ? 0 : vst + 1);
+          step_piece(IntC<i - OPEN>{}, nt, IntC<PART_NEXT>{}, (ST + 1) % KSTAGES, vst + 1 >= VSTAGES ? 0 : vst + 1);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -674,7 +676,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       constexpr int idx = decltype(ic)::value;
       if constexpr (do_qk && DSLOT + idx >= LAST) issue_load(nt, ic);
     });
-    if constexpr (do_qk) vt_next = nt;
+    if constexpr (do_qk) {
+      vt_next = nt;
+      kvc_nxt = blk_count;
+    }
     if constexpr (SPLIT_LOADS) {
       // the V^T rows of this step (requested a phase ago, ahead of this phase's K rows) have landed
       wait_loads_leaving<do_qk ? MLOADS : 0>();
@@ -749,15 +754,16 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     {
       const int kv_count = kvc_cur;
       // accumulator register r of key tile t is key part*KVS + 32t + 8(r/4) + 4*hf + r%4 of the block
-      if (kv_count < BLK) {
-        constexpr int part = ST % C::SPB;
+      // (rare, like the branch below: out of line, the path that every step takes has no jump over it)
+      if (__builtin_expect(kv_count < BLK, 0)) {
+        // (constants against one lane-dependent bound: compared the other way round, the key numbers are 32 registers that
+        // the compiler keeps through the whole loop)
+        const int valid = kv_count - (ST % C::SPB) * KVS - 4 * hf;
 #pragma unroll
         for (int t = 0; t < C::KT; ++t)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int kv = part * KVS + 32 * t + 8 * (r / 4) + 4 * hf + (r % 4);
-            if (kv >= kv_count) sacc[t][r] = -INFINITY;
-          }
+          for (int r = 0; r < 16; ++r)
+            if (32 * t + 8 * (r / 4) + (r % 4) >= valid) sacc[t][r] = -INFINITY;
       }
       // ---- online softmax, one query column per lane ---------------------------------
       // Scores are counted in binades (score * scale * log2 e) from a reference that starts at 0 for
@@ -793,7 +799,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       float rs = probabilities();
       bool outside = rs > kAbove;
       if constexpr (first_of_item) outside = outside || rs < kBelow;
-      if (__any(outside)) {
+      if (__builtin_expect(__any(outside), 0)) {
         float mx = -INFINITY;
 #pragma unroll
         for (int t = 0; t < C::KT; ++t)
@@ -805,9 +811,6 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
           // themselves) must not become the reference, -inf - -inf is no number: below the lowest finite one their
           // probabilities are 0, and the first finite score leaves the window and brings its own reference.
           mref = fmaxf(mx, -3.4028234663852886e38f);
-          // (the step loops behind this rare branch stay where they were within 64 bytes: 8 bytes further on, RSA_DENSE
-          // with 24 heads of 159 blocks takes 4084 us instead of 4070, a layer of 24 heads of 159 blocks 675 instead of 671)
-          asm volatile(".rept 14\n\ts_nop 0\n\t.endr");
         } else {
           const float mnew = fmaxf(mref, mx);
           const float alpha = __builtin_amdgcn_exp2f(mref - mnew);
@@ -881,8 +884,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // *every* outstanding load -- at the first use inside the loop.
     __builtin_amdgcn_s_waitcnt(0x0F70);
     Tile t0;
-    open_block(list_entry(cur, 0), cur.Kbytes, cur.Vtbytes);
-    step_of_block(t0, 0, 0, 0);
+    const int m0 = list_entry(cur, 0);
+    static_for<0, kOpenPieces>([&](auto pc) __attribute__((always_inline)) { open_piece(pc, m0, cur.Kbytes, cur.Vtbytes); });
+    static_for<0, kStepPieces>([&](auto pc) __attribute__((always_inline)) { step_piece(pc, t0, IntC<0>{}, 0, 0); });
     static_for<0, LPS>([&](auto ic) __attribute__((always_inline)) { issue_load(t0, ic); });
     kvc_cur = blk_count;
     fj = 1;

@@ -397,6 +397,29 @@ def test_dense_rows_with_a_workspace(gpu, name):
     assert np.linalg.norm(err) / np.linalg.norm(want) <= parity.OUT_REL_L2
 
 
+@pytest.mark.parametrize("video,text", [(1, 127), (31, 96), (32, 65), (33, 64), (63, 63), (64, 33), (65, 1), (127, 0)])
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("d", [64, 128])
+def test_last_blocks_of_any_length(gpu, d, block, video, text):
+    """Last video and text blocks that end inside, at the end of and before the second step of a key block (a step takes
+    half a block): keys past the end of a block carry no weight and are not read from past the end of the tensor's rows."""
+    import parity
+    from oracle import rsa_oracle as ro
+    video, text = video % block, text % block
+    tokens = 4 * block + video                    # a grid of one row of tiles: any token count
+    cfg = LayerConfig("last_blocks", 1, 2, d, (1, 1, tokens), block + text if text else 0, block, 0.0)
+    Qb, Kb, Vb = synth.make_inputs(cfg, 46)
+    Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
+    for workspace in (False, True):
+        O, _ = _attend_to_all(gpu, cfg, Q, K, V, workspace, workspace)
+        for h in range(cfg.heads):
+            q, k, v = (ro.bf16_bits_to_f64(x[0, h]) for x in (Qb, Kb, Vb))
+            want = ro.dense_attention(q, k, v, 1 / np.sqrt(cfg.head_dim))
+            err = O[0, h].numpy() - want
+            assert np.abs(err).max() <= parity.OUT_MAX_ABS
+            assert np.linalg.norm(err) / np.linalg.norm(want) <= parity.OUT_REL_L2
+
+
 @pytest.mark.parametrize("heads,d,block,blocks,sparsity,unequal,cut", [
     (1, 128, 64, 208, 0.5, False, True),        # 26 rows of 104 key blocks for 128 slots
     (3, 128, 64, 210, 0.5, False, False),       # 78 rows: whole
