@@ -53,7 +53,7 @@ constexpr int VSTAGES = 3;           // ... of its V^T tiles, which are read one
 constexpr bool SPLIT_LOADS = true;   // K rows requested in the MFMA phase, V^T rows in the softmax phase
 constexpr int MWIN = RSA_MWIN;      // MFMA slots between the LDS read of a K operand and its use
 
-template <int D, int BLK>
+template <int D, int BLK, bool HALVES>
 struct AttnCfg {
   static constexpr int NW = BLK / 32;       // waves per group (one per 32 query rows)
   static constexpr int NGRP = 8 / NW;       // groups = query blocks per workgroup: eight waves, two per SIMD
@@ -66,15 +66,20 @@ struct AttnCfg {
   static constexpr int KS = D / 16;         // k-steps of K Q^T
   static constexpr int DT = D / 32;         // channel tiles of O^T
   static constexpr int PC = KVS / 16;       // 16-key chunks per step
+  static constexpr bool VH = HALVES;        // V^T by halves of the channels, all keys of the block at once (see attn_kernel)
+  static constexpr int PPC = VH ? BLK / 16 : PC;     // 16-key chunks of one P V product
+  static constexpr int PDT = VH ? DT / 2 : DT;       // ... and its channel tiles
   static constexpr int KCPR = D / 8;        // 16-byte chunks per K row
-  static constexpr int VCPR = KVS / 8;      // 16-byte chunks per V^T row of one step
+  static constexpr int VCPR = PPC * 2;      // 16-byte chunks per V^T row of a tile
+  static constexpr int VROWS = PDT * 32;    // V^T rows of a tile
   static constexpr int KINST = KVS * KCPR / 64;   // 1 KB direct-to-LDS loads per K step tile
-  static constexpr int VINST = D * VCPR / 64;     // ... per V^T step tile
+  static constexpr int VINST = VROWS * VCPR / 64; // ... per V^T step tile
   static constexpr int KPW = KINST / NW;    // per wave
   static constexpr int VPW = VINST / NW;
   static constexpr int KBUF = KVS * KCPR;   // 16-byte chunks per K buffer
-  static constexpr int VBUF = D * VCPR;     // ... per V^T buffer
+  static constexpr int VBUF = VROWS * VCPR; // ... per V^T buffer
   static constexpr int GROUP = KSTAGES * KBUF + VSTAGES * VBUF;   // 16-byte chunks of one group: [K stages | V^T stages]
+  static_assert(!VH || SPB * PDT == DT, "a half of the channels for each step of a block");
   static_assert(KINST % NW == 0 && VINST % NW == 0, "loads must split evenly over the waves");
   static_assert(KSTAGES == 2 && NGRP * GROUP * 16 <= 160 * 1024, "the rings of all groups must fit the LDS of a CU");
   static_assert(SPB == 2, "the main loop is unrolled twice: over the K stages and over the steps of a key block");
@@ -154,9 +159,18 @@ struct SchedArgs {
   int dense_per_bh, dense_first;
 };
 
-template <int D, int BLK>
+// HALVES (blocks of 64): a V^T row of a key block is 128 bytes, one line, and the 32 keys of a step are half of it. Taken
+// step by step every line is asked for twice, and a step in the sparse layers waits 430 cycles for its tiles (24 heads of
+// 1182 blocks at d = 128: 1.23e9 requests of the L2, 55 GB through the fabric at 6 TB/s). So the two P V products of a
+// block take all its 64 keys and half of the channels each, one step later: M(s) multiplies the probabilities of the
+// block before with the half s % 2 of its V^T rows, whole lines. Probabilities of the block's first step are kept aside (pbn)
+// while the second product of the block before still needs pb, and an item's output is complete, and written, in the second
+// step of the next. Attention of that layer 9320 -> 7090 us, 24 heads of 318 blocks 609 -> 577. Not for RSA_DENSE, where
+// the groups of a CU walk in step and the L1 serves the second half (318 blocks: 4640 -> 4717), nor at d = 64, where the
+// softmax hides the requests and the moves do not (24 heads of 1182: 4712 -> 4840).
+template <int D, int BLK, bool HALVES>
 __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, SchedArgs sc) {
-  using C = AttnCfg<D, BLK>;
+  using C = AttnCfg<D, BLK, HALVES>;
   constexpr int KBUF = C::KBUF;
   constexpr int KVS = C::KVS, NGRP = C::NGRP;
   __shared__ u32x4 lds_all[NGRP * C::GROUP];   // per group: KSTAGES K tiles [KVS][d], then VSTAGES V^T tiles [d][KVS]
@@ -355,7 +369,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       t.klast = (uint32_t)(blk_count - 1) * krow_bytes - skip;
     }
     if constexpr (piece == 1) {
-      t.vp = blk_vp + part * (KVS * 2u);
+      t.vp = blk_vp + part * (C::VH ? C::VROWS * BLK * 2u : KVS * 2u);
       t.kdst = ldsK_addr + kst * (KBUF * 16);
       t.vdst = ldsV_addr + vst * (C::VBUF * 16);
     }
@@ -381,11 +395,11 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 
   // ---- loop-invariant LDS read positions (16-byte chunk index inside stage 0, tile 0) ----
   const u32x4* kread[C::KS];
-  const u32x4* vread[C::PC];
+  const u32x4* vread[C::PPC];
 #pragma unroll
   for (int ks = 0; ks < C::KS; ++ks) kread[ks] = lds + swizzled<C::KCPR>(l32, 2 * ks + hf);
 #pragma unroll
-  for (int pc = 0; pc < C::PC; ++pc) vread[pc] = lds + KSTAGES * KBUF + swizzled<C::VCPR>(l32, 2 * pc + hf);
+  for (int pc = 0; pc < C::PPC; ++pc) vread[pc] = lds + KSTAGES * KBUF + swizzled<C::VCPR>(l32, 2 * pc + hf);
 
   // ---- the item being computed, the one after it, and the one whose output is still to be written
   Item cur = {}, nxt = {};
@@ -417,6 +431,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
   float mref = 0.f, lpart = 0.f;         // softmax reference (log2 domain) and this lane's partial row sum
+  float done_m = 0.f, done_l = 0.f;      // (VH) those of the item whose last P V product is under way
 
   // Epilogue of one item: O = R_n * acc / l + C_n (video rows; text rows: acc / l), bf16; then the
   // running state starts over for the next item. R_n and C_n are requested a step ahead (in the
@@ -448,7 +463,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   };
   // A piece of a row: the accumulators as they are (1 KB per store instruction), row sum and reference.
   auto write_piece = [&]() __attribute__((always_inline)) {
-    const float lsum = half_wave_sum(lpart);
+    const float lsum = half_wave_sum(C::VH ? done_l : lpart);
     const int ln = lane_now();
     float* p = sc.pieces + (size_t)((wg % 8) * sc.pieces_per_queue + done_piece) * (BLK * D + 2 * BLK);
     floatx4* dst = reinterpret_cast<floatx4*>(p) + wave * (C::DT * 4 * 64) + ln;
@@ -457,7 +472,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       dst[i * 64] = floatx4{oacc[i / 4][4 * (i % 4)], oacc[i / 4][4 * (i % 4) + 1], oacc[i / 4][4 * (i % 4) + 2], oacc[i / 4][4 * (i % 4) + 3]};
     if (ln < 32) {
       p[BLK * D + wave * 32 + ln] = lsum;
-      p[BLK * D + BLK + wave * 32 + ln] = mref;
+      p[BLK * D + BLK + wave * 32 + ln] = C::VH ? done_m : mref;
     }
   };
   Tile vt_next = {};          // the tile of step s+1 as M(s) prepared it: its V^T rows are requested in V(s)
@@ -478,7 +493,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(4)));
     const bool do_comp = done_sparse && (a.flags & RSA_COMPENSATE);
     const int q_count = done_q_count;
-    const float lsum = half_wave_sum(lpart);
+    const float lsum = half_wave_sum(C::VH ? done_l : lpart);
     const int ln = lane_now();
     const int hf = ln / 32;                        // (a copy of its own: see lane_now)
     const int q = wave * 32 + ln % 32;
@@ -534,7 +549,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       asm volatile("" ::: "memory");
     }
     if (q < q_count && a.lse && hf == 0)
-      a.lse[((size_t)done_bh * dm.t) + done_q_t0 + q] = (mref + log2f(lsum)) * 0.6931471805599453f;
+      a.lse[((size_t)done_bh * dm.t) + done_q_t0 + q] = ((C::VH ? done_m : mref) + log2f(lsum)) * 0.6931471805599453f;
   };
   auto write_output = [&]() __attribute__((always_inline)) {
     if (done_piece >= 0) write_piece();
@@ -543,20 +558,23 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-    mref = 0.f;
-    lpart = 0.f;
+    if constexpr (!C::VH) {
+      mref = 0.f;
+      lpart = 0.f;
+    }
   };
 
   // Two groups of waves share every SIMD (wave w of group 0 and wave w of group 1). They run
   // the same sequence  [M(s) | barrier | V(s) | barrier] ...  one barrier apart, so that while
   // one group issues MFMAs the other does its softmax on the VALU. s counts the steps of all the
   // items of the group, one after the other without a gap:
-  //   M(s): O^T += V^T P^T of step s-1, then S^T = K Q^T of step s: matrix instructions only, the A
+  //   M(s): O^T += V^T P^T of step s-1 (HALVES: half of the channels, of the block before the one of step s), then
+  //         S^T = K Q^T of step s: matrix instructions only, the A
   //         operand of each read from LDS a few slots ahead (V^T tile of step s-1 from its ring
   //         stage (s-1) % 3, K tile of step s from stage s % 2); the loads of tile s+1 (K into
   //         stage (s+1) % 2, V^T into stage (s+1) % 3) go out one per MFMA slot. Behind the last
   //         step of an item the query rows of the next item are requested.
-  //   V(s): in the first step of an item, the output of the item before it; mask, online softmax
+  //   V(s): in the first step of an item (HALVES: the second), the output of the item before it; mask, online softmax
   //         -> P as bf16 B operands (VALU only); fetch the list entry of step s+2; wait for tile
   //         s+1; read the first V^T operands of M(s+1) ahead of the barrier
   // The barrier after V(s) publishes tile s+1 to the group. A K stage is rewritten two steps
@@ -565,6 +583,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // read. Every item has an even number of steps (SPB = 2 per key block), so the position inside a
   // key block and the K stage both follow from the parity of s, which the unrolled loop knows.
   int m_nxt_e = 0, m_nxt_j = 0;   // key block that the next new-block step opens: entry m_nxt_e of a list, or block m_nxt_j (>= 0) of a dense row
+  uint64_t nxt_Kbytes = 0, nxt_Vtbytes = 0;   // ... and the K rows and V^T tiles of its item, where that may be the next one
   int kvc_cur = BLK;      // valid keys in the block of the current step
   int kvc_nxt = BLK;
   auto group_barrier = [&]() __attribute__((always_inline)) {
@@ -573,36 +592,56 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     asm volatile("" ::: "memory");
   };
   floatx16 sacc[C::KT];
-  u32x4 pb[C::PC];            // probabilities as bf16 B operands, 16 keys per entry
+  u32x4 pb[C::PPC];           // probabilities as bf16 B operands, 16 keys per entry
+  u32x4 pbn[2];               // (VH) those of the first half of a key block, while pb still holds the block before it
 #pragma unroll
-  for (int pc = 0; pc < C::PC; ++pc) pb[pc] = u32x4{0u, 0u, 0u, 0u};
+  for (int pc = 0; pc < C::PPC; ++pc) pb[pc] = u32x4{0u, 0u, 0u, 0u};
+  pbn[0] = pbn[1] = u32x4{0u, 0u, 0u, 0u};
 
   // M(s) is one fixed sequence of NPV + NQK MFMA slots: the P V product of step s-1, then K Q^T
   // of step s. The A operand of a slot (16 bytes per lane of the V^T or K tile) is read from LDS W
   // slots ahead of its MFMA into a ring of W registers, so that LDS latency stays behind MFMAs
   // that already have their operands; the first W operands of a phase are read at the end of the
   // softmax phase before it. The order is pinned slot by slot.
-  constexpr int NPV = C::PC * C::DT, NQK = C::KS * C::KT, NSLOT = NPV + NQK;
+  constexpr int NPV = C::PPC * C::PDT, NQK = C::KS * C::KT, NSLOT = NPV + NQK;
   constexpr int W = MWIN;
-  static_assert(W - W / 2 <= 4, "the operand waits are written out for at most four reads left outstanding");
   static_assert(NPV >= W && NQK >= W, "the operands read ahead of a phase all belong to its first product");
+  static_assert(W - W / 2 <= 4, "the operand waits are written out for at most four reads left outstanding");
   bf16x8 ring[W];
 #pragma unroll
   for (int i = 0; i < W; ++i) ring[i] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
   int vst = 0;                // V^T ring stage of the current step (s % VSTAGES)
-  const u32x4* vcur[C::PC];   // vread[] moved to the V^T stage whose P V product comes next
+  const u32x4* vcur[C::PPC];  // vread[] moved to the V^T stage whose P V product comes next
 #pragma unroll
-  for (int pc = 0; pc < C::PC; ++pc) vcur[pc] = vread[pc];
+  for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc];
   auto read_v_operand = [&](int slot) __attribute__((always_inline)) {      // slot < NPV
-    const int pc = slot / C::DT, dt = slot % C::DT;
+    const int pc = slot / C::PDT, dt = slot % C::PDT;
     ring[slot % W] = __builtin_bit_cast(bf16x8, vcur[pc][dt * 32 * C::VCPR]);
+  };
+  // the operands of the first W slots, at the end of a softmax phase
+  auto read_ahead = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < W; ++j) read_v_operand(j);
+  };
+  constexpr float kAbove = 1.0995116e12f, kBelow = 9.0949470e-13f;        // 2^+-kLazyBits
+  static_assert(kLazyBits == 40.0f, "kAbove and kBelow are 2^+-kLazyBits");
+  // (VH) Probabilities that wait for a P V product when the reference moves up by k binades (references are whole numbers
+  // here): k off the exponents of both bf16 numbers of a register; what would go below 2^-126 saturates at 0.
+  auto scaled = [](u32x4 w, uint32_t k) __attribute__((always_inline)) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 off = __builtin_bit_cast(u16x2, k * 0x00800080u);
+    auto pair = [&](uint32_t u) __attribute__((always_inline)) {
+      return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, u), off));
+    };
+    return u32x4{pair(w.x), pair(w.y), pair(w.z), pair(w.w)};
   };
 
   // Variants of the two phases, all compile-time:
   //   MFMA phase  QK: 0 = the last P V product of the group alone.  LAST: the step is the last of its item
   //               -- the tile of step s+1 may open the next item (that item's K and V^T), and the next
   //               item's query rows are requested behind the last K Q^T.
-  //   softmax phase  FIRST: first step of an item (the output of the item before it is written first);
+  //   softmax phase  FIRST: first step of an item.  OUT: the output of the item before is written first, if that is still to be
+  //               done (the first step; HALVES: the second, and the last, which is the second of an item of one key block);
   //               FETCH: 0 none (odd steps), 1 the next entry of the item's own list, 2 wherever step
   //               s+2 falls (own list, first entry of the next item, or the last entry once more);
   //               LAST: behind it the next item takes the place of the current one.
@@ -636,8 +675,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       // one load of the tile of step s+1 per slot, behind the MFMA of the slot before
       if constexpr (do_qk && i >= DSLOT && i - DSLOT < MLOADS) issue_load(nt, IntC<i - DSLOT>{});
       if constexpr (i < NPV) {
-        constexpr int pc = i / C::DT, dt = i % C::DT;
-        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i % W], __builtin_bit_cast(bf16x8, pb[pc]), oacc[dt], 0, 0, 0);
+        constexpr int pc = i / C::PDT, dt = (C::VH ? ST * C::PDT : 0) + i % C::PDT;
+        // (VH: the first half of a block's probabilities is in pbn for the first product, in pb for the second)
+        const u32x4 p = C::VH && ST == 0 && pc < 2 ? pbn[pc % 2] : pb[pc];
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i % W], __builtin_bit_cast(bf16x8, p), oacc[dt], 0, 0, 0);
       } else {
         constexpr int q = i - NPV, k2 = q / C::KT, t = q % C::KT;
         floatx16 c0 = sacc[t];
@@ -663,8 +704,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         // requests the tile of its last list entry once more, into a stage nobody reads again.
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (i < OPEN) {
-          const bool in_next = last_of_item && nxt_valid;
-          open_piece(ic, m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, in_next ? nxt.Kbytes : cur.Kbytes, in_next ? nxt.Vtbytes : cur.Vtbytes);
+          open_piece(ic, m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, last_of_item ? nxt_Kbytes : cur.Kbytes, last_of_item ? nxt_Vtbytes : cur.Vtbytes);
         } else {
           step_piece(IntC<i - OPEN>{}, nt, IntC<PART_NEXT>{}, (ST + 1) % KSTAGES, vst + 1 >= VSTAGES ? 0 : vst + 1);
         }
@@ -680,8 +720,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       vt_next = nt;
       kvc_nxt = blk_count;
     }
-    if constexpr (SPLIT_LOADS) {
+    if constexpr (SPLIT_LOADS && !(C::VH && do_qk)) {
       // the V^T rows of this step (requested a phase ago, ahead of this phase's K rows) have landed
+      // (VH: not needed for another step, and the wait of the softmax phase covers them)
       wait_loads_leaving<do_qk ? MLOADS : 0>();
     }
     // behind the last K Q^T of an item: the query rows of the next one (they arrive before the end of
@@ -699,9 +740,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 
   int fj = 0;                 // entry of the current item's list that the next even step fetches
   int have_output = 0;        // an item has ended and its output is still in the accumulators
-  auto v_phase = [&](auto stc, auto firstc, auto fetchc, auto lastc) __attribute__((always_inline)) {
+  auto v_phase = [&](auto stc, auto firstc, auto outc, auto fetchc, auto lastc) __attribute__((always_inline)) {
     constexpr int ST = decltype(stc)::value;
-    constexpr bool first_of_item = decltype(firstc)::value != 0, last_of_item = decltype(lastc)::value != 0;
+    constexpr bool first_of_item = decltype(firstc)::value != 0, last_of_item = decltype(lastc)::value != 0, output = decltype(outc)::value != 0;
     constexpr int FETCH = decltype(fetchc)::value;
     __builtin_amdgcn_s_setprio(0);
     constexpr int VLOADS = SPLIT_LOADS ? C::VPW : 0;  // requests of this phase: the V^T rows of step s+1
@@ -710,6 +751,19 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // after the one after the next.
     Entry entry_new = {};
     bool more = false;
+    if constexpr (C::VH && first_of_item) {
+      done_m = mref;
+      done_l = lpart;
+      mref = lpart = 0.f;
+    }
+    const bool had_output = have_output;
+    if constexpr (C::VH && output) {               // (ahead of what the last step of an item of one key block asks for)
+      if (have_output) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
+        write_output();
+        have_output = 0;
+      }
+    }
     if constexpr (last_of_item) {
       request_epilogue(cur);
       more = k_next < n_my_items;
@@ -731,18 +785,20 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       const_list_t lp = follow ? nxt.list : cur.list;
       const int hl = follow ? nxt.has_list : cur.has_list;
       const int j = own ? fj : (follow ? 0 : nlist - 1);
+      nxt_Kbytes = follow ? nxt.Kbytes : cur.Kbytes;
+      nxt_Vtbytes = follow ? nxt.Vtbytes : cur.Vtbytes;
       m_nxt_e = lp[hl ? j : 0];
       m_nxt_j = hl ? -1 : span_first(follow ? nxt.span : cur.span) + j;
       fj += 1;
     }
-    if constexpr (SPLIT_LOADS && !first_of_item) {
+    if constexpr (SPLIT_LOADS && (C::VH || !output)) {
       static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) { issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{}); });
     }
     // the first step of an item: the P V products of the item before it are complete
     // (tile s+1 is waited for first: the loads of the output would otherwise be waited for together
     // with it at the end of the phase, and so would the stores, which now complete under the next
     // MFMA phase)
-    if constexpr (first_of_item) {
+    if constexpr (!C::VH && output) {
       if (have_output) {
         __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
         write_output();
@@ -773,8 +829,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       // sum says that one of them left the window (above it; in the first step of an item, all of
       // them below it, too) is the step done again the long way -- the scores are still in registers
       // -- with the row maximum as the new reference and everything gathered so far rescaled.
-      constexpr float kAbove = 1.0995116e12f, kBelow = 9.0949470e-13f;        // 2^+-kLazyBits
-      static_assert(kLazyBits == 40.0f, "kAbove and kBelow are 2^+-kLazyBits");
+      if constexpr (C::VH && ST == 0) {
+        pb[0] = pbn[0];
+        pb[1] = pbn[1];
+      }
       auto probabilities = [&]() __attribute__((always_inline)) {
         float sum = 0.f;
 #pragma unroll
@@ -789,7 +847,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
             w.y = pack_bf16x2(p[8 * u + 2], p[8 * u + 3]);
             w.z = pack_bf16x2(p[8 * u + 4], p[8 * u + 5]);
             w.w = pack_bf16x2(p[8 * u + 6], p[8 * u + 7]);
-            pb[2 * t + u] = w;
+            if constexpr (!C::VH) pb[2 * t + u] = w;
+            else if constexpr (ST == 0) pbn[u] = w;
+            else pb[2 + u] = w;
 #pragma unroll
             for (int i = 0; i < 8; ++i) sum += p[8 * u + i];
           }
@@ -806,6 +866,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 #pragma unroll
           for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[t][r]);
         mx = half_wave_max(mx) * cs;                   // the scale is positive
+        if constexpr (C::VH) mx = ceilf(mx);           // probabilities that wait are rescaled as they are: by powers of two
         if constexpr (first_of_item) {
           // Accumulators and row sum are empty: nothing to rescale. Scores that are all -inf (keys that mask
           // themselves) must not become the reference, -inf - -inf is no number: below the lowest finite one their
@@ -814,12 +875,28 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         } else {
           const float mnew = fmaxf(mref, mx);
           const float alpha = __builtin_amdgcn_exp2f(mref - mnew);
+          const float before = mref;
           mref = mnew;
           lpart *= alpha;
+          if constexpr (!(C::VH && output && !last_of_item)) {     // (there they have just been emptied)
 #pragma unroll
-          for (int dt = 0; dt < C::DT; ++dt)
+            for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+              for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+          }
+          if constexpr (C::VH) {
+            const uint32_t up = (uint32_t)fminf(mref - before, 255.f);
+            static_for<0, (ST == 1 ? 2 : C::PPC)>([&](auto kc) __attribute__((always_inline)) {
+              constexpr int pc = decltype(kc)::value;
+              if constexpr (ST == 1) {
+                u32x4 w = scaled(pbn[pc], up);
+                asm volatile("" : "+v"(w));      // (or the accumulators are copied between registers in every MFMA phase)
+                pbn[pc] = w;
+              } else {
+                pb[pc] = scaled(pb[pc], up);
+              }
+            });
+          }
         }
         rs = probabilities();
       }
@@ -829,13 +906,14 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // the probabilities are complete here: nothing of the softmax may sink behind the barrier
     // into the MFMA phase, where it would take the other group's VALU time
 #pragma unroll
-    for (int pc = 0; pc < C::PC; ++pc) asm volatile("" : "+v"(pb[pc]));
+    for (int pc = 0; pc < C::PPC; ++pc) asm volatile("" : "+v"(pb[pc]));
+    if constexpr (C::VH) asm volatile("" : "+v"(pbn[0]), "+v"(pbn[1]));
     asm volatile("" : "+v"(lpart), "+v"(mref));
-    // the first V^T operands of M(s+1), from the stage of this step (published a whole step ago)
+    // the first V^T operands of M(s+1), from the stage of this step (published a whole step ago; VH: of the step before)
+    const int vst_read = !C::VH ? vst : vst == 0 ? VSTAGES - 1 : vst - 1;
 #pragma unroll
-    for (int pc = 0; pc < C::PC; ++pc) vcur[pc] = vread[pc] + vst * C::VBUF;
-#pragma unroll
-    for (int j = 0; j < W; ++j) read_v_operand(j);
+    for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc] + vst_read * C::VBUF;
+    read_ahead();
     vst = vst + 1 >= VSTAGES ? 0 : vst + 1;
     if constexpr (last_of_item) {
       // the item has ended: its output waits for the last P V product; the next item takes its place
@@ -858,8 +936,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // tile s+1 has landed (this wave's share; the barrier that follows covers the group), and so
     // have the query rows of the next item
     // (loads return in order: only this phase's own requests may still be out)
-    if constexpr (first_of_item) {
-      if (!have_output) wait_loads_leaving<VLOADS>();
+    if constexpr (output) {
+      if (!had_output) wait_loads_leaving<VLOADS>();
     } else {
       wait_loads_leaving<VLOADS>();
     }
@@ -890,22 +968,20 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     static_for<0, LPS>([&](auto ic) __attribute__((always_inline)) { issue_load(t0, ic); });
     kvc_cur = blk_count;
     fj = 1;
-    // The first MFMA phase multiplies the (zero) probabilities of a step that does not exist with
-    // whatever the last V^T stage holds: make that zeros too (0 x NaN would poison the accumulators).
+    // The first MFMA phase (VH: the first two) multiplies the (zero) probabilities of a step that does not exist with
+    // whatever the last V^T stage (VH: the last two) holds: make that zeros too (0 x NaN would poison the accumulators).
     {
-      u32x4* vlast = lds + KSTAGES * KBUF + (VSTAGES - 1) * C::VBUF;
-      for (int c = wave * 64 + lane; c < C::VBUF; c += C::NW * 64) vlast[c] = u32x4{0u, 0u, 0u, 0u};
+      constexpr int FROM = C::VH ? VSTAGES - 2 : VSTAGES - 1;
+      u32x4* vlast = lds + KSTAGES * KBUF + FROM * C::VBUF;
+      for (int c = wave * 64 + lane; c < (VSTAGES - FROM) * C::VBUF; c += C::NW * 64) vlast[c] = u32x4{0u, 0u, 0u, 0u};
       // ... and the operands read ahead of it come from there
 #pragma unroll
-      for (int pc = 0; pc < C::PC; ++pc) vcur[pc] = vread[pc] + (VSTAGES - 1) * C::VBUF;
+      for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc] + FROM * C::VBUF;
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0070);
   group_barrier();                  // tile 0 of every group is in LDS
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < W; ++j) read_v_operand(j);
-  }
+  if (active) read_ahead();
   if (grp >= NGRP / 2) group_barrier();    // the second half of the groups runs one barrier behind the first
   // Every group turns wg_rounds rounds of two barriers; round s is M(s), V(s) while the group has
   // steps left, the last P V product and the last output in round my_total, and nothing but the
@@ -919,38 +995,81 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       // step 0 of the item
       m_phase(IntC<0>{}, Y{}, N{});
       group_barrier();
-      v_phase(IntC<0>{}, Y{}, IntC<2>{}, N{});
+      v_phase(IntC<0>{}, Y{}, IntC<C::VH ? 0 : 1>{}, IntC<2>{}, N{});
       group_barrier();
-      if (ns >= 4) {
-        // steps 1 .. ns-4 in pairs: nothing but this item's own list and tiles
-        for (int sj = 1; sj + 3 < ns; sj += 2) {
+      if constexpr (C::VH) {
+        if (ns >= 4) {
+          // step 1 writes the output of the item before
           m_phase(IntC<1>{}, Y{}, N{});
           group_barrier();
-          v_phase(IntC<1>{}, N{}, IntC<0>{}, N{});
+          v_phase(IntC<1>{}, N{}, Y{}, IntC<0>{}, N{});
+          group_barrier();
+          // steps 2 .. ns-3 in pairs
+          for (int sj = 2; sj + 2 < ns; sj += 2) {
+            m_phase(IntC<0>{}, Y{}, N{});
+            group_barrier();
+            v_phase(IntC<0>{}, N{}, N{}, IntC<1>{}, N{});
+            group_barrier();
+            m_phase(IntC<1>{}, Y{}, N{});
+            group_barrier();
+            v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, N{});
+            group_barrier();
+          }
+          // step ns-2 fetches the first list entry of the next item
+          m_phase(IntC<0>{}, Y{}, N{});
+          group_barrier();
+          v_phase(IntC<0>{}, N{}, N{}, IntC<2>{}, N{});
+          group_barrier();
+        }
+        // step ns-1 (of an item of one key block: step 1, with the output of the item before)
+        m_phase(IntC<1>{}, Y{}, Y{});
+        group_barrier();
+        v_phase(IntC<1>{}, N{}, Y{}, IntC<0>{}, Y{});
+        group_barrier();
+      } else {
+        if (ns >= 4) {
+          // steps 1 .. ns-4 in pairs: nothing but this item's own list and tiles
+          for (int sj = 1; sj + 3 < ns; sj += 2) {
+            m_phase(IntC<1>{}, Y{}, N{});
+            group_barrier();
+            v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, N{});
+            group_barrier();
+            m_phase(IntC<0>{}, Y{}, N{});
+            group_barrier();
+            v_phase(IntC<0>{}, N{}, N{}, IntC<1>{}, N{});
+            group_barrier();
+          }
+          // steps ns-3 and ns-2: the latter fetches the first list entry of the next item
+          m_phase(IntC<1>{}, Y{}, N{});
+          group_barrier();
+          v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, N{});
           group_barrier();
           m_phase(IntC<0>{}, Y{}, N{});
           group_barrier();
-          v_phase(IntC<0>{}, N{}, IntC<1>{}, N{});
+          v_phase(IntC<0>{}, N{}, N{}, IntC<2>{}, N{});
           group_barrier();
         }
-        // steps ns-3 and ns-2: the latter fetches the first list entry of the next item
-        m_phase(IntC<1>{}, Y{}, N{});
+        // step ns-1
+        m_phase(IntC<1>{}, Y{}, Y{});
         group_barrier();
-        v_phase(IntC<1>{}, N{}, IntC<0>{}, N{});
-        group_barrier();
-        m_phase(IntC<0>{}, Y{}, N{});
-        group_barrier();
-        v_phase(IntC<0>{}, N{}, IntC<2>{}, N{});
+        v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, Y{});
         group_barrier();
       }
-      // step ns-1
-      m_phase(IntC<1>{}, Y{}, Y{});
-      group_barrier();
-      v_phase(IntC<1>{}, N{}, IntC<0>{}, Y{});
-      group_barrier();
       s += ns;
     }
     m_phase(IntC<0>{}, N{}, N{});
+    if constexpr (C::VH) {
+      // the second half of the channels (its V^T tile was published a step ago)
+      pb[0] = pbn[0];
+      pb[1] = pbn[1];
+      const int vst_read = vst == 0 ? VSTAGES - 1 : vst - 1;
+#pragma unroll
+      for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc] + vst_read * C::VBUF;
+      read_ahead();
+      m_phase(IntC<1>{}, N{}, N{});
+      done_m = mref;
+      done_l = lpart;
+    }
     group_barrier();
     __builtin_amdgcn_s_setprio(0);
     write_output();
@@ -987,9 +1106,9 @@ SchedLayout sched_layout(const Dims& dm, const SchedShape& sh) {
   return l;
 }
 
-template <int D, int BLK>
+template <int D, int BLK, bool HALVES>
 hipError_t launch_attn_t(const Dims& dm, const AttnArgs& a, const AttnSched& ws, hipStream_t s) {
-  using C = AttnCfg<D, BLK>;
+  using C = AttnCfg<D, BLK, HALVES>;
   const bool dense_all = (a.flags & RSA_DENSE) != 0;
   const int n_wg = ws.n_wg;
   if (n_wg < 8 || n_wg % 8) return hipErrorInvalidValue;
@@ -1033,7 +1152,7 @@ hipError_t launch_attn_t(const Dims& dm, const AttnArgs& a, const AttnSched& ws,
   if (sh.n_items <= kQueues * sh.slots) aa.row_order = nullptr;
   const hipError_t side = launch_attn_side(dm, aa, da, !dense_all && aa.row_order && deal, compensate, deal, s);
   if (side != hipSuccess) return side;
-  hipLaunchKernelGGL((attn_kernel<D, BLK>), dim3((unsigned)n_wg), dim3(C::NTHR), 0, s, dm, aa, sc);
+  hipLaunchKernelGGL((attn_kernel<D, BLK, HALVES>), dim3((unsigned)n_wg), dim3(C::NTHR), 0, s, dm, aa, sc);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !deal || sh.pieces_per_queue == 0) return e;
   return launch_attn_merge(dm, aa, da, s);
@@ -1053,10 +1172,11 @@ void attn_sched_bytes(const Dims& dm, size_t* schedule, size_t* pieces) {
 }
 
 hipError_t launch_attn(const Dims& dm, const AttnArgs& a, const AttnSched& ws, hipStream_t s) {
-  if (dm.d == 128 && dm.blk == 128) return launch_attn_t<128, 128>(dm, a, ws, s);
-  if (dm.d == 128 && dm.blk == 64) return launch_attn_t<128, 64>(dm, a, ws, s);
-  if (dm.d == 64 && dm.blk == 128) return launch_attn_t<64, 128>(dm, a, ws, s);
-  return launch_attn_t<64, 64>(dm, a, ws, s);
+  if (dm.d == 128 && dm.blk == 128) return launch_attn_t<128, 128, false>(dm, a, ws, s);
+  if (dm.d == 128 && dm.blk == 64 && !(a.flags & RSA_DENSE)) return launch_attn_t<128, 64, true>(dm, a, ws, s);   // (see attn_kernel)
+  if (dm.d == 128 && dm.blk == 64) return launch_attn_t<128, 64, false>(dm, a, ws, s);
+  if (dm.d == 64 && dm.blk == 128) return launch_attn_t<64, 128, false>(dm, a, ws, s);
+  return launch_attn_t<64, 64, false>(dm, a, ws, s);
 }
 
 }  // namespace rsa

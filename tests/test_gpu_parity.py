@@ -269,6 +269,37 @@ def test_scores_far_from_the_softmax_reference(gpu):
             np.testing.assert_allclose(lse[0, 0, rows].cpu().numpy(), want, rtol=2e-5, atol=2e-3)
 
 
+@pytest.mark.parametrize("rise", ["1", "2", "3", "4", "last", "every"])
+@pytest.mark.parametrize("d,block", [(128, 64), (128, 128), (64, 64), (64, 128)])
+def test_reference_moves_at_any_step(gpu, d, block, rise):
+    """Scores that rise by 50 binades at one step of a row (half a key block; the second half of a block and the last step
+    among them), or at every one of the first six: what was gathered before, and probabilities that still wait for their
+    product with V, have to be on the new reference."""
+    import parity
+    from oracle import rsa_oracle as ro
+    cfg = LayerConfig("rise", 1, 2, d, (1, 1, 6 * block - 3), block - 5, block, 0.0)
+    Qb, Kb, Vb = (x.copy() for x in synth.make_inputs(cfg, 47))
+    step = np.arange(cfg.t_total) // (block // 2)
+    last = int(step[-1])
+    at = {"last": last, "every": 0}.get(rise) if rise in ("last", "every") else int(rise)
+    binades = 50.0 * np.minimum(step, 6) if rise == "every" else 50.0 * (step >= at)
+    levels = (binades * np.sqrt(d) / np.log2(np.e) / 8.0).astype(np.float32)
+    Qb[..., 0] = 0x4100                            # 8.0
+    Kb[..., 0] = (levels.view(np.uint32) >> 16).astype(np.uint16)
+    Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
+    for workspace, lists in ((False, True), (True, True), (True, False)):
+        O, lse = _attend_to_all(gpu, cfg, Q, K, V, workspace, lists)
+        for h in range(cfg.heads):
+            q, k, v = (ro.bf16_bits_to_f64(x[0, h]) for x in (Qb, Kb, Vb))
+            want = ro.dense_attention(q, k, v, 1 / np.sqrt(d))
+            err = O[0, h].numpy() - want
+            assert np.abs(err).max() <= parity.OUT_MAX_ABS
+            assert np.linalg.norm(err) / np.linalg.norm(want) <= parity.OUT_REL_L2
+            S = q @ k.T / np.sqrt(d)
+            top = S.max(axis=1)
+            np.testing.assert_allclose(lse[0, h].numpy(), np.log(np.exp(S - top[:, None]).sum(axis=1)) + top, rtol=2e-5, atol=2e-3)
+
+
 def test_attention_without_a_workspace(gpu):
     """ws = NULL is legal without RSA_COMPENSATE: the rows are then launched in index order."""
     _run_and_compare(gpu, EDGE["d128_b64_text"], seed=15, flags=1, attn_workspace=False)
