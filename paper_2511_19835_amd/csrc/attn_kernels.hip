@@ -1141,7 +1141,7 @@ hipError_t launch_attn_t(const Dims& dm, const AttnArgs& a, const AttnSched& ws,
     da.cross = (int2*)(room + l.cross);
     da.pieces = (float*)(room + l.pieces);
     da.cap = sh.cap; da.slots = sh.slots; da.groups = C::NGRP; da.pieces_per_queue = sh.pieces_per_queue;
-    da.rows_per_bh = sh.rows_per_bh; da.n_dense = sh.n_dense; da.dense_per_bh = sh.dense_per_bh > 0 ? sh.dense_per_bh : 1;
+    da.heads_at_once = sh.heads_at_once; da.most_share = sh.most_share; da.rows_per_bh = sh.rows_per_bh; da.n_dense = sh.n_dense; da.dense_per_bh = sh.dense_per_bh > 0 ? sh.dense_per_bh : 1;
     da.dense_first = sh.dense_first; da.n_cross = sh.n_cross; da.min_piece = sh.min_piece; da.switch_cost = sh.switch_cost;
     da.rule = cut_rule(dm);
     sc.table = da.table; sc.nitems = da.nitems; sc.total = da.total; sc.piece0 = da.piece0; sc.pieces = da.pieces;

@@ -31,6 +31,7 @@ __host__ __device__ __forceinline__ size_t piece_floats(int d, int blk) { return
 constexpr int kQueues = 8;                     // one queue of items per XCD
 constexpr int kMaxSlots = 128;                 // slots (resident groups of waves) of an XCD: 32 CUs, at most 4 groups each
 constexpr int kMaxCross = kQueues - 1;         // dense rows cut over all queues: what is left when they do not divide by 8
+constexpr int kMaxTurns = 64;                  // sets of heads that are worked on one after the other
 constexpr int kTailDense = 128;                // dense rows of a queue that may be cut (more: dealt whole, ahead of the others)
 // Rows are cut only where an uneven last round would cost something: below this many rounds of items. (At 24 rounds
 // it still takes 1.4 % off the layer; at 44 the most it could take off is 1.1 % of the attention, for 70 MB of buffers.)
@@ -71,6 +72,8 @@ struct DealArgs {
   float* pieces;            // [queues][pieces][piece_floats]
   int cap, slots, groups;   // slots = slots per queue, groups = slots per workgroup
   int pieces_per_queue;     // 0: no row is cut
+  int heads_at_once;        // heads that the queues work on at the same time
+  int most_share;           // what a queue may get of the average load, in 64ths, before the rows are shared out by load
   int rows_per_bh;          // N, or M under RSA_DENSE (every row is then walked whole, no list)
   int n_dense, dense_per_bh, dense_first;      // text query blocks (none under RSA_DENSE)
   int n_cross;              // the last n_cross dense rows are cut over all queues
@@ -78,14 +81,36 @@ struct DealArgs {
   CutRule rule;
 };
 
+// Heads that the eight queues (XCDs) work on at the same time. With one, every queue has an eighth of the rows of each head and
+// their lists are spread over all of its key blocks; with eight, whole heads, and four to eight times as many resident rows
+// of the same head find each other's tiles in the XCD's L2. Limited by the Infinity Cache (256 MB): the tiles that miss the L2
+// should come from there, and the K rows and V^T tiles of all heads at work have to share it. At d = 128 with blocks of 64,
+// which ask for the most bytes per product, a little over that still pays.
+// Measured, attention in us, one head and as chosen: blocks of 128, 24 heads of 159 blocks 493 and 481, with the full mask
+// rule 1376 and 1260; 40 of 591 (39 MB a head) 9879 and 9737 (eight heads: 9 to 30 more); 24 of 931 (61 MB) 14 930 and 14 910
+// (four: 100 more), full rule 20 930 and 20 330. Blocks of 64: 24 of 318 572 and 559, full rule 1706 and 1180; 24 of 1182
+// (39 MB) at sparsity 0.7 21 400 and 19 980; 24 of 1860 (61 MB) 21 640 and 19 010 (two: 21 250). d = 64: 24 of 160 723 and 712.
+inline int heads_at_once(const Dims& dm) {
+  const int bh = dm.batch * dm.heads, least = (bh + kMaxTurns - 1) / kMaxTurns;
+  const long long head_bytes = 4LL * dm.t * dm.d, most = (dm.d == 128 && dm.blk == 64 ? 250LL : 200LL) * 1000000;
+  int at_once = kQueues;
+  while (at_once > 1 && at_once * head_bytes > most) at_once /= 2;
+  return at_once > least ? at_once : least;
+}
+
 // Sizes of the schedule for `n_wg` resident workgroups of NGRP groups.
 struct SchedShape {
-  int slots, cap, least_cap, n_items, n_dense, dense_per_bh, dense_first, rows_per_bh, n_cross, pieces_per_queue, min_piece, switch_cost;
+  int heads_at_once, most_share, slots, cap, least_cap, n_items, n_dense, dense_per_bh, dense_first, rows_per_bh, n_cross, pieces_per_queue, min_piece, switch_cost;
 };
 inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   SchedShape s;
   const bool dense_all = (flags & RSA_DENSE) != 0;
   const int bh = dm.batch * dm.heads;
+  s.heads_at_once = heads_at_once(dm);
+  // A queue of a sixteenth over the average ends that much later, and still gains where tiles bound the kernel (full mask rule,
+  // heads of 5 % more or less key blocks, 24 of 366 blocks: 4386 us by eighths, 4020 by whole heads, 4250 by load); at d = 64 the
+  // softmax does (24 of 591: 6200, 6560 and 6190).
+  s.most_share = dm.d == 64 ? 65 : 68;
   s.slots = (n_wg / 8) * ngrp;
   s.rows_per_bh = dense_all ? dm.m : dm.n;
   s.dense_per_bh = dense_all ? 0 : dm.mt;

@@ -120,8 +120,13 @@ __global__ __launch_bounds__(256) void compensation_kernel(Dims dm, AttnArgs a) 
 // threads to a row. One workgroup per head sorting the keys took 21 us at 929 rows (24 heads) and 12 us at 159,
 // most of it barriers of a chip that stood still; counting takes 11 and 5 us, the gathering of the keys (a cache
 // line per row, in every workgroup) being most of it.
+// An entry of the order: the row, and the load (key blocks and switches) of the rows before it, in units of 32 key blocks
+// (at most 4095 (4096 + 6) / 32 < 2^20).
 constexpr int kRankRows = 64;
-__global__ __launch_bounds__(256) void row_rank_kernel(Dims dm, AttnArgs a) {
+__device__ __forceinline__ int32_t order_entry(int row, int load) { return (int32_t)((uint32_t)row | (uint32_t)(load / 32) << 12); }
+__device__ __forceinline__ int order_row(int32_t entry) { return entry & 4095; }
+__device__ __forceinline__ int order_load(int32_t entry) { return (int)((uint32_t)entry >> 12); }
+__global__ __launch_bounds__(256) void row_rank_kernel(Dims dm, AttnArgs a, int switch_cost) {
   __shared__ uint64_t keys[RSA_MAX_BLOCKS + 32];
   const int bh = blockIdx.y, tid = threadIdx.x;
   const int padded = (dm.n + 31) & ~31;                     // the counting loop takes 32 keys at a time
@@ -134,19 +139,26 @@ __global__ __launch_bounds__(256) void row_rank_kernel(Dims dm, AttnArgs a) {
     const int32_t* lst = a.block_idx + row * dm.m;          // (all loads at once: what lies past the count is not used)
     const int l0 = lst[0], l1 = lst[e1], l2 = lst[e2];
     const uint64_t i0 = cnt > 0 ? (uint32_t)l0 & 4095 : 4095, i1 = cnt > 1 ? (uint32_t)l1 & 4095 : 4095, i2 = cnt > 2 ? (uint32_t)l2 & 4095 : 4095;
-    keys[i] = i < dm.n ? (i0 << 36) | (i1 << 24) | (i2 << 12) | (uint64_t)i : ~0ull;     // every index < RSA_MAX_BLOCKS = 2^12
+    const uint64_t load = min(max(cnt, 1), dm.m) + switch_cost;                          // < 2^13
+    keys[i] = i < dm.n ? ((i0 << 36) | (i1 << 24) | (i2 << 12) | (uint64_t)i) << 13 | load : ~0ull;   // every index < RSA_MAX_BLOCKS = 2^12
   }
   __syncthreads();
   const int r = blockIdx.x * kRankRows + tid / 4;
   const uint64_t mine = keys[min(r, dm.n - 1)];
-  int below = 0;
+  int below = 0, load = 0;
   for (int i = tid % 4; i < padded; i += 32) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) below += keys[i + 4 * k] < mine ? 1 : 0;
+    for (int k = 0; k < 8; ++k) {
+      const uint64_t key = keys[i + 4 * k];
+      below += key < mine ? 1 : 0;
+      load += key < mine ? (int)(key & 8191) : 0;
+    }
   }
   below += __shfl_xor(below, 1);
   below += __shfl_xor(below, 2);
-  if (r < dm.n && tid % 4 == 0) a.row_order[(size_t)bh * dm.n + below] = r;
+  load += __shfl_xor(load, 1);
+  load += __shfl_xor(load, 2);
+  if (r < dm.n && tid % 4 == 0) a.row_order[(size_t)bh * dm.n + below] = order_entry(r, load);
 }
 
 // Minimum over the 64 lanes of a wave with data-parallel-primitive moves (row shifts inside the rows of
@@ -180,8 +192,8 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
 
 // Deals the items of one launch to the slots of the persistent attention kernel (a slot = one group of
 // waves of one resident workgroup). One workgroup per queue; the slots of a queue run on one XCD. The
-// queue's items: of every head a contiguous eighth of its row order (which eighth turns with the head, so that
-// the queues come out even when the rows do not divide by 8), and its share of the text query blocks.
+// queue's items: its share of the video rows, da.heads_at_once heads at a time (see heads_at_once in attn_sched.hpp),
+// and its share of the text query blocks.
 //
 // The rows go out in rounds by one wave, a lane per slot (SPL slots per lane): in a round every slot whose load
 // (key blocks so far) is within one item of the lightest takes the next item, in slot order -- neighbouring
@@ -204,7 +216,7 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
 constexpr int kDealSegment = 2048;   // rows of a queue staged in LDS at a time
 constexpr int kTailMax = 512;        // at most kTailDense + kMaxCross + 2 kMaxSlots - 1 entries are cut
 static_assert(kTailDense + kMaxCross + 2 * kMaxSlots <= kTailMax && 2 * kMaxSlots <= kDealSegment, "the tail fits its arrays and one segment");
-constexpr int kDealLdsInts = 2 * kDealSegment + 3 * kTailMax + 1 + 2 * kMaxSlots + 2 * kQueues + 4;
+constexpr int kDealLdsInts = 2 * kDealSegment + 3 * kTailMax + 1 + 2 * kMaxSlots + 2 * kQueues + kMaxTurns * (kQueues + 1) + 4;
 
 template <int SPL>
 __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, const DealArgs& da, int q, uint32_t* lds) {
@@ -218,7 +230,8 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
   int32_t* s_cnt = s_load + kMaxSlots;
   int32_t* s_cross = s_cnt + kMaxSlots;           // [8][2]: first and last piece of this queue's part of a cross row
   int32_t* t_cut = rec;                           // (the tail no longer needs the staged rows) pieces of an entry
-  int32_t* s_left = s_cross + 2 * kQueues;        // rows of the last segment still to be dealt: from, to; equal; number of tail entries
+  int32_t* s_part = s_cross + 2 * kQueues;        // [turns][9]: first row of every queue's part of a turn
+  int32_t* s_left = s_part + kMaxTurns * (kQueues + 1);   // rows of the last segment still to be dealt: from, to; equal; number of tail entries
   const int tid = threadIdx.x, lane = tid % 64;
   const bool dense_all = (a.flags & RSA_DENSE) != 0;
   const int bh_total = dm.batch * dm.heads, NR = da.rows_per_bh, S = da.slots;
@@ -227,29 +240,92 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
   const int my_dense = q < n_whole ? (n_whole - q + kQueues - 1) / kQueues : 0;
   const int lead = (split && my_dense <= kTailDense) ? 0 : my_dense;         // text rows dealt whole, ahead of the others
   const int tail_dense = my_dense - lead;
-  auto range_start = [&](int r) __attribute__((always_inline)) { return (int)((long long)r * NR / kQueues); };
-  int n_rows = (bh_total / kQueues) * NR;
-  for (int i = 0; i < bh_total % kQueues; ++i) {
-    const int r = (q + i) % kQueues;
-    n_rows += range_start(r + 1) - range_start(r);
+  // Shares. Heads are taken da.heads_at_once at a time (a turn), their rows head by head in launch order, and cut into eight
+  // parts; which part a queue gets turns. s_part[i][p]: where part p of turn i starts.
+  const int at_once = da.heads_at_once, turns = (bh_total + at_once - 1) / at_once;
+  const int32_t* order = dense_all ? nullptr : a.row_order;
+  auto rows_of_turn = [&](int i) __attribute__((always_inline)) { return min(at_once, bh_total - i * at_once) * NR; };
+  auto total_load = [&](const int32_t* o, int h) __attribute__((always_inline)) { return order_load(o[(size_t)h * NR + NR - 1]) + 1; };
+  auto sum_over_turns = [&](const int32_t* at, int queue) __attribute__((always_inline)) {
+    int n = 0;
+    for (int i = 0; i < turns; ++i) {
+      const int32_t* p = at + i * (kQueues + 1) + (queue + i) % kQueues;
+      n += p[1] - p[0];
+    }
+    return n;
+  };
+  auto largest_and_sum = [&](const int32_t* at, int& sum) __attribute__((always_inline)) {      // over the queues
+    if (tid < kQueues) s_cross[tid] = sum_over_turns(at, tid);
+    __syncthreads();
+    int most = 0;
+    sum = 0;
+    for (int k = 0; k < kQueues; ++k) {
+      most = max(most, s_cross[k]);
+      sum += s_cross[k];
+    }
+    __syncthreads();
+    return most;
+  };
+  // Parts of equal numbers of rows begin and end with a head, or half or quarter of one: rows of unequal length share tiles
+  // only with rows of their head. Kept as long as no queue gets over da.most_share 64ths of the average load.
+  for (int k = tid; k < turns * (kQueues + 1); k += 256) {
+    const int i = k / (kQueues + 1), p = k % (kQueues + 1), rows = rows_of_turn(i), at = (int)((long long)p * rows / kQueues);
+    s_part[k] = at;
+    if (order) {
+      const int32_t* o = order + (size_t)i * at_once * NR;       // the turn's rows
+      int before = at < rows ? order_load(o[at]) : 0;
+      for (int h = 0; h < at / NR; ++h) before += total_load(o, h);
+      rec[k] = before;
+    }
   }
+  __syncthreads();
+  bool by_load = false;
+  if (order) {
+    int sum;
+    const int most = largest_and_sum(rec, sum);
+    by_load = (long long)most * kQueues * 64 > (long long)sum * da.most_share;
+  }
+  if (by_load) {
+    for (int k = tid; k < turns * (kQueues + 1); k += 256) {
+      const int i = k / (kQueues + 1), p = k % (kQueues + 1), heads = rows_of_turn(i) / NR;
+      if (p == 0 || p == kQueues) continue;
+      const int32_t* o = order + (size_t)i * at_once * NR;
+      int all = 0, h = 0;
+      for (int j = 0; j < heads; ++j) all += total_load(o, j);
+      int target = (int)((long long)p * all / kQueues);
+      for (int t = 0; h + 1 < heads && target >= (t = total_load(o, h)); ++h) target -= t;
+      int lo = 0, hi = NR - 1;                                   // the first row of head h that has the target before it
+      while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        if (order_load(o[(size_t)h * NR + mid]) >= target) hi = mid;
+        else lo = mid + 1;
+      }
+      s_part[k] = h * NR + lo;
+    }
+    __syncthreads();
+    // A queue of very short rows might get more of them than its table holds: equal numbers of rows after all.
+    int sum;
+    if (lead + largest_and_sum(s_part, sum) > S * (da.cap - 2)) {
+      for (int k = tid; k < turns * (kQueues + 1); k += 256)
+        s_part[k] = (int)((long long)(k % (kQueues + 1)) * rows_of_turn(k / (kQueues + 1)) / kQueues);
+      __syncthreads();
+    }
+  }
+  const int n_rows = sum_over_turns(s_part, q);
   const int n_bulk = lead + n_rows;
   auto dense_record = [&](int d) __attribute__((always_inline)) {
     return (d / da.dense_per_bh) * RSA_MAX_BLOCKS + da.dense_first + d % da.dense_per_bh;
   };
   auto row_record = [&](int v) __attribute__((always_inline)) {          // v-th row of this queue
-    const int h8 = v / NR;
-    int rem = v % NR, head = 0, pos = 0;
-    for (int i = 0; i < kQueues; ++i) {
-      const int r = (q + i) % kQueues, r0 = range_start(r), sz = range_start(r + 1) - r0;
-      if (rem < sz) {
-        head = h8 * kQueues + i;
-        pos = r0 + rem;
-        break;
-      }
-      rem -= sz;
+    int at = v, i = 0;
+    for (; i + 1 < turns; ++i) {
+      const int32_t* p = s_part + i * (kQueues + 1) + (q + i) % kQueues;
+      if (at < p[1] - p[0]) break;
+      at -= p[1] - p[0];
     }
-    const int qb = (!dense_all && a.row_order) ? a.row_order[(size_t)head * dm.n + pos] : pos;
+    at += s_part[i * (kQueues + 1) + (q + i) % kQueues];
+    const int head = i * at_once + at / NR;
+    const int qb = order ? order_row(order[(size_t)head * NR + at % NR]) : at % NR;
     return head * RSA_MAX_BLOCKS + qb;
   };
 
@@ -683,7 +759,7 @@ hipError_t launch_attn_side_t(const Dims& dm, const AttnArgs& a, const DealArgs&
                               hipStream_t s) {
   const unsigned bh = (unsigned)(dm.batch * dm.heads), tiles = (unsigned)((dm.n + 31) / 32);
   const unsigned comp_lds = comp_lds_bytes<D>(), deal_lds = kDealLdsInts * 4u;
-  if (sort_rows) hipLaunchKernelGGL(row_rank_kernel, dim3((dm.n + kRankRows - 1) / kRankRows, bh), dim3(256), 0, s, dm, a);
+  if (sort_rows) hipLaunchKernelGGL(row_rank_kernel, dim3((dm.n + kRankRows - 1) / kRankRows, bh), dim3(256), 0, s, dm, a, da.switch_cost);
   if (deal && compensate && bh < 65535u) {
     hipLaunchKernelGGL((compensation_schedule_kernel<D>), dim3(tiles > (unsigned)kQueues ? tiles : (unsigned)kQueues, bh + 1), dim3(256),
                        comp_lds > deal_lds ? comp_lds : deal_lds, s, dm, a, da);

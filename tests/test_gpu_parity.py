@@ -486,6 +486,38 @@ def test_rows_without_text_are_cut_where_it_pays(gpu, heads, d, block, blocks, s
     assert torch.equal(outs[0][0], outs[1][0]) != cut
 
 
+@pytest.mark.parametrize("heads,d,block,blocks,lengths", [
+    (12, 64, 128, 90, "one long head"),           # 40 of 90 key blocks in one head, 2 in the others: shared out by load
+    (12, 128, 64, 180, "one long head"),
+    (11, 64, 64, 200, "heads of 1 to 60"),        # ... and a last turn of three heads
+    (13, 128, 128, 70, "rows of 1 to 30"),        # by number: heads alike
+    (9, 64, 64, 230, "short, then long"),         # a queue's share by load has more rows than its table
+    (70, 64, 128, 12, "heads of 1 to 60"),        # more heads than turns
+])
+def test_shares_of_the_queues(gpu, heads, d, block, blocks, lengths):
+    """How the rows are shared out to the eight queues, by number or by load: every row is there once, whatever the lists."""
+    import torch
+    from paper_2511_19835_amd import binding as rb
+    rng = np.random.default_rng(49)
+    Q, K, V = (torch.from_numpy(rng.standard_normal((1, heads, blocks * block, d), dtype=np.float32)).bfloat16().cuda() for _ in range(3))
+    buf = rb.allocate(Q, blocks * block, 0, block)
+    n = {"one long head": np.where(np.arange(heads)[:, None] == 5, 40, 2) * np.ones((1, blocks), dtype=int),
+         "heads of 1 to 60": np.minimum(1 + 59 * np.arange(heads)[:, None] // (heads - 1), blocks) * np.ones((1, blocks), dtype=int),
+         "rows of 1 to 30": rng.integers(1, 31, size=(heads, blocks)),
+         "short, then long": np.where(np.arange(heads)[:, None] < heads - 1, 1, blocks) * np.ones((1, blocks), dtype=int)}[lengths]
+    pick = np.sort(np.where(np.arange(blocks) < n[..., None], rng.permuted(np.tile(np.arange(blocks), (heads, blocks, 1)), axis=-1), blocks), axis=-1)
+    buf.count.copy_(torch.from_numpy(n.astype(np.int32)).reshape(buf.count.shape))
+    buf.block_idx.copy_(torch.from_numpy(pick.astype(np.int32)).reshape(buf.block_idx.shape))
+    rb.rsa_pool_values(buf.shape, V, buf.Vp, buf.Vt)
+    outs = []
+    for ws in (buf.attn_ws, None):
+        O, lse = torch.full_like(Q, float("nan")), torch.full(Q.shape[:3], float("nan"), dtype=torch.float32, device="cuda")
+        rb.rsa_sparse_attn_rectified(buf.shape, Q, K, buf.Vt, buf.block_idx, buf.count, None, None, None, None, None, 0, O, lse, ws)
+        torch.cuda.synchronize()
+        outs.append((O.double().cpu(), lse.double().cpu()))
+    _same_up_to_the_order_of_sums(*outs)
+
+
 @pytest.mark.parametrize("unequal", [False, True])
 @pytest.mark.parametrize("name", ["entries_beyond_the_table", "more_dense_rows_than_the_tail"])
 def test_dealing_of_short_lists_beside_long_rows(gpu, name, unequal):
