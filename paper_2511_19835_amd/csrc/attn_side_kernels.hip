@@ -173,19 +173,18 @@ __device__ __forceinline__ int wave_min_i32(int v) {
   v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
   return __builtin_amdgcn_readlane(v, 63);
 }
-__device__ __forceinline__ int wave_sum_i32(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// Sums the same way (data-parallel-primitive moves: six dependent instructions; a shuffle goes through the LDS crossbar).
+__device__ __forceinline__ int wave_inclusive_scan_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
   return v;
 }
-__device__ __forceinline__ int wave_inclusive_scan_i32(int v, int lane) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int up = __shfl_up(v, o);
-    if (lane >= o) v += up;
-  }
-  return v;
-}
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63); }
+__device__ __forceinline__ int wave_sum_i32(int v) { return last_lane(wave_inclusive_scan_i32(v)); }
 __device__ __forceinline__ int lanes_below(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
@@ -209,8 +208,10 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
 // calls every row is its own round (2 heads of 17 blocks: 23.6 -> 11 us and 4 us of merging). Cuts need piece buffers;
 // without them (pieces_per_queue 0: enough rounds that it does not matter, or no room) the long rows go first and the
 // last rows one at a time to the lightest slot.
-// The dealing itself takes 8-12 us up to 4000 items and 18-32 us at 22 000 to 28 000, beside the compensation that
-// shares the launch (the last 128 rows one at a time took 38 us at 3816 items).
+// The dealing itself takes 6-11 us up to 4000 items and 18-32 us at 22 000 to 28 000, beside the compensation that
+// shares the launch (the last 128 rows one at a time took 38 us at 3816 items). It is one chain of latencies: sums over the
+// slots that went through the LDS crossbar, and a search of the line for both ends of a slot's part and twice more, were a
+// quarter of it (2 heads of 17 blocks: attention 20.7 -> 18.6 us).
 // One queue for all slots of an XCD: with block 64 an XCD has 128 slots, and two queues of 64 on distant ranges of
 // the row order shared less of its L2 (24 heads of 1182 blocks: attention 9.80 -> 9.03 ms).
 constexpr int kDealSegment = 2048;   // rows of a queue staged in LDS at a time
@@ -245,7 +246,9 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
   const int at_once = da.heads_at_once, turns = (bh_total + at_once - 1) / at_once;
   const int32_t* order = dense_all ? nullptr : a.row_order;
   auto rows_of_turn = [&](int i) __attribute__((always_inline)) { return min(at_once, bh_total - i * at_once) * NR; };
-  auto total_load = [&](const int32_t* o, int h) __attribute__((always_inline)) { return order_load(o[(size_t)h * NR + NR - 1]) + 1; };
+  auto total_load = [&](int h) __attribute__((always_inline)) {
+    return h < SEG ? len[h] : order_load(order[(size_t)h * NR + NR - 1]) + 1;
+  };
   auto sum_over_turns = [&](const int32_t* at, int queue) __attribute__((always_inline)) {
     int n = 0;
     for (int i = 0; i < turns; ++i) {
@@ -268,17 +271,22 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
   };
   // Parts of equal numbers of rows begin and end with a head, or half or quarter of one: rows of unequal length share tiles
   // only with rows of their head. Kept as long as no queue gets over da.most_share 64ths of the average load.
+  int32_t* s_total = len;                          // (nothing is staged yet) loads of the heads
+  if (order)
+    for (int h = tid; h < min(bh_total, SEG); h += 256) s_total[h] = order_load(order[(size_t)h * NR + NR - 1]) + 1;
   for (int k = tid; k < turns * (kQueues + 1); k += 256) {
     const int i = k / (kQueues + 1), p = k % (kQueues + 1), rows = rows_of_turn(i), at = (int)((long long)p * rows / kQueues);
     s_part[k] = at;
-    if (order) {
-      const int32_t* o = order + (size_t)i * at_once * NR;       // the turn's rows
-      int before = at < rows ? order_load(o[at]) : 0;
-      for (int h = 0; h < at / NR; ++h) before += total_load(o, h);
-      rec[k] = before;
-    }
+    if (order) rec[k] = at < rows ? order_load(order[(size_t)i * at_once * NR + at]) : 0;
   }
   __syncthreads();
+  if (order) {
+    for (int k = tid; k < turns * (kQueues + 1); k += 256) {
+      const int i = k / (kQueues + 1), heads = s_part[k] / NR;
+      for (int h = 0; h < heads; ++h) rec[k] += total_load(i * at_once + h);
+    }
+    __syncthreads();
+  }
   bool by_load = false;
   if (order) {
     int sum;
@@ -291,9 +299,9 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
       if (p == 0 || p == kQueues) continue;
       const int32_t* o = order + (size_t)i * at_once * NR;
       int all = 0, h = 0;
-      for (int j = 0; j < heads; ++j) all += total_load(o, j);
+      for (int j = 0; j < heads; ++j) all += total_load(i * at_once + j);
       int target = (int)((long long)p * all / kQueues);
-      for (int t = 0; h + 1 < heads && target >= (t = total_load(o, h)); ++h) target -= t;
+      for (int t = 0; h + 1 < heads && target >= (t = total_load(i * at_once + h)); ++h) target -= t;
       int lo = 0, hi = NR - 1;                                   // the first row of head h that has the target before it
       while (lo < hi) {
         const int mid = (lo + hi) / 2;
@@ -476,10 +484,10 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
   const int len0 = TN > 0 ? t_pos[TN - 1] : 0;     // (the length of a row, when all are equal)
   for (int c = 0; c < TN; c += 64) {
     const int v = c + lane < TN ? t_pos[c + lane] : 0;
-    const int incl = wave_inclusive_scan_i32(v, lane);
+    const int incl = wave_inclusive_scan_i32(v);
     asm volatile("" ::: "memory");
     if (c + lane < TN) t_pos[c + lane] = line + incl - v;
-    line += __shfl(incl, 63);
+    line += last_lane(incl);
   }
   if (lane == 0) t_pos[TN] = line;
   asm volatile("" ::: "memory");
@@ -523,10 +531,10 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
 #pragma unroll
     for (int j = 0; j < SPL; ++j) {
       const int room = max(0, level - base[j]);                  // (slots that do not exist: none)
-      const int incl = wave_inclusive_scan_i32(room, lane);
+      const int incl = wave_inclusive_scan_i32(room);
       from[j] = at + incl - room;
       to[j] = at + incl;
-      at += __shfl(incl, 63);
+      at += last_lane(incl);
     }
   }
   auto entry_at = [&](int x) __attribute__((always_inline)) {     // the entry that x lies in (x < line)
@@ -538,22 +546,41 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
     }
     return l;
   };
+  struct Cut { int pos, entry; };                                 // where, and the entry that begins or goes on there
   auto cut_at = [&](int x) __attribute__((always_inline)) {
-    if (x >= line) return line;
+    if (x >= line) return Cut{line, TN};
     const int i = entry_at(x);
     const int p = t_pos[i], e = t_pos[i + 1], h = min(da.min_piece, (e - p + 1) / 2);
-    return x - p < h ? p : (e - x < h ? e : x);
+    return x - p < h ? Cut{p, i} : (e - x < h ? Cut{e, i + 1} : Cut{x, i});
   };
+  // A slot takes the line from its cut to that of the next slot.
+  int start[SPL];
+  {
+    Cut c[SPL];
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) c[j] = cut_at(from[j]);
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      int next = __shfl_down(c[j].pos, 1);
+      if (j + 1 < SPL) {
+        const int first = __builtin_amdgcn_readfirstlane(c[(j + 1) % SPL].pos);
+        if (lane == 63) next = first;
+      } else if (lane == 63) {
+        next = cut_at(to[j]).pos;
+      }
+      from[j] = c[j].pos;
+      to[j] = next;
+      start[j] = c[j].entry;
+    }
+  }
   int n_new[SPL], n_part[SPL], id0[SPL], pieces = 0;
   bool fits = true;
 #pragma unroll
   for (int j = 0; j < SPL; ++j) {
     n_new[j] = n_part[j] = 0;
     if (ok[j]) {
-      from[j] = cut_at(from[j]);
-      to[j] = cut_at(to[j]);
       int pos = from[j];
-      for (int i = pos < to[j] ? entry_at(pos) : TN; i < TN && pos < to[j]; ++i) {
+      for (int i = start[j]; i < TN && pos < to[j]; ++i) {
         const int e = min(t_pos[i + 1], to[j]);
         if (e <= pos) continue;
         n_new[j] += 1;
@@ -563,9 +590,9 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
       }
       fits = fits && cnt[j] + n_new[j] <= da.cap;
     }
-    const int incl = wave_inclusive_scan_i32(n_part[j], lane);
+    const int incl = wave_inclusive_scan_i32(n_part[j]);
     id0[j] = pieces + incl - n_part[j];
-    pieces += __shfl(incl, 63);
+    pieces += last_lane(incl);
   }
   fits = __ballot(!fits) == 0 && pieces <= da.pieces_per_queue;
   int total[SPL];
@@ -577,7 +604,7 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
     for (int j = 0; j < SPL; ++j) {
       if (!ok[j]) continue;
       int pos = from[j], id = id0[j];
-      for (int i = pos < to[j] ? entry_at(pos) : TN; i < TN && pos < to[j]; ++i) {
+      for (int i = start[j]; i < TN && pos < to[j]; ++i) {
         const int p = t_pos[i], pe = t_pos[i + 1], e = min(pe, to[j]);
         if (e <= pos) continue;
         const int cross = t_fc[i] >> 16;
