@@ -28,8 +28,8 @@
 // 4*B*B*d flop per (query block, key block) pair against 2*B*d*2 bytes of K/V traffic.
 // The small kernels around this one are in attn_side_kernels.hip. row_rank_kernel orders the video query blocks of a head by
 // their first three kept key blocks; schedule_kernel deals that order to the groups so that each XCD (workgroup id modulo 8)
-// owns a contiguous range of every head and groups resident together walk similar lists and share K/V tiles in the
-// XCD's L2. With few rounds of items the rows of the last round and the text rows are cut into pieces, where that is faster,
+// owns contiguous ranges of it, of a whole head at a time where the caches hold the heads at work, and groups resident
+// together walk similar lists and share K/V tiles in the XCD's L2. With few rounds of items the rows of the last round and the text rows are cut into pieces, where that is faster,
 // and all groups end at about the same key block (merge_kernel adds the pieces); with many, the text rows go first and the
 // groups end within one item of each other.
 #include "attn_sched.hpp"
@@ -410,21 +410,22 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   int done_piece = -1, next_piece = sc.table ? sc.piece0[slot] : 0;      // piece buffer it goes to (-1: to O), and the next one free
   int64_t done_qo_off = 0;
 
-  // Q as the B operand of S^T = K Q^T, resident in registers; the next item's rows replace it right
-  // behind the last K Q^T of the current one.
-  bf16x8 qreg[C::KS];
+  // Q as the B operand of S^T = K Q^T, resident in registers; the next item's rows come into registers of their own, a
+  // step ahead: they come from HBM, and asked for behind the last K Q^T, with nothing but a softmax before their use, they kept
+  // both groups waiting for some 5000 cycles of every item (24 heads of 931 blocks, lists of 94: 14642 us and 14532; 591 blocks,
+  // lists of 60: 9828 and 9755; shorter lists 0.2 %; where the power limit or the fabric bounds the kernel, equal). Rows past the end of a ragged block repeat its last row: the number
+  // of loads in flight is the same for every wave, and the waits below count on it.
+  bf16x8 qreg[C::KS], qnext[C::KS];
   const float cs = dm.scale * kLog2e;   // scores -> binades
-  auto load_q = [&](const Item& it) __attribute__((always_inline)) {
+  auto load_q = [&](bf16x8 (&dst)[C::KS], int64_t qo_off, int q_count) __attribute__((always_inline)) {
     const int ln = lane_now();
-    const int q = wave * 32 + ln % 32;
-    const uint16_t* qrow = a.Q + it.qo_off + (int64_t)q * dm.st + 8 * (ln / 32);
+    const int q = min(wave * 32 + ln % 32, q_count - 1);
+    const uint16_t* qrow = a.Q + qo_off + (int64_t)q * dm.st + 8 * (ln / 32);
 #pragma unroll
-    for (int s = 0; s < C::KS; ++s) {
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (q < it.q_count) v = *reinterpret_cast<const uint4*>(qrow + 16 * s);
-      qreg[s] = __builtin_bit_cast(bf16x8, v);
-    }
+    for (int s = 0; s < C::KS; ++s) dst[s] = *reinterpret_cast<const bf16x8*>(qrow + 16 * s);
   };
+#pragma unroll
+  for (int s = 0; s < C::KS; ++s) qnext[s] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
   floatx16 oacc[C::DT];
 #pragma unroll
   for (int dt = 0; dt < C::DT; ++dt)
@@ -434,32 +435,52 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   float done_m = 0.f, done_l = 0.f;      // (VH) those of the item whose last P V product is under way
 
   // Epilogue of one item: O = R_n * acc / l + C_n (video rows; text rows: acc / l), bf16; then the
-  // running state starts over for the next item. R_n and C_n are requested a step ahead (in the
-  // softmax phase of the item's last step): lane j holds elements CV*j .. CV*j+CV-1 of C_n, and every
+  // running state starts over for the next item. R_n and C_n are requested with the next
+  // query rows: lane j holds elements CV*j .. CV*j+CV-1 of C_n, and every
   // lane collects the 64 it needs through the LDS crossbar -- no memory latency is left in here.
   constexpr int CV = D / 64;
-  float done_comp[CV];
+  float done_comp[CV], next_comp[CV];            // of the item whose output is to be written; of the current one
 #pragma unroll
-  for (int j = 0; j < CV; ++j) done_comp[j] = 0.f;
-  float done_rfac = 1.0f;
-  auto request_epilogue = [&](const Item& it) __attribute__((always_inline)) {
-    const size_t vrow = (size_t)it.bh * dm.n + it.qb;          // row of the per-video-block tensors
-    done_rfac = 1.0f;
-    if (it.has_list && (a.flags & RSA_RECTIFY_CRITICAL)) {
+  for (int j = 0; j < CV; ++j) done_comp[j] = next_comp[j] = 0.f;
+  float done_rfac = 1.0f, next_rfac = 1.0f;
+  // The query rows of the next item, and R_n and C_n of this one: asked for in the softmax phase of the last step but one (of an
+  // item of two steps: in its last). The same number of vector loads in any case (NREQ).
+  constexpr int NREQ = C::KS + 1;
+  auto request_switch = [&]() __attribute__((always_inline)) {
+    load_q(qnext, nxt_valid ? nxt.qo_off : cur.qo_off, nxt_valid ? nxt.q_count : cur.q_count);
+    const size_t vrow = (size_t)cur.bh * dm.n + cur.qb;        // row of the per-video-block tensors
+    next_rfac = 1.0f;
+    if (cur.has_list && (a.flags & RSA_RECTIFY_CRITICAL)) {
       typedef const float __attribute__((address_space(4))) * const_f32_t;    // scalar load
-      done_rfac = ((const_f32_t)(uintptr_t)a.R)[vrow];
+      next_rfac = ((const_f32_t)(uintptr_t)a.R)[vrow];
     }
-    if (it.has_list && (a.flags & RSA_COMPENSATE)) {
-      const float* crow = a.comp + vrow * D + lane_now() * CV;
-#pragma unroll
-      for (int j = 0; j < CV; ++j) done_comp[j] = crow[j];
+    // (an item without C_n: any readable words)
+    const bool has_comp = cur.has_list && (a.flags & RSA_COMPENSATE);
+    typedef float comp_t __attribute__((ext_vector_type(2), aligned(4)));
+    const float* crow = has_comp ? a.comp + vrow * D : reinterpret_cast<const float*>(a.Q);
+    const float* cp = crow + (has_comp ? lane_now() * CV : 0);
+    if constexpr (CV == 2) {
+      const comp_t c = *reinterpret_cast<const comp_t*>(cp);
+      next_comp[0] = c.x;
+      next_comp[CV - 1] = c.y;
+    } else {
+      next_comp[0] = *cp;
     }
   };
-  auto settle_item_loads = [&]() __attribute__((always_inline)) {       // a use of everything load_q and request_epilogue asked for
+  // The current item ends: what was asked for takes its place. (The compiler waits for the loads it knows of where they are
+  // used, and such a wait covers the tile requests as well: here the youngest is a whole phase old.)
+  auto settle_switch = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+    for (int ks = 0; ks < C::KS; ++ks) {
+      qreg[ks] = qnext[ks];
+      asm volatile("" : "+v"(qreg[ks]));
+    }
 #pragma unroll
-    for (int j = 0; j < CV; ++j) asm volatile("" : "+v"(done_comp[j]));
+    for (int j = 0; j < CV; ++j) {
+      done_comp[j] = next_comp[j];
+      asm volatile("" : "+v"(done_comp[j]));
+    }
+    done_rfac = next_rfac;
   };
   // A piece of a row: the accumulators as they are (1 KB per store instruction), row sum and reference.
   auto write_piece = [&]() __attribute__((always_inline)) {
@@ -572,11 +593,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   //         S^T = K Q^T of step s: matrix instructions only, the A
   //         operand of each read from LDS a few slots ahead (V^T tile of step s-1 from its ring
   //         stage (s-1) % 3, K tile of step s from stage s % 2); the loads of tile s+1 (K into
-  //         stage (s+1) % 2, V^T into stage (s+1) % 3) go out one per MFMA slot. Behind the last
-  //         step of an item the query rows of the next item are requested.
+  //         stage (s+1) % 2, V^T into stage (s+1) % 3) go out one per MFMA slot.
   //   V(s): in the first step of an item (HALVES: the second), the output of the item before it; mask, online softmax
-  //         -> P as bf16 B operands (VALU only); fetch the list entry of step s+2; wait for tile
-  //         s+1; read the first V^T operands of M(s+1) ahead of the barrier
+  //         -> P as bf16 B operands (VALU only); fetch the list entry of step s+2; in the last step but one of an item
+  //         request the query rows of the next item; wait for tile s+1; read the first V^T operands of M(s+1) ahead of the barrier
   // The barrier after V(s) publishes tile s+1 to the group. A K stage is rewritten two steps
   // after it was read, a V^T stage (read in M(s+1), one phase after its K tile) three steps after
   // it was filled: by then every wave of the group has passed the barrier that follows its last
@@ -638,8 +658,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 
   // Variants of the two phases, all compile-time:
   //   MFMA phase  QK: 0 = the last P V product of the group alone.  LAST: the step is the last of its item
-  //               -- the tile of step s+1 may open the next item (that item's K and V^T), and the next
-  //               item's query rows are requested behind the last K Q^T.
+  //               -- the tile of step s+1 may open the next item (that item's K and V^T).
   //   softmax phase  FIRST: first step of an item.  OUT: the output of the item before is written first, if that is still to be
   //               done (the first step; HALVES: the second, and the last, which is the second of an item of one key block);
   //               FETCH: 0 none (odd steps), 1 the next entry of the item's own list, 2 wherever step
@@ -723,12 +742,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     if constexpr (SPLIT_LOADS && !(C::VH && do_qk)) {
       // the V^T rows of this step (requested a phase ago, ahead of this phase's K rows) have landed
       // (VH: not needed for another step, and the wait of the softmax phase covers them)
-      wait_loads_leaving<do_qk ? MLOADS : 0>();
-    }
-    // behind the last K Q^T of an item: the query rows of the next one (they arrive before the end of
-    // the softmax phase, which waits for every load)
-    if constexpr (do_qk && last_of_item) {
-      if (nxt_valid) load_q(nxt);
+      if (last_of_item && cur.ns > C::SPB) wait_loads_leaving<do_qk ? MLOADS + NREQ : 0>();
+      else wait_loads_leaving<do_qk ? MLOADS : 0>();
     }
   };
 
@@ -746,9 +761,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     constexpr int FETCH = decltype(fetchc)::value;
     __builtin_amdgcn_s_setprio(0);
     constexpr int VLOADS = SPLIT_LOADS ? C::VPW : 0;  // requests of this phase: the V^T rows of step s+1
-    // The last step of an item: what the switch to the next item and the epilogue need from memory is
-    // requested here, a whole softmax ahead of its use -- R_n and C_n of this item, the entry of the item
-    // after the one after the next.
+    // The last step of an item asks for the entry of the item after the one after the next.
     Entry entry_new = {};
     bool more = false;
     if constexpr (C::VH && first_of_item) {
@@ -765,7 +778,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       }
     }
     if constexpr (last_of_item) {
-      request_epilogue(cur);
+      if (cur.ns == C::SPB) request_switch();
       more = k_next < n_my_items;
       if (k_next + 1 < n_my_items) entry_new = my_entry(k_next + 1);
     }
@@ -794,6 +807,11 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     if constexpr (SPLIT_LOADS && (C::VH || !output)) {
       static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) { issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{}); });
     }
+    // Step ns-2 of an item of two key blocks or more; an item of one block asks in its last phase instead (a request under a
+    // condition in the first phase would leave the compiler with loads that may be pending on its way into the loop of steps,
+    // and with a wait for them in every other step).
+    constexpr bool requests = FETCH == 2 && !first_of_item;
+    if constexpr (requests) request_switch();
     // the first step of an item: the P V products of the item before it are complete
     // (tile s+1 is waited for first: the loads of the output would otherwise be waited for together
     // with it at the end of the phase, and so would the stores, which now complete under the next
@@ -933,20 +951,15 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         k_next += 1;
       }
     }
-    // tile s+1 has landed (this wave's share; the barrier that follows covers the group), and so
-    // have the query rows of the next item
-    // (loads return in order: only this phase's own requests may still be out)
+    // tile s+1 has landed (this wave's share; the barrier that follows covers the group; loads return in order: only this
+    // phase's own requests may still be out)
+    constexpr int LEAVING = VLOADS + (requests ? NREQ : 0);
     if constexpr (output) {
-      if (!had_output) wait_loads_leaving<VLOADS>();
+      if (!had_output) wait_loads_leaving<LEAVING>();
     } else {
-      wait_loads_leaving<VLOADS>();
+      wait_loads_leaving<LEAVING>();
     }
-    if constexpr (last_of_item) {
-      // The compiler waits for the loads it knows of (the query rows, C_n) where they are first used, and
-      // such a wait covers the tile requests as well: it belongs here, where the youngest request is a
-      // whole phase old, not behind the first requests of the next MFMA phase.
-      settle_item_loads();
-    }
+    if constexpr (last_of_item) settle_switch();
   };
 
   const bool active = n_my_items > 0;
@@ -956,16 +969,17 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     if (nxt_valid) nxt = load_item(1);
     k_next = 2;
     if (n_my_items > 2) ahead = my_entry(2);
-    load_q(cur);
-    // Q must have arrived before the first direct-to-LDS load is requested: the compiler
-    // does not see those loads, and would otherwise place its own wait for Q -- a wait for
-    // *every* outstanding load -- at the first use inside the loop.
-    __builtin_amdgcn_s_waitcnt(0x0F70);
+    load_q(qreg, cur.qo_off, cur.q_count);
     Tile t0;
     const int m0 = list_entry(cur, 0);
     static_for<0, kOpenPieces>([&](auto pc) __attribute__((always_inline)) { open_piece(pc, m0, cur.Kbytes, cur.Vtbytes); });
     static_for<0, kStepPieces>([&](auto pc) __attribute__((always_inline)) { step_piece(pc, t0, IntC<0>{}, 0, 0); });
     static_for<0, LPS>([&](auto ic) __attribute__((always_inline)) { issue_load(t0, ic); });
+    // The compiler does not see the direct-to-LDS loads: it has to place its wait for Q here, not at the first use inside
+    // the loop, where it would be a wait for every load outstanding.
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+    for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
     kvc_cur = blk_count;
     fj = 1;
     // The first MFMA phase (VH: the first two) multiplies the (zero) probabilities of a step that does not exist with
