@@ -451,6 +451,18 @@ def test_last_blocks_of_any_length(gpu, d, block, video, text):
             assert np.linalg.norm(err) / np.linalg.norm(want) <= parity.OUT_REL_L2
 
 
+@pytest.mark.parametrize("kept,workspace", [(1, True), (1, False), (2, True)])
+@pytest.mark.parametrize("d,block", [(128, 64), (128, 128), (64, 64), (64, 128)])
+def test_short_rows_in_sequence(gpu, d, block, kept, workspace):
+    """Groups that work through two or three rows of one or two key blocks one after the other, the last row of every head
+    ragged: the query rows, R_n and C_n of a row are requested while the row before it is under way."""
+    heads = 40 if block == 128 else 80
+    cfg = LayerConfig("short_rows", 1, heads, d, (1, 1, 32 * block + 29), 0, block, 0.0)
+    out, _, _ = _run_and_compare(gpu, cfg, seed=49, sparsity=(33 - kept) / 33, flags=3 if workspace else 1,
+                                 attn_workspace=workspace)
+    assert (out["count"] == kept).all()
+
+
 @pytest.mark.parametrize("heads,d,block,blocks,sparsity,unequal,cut", [
     (1, 128, 64, 208, 0.5, False, True),        # 26 rows of 104 key blocks for 128 slots
     (3, 128, 64, 210, 0.5, False, False),       # 78 rows: whole
