@@ -311,9 +311,11 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
       s_part[k] = h * NR + lo;
     }
     __syncthreads();
-    // A queue of very short rows might get more of them than its table holds: equal numbers of rows after all.
+    // A queue of very short rows might get more of them than its table holds: equal numbers of rows after all. Everything
+    // that goes into the table counts, text rows that may be cut and parts of cross rows too: whatever is given out,
+    // some slot then has cap - 2 entries at most (the whole entries of a line that is not cut ask for such a slot).
     int sum;
-    if (lead + largest_and_sum(s_part, sum) > S * (da.cap - 2)) {
+    if (my_dense + da.n_cross + largest_and_sum(s_part, sum) > S * (da.cap - 2)) {
       for (int k = tid; k < turns * (kQueues + 1); k += 256)
         s_part[k] = (int)((long long)(k % (kQueues + 1)) * rows_of_turn(k / (kQueues + 1)) / kQueues);
       __syncthreads();
@@ -622,7 +624,8 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
       }
     }
   } else {
-    // (the table has no room for the cuts: very unequal rows) whole entries, one at a time to the lightest slot
+    // (the table has no room for the cuts: very unequal rows) whole entries, one at a time to the lightest slot that has room:
+    // there is one, shares by load leave it (see above), and by number a queue has about the average that cap is twice of
     pieces = da.n_cross;
 #pragma unroll
     for (int j = 0; j < SPL; ++j) id0[j] = j == 0 && lane < da.n_cross ? lane : 0;

@@ -498,26 +498,67 @@ def test_rows_without_text_are_cut_where_it_pays(gpu, heads, d, block, blocks, s
     assert torch.equal(outs[0][0], outs[1][0]) != cut
 
 
-@pytest.mark.parametrize("heads,d,block,blocks,lengths", [
-    (12, 64, 128, 90, "one long head"),           # 40 of 90 key blocks in one head, 2 in the others: shared out by load
-    (12, 128, 64, 180, "one long head"),
-    (11, 64, 64, 200, "heads of 1 to 60"),        # ... and a last turn of three heads
-    (13, 128, 128, 70, "rows of 1 to 30"),        # by number: heads alike
-    (9, 64, 64, 230, "short, then long"),         # a queue's share by load has more rows than its table
-    (70, 64, 128, 12, "heads of 1 to 60"),        # more heads than turns
+def _shares_of_the_queues(n, pick, d, block, text_blocks):
+    """What deal_queue decides for lists of n[heads][N] of the blocks pick[heads][N][M]: whether shares by number are uneven
+    enough to be replaced by shares by load, and the largest number of rows that a queue would get by load."""
+    heads, N = n.shape
+    first = np.where(np.arange(3) < n[..., None], pick[..., :3], 4095)
+    order = np.argsort((first[..., 0] * 4096 + first[..., 1]) * 4096 + first[..., 2], axis=1, kind="stable")
+    cost = np.take_along_axis(n, order, axis=1) + (3 if block == 128 else 6)
+    before = (np.cumsum(cost, axis=1) - cost) // 32                   # of every row of the launch order
+    total = before[:, -1] + 1
+    at_once = 8
+    while at_once > 1 and at_once * 4 * (N + text_blocks) * block * d > (250e6 if (d, block) == (128, 64) else 200e6):
+        at_once //= 2
+    at_once = max(at_once, -(-heads // 64))
+    load, rows = np.zeros(8, dtype=int), np.zeros(8, dtype=int)
+    for turn, h0 in enumerate(range(0, heads, at_once)):
+        h = slice(h0, min(h0 + at_once, heads))
+        ends = np.concatenate([[0], np.cumsum(total[h])])
+        start = (ends[:-1, None] + before[h]).ravel()                  # load ahead of every row of the turn
+        number = np.arange(9) * start.size // 8
+        at = np.append(start, ends[-1])[number]
+        by_load = np.searchsorted(start, np.arange(8) * ends[-1] // 8)
+        queues = (np.arange(8) - turn) % 8
+        load[queues] += np.diff(at)
+        rows[queues] += np.diff(np.append(by_load, start.size))
+    return load.max() * 8 * 64 > load.sum() * (65 if d == 64 else 68), rows.max()
+
+
+def _table_of_the_queues(heads, N, text_blocks, block):
+    """Entries that the tables of a queue's slots hold when two places in each are left free."""
+    slots = 64 if block == 128 else 128
+    longest = heads * -(-N // 8) + -(-heads * text_blocks // 8)
+    return slots * (2 * -(-longest // slots) + 6)
+
+
+@pytest.mark.parametrize("heads,d,block,blocks,text,lengths,shares", [
+    (12, 64, 128, 90, 0, "one long head", "load"),       # 40 of 90 key blocks in one head, 2 in the others
+    (12, 128, 64, 180, 0, "one long head", "load"),
+    (11, 64, 64, 200, 0, "heads of 1 to 60", "load"),    # ... and a last turn of three heads
+    (13, 128, 128, 70, 0, "rows of 1 to 30", "number"),  # heads alike
+    (9, 64, 64, 230, 0, "short, then long", "number"),   # the long head is a turn by itself
+    (70, 64, 128, 12, 0, "heads of 1 to 60", "load"),    # nine turns, the last of six heads
+    (8, 128, 128, 260, 120, "half 1, half 57", "table"), # by load, a queue would get more than its tables hold
 ])
-def test_shares_of_the_queues(gpu, heads, d, block, blocks, lengths):
+def test_shares_of_the_queues(gpu, heads, d, block, blocks, text, lengths, shares):
     """How the rows are shared out to the eight queues, by number or by load: every row is there once, whatever the lists."""
     import torch
     from paper_2511_19835_amd import binding as rb
     rng = np.random.default_rng(49)
-    Q, K, V = (torch.from_numpy(rng.standard_normal((1, heads, blocks * block, d), dtype=np.float32)).bfloat16().cuda() for _ in range(3))
-    buf = rb.allocate(Q, blocks * block, 0, block)
-    n = {"one long head": np.where(np.arange(heads)[:, None] == 5, 40, 2) * np.ones((1, blocks), dtype=int),
-         "heads of 1 to 60": np.minimum(1 + 59 * np.arange(heads)[:, None] // (heads - 1), blocks) * np.ones((1, blocks), dtype=int),
-         "rows of 1 to 30": rng.integers(1, 31, size=(heads, blocks)),
-         "short, then long": np.where(np.arange(heads)[:, None] < heads - 1, 1, blocks) * np.ones((1, blocks), dtype=int)}[lengths]
-    pick = np.sort(np.where(np.arange(blocks) < n[..., None], rng.permuted(np.tile(np.arange(blocks), (heads, blocks, 1)), axis=-1), blocks), axis=-1)
+    M = blocks + text
+    Q, K, V = (torch.from_numpy(rng.standard_normal((1, heads, M * block, d), dtype=np.float32)).bfloat16().cuda() for _ in range(3))
+    buf = rb.allocate(Q, blocks * block, text * block, block)
+    head = np.arange(heads)[:, None]
+    n = {"one long head": lambda: np.where(head == 5, 40, 2),
+         "heads of 1 to 60": lambda: np.minimum(1 + 59 * head // (heads - 1), blocks),
+         "rows of 1 to 30": lambda: rng.integers(1, 31, size=(heads, blocks)),
+         "short, then long": lambda: np.where(head < heads - 1, 1, blocks),
+         "half 1, half 57": lambda: np.where(head < heads // 2, 1, 57)}[lengths]() * np.ones((1, blocks), dtype=int)
+    pick = np.sort(np.where(np.arange(M) < n[..., None], rng.permuted(np.tile(np.arange(M), (heads, blocks, 1)), axis=-1), M), axis=-1)
+    uneven, most_rows = _shares_of_the_queues(n, pick, d, block, text)
+    entries = most_rows + -(-heads * text // 8)
+    assert shares == ("number" if not uneven else "load" if entries <= _table_of_the_queues(heads, blocks, text, block) else "table")
     buf.count.copy_(torch.from_numpy(n.astype(np.int32)).reshape(buf.count.shape))
     buf.block_idx.copy_(torch.from_numpy(pick.astype(np.int32)).reshape(buf.block_idx.shape))
     rb.rsa_pool_values(buf.shape, V, buf.Vp, buf.Vt)
@@ -526,7 +567,7 @@ def test_shares_of_the_queues(gpu, heads, d, block, blocks, lengths):
         O, lse = torch.full_like(Q, float("nan")), torch.full(Q.shape[:3], float("nan"), dtype=torch.float32, device="cuda")
         rb.rsa_sparse_attn_rectified(buf.shape, Q, K, buf.Vt, buf.block_idx, buf.count, None, None, None, None, None, 0, O, lse, ws)
         torch.cuda.synchronize()
-        outs.append((O.double().cpu(), lse.double().cpu()))
+        outs.append((O.double(), lse.double().cpu()))
     _same_up_to_the_order_of_sums(*outs)
 
 
