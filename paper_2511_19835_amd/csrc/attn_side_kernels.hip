@@ -313,9 +313,11 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
     __syncthreads();
     // A queue of very short rows might get more of them than its table holds: equal numbers of rows after all. Everything
     // that goes into the table counts, text rows that may be cut and parts of cross rows too: whatever is given out,
-    // some slot then has cap - 2 entries at most (the whole entries of a line that is not cut ask for such a slot).
+    // some slot then has cap - 2 entries at most (the whole entries of a line that is not cut ask for such a slot). All queues
+    // have to decide alike, or their rows overlap and leave gaps: the most text rows of any queue, not this one's.
+    const int most_dense = (n_whole + kQueues - 1) / kQueues;
     int sum;
-    if (my_dense + da.n_cross + largest_and_sum(s_part, sum) > S * (da.cap - 2)) {
+    if (most_dense + da.n_cross + largest_and_sum(s_part, sum) > S * (da.cap - 2)) {
       for (int k = tid; k < turns * (kQueues + 1); k += 256)
         s_part[k] = (int)((long long)(k % (kQueues + 1)) * rows_of_turn(k / (kQueues + 1)) / kQueues);
       __syncthreads();

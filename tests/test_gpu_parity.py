@@ -540,9 +540,11 @@ def _table_of_the_queues(heads, N, text_blocks, block):
     (9, 64, 64, 230, 0, "short, then long", "number"),   # the long head is a turn by itself
     (70, 64, 128, 12, 0, "heads of 1 to 60", "load"),    # nine turns, the last of six heads
     (8, 128, 128, 260, 120, "half 1, half 57", "table"), # by load, a queue would get more than its tables hold
+    (5, 128, 128, 159, 6, "2, last head 142", "table"),  # ... by one entry, and only a queue with 4 text rows: others have 3
 ])
 def test_shares_of_the_queues(gpu, heads, d, block, blocks, text, lengths, shares):
-    """How the rows are shared out to the eight queues, by number or by load: every row is there once, whatever the lists."""
+    """How the rows are shared out to the eight queues, by number or by load: every row is there once, whatever the lists,
+    with a workspace (rows may be cut) and with the scratch of the static entry point (no room for pieces here)."""
     import torch
     from paper_2511_19835_amd import binding as rb
     rng = np.random.default_rng(49)
@@ -554,7 +556,8 @@ def test_shares_of_the_queues(gpu, heads, d, block, blocks, text, lengths, share
          "heads of 1 to 60": lambda: np.minimum(1 + 59 * head // (heads - 1), blocks),
          "rows of 1 to 30": lambda: rng.integers(1, 31, size=(heads, blocks)),
          "short, then long": lambda: np.where(head < heads - 1, 1, blocks),
-         "half 1, half 57": lambda: np.where(head < heads // 2, 1, 57)}[lengths]() * np.ones((1, blocks), dtype=int)
+         "half 1, half 57": lambda: np.where(head < heads // 2, 1, 57),
+         "2, last head 142": lambda: np.where(head < heads - 1, 2, 142)}[lengths]() * np.ones((1, blocks), dtype=int)
     pick = np.sort(np.where(np.arange(M) < n[..., None], rng.permuted(np.tile(np.arange(M), (heads, blocks, 1)), axis=-1), M), axis=-1)
     uneven, most_rows = _shares_of_the_queues(n, pick, d, block, text)
     entries = most_rows + -(-heads * text // 8)
@@ -562,13 +565,17 @@ def test_shares_of_the_queues(gpu, heads, d, block, blocks, text, lengths, share
     buf.count.copy_(torch.from_numpy(n.astype(np.int32)).reshape(buf.count.shape))
     buf.block_idx.copy_(torch.from_numpy(pick.astype(np.int32)).reshape(buf.block_idx.shape))
     rb.rsa_pool_values(buf.shape, V, buf.Vp, buf.Vt)
+    args = (buf.shape, Q, K, buf.Vt, buf.block_idx, buf.count, None, None, None, None, None, 0)
     outs = []
-    for ws in (buf.attn_ws, None):
+    for call in (lambda *out: rb.rsa_sparse_attn_rectified(*args, *out, None),
+                 lambda *out: rb.rsa_sparse_attn_rectified(*args, *out, buf.attn_ws),
+                 lambda *out: rb.rsa_sparse_attn_rectified_static(*args, *out)):
         O, lse = torch.full_like(Q, float("nan")), torch.full(Q.shape[:3], float("nan"), dtype=torch.float32, device="cuda")
-        rb.rsa_sparse_attn_rectified(buf.shape, Q, K, buf.Vt, buf.block_idx, buf.count, None, None, None, None, None, 0, O, lse, ws)
+        call(O, lse)
         torch.cuda.synchronize()
         outs.append((O.double(), lse.double().cpu()))
-    _same_up_to_the_order_of_sums(*outs)
+    _same_up_to_the_order_of_sums(outs[1], outs[0])
+    _same_up_to_the_order_of_sums(outs[2], outs[0])
 
 
 @pytest.mark.parametrize("unequal", [False, True])
