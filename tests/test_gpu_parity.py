@@ -539,6 +539,8 @@ def _table_of_the_queues(heads, N, text_blocks, block):
     (13, 128, 128, 70, 0, "rows of 1 to 30", "number"),  # heads alike
     (9, 64, 64, 230, 0, "short, then long", "number"),   # the long head is a turn by itself
     (70, 64, 128, 12, 0, "heads of 1 to 60", "load"),    # nine turns, the last of six heads
+    (520, 64, 128, 12, 0, "heads of 1 to 60", "number"), # nine heads at a time: no more than 64 turns
+    (8, 64, 64, 400, 0, "short, then long", "table"),    # the long head among the others: too many rows for a queue's tables
     (8, 128, 128, 260, 120, "half 1, half 57", "table"), # by load, a queue would get more than its tables hold
     (5, 128, 128, 159, 6, "2, last head 142", "table"),  # ... by one entry, and only a queue with 4 text rows: others have 3
 ])
