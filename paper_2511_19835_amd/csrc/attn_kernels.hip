@@ -7,7 +7,8 @@
 // schedule_kernel dealt to it, as one unbroken stream of steps: a video query block walks its
 // compact, ascending list of critical key blocks, a text query block (and every block under
 // RSA_DENSE) all M key blocks, KVS keys per step. For each step the K rows [KVS][d] and the
-// channel-major V rows [d][KVS] are brought into the group's own LDS rings by direct-to-LDS loads
+// channel-major V rows [d][KVS] (HALVES, see attn_kernel: half of the channels of all keys of the block,
+// [d/2][BLK]) are brought into the group's own LDS rings by direct-to-LDS loads
 // (global_load_lds_dwordx4: no staging registers), one step ahead -- also across the boundary
 // between two items, so the matrix pipe never drains. Each wave computes, with
 // v_mfma_f32_32x32x16_bf16,
@@ -22,16 +23,17 @@
 // reads a few slots ahead and the requests for the next tile, one per slot) and a softmax phase
 // (VALU only). The groups run one barrier apart, so that on every SIMD one wave feeds the matrix
 // pipe while the other uses the VALU. When an item ends its output is written in the softmax phase
-// of the next item's first step: O = R_n * acc / l + C_n, C_n = sum_{m: not kept and M_c}
+// of the next item's first step (HALVES: its second): O = R_n * acc / l + C_n, C_n = sum_{m: not kept and M_c}
 // A^pool[n][m] v^pool_m (computed beforehand by compensation_kernel into the workspace).
 //
 // 4*B*B*d flop per (query block, key block) pair against 2*B*d*2 bytes of K/V traffic.
-// The small kernels around this one are in attn_side_kernels.hip. row_rank_kernel orders the video query blocks of a head by
-// their first three kept key blocks; schedule_kernel deals that order to the groups so that each XCD (workgroup id modulo 8)
-// owns contiguous ranges of it, of a whole head at a time where the caches hold the heads at work, and groups resident
-// together walk similar lists and share K/V tiles in the XCD's L2. With few rounds of items the rows of the last round and the text rows are cut into pieces, where that is faster,
-// and all groups end at about the same key block (merge_kernel adds the pieces); with many, the text rows go first and the
-// groups end within one item of each other.
+// The small kernels around this one are in attn_side_kernels.hip. row_rank_kernel orders the video query
+// blocks of a head by their first three kept key blocks; schedule_kernel deals that order to the groups so
+// that each XCD (workgroup id modulo 8) owns contiguous ranges of it, of a whole head at a time where the
+// caches hold the heads at work, and groups resident together walk similar lists and share K/V tiles in the
+// XCD's L2. With few rounds of items the rows of the last round and the text rows are cut into pieces, where
+// that is faster, and all groups end at about the same key block (merge_kernel adds the pieces); with many,
+// the text rows go first and the groups end within one item of each other.
 #include "attn_sched.hpp"
 #include "lds_dma.hpp"
 #include "rsa_common.hpp"
@@ -167,7 +169,9 @@ struct SchedArgs {
 // while the second product of the block before still needs pb, and an item's output is complete, and written, in the second
 // step of the next. Attention of that layer 9320 -> 7090 us, 24 heads of 318 blocks 609 -> 577. Not for RSA_DENSE, where
 // the groups of a CU walk in step and the L1 serves the second half (318 blocks: 4640 -> 4717), nor at d = 64, where the
-// softmax hides the requests and the moves do not (24 heads of 1182: 4712 -> 4840).
+// softmax hides the requests and the moves do not (24 heads of 1182: 4712 -> 4840). The bits of the output are those of the
+// step-by-step form as long as the softmax reference stays at 0; where it moves, it is rounded up to a whole number here,
+// so that probabilities that wait can follow it in their exponents (below 2^-126 they become 0).
 template <int D, int BLK, bool HALVES>
 __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, SchedArgs sc) {
   using C = AttnCfg<D, BLK, HALVES>;
@@ -229,7 +233,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     }
   }
   if (wg_rounds == 0) return;                        // the whole workgroup: nothing was dealt to it
-  // k-th entry of this group: record and span. Scalar loads (one with a table), so that it can be asked for well ahead of make_item.
+  // k-th entry of this group: record and span. Scalar loads (one with a table), so that it can be asked for
+  // well ahead of make_item.
   struct Entry { int rec, span; };
   auto my_entry = [&](int k) __attribute__((always_inline)) {
     typedef const int32_t __attribute__((address_space(4))) * const_i32_t;
@@ -407,14 +412,16 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   Entry ahead = {};                    // ... and its entry, read an item ahead
   // what the epilogue needs of the item that has just ended
   int done_bh = 0, done_sparse = 0, done_q_t0 = 0, done_q_count = 0;
-  int done_piece = -1, next_piece = sc.table ? sc.piece0[slot] : 0;      // piece buffer it goes to (-1: to O), and the next one free
+  int done_piece = -1;                                       // piece buffer it goes to (-1: to O),
+  int next_piece = sc.table ? sc.piece0[slot] : 0;           // and the next one free
   int64_t done_qo_off = 0;
 
   // Q as the B operand of S^T = K Q^T, resident in registers; the next item's rows come into registers of their own, a
   // step ahead: they come from HBM, and asked for behind the last K Q^T, with nothing but a softmax before their use, they kept
   // both groups waiting for some 5000 cycles of every item (24 heads of 931 blocks, lists of 94: 14642 us and 14532; 591 blocks,
-  // lists of 60: 9828 and 9755; shorter lists 0.2 %; where the power limit or the fabric bounds the kernel, equal). Rows past the end of a ragged block repeat its last row: the number
-  // of loads in flight is the same for every wave, and the waits below count on it.
+  // lists of 60: 9828 and 9755; shorter lists 0.2 %; where the power limit or the fabric bounds the kernel, equal). Rows past
+  // the end of a ragged block repeat its last row: the number of loads in flight is the same for every wave, and the waits
+  // below count on it.
   bf16x8 qreg[C::KS], qnext[C::KS];
   const float cs = dm.scale * kLog2e;   // scores -> binades
   auto load_q = [&](bf16x8 (&dst)[C::KS], int64_t qo_off, int q_count) __attribute__((always_inline)) {
@@ -469,8 +476,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       next_comp[0] = *cp;
     }
   };
-  // The current item ends: what was asked for takes its place. (The compiler waits for the loads it knows of where they are
-  // used, and such a wait covers the tile requests as well: here the youngest is a whole phase old.)
+  // The current item ends: what was asked for takes its place. The compiler waits for the loads it knows of where they are
+  // copied here, down to none outstanding; as it does not see the tile requests, this drains those as well, the V^T rows of
+  // the same phase among them, which no one needs for another step: a cost of every item that has not been measured.
   auto settle_switch = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) {
@@ -574,7 +582,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         const int r = i * RPC + rsub;
         const u32x4 v = *(const lds_u32x4*)(uintptr_t)(vt_next.vdst + i * V_LDS_PASS + ln * 16);
         if (wave * 32 + r < q_count)
-          *reinterpret_cast<u32x4_u*>(obase + (ooff + (uint32_t)(i * RPC) * row_bytes + half * ROWB + 16 * ((ln % RCH) ^ row_key(r)))) = v;
+          *reinterpret_cast<u32x4_u*>(obase + (ooff + (uint32_t)(i * RPC) * row_bytes + half * ROWB +
+                                               16 * ((ln % RCH) ^ row_key(r)))) = v;
       }
       asm volatile("" ::: "memory");
     }
@@ -601,17 +610,21 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   //   M(s): O^T += V^T P^T of step s-1 (HALVES: half of the channels, of the block before the one of step s), then
   //         S^T = K Q^T of step s: matrix instructions only, the A
   //         operand of each read from LDS a few slots ahead (V^T tile of step s-1 from its ring
-  //         stage (s-1) % 3, K tile of step s from stage s % 2); the loads of tile s+1 (K into
-  //         stage (s+1) % 2, V^T into stage (s+1) % 3) go out one per MFMA slot.
-  //   V(s): in the first step of an item (HALVES: the second), the output of the item before it; mask, online softmax
-  //         -> P as bf16 B operands (VALU only); fetch the list entry of step s+2; in the last step but one of an item
-  //         request the query rows of the next item; wait for tile s+1; read the first V^T operands of M(s+1) ahead of the barrier
-  // The barrier after V(s) publishes tile s+1 to the group. A K stage is rewritten two steps
-  // after it was read, a V^T stage (read in M(s+1), one phase after its K tile) three steps after
-  // it was filled: by then every wave of the group has passed the barrier that follows its last
-  // read. Every item has an even number of steps (SPB = 2 per key block), so the position inside a
-  // key block and the K stage both follow from the parity of s, which the unrolled loop knows.
-  int m_nxt_e = 0, m_nxt_j = 0;   // key block that the next new-block step opens: entry m_nxt_e of a list, or block m_nxt_j (>= 0) of a dense row
+  //         stage (s-1) % 3, HALVES: of step s-2; K tile of step s from stage s % 2); the K rows of tile s+1
+  //         (into stage (s+1) % 2) are requested one per MFMA slot.
+  //   V(s): in the first step of an item (HALVES: the second), the output of the item before it; the V^T rows of
+  //         tile s+1 are requested (into stage (s+1) % 3); mask, online softmax -> P as bf16 B operands (VALU
+  //         only); fetch the list entry of step s+2; in the last step but one of an item request the query rows
+  //         of the next item; wait for tile s+1 (its V^T rows: in M(s+1), HALVES: in V(s+1)); read the first
+  //         V^T operands of M(s+1) ahead of the barrier
+  // The barrier after V(s) publishes the K rows of tile s+1 to the group, the one after M(s+1) (HALVES:
+  // V(s+1)) its V^T rows. A K stage is rewritten two steps after it was read, a V^T stage (read ahead of and
+  // in M(s+1), HALVES: M(s+2)) three steps after it was filled: by then every wave of the group has passed
+  // the barrier that follows its last read. Every item has an even number of steps (SPB = 2 per key block),
+  // so the position inside a key block and the K stage both follow from the parity of s, which the unrolled
+  // loop knows.
+  // key block that the next new-block step opens: entry m_nxt_e of a list, or block m_nxt_j (>= 0) of a dense row
+  int m_nxt_e = 0, m_nxt_j = 0;
   uint64_t nxt_Kbytes = 0, nxt_Vtbytes = 0;   // ... and the K rows and V^T tiles of its item, where that may be the next one
   int kvc_cur = BLK;      // valid keys in the block of the current step
   int kvc_nxt = BLK;
@@ -732,7 +745,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         // requests the tile of its last list entry once more, into a stage nobody reads again.
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (i < OPEN) {
-          open_piece(ic, m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, last_of_item ? nxt_Kbytes : cur.Kbytes, last_of_item ? nxt_Vtbytes : cur.Vtbytes);
+          open_piece(ic, m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, last_of_item ? nxt_Kbytes : cur.Kbytes,
+                     last_of_item ? nxt_Vtbytes : cur.Vtbytes);
         } else {
           step_piece(IntC<i - OPEN>{}, nt, IntC<PART_NEXT>{}, (ST + 1) % KSTAGES, vst + 1 >= VSTAGES ? 0 : vst + 1);
         }
@@ -766,7 +780,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   int have_output = 0;        // an item has ended and its output is still in the accumulators
   auto v_phase = [&](auto stc, auto firstc, auto outc, auto fetchc, auto lastc) __attribute__((always_inline)) {
     constexpr int ST = decltype(stc)::value;
-    constexpr bool first_of_item = decltype(firstc)::value != 0, last_of_item = decltype(lastc)::value != 0, output = decltype(outc)::value != 0;
+    constexpr bool first_of_item = decltype(firstc)::value != 0, last_of_item = decltype(lastc)::value != 0;
+    constexpr bool output = decltype(outc)::value != 0;
     constexpr int FETCH = decltype(fetchc)::value;
     __builtin_amdgcn_s_setprio(0);
     constexpr int VLOADS = SPLIT_LOADS ? C::VPW : 0;  // requests of this phase: the V^T rows of step s+1
@@ -814,7 +829,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       fj += 1;
     }
     if constexpr (SPLIT_LOADS && (C::VH || !output)) {
-      static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) { issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{}); });
+      static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) {
+        issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{});
+      });
     }
     // Step ns-2 of an item of two key blocks or more; an item of one block asks in its last phase instead (a request under a
     // condition in the first phase would leave the compiler with loads that may be pending on its way into the loop of steps,
@@ -831,7 +848,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         write_output();
       }
       if constexpr (SPLIT_LOADS) {
-        static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) { issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{}); });
+        static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) {
+          issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{});
+        });
       }
     }
     {
@@ -1164,7 +1183,8 @@ hipError_t launch_attn_t(const Dims& dm, const AttnArgs& a, const AttnSched& ws,
     da.cross = (int2*)(room + l.cross);
     da.pieces = (float*)(room + l.pieces);
     da.cap = sh.cap; da.slots = sh.slots; da.groups = C::NGRP; da.pieces_per_queue = sh.pieces_per_queue;
-    da.heads_at_once = sh.heads_at_once; da.most_share = sh.most_share; da.rows_per_bh = sh.rows_per_bh; da.n_dense = sh.n_dense; da.dense_per_bh = sh.dense_per_bh > 0 ? sh.dense_per_bh : 1;
+    da.heads_at_once = sh.heads_at_once; da.most_share = sh.most_share; da.rows_per_bh = sh.rows_per_bh;
+    da.n_dense = sh.n_dense; da.dense_per_bh = sh.dense_per_bh > 0 ? sh.dense_per_bh : 1;
     da.dense_first = sh.dense_first; da.n_cross = sh.n_cross; da.min_piece = sh.min_piece; da.switch_cost = sh.switch_cost;
     da.rule = cut_rule(dm);
     sc.table = da.table; sc.nitems = da.nitems; sc.total = da.total; sc.piece0 = da.piece0; sc.pieces = da.pieces;
@@ -1196,7 +1216,7 @@ void attn_sched_bytes(const Dims& dm, size_t* schedule, size_t* pieces) {
 
 hipError_t launch_attn(const Dims& dm, const AttnArgs& a, const AttnSched& ws, hipStream_t s) {
   if (dm.d == 128 && dm.blk == 128) return launch_attn_t<128, 128, false>(dm, a, ws, s);
-  if (dm.d == 128 && dm.blk == 64 && !(a.flags & RSA_DENSE)) return launch_attn_t<128, 64, true>(dm, a, ws, s);   // (see attn_kernel)
+  if (dm.d == 128 && dm.blk == 64 && !(a.flags & RSA_DENSE)) return launch_attn_t<128, 64, true>(dm, a, ws, s);   // (HALVES)
   if (dm.d == 128 && dm.blk == 64) return launch_attn_t<128, 64, false>(dm, a, ws, s);
   if (dm.d == 64 && dm.blk == 128) return launch_attn_t<64, 128, false>(dm, a, ws, s);
   return launch_attn_t<64, 64, false>(dm, a, ws, s);

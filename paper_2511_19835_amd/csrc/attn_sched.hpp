@@ -100,7 +100,8 @@ inline int heads_at_once(const Dims& dm) {
 
 // Sizes of the schedule for `n_wg` resident workgroups of NGRP groups.
 struct SchedShape {
-  int heads_at_once, most_share, slots, cap, least_cap, n_items, n_dense, dense_per_bh, dense_first, rows_per_bh, n_cross, pieces_per_queue, min_piece, switch_cost;
+  int heads_at_once, most_share, slots, cap, least_cap, n_items;
+  int n_dense, dense_per_bh, dense_first, rows_per_bh, n_cross, pieces_per_queue, min_piece, switch_cost;
 };
 inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   SchedShape s;

@@ -123,7 +123,9 @@ __global__ __launch_bounds__(256) void compensation_kernel(Dims dm, AttnArgs a) 
 // An entry of the order: the row, and the load (key blocks and switches) of the rows before it, in units of 32 key blocks
 // (at most 4095 (4096 + 6) / 32 < 2^20).
 constexpr int kRankRows = 64;
-__device__ __forceinline__ int32_t order_entry(int row, int load) { return (int32_t)((uint32_t)row | (uint32_t)(load / 32) << 12); }
+__device__ __forceinline__ int32_t order_entry(int row, int load) {
+  return (int32_t)((uint32_t)row | (uint32_t)(load / 32) << 12);
+}
 __device__ __forceinline__ int order_row(int32_t entry) { return entry & 4095; }
 __device__ __forceinline__ int order_load(int32_t entry) { return (int)((uint32_t)entry >> 12); }
 __global__ __launch_bounds__(256) void row_rank_kernel(Dims dm, AttnArgs a, int switch_cost) {
@@ -140,7 +142,8 @@ __global__ __launch_bounds__(256) void row_rank_kernel(Dims dm, AttnArgs a, int 
     const int l0 = lst[0], l1 = lst[e1], l2 = lst[e2];
     const uint64_t i0 = cnt > 0 ? (uint32_t)l0 & 4095 : 4095, i1 = cnt > 1 ? (uint32_t)l1 & 4095 : 4095, i2 = cnt > 2 ? (uint32_t)l2 & 4095 : 4095;
     const uint64_t load = min(max(cnt, 1), dm.m) + switch_cost;                          // < 2^13
-    keys[i] = i < dm.n ? ((i0 << 36) | (i1 << 24) | (i2 << 12) | (uint64_t)i) << 13 | load : ~0ull;   // every index < RSA_MAX_BLOCKS = 2^12
+    // (every index < RSA_MAX_BLOCKS = 2^12)
+    keys[i] = i < dm.n ? ((i0 << 36) | (i1 << 24) | (i2 << 12) | (uint64_t)i) << 13 | load : ~0ull;
   }
   __syncthreads();
   const int r = blockIdx.x * kRankRows + tid / 4;
@@ -200,8 +203,8 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
 //
 // What is left at the end -- fewer rows than slots when all lists are equally long, up to twice as many
 // otherwise -- and the long text rows are cut (video rows only where that is faster, see there): laid end to end and
-// divided over the slots so that every slot ends at the same key block, give or take min_piece. A row that is cut is put together by merge_kernel. Cut points
-// closer than min_piece to the end of a row move there. Without that, an uneven last round
+// divided over the slots so that every slot ends at the same key block, give or take min_piece. A row that is cut is
+// put together by merge_kernel. Cut points closer than min_piece to the end of a row move there. Without that, an uneven last round
 // leaves slots idle (159 blocks of 24 heads on 512 slots: 7.45 rounds took 8; the dense layer of that shape
 // 4.25 -> 4.08 ms) and a text row, which walks all M blocks, can be longer than the whole share of a slot
 // (3 heads of 931 blocks, 6 text rows: a slot's share is 522 blocks; attention 2.79 -> 1.95 ms). In the smallest
@@ -232,7 +235,7 @@ __device__ __forceinline__ void deal_queue(const Dims& dm, const AttnArgs& a, co
   int32_t* s_cross = s_cnt + kMaxSlots;           // [8][2]: first and last piece of this queue's part of a cross row
   int32_t* t_cut = rec;                           // (the tail no longer needs the staged rows) pieces of an entry
   int32_t* s_part = s_cross + 2 * kQueues;        // [turns][9]: first row of every queue's part of a turn
-  int32_t* s_left = s_part + kMaxTurns * (kQueues + 1);   // rows of the last segment still to be dealt: from, to; equal; number of tail entries
+  int32_t* s_left = s_part + kMaxTurns * (kQueues + 1);   // rows of the last segment to be dealt: from, to; equal; tail entries
   const int tid = threadIdx.x, lane = tid % 64;
   const bool dense_all = (a.flags & RSA_DENSE) != 0;
   const int bh_total = dm.batch * dm.heads, NR = da.rows_per_bh, S = da.slots;

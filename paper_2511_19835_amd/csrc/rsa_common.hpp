@@ -141,7 +141,9 @@ struct AttnArgs {
   uint16_t* O;
   float* lse;
   float* comp;             // workspace [b][h][N][d]: pooled compensation term C_n
-  int32_t* row_order;      // workspace [b][h][N]: launch order of the video query blocks and their lengths (order_entry; NULL: natural)
+  // workspace [b][h][N]: launch order of the video query blocks, with the load of all rows before each (order_entry: row |
+  // key blocks and switch costs / 32 << 12; NULL: natural order)
+  int32_t* row_order;
   int flags;
 };
 // Persistent attention kernel: number of resident workgroups and (optional) room for its schedule.
