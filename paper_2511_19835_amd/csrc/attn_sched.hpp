@@ -88,8 +88,9 @@ struct DealArgs {
 // which ask for the most bytes per product, a little over that still pays.
 // Measured, attention in us, one head and as chosen: blocks of 128, 24 heads of 159 blocks 493 and 481, with the full mask
 // rule 1376 and 1260; 40 of 591 (39 MB a head) 9879 and 9737 (eight heads: 9 to 30 more); 24 of 931 (61 MB) 14 930 and 14 910
-// (four: 100 more), full rule 20 930 and 20 330. Blocks of 64: 24 of 318 572 and 559, full rule 1706 and 1180; 24 of 1182
-// (39 MB) at sparsity 0.7 21 400 and 19 980; 24 of 1860 (61 MB) 21 640 and 19 010 (two: 21 250). d = 64: 24 of 160 723 and 712.
+// (four: 100 more), full rule 20 750 and 20 190 (one box of three: equal). Blocks of 64: 24 of 318 572 and 559, full rule 1706
+// and 1180; 24 of 1182 (39 MB) at sparsity 0.7 21 400 and 19 980; 24 of 1860 (61 MB) 21 640 and 19 010 (two: 21 250). d = 64,
+// bound by its softmax: 24 of 160 728 and 725, 24 of 591 3864 and 3814, blocks of 64, 24 of 318 369 and 365.
 inline int heads_at_once(const Dims& dm) {
   const int bh = dm.batch * dm.heads, least = (bh + kMaxTurns - 1) / kMaxTurns;
   const long long head_bytes = 4LL * dm.t * dm.d, most = (dm.d == 128 && dm.blk == 64 ? 250LL : 200LL) * 1000000;
