@@ -116,24 +116,33 @@ def cpu_baseline(cfg, sparsity, Qb, Kb, Vb, gpu_O_bits, gpu_mask, gpu_Mc, budget
 # (counter KiB x 1024 x the scale the same counter shows for a plain copy kernel: 2.0 fetch, 1.0 write).
 # A counter run cannot be made from inside the timed process, so the figure is carried here for the
 # exact workload it was taken on and is null for any other. Provenance: the two runs listed in
-# profiles/attn_kernel_hunyuan_pmc.md, taken with the attention kernel named by the hash below: FETCH_SIZE 19.27e6 KiB
-# (four launches: 19.09e6 to 19.45e6), WRITE_SIZE 714.3e3 KiB per launch.
-# The figure is reported only while csrc/attn_kernels.hip is byte for byte the source the counters were
-# taken on (hash below); after any change to it, re-measure and update figure, hash and profile together.
-MEASURED_TRAFFIC_BYTES = {("hunyuan", 0.9, 0, 24, 128, 128): 17.54e6 * 2.0 * 1024 + 714.3e3 * 1024}
+# profiles/attn_kernel_hunyuan_pmc.md: FETCH_SIZE 17.53e6 KiB (four launches: 17.50e6 to 17.56e6), WRITE_SIZE 714.3e3 KiB
+# per launch. The figure is reported only while the sources that decide the bytes -- the kernel, the kernels that order
+# its rows and deal its schedule, and the schedule's rules -- are byte for byte those that the counters were taken on (hash
+# below); after any change to them, re-measure and update figure, hash and profile together.
+MEASURED_TRAFFIC_BYTES = {("hunyuan", 0.9, 0, 24, 128, 128): 17.53e6 * 2.0 * 1024 + 714.3e3 * 1024}
 MEASURED_TRAFFIC_SOURCE = "profiles/attn_kernel_hunyuan_pmc.md"
-MEASURED_TRAFFIC_KERNEL_SHA = "48788c6933c712e7"      # first 16 hex digits of sha256(csrc/attn_kernels.hip) at the time of the counter runs
+MEASURED_TRAFFIC_FILES = ("attn_kernels.hip", "attn_side_kernels.hip", "attn_sched.hpp")
+MEASURED_TRAFFIC_SHA = "099917ed0449dbcf"
+
+
+def traffic_sources_sha(csrc):
+    """First 16 hex digits of the sha256 of the files in `csrc` that decide the fabric bytes of an attention launch."""
+    h = hashlib.sha256()
+    for name in MEASURED_TRAFFIC_FILES:
+        with open(os.path.join(csrc, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(cfg, sparsity, args):
-    """The carried counter figure, or None: for another workload, or once the kernel source has changed since."""
+    """The carried counter figure, or None: for another workload, or once one of the sources has changed since."""
     if args.mask_rule != "topk":
         return None
-    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2511_19835_amd", "csrc", "attn_kernels.hip")
+    csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2511_19835_amd", "csrc")
     try:
-        with open(src, "rb") as f:
-            if hashlib.sha256(f.read()).hexdigest()[:16] != MEASURED_TRAFFIC_KERNEL_SHA:
-                return None
+        if traffic_sources_sha(csrc) != MEASURED_TRAFFIC_SHA:
+            return None
     except OSError:
         return None
     return MEASURED_TRAFFIC_BYTES.get((cfg.name, round(float(sparsity), 6), args.seed, cfg.heads, cfg.head_dim, cfg.block))
