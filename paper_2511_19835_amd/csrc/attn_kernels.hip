@@ -11,16 +11,25 @@
 // [d/2][BLK]) are brought into the group's own LDS rings by direct-to-LDS loads
 // (global_load_lds_dwordx4: no staging registers), one step ahead -- also across the boundary
 // between two items, so the matrix pipe never drains. Each wave computes, with
-// v_mfma_f32_32x32x16_bf16,
-//     S^T = K Q^T      (M = key, N = query, k = channel)      -> accumulators: one query
-//     O^T += V^T P^T   (M = channel, N = query, k = key)         column per lane
-// so the online softmax is lane-local except for one exchange between the two half-waves,
+// v_mfma_f32_16x16x32_bf16,
+//     S^T = K Q^T      (M = key, N = query, k = channel)      -> accumulators: two query columns per lane,
+//     O^T += V^T P^T   (M = channel, N = query, k = key)         one of either query tile of 16
+// so the online softmax is lane-local except for sums over four lanes at the end of an item,
 // and the probabilities a lane holds after the first product are exactly the B operand it
-// needs for the second (rsa_pool stores V in that key order).
+// needs for the second (rsa_pool stores V in that key order, and the K operands take their rows
+// to match, key_row).
+//
+// What bounds it is the power that the chip may draw, and the instruction decides what a product costs of it. In a loop of
+// the same two phases without loads of tiles, 16 x 16 x 32 sustains 1600 TFLOP/s and 32 x 32 x 16 1470 (2308 and 2206
+// cycles a step at 1.72 and 1.50 GHz; products alone from registers 2050 and 1785). The price is the vector ALU's: beside
+// products of 16 x 16 it issues two instructions in 16 cycles, so that the softmax phase is now the longer of the two,
+// and requests are all made in the MFMA phase. Against the larger instruction, us: 24 heads of 931 blocks, lists of 94, layer
+// 16 970 and 15 830; 40 of 591 11 040 and 10 650; 24 of 159, lists of 16, 633 and 607, all blocks 4040 and 3720; d = 64, 24 of 160
+// 794 and 758; blocks of 64, 24 of 1182 equal, all of 380 blocks 6300 and 6090.
 //
 // A step of a group is two phases, separated by workgroup barriers: an MFMA phase (the P V
 // product of the previous step, then K Q^T of this one: matrix instructions, their LDS operand
-// reads a few slots ahead and the requests for the next tile, one per slot) and a softmax phase
+// reads a few slots ahead and the requests for the next tile, between the two products of a slot) and a softmax phase
 // (VALU only). The groups run one barrier apart, so that on every SIMD one wave feeds the matrix
 // pipe while the other uses the VALU. When an item ends its output is written in the softmax phase
 // of the next item's first step (HALVES: its second): O = R_n * acc / l + C_n, C_n = sum_{m: not kept and M_c}
@@ -52,7 +61,6 @@ constexpr int VSTAGES = 3;           // ... of its V^T tiles, which are read one
 #ifndef RSA_MWIN
 #define RSA_MWIN 4
 #endif
-constexpr bool SPLIT_LOADS = true;   // K rows requested in the MFMA phase, V^T rows in the softmax phase
 constexpr int MWIN = RSA_MWIN;      // MFMA slots between the LDS read of a K operand and its use
 
 template <int D, int BLK, bool HALVES>
@@ -64,16 +72,16 @@ struct AttnCfg {
   // number of them (the loop over the steps is unrolled twice)
   static constexpr int KVS = BLK / 2;
   static constexpr int SPB = BLK / KVS;     // steps per key block
-  static constexpr int KT = KVS / 32;       // key tiles of S^T per step
-  static constexpr int KS = D / 16;         // k-steps of K Q^T
-  static constexpr int DT = D / 32;         // channel tiles of O^T
-  static constexpr int PC = KVS / 16;       // 16-key chunks per step
+  static constexpr int KT = KVS / 16;       // key tiles of S^T per step
+  static constexpr int KS = D / 32;         // k-steps of K Q^T
+  static constexpr int DT = D / 16;         // channel tiles of O^T
+  static constexpr int PC = KVS / 32;       // 32-key chunks per step
   static constexpr bool VH = HALVES;        // V^T by halves of the channels, all keys of the block at once (see attn_kernel)
-  static constexpr int PPC = VH ? BLK / 16 : PC;     // 16-key chunks of one P V product
+  static constexpr int PPC = VH ? BLK / 32 : PC;     // 32-key chunks of one P V product
   static constexpr int PDT = VH ? DT / 2 : DT;       // ... and its channel tiles
   static constexpr int KCPR = D / 8;        // 16-byte chunks per K row
-  static constexpr int VCPR = PPC * 2;      // 16-byte chunks per V^T row of a tile
-  static constexpr int VROWS = PDT * 32;    // V^T rows of a tile
+  static constexpr int VCPR = PPC * 4;      // 16-byte chunks per V^T row of a tile
+  static constexpr int VROWS = PDT * 16;    // V^T rows of a tile
   static constexpr int KINST = KVS * KCPR / 64;   // 1 KB direct-to-LDS loads per K step tile
   static constexpr int VINST = VROWS * VCPR / 64; // ... per V^T step tile
   static constexpr int KPW = KINST / NW;    // per wave
@@ -88,33 +96,59 @@ struct AttnCfg {
   static_assert(NGRP % 2 == 0 && BLK % KVS == 0, "groups pair up on the SIMDs; a block is a whole number of steps");
 };
 
-// LDS tiles are unpadded; the 16-byte chunk c of row r is stored at chunk position
-// c ^ key(r) so that 16 consecutive rows read at one logical chunk index hit 16 different
-// positions (all banks once). CPR = chunks per row (8 or 16).
+// LDS tiles are unpadded; the 16-byte chunk c of row r is stored at chunk position c ^ key(r) so that the 16 rows of an
+// operand, read at one logical chunk index, hit 16 different positions (all banks once), and also where an access takes
+// four rows each from lanes whose chunk indices differ in their lowest bit. CPR = chunks per row (4, 8 or 16). V^T operands
+// are 16 consecutive rows, K operands the rows key_row below: eight consecutive ones and the eight that are 16 further on.
 template <int CPR>
-__device__ __forceinline__ int swz_key(int r) { return (r / (16 / CPR)) & (CPR - 1); }
+__device__ __forceinline__ int swz_v_key(int r) {
+  if constexpr (CPR == 4) return ((r / 4 ^ r / 8) & 1) * 2 | (r / 8 & 1);
+  return (r / (16 / CPR)) & (CPR - 1);
+}
 template <int CPR>
-__device__ __forceinline__ int swizzled(int r, int c) { return r * CPR + (c ^ swz_key<CPR>(r)); }
+__device__ __forceinline__ int swz_k_key(int r) { return CPR == 16 ? (r & 7) | (r & 16) / 2 : (r / 2 & 3) | (r & 16) / 4; }
+// Row of a run of 32 keys that lane row i of a K operand takes (its partner operand: 8 further on): the keys whose scores
+// a lane then holds, four from either operand, are the eight of its B operand in the order that rsa_pool stores V^T in.
+__device__ __forceinline__ int key_row(int i) { return (i & 7) + 2 * (i & 8); }
 
-// Exchange between the two half-waves (lane l <-> lane l^32) with v_permlane32_swap.
+// Values that the four lanes of a query column (lane l, l ^ 16, l ^ 32, l ^ 48) hold, put together with
+// v_permlane16_swap and v_permlane32_swap; all four get the same bits.
 // The vector elements are copied to scalars before the bit casts: a bit cast applied
 // directly to an element expression reads element 0 whatever the index.
-__device__ __forceinline__ void half_wave_pair(float v, float& lo, float& hi) {
+template <class F>
+__device__ __forceinline__ float over_column(float v, F&& f) {
   const uint32_t u = __builtin_bit_cast(uint32_t, v);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const uint32_t r0 = r[0], r1 = r[1];
-  lo = __builtin_bit_cast(float, r0);   // value held by lane l%32
-  hi = __builtin_bit_cast(float, r1);   // value held by lane l%32 + 32
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t a0 = a[0], a1 = a[1];
+  const uint32_t w = __builtin_bit_cast(uint32_t, f(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1)));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  const uint32_t b0 = b[0], b1 = b[1];
+  return f(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
 }
-__device__ __forceinline__ float half_wave_max(float v) {
-  float lo, hi;
-  half_wave_pair(v, lo, hi);
-  return fmaxf(lo, hi);
+__device__ __forceinline__ float column_max(float v) {
+  return over_column(v, [](float a, float b) { return fmaxf(a, b); });
 }
-__device__ __forceinline__ float half_wave_sum(float v) {
-  float lo, hi;
-  half_wave_pair(v, lo, hi);
-  return lo + hi;
+__device__ __forceinline__ float column_sum(float v) {
+  return over_column(v, [](float a, float b) { return a + b; });
+}
+
+// Matrix products as inline asm, because only there the accumulator can be held to its place: the compiler gives this
+// instruction a destination of its own, and the accumulators then wander through the registers and into scratch. Its hazards
+// are ours in return: an accumulator is used by the next product at the earliest four products on (the matrix pipe needs 16
+// cycles for each), and before any other use stands settle_products. Operands come from LDS reads (waited for) and from the
+// phase before (a barrier away).
+__device__ __forceinline__ void mfma_add(floatx4& c, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_first(floatx4& c, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+}
+// The products into c[][] are complete (an XDL result of 4 passes may be read by the vector ALU some ten wait states on).
+template <int NOPS, int N>
+__device__ __forceinline__ void settle_products(floatx4 (&c)[N][2]) {
+  asm volatile("s_nop %0" ::"n"(NOPS - 1) : "memory");
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(c[i][0]), "+v"(c[i][1]));
 }
 
 // The lane number, worked out where it is asked for. What happens once per item (query rows, epilogue)
@@ -185,7 +219,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   const int grp = wave_wg / C::NW;                   // which group of this workgroup
   const int wave = wave_wg % C::NW;                  // wave inside the group (groups g and g + NGRP/2 share their SIMDs)
   const int lane = tid % 64;
-  const int l32 = lane % 32, hf = lane / 32;
+  const int l16 = lane % 16, g4 = lane / 16;         // query column (of either query tile) and k-group of this lane
   u32x4* lds = lds_all + grp * C::GROUP;
 
   // ---- the items of this group, and how many rounds the workgroup turns -------------------
@@ -288,10 +322,10 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // ---- direct-to-LDS loads ---------------------------------------------------------------
   // A load fills 1 KB of LDS = RK consecutive K rows (RV consecutive V^T rows). Load ii of
   // wave w covers rows pass*ROWS_PER_PASS + (class*NW + w)*RK + (lane / chunks-per-row): the
-  // swizzle key of a lane's row then depends on the class only, so KOFF (usually 1) per-lane
-  // byte offsets serve all of a wave's loads and everything else is scalar.
+  // swizzle key of a lane's row then depends on the class only (it repeats every 32 K rows and every 16 V^T
+  // rows), so KOFF (VOFF: 1) per-lane byte offsets serve all of a wave's loads and everything else is scalar.
   constexpr int RK = 64 / C::KCPR, RV = 64 / C::VCPR;
-  constexpr int KOFF = (C::NW * RK >= 16) ? 1 : 16 / (C::NW * RK);
+  constexpr int KOFF = (C::NW * RK >= 32) ? 1 : 32 / (C::NW * RK);
   constexpr int VOFF = (C::NW * RV >= 16) ? 1 : 16 / (C::NW * RV);
   static_assert(C::KPW % KOFF == 0 && C::VPW % VOFF == 0, "row classes must divide a wave's loads");
   int k_r0[KOFF], k_col[KOFF];
@@ -299,13 +333,13 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 #pragma unroll
   for (int c = 0; c < KOFF; ++c) {
     k_r0[c] = (c * C::NW + wave) * RK + lane / C::KCPR;
-    k_col[c] = ((lane % C::KCPR) ^ swz_key<C::KCPR>(k_r0[c])) * 8;              // element offset in the row
+    k_col[c] = ((lane % C::KCPR) ^ swz_k_key<C::KCPR>(k_r0[c])) * 8;              // element offset in the row
     k_voff[c] = (uint32_t)((k_r0[c] * dm.st + k_col[c]) * 2);
   }
 #pragma unroll
   for (int c = 0; c < VOFF; ++c) {
     const int r0 = (c * C::NW + wave) * RV + lane / C::VCPR;
-    v_voff[c] = (uint32_t)((r0 * BLK + ((lane % C::VCPR) ^ swz_key<C::VCPR>(r0)) * 8) * 2);
+    v_voff[c] = (uint32_t)((r0 * BLK + ((lane % C::VCPR) ^ swz_v_key<C::VCPR>(r0)) * 8) * 2);
   }
   constexpr int K_ROWS_PER_PASS = C::NW * RK * KOFF, V_ROWS_PER_PASS = C::NW * RV * VOFF;
   constexpr int K_LDS_CLASS = C::NW * RK * C::KCPR * 16, V_LDS_CLASS = C::NW * RV * C::VCPR * 16;
@@ -324,12 +358,6 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   const int64_t text_adjust = ((int64_t)dm.tv - (int64_t)dm.n * BLK) * dm.st * 2;   // text blocks start at T_v, not N*B
   const int last_video_count = dm.block_count(dm.n - 1), last_count = dm.block_count(dm.m - 1);
   constexpr uint32_t kVtBlockBytes = (uint32_t)D * BLK * 2u;
-  auto count_of = [&](int m) __attribute__((always_inline)) {
-    int c = BLK;
-    if (m == dm.n - 1) c = last_video_count;
-    if (m == dm.m - 1) c = last_count;
-    return c;
-  };
   constexpr int LPS = C::KPW + C::VPW;           // loads per step per wave
   uint32_t kvo[C::KPW], vvo[C::VPW];             // per-lane byte offsets of this wave's loads of a full tile
 #pragma unroll
@@ -347,45 +375,42 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   uint64_t blk_kp = 0, blk_vp = 0;
   int blk_count = BLK;
   const uint32_t krow_bytes = (uint32_t)dm.st * 2u;
-  // A tile is prepared in pieces of a few instructions each, so that the caller can put one behind each of its first
-  // MFMAs: a matrix instruction covers 32 cycles and a wave issues an instruction every five or so, so that with all forty
-  // (two branches among them) behind one MFMA the matrix pipe stood still (MFMA phase at d = 128, blocks of 128: 1440 cycles
-  // of the 1024 that its instructions take, now 1290; 24 heads of 931 blocks 15 310 -> 14 800 us, 40 of 591 10 280 -> 9870,
-  // where the power limit gives a part of it back in clock; d = 64, bound by its softmax, 728 -> 723). Pieces
-  // 0 .. kOpenPieces-1 open the key block m (first step of a block), the kStepPieces after them are taken for every step.
+  // A tile is prepared in pieces of two or three instructions each, so that the caller can put one between the two MFMAs of
+  // each of its slots: a matrix instruction covers 16 cycles and a wave issues an instruction every five or so, so that with
+  // all forty in one place (or four behind every second MFMA) the matrix pipe stood still. Pieces 0 .. kOpenPieces-1 open the
+  // key block m (first step of a block), the step pieces after them are taken for every step.
   // In a ragged key block (the last video block, the last text block) rows past its end re-read its last row (masked
   // later; V^T is zero-padded in HBM): the byte offset of every lane is held to that row's, without a branch.
-  constexpr int kOpenPieces = 4, kStepPieces = 3;
-  uint64_t open_base = 0;
+  constexpr int kOpenPieces = 7, kStepPieces = 6 + KOFF;
+  uint64_t open_base = 0, open_off = 0;
+  int open_count = BLK;
   auto open_piece = [&](auto pc, int m, uint64_t Kbytes, uint64_t Vtbytes) __attribute__((always_inline)) {
     constexpr int piece = decltype(pc)::value;
-    if constexpr (piece == 0) open_base = Kbytes + (uint64_t)(m >= dm.n ? text_adjust : 0);
-    if constexpr (piece == 1) blk_kp = open_base + (uint64_t)(uint32_t)m * kblock_bytes;
-    if constexpr (piece == 2) blk_count = count_of(m);
-    if constexpr (piece == 3) blk_vp = Vtbytes + (uint64_t)(uint32_t)m * kVtBlockBytes;
+    if constexpr (piece == 0) open_off = (uint64_t)(m >= dm.n ? text_adjust : 0);
+    if constexpr (piece == 1) open_base = Kbytes + open_off;
+    if constexpr (piece == 2) open_off = (uint64_t)(uint32_t)m * kblock_bytes;
+    if constexpr (piece == 3) blk_kp = open_base + open_off;
+    if constexpr (piece == 4) open_count = m == dm.n - 1 ? last_video_count : BLK;
+    if constexpr (piece == 5) blk_count = m == dm.m - 1 ? last_count : open_count;
+    if constexpr (piece == 6) blk_vp = Vtbytes + (uint64_t)(uint32_t)m * kVtBlockBytes;
   };
+  uint32_t step_skip = 0;
   auto step_piece = [&](auto pc, Tile& t, auto partc, int kst, int vst) __attribute__((always_inline)) {
     constexpr int piece = decltype(pc)::value;
     constexpr int part = decltype(partc)::value;
-    if constexpr (piece == 0) {
-      // (a block that ends before its second step: the step reads the rows of the first, all of them masked)
-      const uint32_t skip = part > 0 && blk_count > part * KVS ? part * kstep_bytes : 0u;
-      t.kp = blk_kp + skip;
-      t.klast = (uint32_t)(blk_count - 1) * krow_bytes - skip;
-    }
-    if constexpr (piece == 1) {
-      t.vp = blk_vp + part * (C::VH ? C::VROWS * BLK * 2u : KVS * 2u);
-      t.kdst = ldsK_addr + kst * (KBUF * 16);
-      t.vdst = ldsV_addr + vst * (C::VBUF * 16);
-    }
-    if constexpr (piece == 2) {
+    // (a block that ends before its second step: the step reads the rows of the first, all of them masked)
+    if constexpr (piece == 0) step_skip = part > 0 && blk_count > part * KVS ? part * kstep_bytes : 0u;
+    if constexpr (piece == 1) t.kp = blk_kp + step_skip;
+    if constexpr (piece == 2) t.klast = (uint32_t)(blk_count - 1) * krow_bytes - step_skip;
+    if constexpr (piece == 3) t.kdst = ldsK_addr + kst * (KBUF * 16);
+    if constexpr (piece >= 4 && piece < 4 + KOFF) {
+      constexpr int c = piece - 4;
+      const uint32_t last = t.klast + (uint32_t)k_col[c] * 2u;
 #pragma unroll
-      for (int c = 0; c < KOFF; ++c) {
-        const uint32_t last = t.klast + (uint32_t)k_col[c] * 2u;
-#pragma unroll
-        for (int ii = c; ii < C::KPW; ii += KOFF) t.koff[ii] = min(kvo[ii], last);
-      }
+      for (int ii = c; ii < C::KPW; ii += KOFF) t.koff[ii] = min(kvo[ii], last);
     }
+    if constexpr (piece == 4 + KOFF) t.vp = blk_vp + part * (C::VH ? C::VROWS * BLK * 2u : KVS * 2u);
+    if constexpr (piece == 5 + KOFF) t.vdst = ldsV_addr + vst * (C::VBUF * 16);
   };
   auto issue_load = [&](const Tile& t, auto idxc) __attribute__((always_inline)) {
     constexpr int idx = decltype(idxc)::value;
@@ -402,9 +427,11 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   const u32x4* kread[C::KS];
   const u32x4* vread[C::PPC];
 #pragma unroll
-  for (int ks = 0; ks < C::KS; ++ks) kread[ks] = lds + swizzled<C::KCPR>(l32, 2 * ks + hf);
+  for (int ks = 0; ks < C::KS; ++ks)
+    kread[ks] = lds + key_row(l16) * C::KCPR + ((4 * ks + g4) ^ swz_k_key<C::KCPR>(key_row(l16)));
 #pragma unroll
-  for (int pc = 0; pc < C::PPC; ++pc) vread[pc] = lds + KSTAGES * KBUF + swizzled<C::VCPR>(l32, 2 * pc + hf);
+  for (int pc = 0; pc < C::PPC; ++pc)
+    vread[pc] = lds + KSTAGES * KBUF + l16 * C::VCPR + ((4 * pc + g4) ^ swz_v_key<C::VCPR>(l16));
 
   // ---- the item being computed, the one after it, and the one whose output is still to be written
   Item cur = {}, nxt = {};
@@ -422,24 +449,29 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // lists of 60: 9828 and 9755; shorter lists 0.2 %; where the power limit or the fabric bounds the kernel, equal). Rows past
   // the end of a ragged block repeat its last row: the number of loads in flight is the same for every wave, and the waits
   // below count on it.
-  bf16x8 qreg[C::KS], qnext[C::KS];
+  bf16x8 qreg[C::KS][2], qnext[C::KS][2];      // (k-step, query tile)
   const float cs = dm.scale * kLog2e;   // scores -> binades
-  auto load_q = [&](bf16x8 (&dst)[C::KS], int64_t qo_off, int q_count) __attribute__((always_inline)) {
+  auto load_q = [&](bf16x8 (&dst)[C::KS][2], int64_t qo_off, int q_count) __attribute__((always_inline)) {
     const int ln = lane_now();
-    const int q = min(wave * 32 + ln % 32, q_count - 1);
-    const uint16_t* qrow = a.Q + qo_off + (int64_t)q * dm.st + 8 * (ln / 32);
 #pragma unroll
-    for (int s = 0; s < C::KS; ++s) dst[s] = *reinterpret_cast<const bf16x8*>(qrow + 16 * s);
+    for (int f = 0; f < 2; ++f) {
+      const int q = min(wave * 32 + 16 * f + ln % 16, q_count - 1);
+      const uint16_t* qrow = a.Q + qo_off + (int64_t)q * dm.st + 8 * (ln / 16);
+#pragma unroll
+      for (int s = 0; s < C::KS; ++s) dst[s][f] = *reinterpret_cast<const bf16x8*>(qrow + 32 * s);
+    }
   };
 #pragma unroll
-  for (int s = 0; s < C::KS; ++s) qnext[s] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-  floatx16 oacc[C::DT];
+  for (int s = 0; s < C::KS; ++s)
 #pragma unroll
-  for (int dt = 0; dt < C::DT; ++dt)
+    for (int f = 0; f < 2; ++f) qnext[s][f] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+  const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  floatx4 oacc[C::DT][2];                // (channel tile, query tile)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-  float mref = 0.f, lpart = 0.f;         // softmax reference (log2 domain) and this lane's partial row sum
-  float done_m = 0.f, done_l = 0.f;      // (VH) those of the item whose last P V product is under way
+  for (int dt = 0; dt < C::DT; ++dt) oacc[dt][0] = oacc[dt][1] = zero4;
+  // by query tile: softmax reference (log2 domain) and this lane's partial row sum
+  float mref[2] = {0.f, 0.f}, lpart[2] = {0.f, 0.f};
+  float done_m[2] = {0.f, 0.f}, done_l[2] = {0.f, 0.f};      // (VH) those of the item whose last P V product is under way
 
   // Epilogue of one item: O = R_n * acc / l + C_n (video rows; text rows: acc / l), bf16; then the
   // running state starts over for the next item. R_n and C_n are requested with the next
@@ -454,7 +486,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   float done_rfac = 1.0f, next_rfac = 1.0f;
   // The query rows of the next item, and R_n and C_n of this one: asked for in the softmax phase of the last step but one (of an
   // item of two steps: in its last). The same number of vector loads in any case (NREQ).
-  constexpr int NREQ = C::KS + 1;
+  constexpr int NREQ = 2 * C::KS + 1;
   auto request_switch = [&]() __attribute__((always_inline)) {
     load_q(qnext, nxt_valid ? nxt.qo_off : cur.qo_off, nxt_valid ? nxt.q_count : cur.q_count);
     const size_t vrow = (size_t)cur.bh * dm.n + cur.qb;        // row of the per-video-block tensors
@@ -477,14 +509,16 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     }
   };
   // The current item ends: what was asked for takes its place. The compiler waits for the loads it knows of where they are
-  // copied here, down to none outstanding; as it does not see the tile requests, this drains those as well, the V^T rows of
-  // the same phase among them, which no one needs for another step: a cost of every item that has not been measured.
+  // copied here, down to none outstanding; as it does not see the tile requests, this drains those as well, the V^T rows that
+  // no one needs for another step among them.
   auto settle_switch = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) {
-      qreg[ks] = qnext[ks];
-      asm volatile("" : "+v"(qreg[ks]));
-    }
+    for (int ks = 0; ks < C::KS; ++ks)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        qreg[ks][f] = qnext[ks][f];
+        asm volatile("" : "+v"(qreg[ks][f]));
+      }
 #pragma unroll
     for (int j = 0; j < CV; ++j) {
       done_comp[j] = next_comp[j];
@@ -492,33 +526,40 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     }
     done_rfac = next_rfac;
   };
-  // A piece of a row: the accumulators as they are (1 KB per store instruction), row sum and reference.
+  // A piece of a row: the accumulators, four channels of a row to a lane, at the places where merge_kernel reads them (runs
+  // of 256 bytes: [wave][32 channels][8 of them][the four channels][row]), row sums and references.
   auto write_piece = [&]() __attribute__((always_inline)) {
-    const float lsum = half_wave_sum(C::VH ? done_l : lpart);
     const int ln = lane_now();
+    const int l16 = ln % 16, g4 = ln / 16;
     float* p = sc.pieces + (size_t)((wg % 8) * sc.pieces_per_queue + done_piece) * (BLK * D + 2 * BLK);
-    floatx4* dst = reinterpret_cast<floatx4*>(p) + wave * (C::DT * 4 * 64) + ln;
+    floatx4* dst = reinterpret_cast<floatx4*>(p) + wave * (C::DT * 2 * 64) + (g4 / 2) * 64 + (g4 % 2) * 32 + l16;
 #pragma unroll
-    for (int i = 0; i < C::DT * 4; ++i)
-      dst[i * 64] = floatx4{oacc[i / 4][4 * (i % 4)], oacc[i / 4][4 * (i % 4) + 1], oacc[i / 4][4 * (i % 4) + 2], oacc[i / 4][4 * (i % 4) + 3]};
-    if (ln < 32) {
-      p[BLK * D + wave * 32 + ln] = lsum;
-      p[BLK * D + BLK + wave * 32 + ln] = C::VH ? done_m : mref;
+    for (int f = 0; f < 2; ++f) {
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt) dst[dt * 128 + 16 * f] = oacc[dt][f];
+      const float lsum = column_sum(C::VH ? done_l[f] : lpart[f]);
+      if (g4 == 0) {
+        p[BLK * D + wave * 32 + 16 * f + l16] = lsum;
+        p[BLK * D + BLK + wave * 32 + 16 * f + l16] = C::VH ? done_m[f] : mref[f];
+      }
     }
   };
-  Tile vt_next = {};          // the tile of step s+1 as M(s) prepared it: its V^T rows are requested in V(s)
+  Tile vt_next = {};          // (VH) the tile of step s+1 as M(s) prepared it: its V^T rows are requested in M(s+1)
   // The rows of O go out whole: an accumulator lane holds four channels of one row at a time, and stored like that
   // (8 bytes of 32 rows per instruction) an item kept the address unit of the CU busy for 16 x 32 lines and wave. So
-  // half of the channels at a time is turned through LDS: the V^T stage of step s+1 is free here (its last tile was
-  // read a whole step ago, and its next is requested behind the output), and a wave uses only the 1 KB pieces that
-  // its own requests fill, so no other wave can get in the way. 16-byte chunk c of row r lies at chunk c ^ row_key(r).
+  // half of the channels at a time is turned through LDS: the V^T stage whose tile was read in the MFMA phase just ended is
+  // free here (its next tile is requested in the one to come), and a wave uses only the 1 KB pieces that its own requests
+  // fill, so no other wave can get in the way. 16-byte chunk c of row r lies at chunk c ^ row_key(r).
   // (24 heads of 159 blocks, lists of 16: layer 684 -> 680 us; 2 x 12 heads of 160, d = 64: 860 -> 848; 24 heads of
   // 1182 blocks of 64: 11164 -> 11090; the longer the lists the less: 24 heads of 931, lists of 94: 17295 -> 17277.)
   constexpr int ROWB = D;                          // bytes of half a row
   constexpr int RCH = ROWB / 16, RPC = 1024 / ROWB;   // chunks of half a row, rows per piece
   static_assert(VOFF == 1 && C::VPW * 1024 == 32 * ROWB, "a wave's own pieces of a V^T stage hold half of its 32 rows");
   auto row_key = [](int r) __attribute__((always_inline)) { return (r / (256 / ROWB)) % RCH; };
+  int vst = 0;                // V^T ring stage of the current step (s % VSTAGES)
   auto write_rows = [&]() __attribute__((always_inline)) {
+    const int vfree = C::VH ? (vst + 1 >= VSTAGES ? 0 : vst + 1) : (vst == 0 ? VSTAGES - 1 : vst - 1);
+    const uint32_t turn = ldsV_addr + vfree * (C::VBUF * 16);
     typedef u32x2 __attribute__((address_space(3))) lds_u32x2;
     typedef u32x4 __attribute__((address_space(3))) lds_u32x4;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -527,13 +568,17 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(4)));
     const bool do_comp = done_sparse && (a.flags & RSA_COMPENSATE);
     const int q_count = done_q_count;
-    const float lsum = half_wave_sum(C::VH ? done_l : lpart);
     const int ln = lane_now();
-    const int hf = ln / 32;                        // (a copy of its own: see lane_now)
-    const int q = wave * 32 + ln % 32;
-    const float f = done_rfac / lsum;
-    const int wrow = ln % 32, wkey = row_key(wrow);
-    const uint32_t wbase = vt_next.vdst + (wrow / RPC) * V_LDS_PASS + (wrow % RPC) * ROWB + 8 * hf;
+    const int l16 = ln % 16, g4 = ln / 16;         // (copies of their own: see lane_now)
+    float lsum[2], fac[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      lsum[f] = column_sum(C::VH ? done_l[f] : lpart[f]);
+      fac[f] = done_rfac / lsum[f];
+    }
+    static_assert(16 % (256 / ROWB * RCH) == 0, "rows 16 apart have the same key");
+    const int wkey = row_key(l16);
+    const uint32_t wbase = turn + (l16 / RPC) * V_LDS_PASS + (l16 % RPC) * ROWB + 8 * (g4 % 2);
     const int rsub = ln / RCH;                     // row of a piece that this lane stores
     // (rows of one block: 32-bit byte offsets from the block's first row)
     char* obase = reinterpret_cast<char*>(a.O + done_qo_off);
@@ -541,65 +586,64 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     const uint32_t ooff = (uint32_t)(wave * 32 + rsub) * row_bytes;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      // the elements of C_n that go with these accumulators (32 dt + 8 g + 4 hf + e): through the wave's first piece, which the
+      // the elements of C_n that go with these accumulators (16 dt + 4 g4 + e): through the wave's first piece, which the
       // rows of O take next
-      f32x4 cadd[C::DT / 2][4];
+      f32x4 cadd[C::DT / 2];
 #pragma unroll
-      for (int d2 = 0; d2 < C::DT / 2; ++d2)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) cadd[d2][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int d2 = 0; d2 < C::DT / 2; ++d2) cadd[d2] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (do_comp) {
 #pragma unroll
-        for (int j = 0; j < CV; ++j) *(lds_f32*)(uintptr_t)(vt_next.vdst + (uint32_t)(ln * CV + j) * 4u) = done_comp[j];
+        for (int j = 0; j < CV; ++j) *(lds_f32*)(uintptr_t)(turn + (uint32_t)(ln * CV + j) * 4u) = done_comp[j];
         asm volatile("" ::: "memory");             // (LDS instructions of a wave run in order)
 #pragma unroll
         for (int d2 = 0; d2 < C::DT / 2; ++d2)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            cadd[d2][g] = *(const lds_f32x4*)(uintptr_t)(vt_next.vdst + 16 * hf + 128 * (half * (C::DT / 2) + d2) + 32 * g);
+          cadd[d2] = *(const lds_f32x4*)(uintptr_t)(turn + 16 * g4 + 64 * (half * (C::DT / 2) + d2));
         asm volatile("" ::: "memory");
       }
 #pragma unroll
       for (int d2 = 0; d2 < C::DT / 2; ++d2) {
         const int dt = half * (C::DT / 2) + d2;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int f = 0; f < 2; ++f) {
           float o[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float c = cadd[d2][g][e];
-            o[e] = fmaf(oacc[dt][4 * g + e], f, c);
+            const float c = cadd[d2][e];
+            o[e] = fmaf(oacc[dt][f][e], fac[f], c);
           }
           u32x2 w;
           w.x = pack_bf16x2(o[0], o[1]);
           w.y = pack_bf16x2(o[2], o[3]);
-          *(lds_u32x2*)(uintptr_t)(wbase + (((4 * d2 + g) ^ wkey) * 16)) = w;
+          *(lds_u32x2*)(uintptr_t)(wbase + f * (16 / RPC) * V_LDS_PASS + (((2 * d2 + g4 / 2) ^ wkey) * 16)) = w;
         }
       }
       asm volatile("" ::: "memory");               // (LDS instructions of a wave run in order)
 #pragma unroll
       for (int i = 0; i < C::VPW; ++i) {
         const int r = i * RPC + rsub;
-        const u32x4 v = *(const lds_u32x4*)(uintptr_t)(vt_next.vdst + i * V_LDS_PASS + ln * 16);
+        const u32x4 v = *(const lds_u32x4*)(uintptr_t)(turn + i * V_LDS_PASS + ln * 16);
         if (wave * 32 + r < q_count)
           *reinterpret_cast<u32x4_u*>(obase + (ooff + (uint32_t)(i * RPC) * row_bytes + half * ROWB +
                                                16 * ((ln % RCH) ^ row_key(r)))) = v;
       }
       asm volatile("" ::: "memory");
     }
-    if (q < q_count && a.lse && hf == 0)
-      a.lse[((size_t)done_bh * dm.t) + done_q_t0 + q] = ((C::VH ? done_m : mref) + log2f(lsum)) * 0.6931471805599453f;
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      const int q = wave * 32 + 16 * f + l16;
+      if (q < q_count && a.lse && g4 == 0)
+        a.lse[((size_t)done_bh * dm.t) + done_q_t0 + q] = ((C::VH ? done_m[f] : mref[f]) + log2f(lsum[f])) * 0.6931471805599453f;
+    }
   };
   auto write_output = [&]() __attribute__((always_inline)) {
+    settle_products<16>(oacc);
     if (done_piece >= 0) write_piece();
     else write_rows();
 #pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
+    for (int dt = 0; dt < C::DT; ++dt) oacc[dt][0] = oacc[dt][1] = zero4;
     if constexpr (!C::VH) {
-      mref = 0.f;
-      lpart = 0.f;
+      mref[0] = mref[1] = 0.f;
+      lpart[0] = lpart[1] = 0.f;
     }
   };
 
@@ -608,18 +652,18 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // one group issues MFMAs the other does its softmax on the VALU. s counts the steps of all the
   // items of the group, one after the other without a gap:
   //   M(s): O^T += V^T P^T of step s-1 (HALVES: half of the channels, of the block before the one of step s), then
-  //         S^T = K Q^T of step s: matrix instructions only, the A
-  //         operand of each read from LDS a few slots ahead (V^T tile of step s-1 from its ring
-  //         stage (s-1) % 3, HALVES: of step s-2; K tile of step s from stage s % 2); the K rows of tile s+1
-  //         (into stage (s+1) % 2) are requested one per MFMA slot.
-  //   V(s): in the first step of an item (HALVES: the second), the output of the item before it; the V^T rows of
-  //         tile s+1 are requested (into stage (s+1) % 3); mask, online softmax -> P as bf16 B operands (VALU
-  //         only); fetch the list entry of step s+2; in the last step but one of an item request the query rows
-  //         of the next item; wait for tile s+1 (its V^T rows: in M(s+1), HALVES: in V(s+1)); read the first
-  //         V^T operands of M(s+1) ahead of the barrier
-  // The barrier after V(s) publishes the K rows of tile s+1 to the group, the one after M(s+1) (HALVES:
-  // V(s+1)) its V^T rows. A K stage is rewritten two steps after it was read, a V^T stage (read ahead of and
-  // in M(s+1), HALVES: M(s+2)) three steps after it was filled: by then every wave of the group has passed
+  //         S^T = K Q^T of step s: matrix instructions, the A operand of each pair read from LDS a few slots ahead (V^T
+  //         tile of step s-1 from its ring stage (s-1) % 3, HALVES: of s-2; K tile of step s from stage s % 2). Between
+  //         them go the requests for the K rows of tile s+1 (into stage (s+1) % 2) and the V^T rows of tile s+1 (into
+  //         stage (s+1) % 3; HALVES: of tile s, into s % 3). In the softmax phase, the longer of the two, a request
+  //         costs some 50 cycles, here ten (all in V(s): 2700 cycles a step, half and half 2500, all here 2400).
+  //   V(s): in the first step of an item (HALVES: the second), the output of the item before it; read the first V^T
+  //         operands of M(s+1); mask, online softmax -> P as bf16 B operands (VALU only); fetch the list entry of step
+  //         s+2; in the last step but one of an item request the query rows of the next item; wait for the K rows of
+  //         tile s+1
+  // The barrier after V(s) publishes the K rows of tile s+1 to the group, the one after M(s+1) the V^T rows that M(s)
+  // requested. A K stage is rewritten two steps after it was read, a V^T stage three steps after it was
+  // filled: by then every wave of the group has passed
   // the barrier that follows its last read. Every item has an even number of steps (SPB = 2 per key block),
   // so the position inside a key block and the K stage both follow from the parity of s, which the unrolled
   // loop knows.
@@ -633,16 +677,17 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  floatx16 sacc[C::KT];
-  u32x4 pb[C::PPC];           // probabilities as bf16 B operands, 16 keys per entry
+  floatx4 sacc[C::KT][2];     // (key tile, query tile)
+  u32x4 pb[C::PPC][2];        // probabilities as bf16 B operands: (32 keys, query tile)
   u32x4 pbn[2];               // (VH) those of the first half of a key block, while pb still holds the block before it
 #pragma unroll
-  for (int pc = 0; pc < C::PPC; ++pc) pb[pc] = u32x4{0u, 0u, 0u, 0u};
+  for (int pc = 0; pc < C::PPC; ++pc) pb[pc][0] = pb[pc][1] = u32x4{0u, 0u, 0u, 0u};
   pbn[0] = pbn[1] = u32x4{0u, 0u, 0u, 0u};
 
-  // M(s) is one fixed sequence of NPV + NQK MFMA slots: the P V product of step s-1, then K Q^T
-  // of step s. The A operand of a slot (16 bytes per lane of the V^T or K tile) is read from LDS W
-  // slots ahead of its MFMA into a ring of W registers, so that LDS latency stays behind MFMAs
+  // M(s) is one fixed sequence of NPV + NQK slots of two MFMAs: the P V product of step s-1, then K Q^T
+  // of step s. A slot takes one A operand (16 bytes per lane of the V^T or K tile) with the B operands of both query
+  // tiles, which change places from slot to slot, so that every instruction shares an operand with the one before it. The A
+  // operand is read from LDS W slots ahead of its MFMAs into a ring of W registers, so that LDS latency stays behind MFMAs
   // that already have their operands; the first W operands of a phase are read at the end of the
   // softmax phase before it. The order is pinned slot by slot.
   constexpr int NPV = C::PPC * C::PDT, NQK = C::KS * C::KT, NSLOT = NPV + NQK;
@@ -652,13 +697,12 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   bf16x8 ring[W];
 #pragma unroll
   for (int i = 0; i < W; ++i) ring[i] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-  int vst = 0;                // V^T ring stage of the current step (s % VSTAGES)
   const u32x4* vcur[C::PPC];  // vread[] moved to the V^T stage whose P V product comes next
 #pragma unroll
   for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc];
   auto read_v_operand = [&](int slot) __attribute__((always_inline)) {      // slot < NPV
     const int pc = slot / C::PDT, dt = slot % C::PDT;
-    ring[slot % W] = __builtin_bit_cast(bf16x8, vcur[pc][dt * 32 * C::VCPR]);
+    ring[slot % W] = __builtin_bit_cast(bf16x8, vcur[pc][dt * 16 * C::VCPR]);
   };
   // the operands of the first W slots, at the end of a softmax phase
   auto read_ahead = [&]() __attribute__((always_inline)) {
@@ -693,9 +737,15 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     constexpr bool do_qk = decltype(qkc)::value != 0, last_of_item = decltype(lastc)::value != 0;
     constexpr int PART_NEXT = (ST + 1) % C::SPB;
     constexpr int OPEN = PART_NEXT == 0 ? kOpenPieces : 0;
-    constexpr int DSLOT = OPEN + kStepPieces;         // the slot in which the requests for the next tile start
-    constexpr int MLOADS = SPLIT_LOADS ? C::KPW : LPS;   // requests of this phase: the K rows, or the whole tile
-    constexpr int LAST = do_qk ? NSLOT : NPV;         // slots that hold an MFMA
+    constexpr int MLOADS = LPS;                       // requests of this phase: K rows of step s+1, V^T rows of s+1 (VH: of step s)
+    constexpr int LAST = do_qk ? NSLOT : NPV;         // slots that hold MFMAs
+    // What goes between the MFMAs: the addresses of the tile of step s+1, then the requests. Whether that
+    // step opens a new key block (its list entry came in during V(s-1)) follows from the parity of s. A group whose last step this
+    // is requests the tile of its last list entry once more, into a stage nobody reads again.
+    constexpr int REQ = OPEN + kStepPieces, TASKS = do_qk ? REQ + MLOADS : 0;
+    constexpr int TPS = (TASKS + LAST - 1) / LAST;    // tasks per slot
+    // (requests of the four waves meet in the CU's one address unit, 16 cycles for each: with room for it, one in two or three slots)
+    constexpr int GAP = TPS > 1 || !do_qk ? 1 : (LAST - REQ) / MLOADS > 3 ? 3 : (LAST - REQ) / MLOADS;
     constexpr int WB = W / 2;                         // operands are waited for WB at a time
     Tile nt = {};
     // The wave that feeds the matrix pipe goes first wherever the two waves of a SIMD compete for an
@@ -703,6 +753,19 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // group run a fifth longer than those of the other.
     __builtin_amdgcn_s_setprio(3);
     __builtin_amdgcn_sched_barrier(0);
+    auto task = [&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value;
+      const int vnext = vst + 1 >= VSTAGES ? 0 : vst + 1;
+      if constexpr (k < OPEN) {
+        open_piece(kc, m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, last_of_item ? nxt_Kbytes : cur.Kbytes,
+                   last_of_item ? nxt_Vtbytes : cur.Vtbytes);
+      } else if constexpr (k < REQ) {
+        step_piece(IntC<k - OPEN>{}, nt, IntC<PART_NEXT>{}, (ST + 1) % KSTAGES, vnext);
+      } else if constexpr (k < TASKS) {
+        if constexpr (C::VH && k - REQ >= C::KPW) issue_load(vt_next, IntC<k - REQ>{});
+        else issue_load(nt, IntC<k - REQ>{});
+      }
+    };
     static_for<0, LAST>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
       // The operands of slots i .. i+WB-1 have arrived once at most the reads behind them are
@@ -713,22 +776,32 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         __builtin_amdgcn_s_waitcnt(0xC07F | (behind << 8));
         __builtin_amdgcn_sched_barrier(0);
       }
-      // one load of the tile of step s+1 per slot, behind the MFMA of the slot before
-      if constexpr (do_qk && i >= DSLOT && i - DSLOT < MLOADS) issue_load(nt, IntC<i - DSLOT>{});
-      if constexpr (i < NPV) {
-        constexpr int pc = i / C::PDT, dt = (C::VH ? ST * C::PDT : 0) + i % C::PDT;
-        // (VH: the first half of a block's probabilities is in pbn for the first product, in pb for the second)
-        const u32x4 p = C::VH && ST == 0 && pc < 2 ? pbn[pc % 2] : pb[pc];
-        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i % W], __builtin_bit_cast(bf16x8, p), oacc[dt], 0, 0, 0);
-      } else {
-        constexpr int q = i - NPV, k2 = q / C::KT, t = q % C::KT;
-        floatx16 c0 = sacc[t];
-        if constexpr (k2 == 0) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) c0[r] = 0.f;           // folds into the instruction's constant C operand
+      auto product = [&](auto fc) __attribute__((always_inline)) {
+        constexpr int f = decltype(fc)::value;
+        if constexpr (i < NPV) {
+          constexpr int pc = i / C::PDT, dt = (C::VH ? ST * C::PDT : 0) + i % C::PDT;
+          // (VH: the first half of a block's probabilities is in pbn for the first product, in pb for the second)
+          const u32x4 p = C::VH && ST == 0 && pc == 0 ? pbn[f] : pb[pc][f];
+          mfma_add(oacc[dt][f], ring[i % W], __builtin_bit_cast(bf16x8, p));
+        } else {
+          constexpr int q = i - NPV, k2 = q / C::KT, t = q % C::KT;
+          if constexpr (k2 == 0) mfma_first(sacc[t][f], ring[i % W], qreg[k2][f]);
+          else mfma_add(sacc[t][f], ring[i % W], qreg[k2][f]);
         }
-        sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i % W], qreg[k2], c0, 0, 0, 0);
+      };
+      product(IntC<i % 2>{});
+      if constexpr (TASKS > 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (GAP < 2) {
+          static_for<TPS * i, TPS * (i + 1)>(task);
+        } else if constexpr (i < REQ) {
+          task(ic);
+        } else {
+          if constexpr ((i - REQ) % GAP == 0) task(IntC<REQ + (i - REQ) / GAP>{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
+      product(IntC<1 - i % 2>{});
       // the ring entry this slot used takes the operand of slot i + W
       if constexpr (i + W < LAST) {
         constexpr int slot = i + W;
@@ -736,38 +809,18 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
           read_v_operand(slot);
         } else {
           constexpr int q = slot - NPV, k2 = q / C::KT, t = q % C::KT;
-          ring[slot % W] = __builtin_bit_cast(bf16x8, kread[k2][(ST % KSTAGES) * KBUF + t * 32 * C::KCPR]);
-        }
-      }
-      if constexpr (do_qk && i < OPEN + kStepPieces) {
-        // behind the first MFMAs, one piece each: addresses of the tile of step s+1. Whether that step opens a new key block
-        // (its list entry came in during V(s-1)) follows from the parity of s. A group whose last step this is
-        // requests the tile of its last list entry once more, into a stage nobody reads again.
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (i < OPEN) {
-          open_piece(ic, m_nxt_j >= 0 ? m_nxt_j : m_nxt_e, last_of_item ? nxt_Kbytes : cur.Kbytes,
-                     last_of_item ? nxt_Vtbytes : cur.Vtbytes);
-        } else {
-          step_piece(IntC<i - OPEN>{}, nt, IntC<PART_NEXT>{}, (ST + 1) % KSTAGES, vst + 1 >= VSTAGES ? 0 : vst + 1);
+          ring[slot % W] = __builtin_bit_cast(bf16x8, kread[k2][(ST % KSTAGES) * KBUF + (32 * (t / 2) + 8 * (t % 2)) * C::KCPR]);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    // a phase with fewer slots than loads sends the rest here
-    static_for<0, MLOADS>([&](auto ic) __attribute__((always_inline)) {
-      constexpr int idx = decltype(ic)::value;
-      if constexpr (do_qk && DSLOT + idx >= LAST) issue_load(nt, ic);
-    });
     if constexpr (do_qk) {
-      vt_next = nt;
+      if constexpr (C::VH) vt_next = nt;
       kvc_nxt = blk_count;
     }
-    if constexpr (SPLIT_LOADS && !(C::VH && do_qk)) {
-      // the V^T rows of this step (requested a phase ago, ahead of this phase's K rows) have landed
-      // (VH: not needed for another step, and the wait of the softmax phase covers them)
-      if (last_of_item && cur.ns > C::SPB) wait_loads_leaving<do_qk ? MLOADS + NREQ : 0>();
-      else wait_loads_leaving<do_qk ? MLOADS : 0>();
-    }
+    // the V^T rows requested in the MFMA phase before this one have landed: the softmax phase reads the first of them
+    if (last_of_item && cur.ns > C::SPB) wait_loads_leaving<do_qk ? MLOADS + NREQ : 0>();
+    else wait_loads_leaving<do_qk ? MLOADS : 0>();
   };
 
   // entry j of an item's list; a dense row: j itself
@@ -784,14 +837,17 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     constexpr bool output = decltype(outc)::value != 0;
     constexpr int FETCH = decltype(fetchc)::value;
     __builtin_amdgcn_s_setprio(0);
-    constexpr int VLOADS = SPLIT_LOADS ? C::VPW : 0;  // requests of this phase: the V^T rows of step s+1
+    constexpr int VLOADS = C::VPW;  // the last requests of M(s): V^T rows, which may still be out when this phase ends
     // The last step of an item asks for the entry of the item after the one after the next.
     Entry entry_new = {};
     bool more = false;
     if constexpr (C::VH && first_of_item) {
-      done_m = mref;
-      done_l = lpart;
-      mref = lpart = 0.f;
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        done_m[f] = mref[f];
+        done_l[f] = lpart[f];
+        mref[f] = lpart[f] = 0.f;
+      }
     }
     const bool had_output = have_output;
     if constexpr (C::VH && output) {               // (ahead of what the last step of an item of one key block asks for)
@@ -828,46 +884,90 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       m_nxt_j = hl ? -1 : span_first(follow ? nxt.span : cur.span) + j;
       fj += 1;
     }
-    if constexpr (SPLIT_LOADS && (C::VH || !output)) {
-      static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) {
-        issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{});
-      });
-    }
     // Step ns-2 of an item of two key blocks or more; an item of one block asks in its last phase instead (a request under a
     // condition in the first phase would leave the compiler with loads that may be pending on its way into the loop of steps,
     // and with a wait for them in every other step).
     constexpr bool requests = FETCH == 2 && !first_of_item;
-    if constexpr (requests) request_switch();
     // the first step of an item: the P V products of the item before it are complete
-    // (tile s+1 is waited for first: the loads of the output would otherwise be waited for together
-    // with it at the end of the phase, and so would the stores, which now complete under the next
-    // MFMA phase)
+    // (the K rows of tile s+1 are waited for first: at the end of the phase the stores would be waited for with them,
+    // which now complete under the next MFMA phase)
     if constexpr (!C::VH && output) {
       if (have_output) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
+        wait_loads_leaving<VLOADS>();
         write_output();
       }
-      if constexpr (SPLIT_LOADS) {
-        static_for<0, C::VPW>([&](auto ic) __attribute__((always_inline)) {
-          issue_load(vt_next, IntC<C::KPW + decltype(ic)::value>{});
-        });
-      }
     }
+    // the first V^T operands of M(s+1), from the stage of this step (VH: of the step before), published before the barrier
+    // that this phase began with
+    const int vst_read = !C::VH ? vst : vst == 0 ? VSTAGES - 1 : vst - 1;
+#pragma unroll
+    for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc] + vst_read * C::VBUF;
+    read_ahead();
+    __builtin_amdgcn_sched_barrier(0);
+    float rs[2];
+    // The scores go through in a line, the two query tiles together: multiplied and taken from the reference, two places on
+    // to the exponential, two further on to the sum and the conversion. Beside the other group's products the vector
+    // ALU takes two instructions (one exponential) for each of them, and an instruction whose operand has only just been asked
+    // for takes as long as two that wait for nothing (left to the compiler, which chained them: 150 cycles more).
+    auto probabilities = [&]() __attribute__((always_inline)) {
+      constexpr int NE = 16 * C::PC, LAG = 2;
+      float x[NE], p[NE];
+      uint32_t w[NE / 2];
+      static_for<0, NE / 2 + 2 * LAG>([&](auto ec) __attribute__((always_inline)) {
+        constexpr int e = 2 * decltype(ec)::value, E = e - 2 * LAG, A = e - 4 * LAG;
+        if constexpr (e < NE) {
+          constexpr int j = e / 16, i = e / 2 % 8;
+#pragma unroll
+          for (int f = 0; f < 2; ++f) x[e + f] = fmaf(sacc[2 * j + i / 4][f][i % 4], cs, -mref[f]);
+        }
+        if constexpr (E >= 0 && E < NE) {
+#pragma unroll
+          for (int f = 0; f < 2; ++f) p[E + f] = __builtin_amdgcn_exp2f(x[E + f]);
+        }
+        if constexpr (A >= 0) {
+          constexpr int j = A / 16, i = A / 2 % 8;
+#pragma unroll
+          for (int f = 0; f < 2; ++f) rs[f] = A == 0 ? p[f] : rs[f] + p[A + f];
+          if constexpr (i % 2 == 1) {
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              uint32_t u = pack_bf16x2(p[A - 2 + f], p[A + f]);
+              asm volatile("" : "+v"(u));          // (here, and not behind the branch that may want it otherwise)
+              w[8 * j + 4 * f + i / 2] = u;
+            }
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+#pragma unroll
+      for (int j = 0; j < C::PC; ++j)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+          const u32x4 v = {w[8 * j + 4 * f], w[8 * j + 4 * f + 1], w[8 * j + 4 * f + 2], w[8 * j + 4 * f + 3]};
+          if constexpr (!C::VH) pb[j][f] = v;
+          else if constexpr (ST == 0) pbn[f] = v;
+          else pb[1][f] = v;
+        }
+    };
     {
       const int kv_count = kvc_cur;
-      // accumulator register r of key tile t is key part*KVS + 32t + 8(r/4) + 4*hf + r%4 of the block
+      // (the first scores taken are those of tiles 0 and 1, whose last products four others followed where there are more tiles)
+      settle_products<(C::KT > 2 ? 1 : 8)>(sacc);
+      // accumulator register r of key tile t is key part*KVS + 32(t/2) + 8(t%2) + r + key_row(4*g4) of the block
       // (rare, like the branch below: out of line, the path that every step takes has no jump over it)
       if (__builtin_expect(kv_count < BLK, 0)) {
         // (constants against one lane-dependent bound: compared the other way round, the key numbers are 32 registers that
         // the compiler keeps through the whole loop)
-        const int valid = kv_count - (ST % C::SPB) * KVS - 4 * hf;
+        const int valid = kv_count - (ST % C::SPB) * KVS - key_row(4 * g4);
 #pragma unroll
         for (int t = 0; t < C::KT; ++t)
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (32 * t + 8 * (r / 4) + (r % 4) >= valid) sacc[t][r] = -INFINITY;
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (32 * (t / 2) + 8 * (t % 2) + r >= valid) sacc[t][f][r] = -INFINITY;
       }
-      // ---- online softmax, one query column per lane ---------------------------------
+      // ---- online softmax, two query columns per lane, one of each query tile ---------------------------------
       // Scores are counted in binades (score * scale * log2 e) from a reference that starts at 0 for
       // every item and moves rarely: fp32 sums and bf16 operands span 2^+-126, so probabilities may
       // sit anywhere within 2^+-kLazyBits of one another's scale. No maximum is taken on the way: the
@@ -876,90 +976,73 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       // them below it, too) is the step done again the long way -- the scores are still in registers
       // -- with the row maximum as the new reference and everything gathered so far rescaled.
       if constexpr (C::VH && ST == 0) {
-        pb[0] = pbn[0];
-        pb[1] = pbn[1];
+        pb[0][0] = pbn[0];
+        pb[0][1] = pbn[1];
       }
-      auto probabilities = [&]() __attribute__((always_inline)) {
-        float sum = 0.f;
-#pragma unroll
-        for (int t = 0; t < C::KT; ++t) {
-          float p[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(sacc[t][r], cs, -mref));
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            u32x4 w;
-            w.x = pack_bf16x2(p[8 * u + 0], p[8 * u + 1]);
-            w.y = pack_bf16x2(p[8 * u + 2], p[8 * u + 3]);
-            w.z = pack_bf16x2(p[8 * u + 4], p[8 * u + 5]);
-            w.w = pack_bf16x2(p[8 * u + 6], p[8 * u + 7]);
-            if constexpr (!C::VH) pb[2 * t + u] = w;
-            else if constexpr (ST == 0) pbn[u] = w;
-            else pb[2 + u] = w;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sum += p[8 * u + i];
-          }
-        }
-        return sum;
-      };
-      float rs = probabilities();
-      bool outside = rs > kAbove;
-      if constexpr (first_of_item) outside = outside || rs < kBelow;
+      probabilities();
+      float largest;             // (fmaxf would put two more instructions into this chain, to quiet signalling NaNs)
+      asm("v_max_f32 %0, %1, %2" : "=v"(largest) : "v"(rs[0]), "v"(rs[1]));
+      bool outside = largest > kAbove;
+      if constexpr (first_of_item) outside = outside || rs[0] < kBelow || rs[1] < kBelow;
       if (__builtin_expect(__any(outside), 0)) {
-        float mx = -INFINITY;
 #pragma unroll
-        for (int t = 0; t < C::KT; ++t)
+        for (int f = 0; f < 2; ++f) {
+          float mx = -INFINITY;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[t][r]);
-        mx = half_wave_max(mx) * cs;                   // the scale is positive
-        if constexpr (C::VH) mx = ceilf(mx);           // probabilities that wait are rescaled as they are: by powers of two
-        if constexpr (first_of_item) {
-          // Accumulators and row sum are empty: nothing to rescale. Scores that are all -inf (keys that mask
-          // themselves) must not become the reference, -inf - -inf is no number: below the lowest finite one their
-          // probabilities are 0, and the first finite score leaves the window and brings its own reference.
-          mref = fmaxf(mx, -3.4028234663852886e38f);
-        } else {
-          const float mnew = fmaxf(mref, mx);
-          const float alpha = __builtin_amdgcn_exp2f(mref - mnew);
-          const float before = mref;
-          mref = mnew;
-          lpart *= alpha;
-          if constexpr (!(C::VH && output && !last_of_item)) {     // (there they have just been emptied)
+          for (int t = 0; t < C::KT; ++t)
 #pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt)
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sacc[t][f][r]);
+          mx = column_max(mx) * cs;                      // the scale is positive
+          if constexpr (C::VH) mx = ceilf(mx);           // probabilities that wait are rescaled as they are: by powers of two
+          if constexpr (first_of_item) {
+            // Accumulators and row sum are empty: nothing to rescale. Scores that are all -inf (keys that mask
+            // themselves) must not become the reference, -inf - -inf is no number: below the lowest finite one their
+            // probabilities are 0, and the first finite score leaves the window and brings its own reference.
+            mref[f] = fmaxf(mx, -3.4028234663852886e38f);
+          } else {
+            const float mnew = fmaxf(mref[f], mx);
+            const float alpha = __builtin_amdgcn_exp2f(mref[f] - mnew);
+            const float before = mref[f];
+            mref[f] = mnew;
+            lpart[f] *= alpha;
+            if constexpr (!(C::VH && output && !last_of_item)) {     // (there they have just been emptied)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
-          }
-          if constexpr (C::VH) {
-            const uint32_t up = (uint32_t)fminf(mref - before, 255.f);
-            static_for<0, (ST == 1 ? 2 : C::PPC)>([&](auto kc) __attribute__((always_inline)) {
-              constexpr int pc = decltype(kc)::value;
-              if constexpr (ST == 1) {
-                u32x4 w = scaled(pbn[pc], up);
-                asm volatile("" : "+v"(w));      // (or the accumulators are copied between registers in every MFMA phase)
-                pbn[pc] = w;
-              } else {
-                pb[pc] = scaled(pb[pc], up);
+              for (int dt = 0; dt < C::DT; ++dt) {
+                floatx4 o = oacc[dt][f];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] *= alpha;
+                asm volatile("" : "+v"(o));      // (or the accumulators are copied between registers in every phase)
+                oacc[dt][f] = o;
               }
-            });
+            }
+            if constexpr (C::VH) {
+              const uint32_t up = (uint32_t)fminf(mref[f] - before, 255.f);
+              if constexpr (ST == 1) {
+                u32x4 w = scaled(pbn[f], up);
+                asm volatile("" : "+v"(w));      // (or the accumulators are copied between registers in every MFMA phase)
+                pbn[f] = w;
+              } else {
+#pragma unroll
+                for (int pc = 0; pc < C::PPC; ++pc) pb[pc][f] = scaled(pb[pc][f], up);
+              }
+            }
           }
         }
-        rs = probabilities();
+        probabilities();
       }
-      lpart += rs;
+      lpart[0] += rs[0];
+      lpart[1] += rs[1];
     }
+    if constexpr (requests) request_switch();
     kvc_cur = kvc_nxt;
     // the probabilities are complete here: nothing of the softmax may sink behind the barrier
     // into the MFMA phase, where it would take the other group's VALU time
 #pragma unroll
-    for (int pc = 0; pc < C::PPC; ++pc) asm volatile("" : "+v"(pb[pc]));
+    for (int pc = 0; pc < C::PPC; ++pc) asm volatile("" : "+v"(pb[pc][0]), "+v"(pb[pc][1]));
     if constexpr (C::VH) asm volatile("" : "+v"(pbn[0]), "+v"(pbn[1]));
-    asm volatile("" : "+v"(lpart), "+v"(mref));
-    // the first V^T operands of M(s+1), from the stage of this step (published a whole step ago; VH: of the step before)
-    const int vst_read = !C::VH ? vst : vst == 0 ? VSTAGES - 1 : vst - 1;
-#pragma unroll
-    for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc] + vst_read * C::VBUF;
-    read_ahead();
+    // (the list entry is waited for here, where nothing else is under way, and not in M(s+1) together with its operands)
+    if constexpr (FETCH != 0) asm volatile("" : "+s"(m_nxt_e));
+    asm volatile("" : "+v"(lpart[0]), "+v"(mref[0]), "+v"(lpart[1]), "+v"(mref[1]));
     vst = vst + 1 >= VSTAGES ? 0 : vst + 1;
     if constexpr (last_of_item) {
       // the item has ended: its output waits for the last P V product; the next item takes its place
@@ -979,15 +1062,17 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
         k_next += 1;
       }
     }
-    // tile s+1 has landed (this wave's share; the barrier that follows covers the group; loads return in order: only this
-    // phase's own requests may still be out)
-    constexpr int LEAVING = VLOADS + (requests ? NREQ : 0);
+    // the K rows of tile s+1 have landed (this wave's share; the barrier that follows covers the group; loads return in order:
+    // only the V^T rows behind them and this phase's own requests may still be out)
+    // (VH: behind the last step of all there is no other phase to wait for its V^T rows)
+    constexpr int LEAVING = C::VH && last_of_item ? 0 : VLOADS + (requests ? NREQ : 0);
     if constexpr (output) {
       if (!had_output) wait_loads_leaving<LEAVING>();
     } else {
       wait_loads_leaving<LEAVING>();
     }
     if constexpr (last_of_item) settle_switch();
+    group_barrier();
   };
 
   const bool active = n_my_items > 0;
@@ -1002,12 +1087,13 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     const int m0 = list_entry(cur, 0);
     static_for<0, kOpenPieces>([&](auto pc) __attribute__((always_inline)) { open_piece(pc, m0, cur.Kbytes, cur.Vtbytes); });
     static_for<0, kStepPieces>([&](auto pc) __attribute__((always_inline)) { step_piece(pc, t0, IntC<0>{}, 0, 0); });
-    static_for<0, LPS>([&](auto ic) __attribute__((always_inline)) { issue_load(t0, ic); });
+    static_for<0, (C::VH ? C::KPW : LPS)>([&](auto ic) __attribute__((always_inline)) { issue_load(t0, ic); });
+    if constexpr (C::VH) vt_next = t0;
     // The compiler does not see the direct-to-LDS loads: it has to place its wait for Q here, not at the first use inside
     // the loop, where it would be a wait for every load outstanding.
     __builtin_amdgcn_s_waitcnt(0x0F70);
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+    for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : "+v"(qreg[ks][0]), "+v"(qreg[ks][1]));
     kvc_cur = blk_count;
     fj = 1;
     // The first MFMA phase (VH: the first two) multiplies the (zero) probabilities of a step that does not exist with
@@ -1038,36 +1124,30 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       m_phase(IntC<0>{}, Y{}, N{});
       group_barrier();
       v_phase(IntC<0>{}, Y{}, IntC<C::VH ? 0 : 1>{}, IntC<2>{}, N{});
-      group_barrier();
       if constexpr (C::VH) {
         if (ns >= 4) {
           // step 1 writes the output of the item before
           m_phase(IntC<1>{}, Y{}, N{});
           group_barrier();
           v_phase(IntC<1>{}, N{}, Y{}, IntC<0>{}, N{});
-          group_barrier();
           // steps 2 .. ns-3 in pairs
           for (int sj = 2; sj + 2 < ns; sj += 2) {
             m_phase(IntC<0>{}, Y{}, N{});
             group_barrier();
             v_phase(IntC<0>{}, N{}, N{}, IntC<1>{}, N{});
-            group_barrier();
             m_phase(IntC<1>{}, Y{}, N{});
             group_barrier();
             v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, N{});
-            group_barrier();
           }
           // step ns-2 fetches the first list entry of the next item
           m_phase(IntC<0>{}, Y{}, N{});
           group_barrier();
           v_phase(IntC<0>{}, N{}, N{}, IntC<2>{}, N{});
-          group_barrier();
         }
         // step ns-1 (of an item of one key block: step 1, with the output of the item before)
         m_phase(IntC<1>{}, Y{}, Y{});
         group_barrier();
         v_phase(IntC<1>{}, N{}, Y{}, IntC<0>{}, Y{});
-        group_barrier();
       } else {
         if (ns >= 4) {
           // steps 1 .. ns-4 in pairs: nothing but this item's own list and tiles
@@ -1075,42 +1155,40 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
             m_phase(IntC<1>{}, Y{}, N{});
             group_barrier();
             v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, N{});
-            group_barrier();
             m_phase(IntC<0>{}, Y{}, N{});
             group_barrier();
             v_phase(IntC<0>{}, N{}, N{}, IntC<1>{}, N{});
-            group_barrier();
           }
           // steps ns-3 and ns-2: the latter fetches the first list entry of the next item
           m_phase(IntC<1>{}, Y{}, N{});
           group_barrier();
           v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, N{});
-          group_barrier();
           m_phase(IntC<0>{}, Y{}, N{});
           group_barrier();
           v_phase(IntC<0>{}, N{}, N{}, IntC<2>{}, N{});
-          group_barrier();
         }
         // step ns-1
         m_phase(IntC<1>{}, Y{}, Y{});
         group_barrier();
         v_phase(IntC<1>{}, N{}, N{}, IntC<0>{}, Y{});
-        group_barrier();
       }
       s += ns;
     }
     m_phase(IntC<0>{}, N{}, N{});
     if constexpr (C::VH) {
       // the second half of the channels (its V^T tile was published a step ago)
-      pb[0] = pbn[0];
-      pb[1] = pbn[1];
+      pb[0][0] = pbn[0];
+      pb[0][1] = pbn[1];
       const int vst_read = vst == 0 ? VSTAGES - 1 : vst - 1;
 #pragma unroll
       for (int pc = 0; pc < C::PPC; ++pc) vcur[pc] = vread[pc] + vst_read * C::VBUF;
       read_ahead();
       m_phase(IntC<1>{}, N{}, N{});
-      done_m = mref;
-      done_l = lpart;
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        done_m[f] = mref[f];
+        done_l[f] = lpart[f];
+      }
     }
     group_barrier();
     __builtin_amdgcn_s_setprio(0);
