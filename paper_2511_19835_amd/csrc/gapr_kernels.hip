@@ -237,10 +237,12 @@ constexpr int kDevCols = 32 * kDevWaves;         // pooled vectors of an iterati
 // clear whatever DA is. The query side (GATE) lists the key blocks with |S| > DB first (44 to 63 % of them on smooth
 // clips) and multiplies those only, gathering their vectors out of the operand layout; the bits are the same. For
 // that the key side leaves DB as [N][M], rows that the query side reads whole, ahead of its product. A workgroup
-// takes 128 token rows (two blocks of 64: half the operand traffic per row, one list for both), two row tiles at a
+// takes 128 token rows (two blocks of 64: half the operand traffic per row, one list for both), 64 of them at a
 // time and one register set for the other operand, reloaded as it is used up: four waves per SIMD on the key side,
-// three on the query side.
-// Both launches together, against the pair of launches above (us): 24 heads of 931 blocks 1256 -> 1129, 40 heads of
+// three on the query side. The products are of 16 x 16 x 32: those of 32 x 32 x 16 draw more power for the same work, and
+// the clock is what power leaves. Key side and query side, us, products of 32 and of 16: 24 heads of 931 blocks 678 -> 590
+// and 495 -> 466, 24 of 1182 blocks of 64 578 -> 500 and 543 -> 498.
+// Both launches together, against the pair of launches above (us; both with products of 32 x 32 x 16): 24 heads of 931 blocks 1256 -> 1129, 40 heads of
 // 591 916 -> 836, 24 heads of 1182 blocks of 64 1306 -> 1093, 3 heads of 931 174 -> 158. Building the list costs a
 // workgroup about 3 us, which short rows do not earn back (24 heads of 516 blocks 437 -> 466, 2 of 17 7.2 -> 10.0) and
 // a single round of workgroups cannot hide (3 heads of 636 blocks of 64: no gain): hence the two conditions.
@@ -263,10 +265,10 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
                                                           const float* __restrict__ DB,
                                                           uint32_t* __restrict__ Mc_bits, ScoreArgs text, int text_wgs) {
   constexpr int NT = kDevThreads, NW = kDevWaves;
-  constexpr int MT = kDevRows / 32, KS = D / 16, CPR = D / 8;
+  constexpr int KS = D / 32, CPR = D / 8;        // k-steps of 32 channels
   constexpr int RB = kDevRows / BLK;             // token blocks of the workgroup
-  constexpr int TB = BLK / 32;                   // row tiles of a token block
-  constexpr int TP = 2;                          // row tiles of a pass over the k-steps (a block has 2 or 4)
+  constexpr int NPASS = kDevRows / 64;           // passes over the k-steps, of four row tiles each
+  constexpr int PB_ROWS = BLK / 64;              // passes of a token block
   constexpr int RPP = NT / CPR;                  // rows staged per pass of the workgroup
   constexpr int NP = kDevRows / RPP, PB_ = BLK / RPP;   // passes in all and of one token block
   constexpr int LU = 4 / RB;                     // chunks of 64 key blocks whose scores and deviations a wave asks for at a time
@@ -285,15 +287,15 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
   const int xb0 = (item % groups_x) * RB, bh = item / groups_x;
   const int b = bh / dm.heads, h = bh % dm.heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int l32 = lane % 32, hf = lane / 32;
+  const int l16 = lane % 16, q = lane / 16;
   const uint16_t* Xb = X + (int64_t)b * dm.sb + (int64_t)h * dm.sh;
   int count[RB];                                 // rows of each token block (0: the block does not exist)
 #pragma unroll
   for (int k = 0; k < RB; ++k) count[k] = xb0 + k < n_blocks_x ? dm.block_count(xb0 + k) : 0;
 
   // Pooled vectors of the other side: fp16, in the layout of gate_operand_offset: of 32 consecutive vectors
-  // one k-step is 1 KB in a row, 16 bytes per lane
-  const uint16_t* PBh = PB + (size_t)bh * gate_operand_vectors(n_other) * D + 256 * hf;
+  // eight channels are 512 bytes in a row, those of 16 vectors two whole lines
+  const uint16_t* PBh = PB + (size_t)bh * gate_operand_vectors(n_other) * D + 256 * q;
 
   // ---- stage the centred block: thread -> chunk column tid % CPR, rows tid / CPR + RPP*i ----
   const int cc = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
@@ -406,8 +408,8 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
     }
   }
   __syncthreads();
-  const u32x4* arow = atile + l32 * CPR;
-  const int akey = (l32 / (16 / CPR)) & (CPR - 1);     // (the same for every row tile: 32 rows are whole periods of the key)
+  const u32x4* arow = atile + l16 * CPR;
+  const int akey = (l16 / (16 / CPR)) & (CPR - 1);     // (the same for every row tile: 16 rows are whole periods of the key)
 
   float outscale[RB];
 #pragma unroll
@@ -424,26 +426,40 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
     if (!GATE) return j;
     return (int)list[j < seg1 ? j : j < seg2 ? j - seg1 + range : j < seg3 ? j - seg2 + 2 * range : j - seg3 + 3 * range];
   };
-  // the B operand of an iteration: lane (l32, hf) supplies channels 16s + 8hf .. +7 of column o0 + l32 in k-step s
-  auto vector_of = [&](int o0) __attribute__((always_inline)) {
-    const int m = block_of(o0 + l32);
-    return PBh + (size_t)(m / 32) * (KS * 512) + (m % 32) * 8;
-  };
-  u32x4 bv[KS];
-  u32x4 av[2][TP];
-  auto load_a = [&](int set, int step) __attribute__((always_inline)) {        // step: pass * KS + k-step
-    const u32x4* p = arow + ((2 * (step % KS) + hf) ^ akey) + (step / KS) * (TP * 32 * CPR);
+  // The B operands of an iteration are two column tiles of 16: lane (l16, q) supplies channels 32s + 8q .. +7 of columns
+  // o0 + l16 and o0 + 16 + l16 in k-step s.
+  const uint16_t* pv[2];
+  auto find_vectors = [&](int o0) __attribute__((always_inline)) {
+    if constexpr (GATE) {
 #pragma unroll
-    for (int t = 0; t < TP; ++t) av[set][t] = p[t * 32 * CPR];
+      for (int c = 0; c < 2; ++c) {
+        const int m = block_of(o0 + 16 * c + l16);
+        pv[c] = PBh + (size_t)(m / 32) * (KS * 1024) + (m % 32) * 8;
+      }
+    } else {                                       // (vectors past the end of the last 32 are padding: they feed columns that are not stored)
+      pv[0] = PBh + (size_t)(o0 / 32) * (KS * 1024) + l16 * 8;
+      pv[1] = pv[0] + 16 * 8;
+    }
   };
-  // 32 columns of the wave against the 128 rows, TP row tiles at a time. The A operand (rows) of a k-step is read
-  // from LDS a k-step ahead; a register of B is reloaded for the next iteration as soon as its last k-step is done.
+  u32x4 bv[KS][2];
+  u32x4 av[2][2];
+  auto load_vectors = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) bv[s][c] = *reinterpret_cast<const u32x4*>(pv[c] + 1024 * s);
+  };
+  // half steps: two of the four row tiles of a pass
+  auto load_a = [&](int set, int half_step) __attribute__((always_inline)) {   // half_step: (pass * KS + k-step) * 2 + half
+    const int s = half_step / 2 % KS, tile = half_step / 2 / KS * 4 + half_step % 2 * 2;
+    const u32x4* p = arow + ((4 * s + q) ^ akey) + tile * (16 * CPR);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) av[set][t] = p[t * 16 * CPR];
+  };
+  // 32 columns of the wave against the 128 rows, 64 rows at a time. The A operand (rows) is read from LDS half a k-step
+  // ahead; the registers of B are reloaded for the next iteration as soon as their last product is issued.
   auto iteration = [&](int o0, auto morec) __attribute__((always_inline)) {
     constexpr bool more = decltype(morec)::value != 0;
-    constexpr int NPASS = MT / TP;
-    const uint16_t* pn = nullptr;
-    if constexpr (more) pn = vector_of(o0 + kDevCols);
-    const int j = o0 + l32;                        // this lane's column
+    if constexpr (more) find_vectors(o0 + kDevCols);
+    const int j = o0 + lane % 32;                  // the column that this lane decides or stores
     int m = 0;
     float s_val[RB], db_val[RB];
     if constexpr (GATE) {
@@ -455,56 +471,62 @@ __global__ __launch_bounds__(kDevThreads, GATE ? 3 : 4) void deviation_long_kern
         db_val[k] = DBrow[(size_t)kk * n_other + m];
       }
     }
-    float dv4[4];                                  // four partial sums: no long chain of dependent adds
+    float dv[2][2];                                // two partial sums per column tile: no long chain of dependent adds
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
-      floatx16 acc[TP];
+      floatx4 acc[4][2];
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        asm volatile("" ::: "memory");      // the A operand is re-read every iteration: no hoisting into registers
-        load_a((pass * KS + s + 1) % 2, (pass * KS + s + 1) % (NPASS * KS));
 #pragma unroll
-        for (int t = 0; t < TP; ++t) {
-          floatx16 c0 = acc[t];
-          if (s == 0) {
+        for (int half = 0; half < 2; ++half) {
+          const int hs = (pass * KS + s) * 2 + half;
+          asm volatile("" ::: "memory");      // the A operand is re-read every iteration: no hoisting into registers
+          load_a((hs + 1) % 2, (hs + 1) % (NPASS * KS * 2));
 #pragma unroll
-            for (int r = 0; r < 16; ++r) c0[r] = 0.f;
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              floatx4 c0 = acc[2 * half + t][c];
+              if (s == 0) c0 = floatx4{0.f, 0.f, 0.f, 0.f};
+              acc[2 * half + t][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, av[hs % 2][t]),
+                                                                            __builtin_bit_cast(halfx8, bv[s][c]), c0, 0, 0, 0);
+            }
+          if constexpr (more) {
+            if (pass == NPASS - 1 && half == 1) load_vectors(s);
           }
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, av[(pass * KS + s) % 2][t]),
-                                                          __builtin_bit_cast(halfx8, bv[s]), c0, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (more) {
-          if (pass == NPASS - 1) bv[s] = *reinterpret_cast<const u32x4*>(pn + 512 * s);
-        }
-        __builtin_amdgcn_sched_barrier(0);
       }
-      // every accumulator of a lane belongs to its column; its rows are spread over the registers, the row
-      // tiles of the block and the two half-waves
+      // every accumulator of a lane belongs to column l16 of its tile; the rows are spread over the registers, the row
+      // tiles of the block and the four quarters of the wave
 #pragma unroll
-      for (int t = 0; t < TP; ++t) {
-        const int tile = pass * TP + t;
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) dv4[r % 4] = (tile % TB == 0 && r < 4 ? 0.f : dv4[r % 4]) + fabsf(acc[t][r]);
-        if (tile % TB == TB - 1) {
-          const int k = tile / TB;
-          float dv = (dv4[0] + dv4[1]) + (dv4[2] + dv4[3]);
-          dv += __shfl_xor(dv, 32);
-          if constexpr (GATE) {
-            if (hf == 0 && j < n_cols && fabsf(s_val[k]) > dv * outscale[k] + db_val[k]) atomicOr(&words[k][m / 32], 1u << (m % 32));
-          } else {
-            // transposed, [N][M]: the query side reads whole rows. The stores are 4 bytes each, but the key blocks of
-            // a line are neighbours and meet in the L2 of their XCD.
-            if (hf == 0 && j < n_cols && count[k] > 0) out[((size_t)bh * n_other + j) * n_blocks_x + xb0 + k] = dv * outscale[k];
-          }
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            dv[c][r % 2] = (pass % PB_ROWS == 0 && t == 0 && r < 2 ? 0.f : dv[c][r % 2]) + fabsf(acc[t][c][r]);
+      if (pass % PB_ROWS == PB_ROWS - 1) {
+        const int k = pass / PB_ROWS;
+        // odd quarters finish the second column tile, even ones the first: lanes 0 to 31 hold the 32 columns
+        const float d0 = dv[0][0] + dv[0][1], d1 = dv[1][0] + dv[1][1];
+        float d = (q & 1 ? d1 : d0) + __shfl_xor(q & 1 ? d0 : d1, 16);
+        d += __shfl_xor(d, 32);
+        if constexpr (GATE) {
+          if (lane < 32 && j < n_cols && fabsf(s_val[k]) > d * outscale[k] + db_val[k]) atomicOr(&words[k][m / 32], 1u << (m % 32));
+        } else {
+          // transposed, [N][M]: the query side reads whole rows. The stores are 4 bytes each, but the key blocks of
+          // a line are neighbours and meet in the L2 of their XCD.
+          if (lane < 32 && j < n_cols && count[k] > 0) out[((size_t)bh * n_other + j) * n_blocks_x + xb0 + k] = d * outscale[k];
         }
       }
     }
   };
   int o0 = 32 * wave;
   if (o0 < n_cols) {
-    const uint16_t* p = vector_of(o0);
+    find_vectors(o0);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) bv[s] = *reinterpret_cast<const u32x4*>(p + 512 * s);
+    for (int s = 0; s < KS; ++s) load_vectors(s);
     load_a(0, 0);
     for (; o0 + kDevCols < n_cols; o0 += kDevCols) iteration(o0, std::integral_constant<int, 1>{});
     iteration(o0, std::integral_constant<int, 0>{});
