@@ -18,18 +18,23 @@ namespace {
 // N = channel, k = key block: the lower half-wave takes blocks 8u .. 8u+3 of a run of eight, the
 // upper one 8u+4 .. 8u+7, both operands alike). Blocks past the end of the row carry weight 0.
 // v^pool of a head is read once per workgroup (from L2) instead of once per compensated pair.
+// Four workgroups fit a CU (40 KB of LDS, 97 registers): 24 heads of 1182 blocks 154 -> 121 us against three.
 constexpr int kCompChunk = 64;                   // key blocks per pass
-constexpr int kCompStride = kCompChunk + 4;      // floats per row of the weight tile (16-byte rows, spread over the banks)
 template <int D>
-constexpr unsigned comp_lds_bytes() { return (32 * kCompStride + kCompChunk * D) * 4; }
+constexpr unsigned comp_lds_bytes() { return (32 * kCompChunk + kCompChunk * D) * 4; }
+// 16-byte chunk c of row r of the weight tile sits at chunk position c ^ r % 16: sixteen rows read at one chunk index touch
+// every bank once. (Padded rows did too, but then only three workgroups fit a CU: 24 heads of 1182 blocks, 888 workgroups,
+// took a second round on 768 places.)
+__device__ __forceinline__ int comp_weight_at(int r, int c) { return r * kCompChunk + 4 * (c ^ (r & 15)); }
+static_assert(kCompChunk == 64, "sixteen chunks to a row");
 
 template <int D>
 __device__ __forceinline__ void compensate_tile(const Dims& dm, const AttnArgs& a, int n0, int bh, uint32_t* lds) {
-  constexpr int MC = kCompChunk, AS = kCompStride;
+  constexpr int MC = kCompChunk;
   constexpr int CT = D / 32;                     // channel tiles = waves with matrix work
   constexpr int VL = MC * D / 4 / 256;           // 16-byte loads of v^pool per thread and pass
-  float* wt = reinterpret_cast<float*>(lds);     // [32][AS]
-  float* vt = wt + 32 * AS;                      // [MC][D]
+  float* wt = reinterpret_cast<float*>(lds);     // [32][MC], comp_weight_at
+  float* vt = wt + 32 * MC;                      // [MC][D]
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, l32 = lane % 32, hf = lane / 32;
   const float* Vp = a.Vp + (size_t)bh * dm.m * D;
@@ -76,8 +81,8 @@ __device__ __forceinline__ void compensate_tile(const Dims& dm, const AttnArgs& 
     __syncthreads();                             // the tiles of the pass before have been read
 #pragma unroll
     for (int e = 0; e < 8; ++e) w[e] = ((on >> e) & 1u) ? w[e] : 0.f;
-    *reinterpret_cast<floatx4*>(wt + wr * AS + wc) = floatx4{w[0], w[1], w[2], w[3]};
-    *reinterpret_cast<floatx4*>(wt + wr * AS + wc + 4) = floatx4{w[4], w[5], w[6], w[7]};
+    *reinterpret_cast<floatx4*>(wt + comp_weight_at(wr, wc / 4)) = floatx4{w[0], w[1], w[2], w[3]};
+    *reinterpret_cast<floatx4*>(wt + comp_weight_at(wr, wc / 4 + 1)) = floatx4{w[4], w[5], w[6], w[7]};
 #pragma unroll
     for (int i = 0; i < VL; ++i) {
       const int idx = tid + 256 * i;
@@ -88,7 +93,7 @@ __device__ __forceinline__ void compensate_tile(const Dims& dm, const AttnArgs& 
     if (wave < CT) {
 #pragma unroll
       for (int u = 0; u < MC / 8; ++u) {
-        const floatx4 a4 = *reinterpret_cast<const floatx4*>(wt + l32 * AS + 8 * u + 4 * hf);
+        const floatx4 a4 = *reinterpret_cast<const floatx4*>(wt + comp_weight_at(l32, 2 * u + hf));
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4[e], vt[(8 * u + 4 * hf + e) * D + 32 * wave + l32], acc, 0, 0, 0);
