@@ -14,13 +14,16 @@
 // launch pools it as well: the only pass over K of the whole preparation), centred on its
 // pooled vector (x_i - x^pool, fp32 subtraction, rounded to fp16) and parked in LDS; every
 // wave then walks the pooled vectors of the other side 32 at a time against the whole centred
-// block (the MFMA A operand, read from LDS just ahead of each MFMA), so the accumulators hold
-// the deviations themselves and the epilogue is one |.|-add per element. Three waves per SIMD.
+// block (the MFMA A operand, read from LDS half a k-step ahead), so the accumulators hold
+// the deviations themselves and the epilogue is one |.|-add per element. Four waves per SIMD.
 // The key side runs first and leaves DB transposed ([M][N]) in the workspace; the query side runs second
 // and never stores DA: it decides the bits of M_c from its registers, S[n][m] and DBt[m][n]. Many long rows take
-// deviation_long_kernel instead (below). Measured with 24 heads of 931 blocks, before those went there: 0.64 ms per side,
-// 0.52 ms with the pooled-operand loads switched off (they are 8 KB from L2 per 32 MFMAs and wave), 0.36 ms of MFMA time at
-// the clock the chip holds; a resident copy of the block in registers at two waves per SIMD: 0.65. The pooled operand is rounded to
+// deviation_long_kernel instead (below). What bounds it is the latency of its operands beside matrix work at the clock
+// that power leaves: products of 16 x 16 x 32 (less power than 32 x 32 x 16), and one register set for the pooled operand, reloaded
+// as it is used up, so that four waves fit a SIMD (two sets, a whole iteration ahead, three waves: 219 and 225 us where
+// one takes 208 and 211). Against products of 32 x 32 x 16 with two sets, key side and query side, us: 24 heads of 516 blocks 224 -> 208
+// and 229 -> 211, 24 of 159 45 -> 44 and 40 -> 39, d = 64 24.4 -> 24.1 and 20.4 -> 19.5; 24 of 317 blocks of 64 equal (67 -> 66 and 66 ->
+// 70, the runs differ by 3). The pooled operand is rounded to
 // fp16 as well; accumulation is fp32. fp16 rather than bf16 because both operands are O(1)
 // quantities whose 2^-12 relative rounding leaves DA / DB within 2e-4 relative of fp64
 // arithmetic (bf16 operands: up to 1.5e-3, wider than the 1e-3 band in which the gate may
@@ -44,7 +47,7 @@ template <int CPR>
 __device__ __forceinline__ int swizzled(int r, int c) { return r * CPR + (c ^ ((r / (16 / CPR)) & (CPR - 1))); }
 
 #ifndef RSA_DEV_OCC
-#define RSA_DEV_OCC 3
+#define RSA_DEV_OCC 4
 #endif
 // The first workgroups of a key-side launch, `text_wgs` for every (batch, head), make the text log-masses (they need
 // the pooled queries, like this launch, and the implicit attention that follows needs them). Counts them off `wg`.
@@ -76,7 +79,7 @@ __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, con
                                                            const float* __restrict__ Spool,
                                                            const float* __restrict__ DBt,
                                                            uint32_t* __restrict__ Mc_bits, ScoreArgs text, int text_wgs) {
-  constexpr int MT = BLK / 32, KS = D / 16, CPR = D / 8;
+  constexpr int MT = BLK / 16, KS = D / 32, CPR = D / 8;   // row tiles of 16, k-steps of 32 channels
   constexpr int NW = NT / 64;                    // waves per workgroup
   constexpr int RPP = NT / CPR;                  // rows staged per pass of the workgroup
   __shared__ u32x4 atile[BLK * CPR];
@@ -94,7 +97,7 @@ __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, con
   const int xb = item % n_blocks_x, bh = item / n_blocks_x;
   const int b = bh / dm.heads, h = bh % dm.heads;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int l32 = lane % 32, hf = lane / 32;
+  const int l16 = lane % 16, q = lane / 16;
   const int count = dm.block_count(xb);
   const int64_t t0 = dm.block_start(xb);
   const uint16_t* Xb = X + (int64_t)b * dm.sb + (int64_t)h * dm.sh;
@@ -155,75 +158,97 @@ __global__ __launch_bounds__(NT, RSA_DEV_OCC) void deviation_kernel(Dims dm, con
     }
   }
   __syncthreads();
-  // the A operand of an MFMA is read from LDS just ahead of it: the registers that a resident copy
-  // of the block would take (128 at d = 128) buy a third wave per SIMD instead
-  const u32x4* arow[MT];
-#pragma unroll
-  for (int t = 0; t < MT; ++t) arow[t] = atile + (32 * t + l32) * CPR;
-  const int akey = (l32 / (16 / CPR)) & (CPR - 1);
-#define RSA_DEV_A(t, s) __builtin_bit_cast(halfx8, arow[t][(2 * (s) + hf) ^ akey])
+  const u32x4* arow = atile + l16 * CPR;
+  const int akey = (l16 / (16 / CPR)) & (CPR - 1);     // (the same for every row tile: 16 rows are whole periods of the key)
 
   const float outscale = dm.scale / (float)count;
   float* orow = out + ((size_t)bh * n_blocks_x + xb) * n_other;
-  // pooled vectors of the other side, fp16, in the layout of gate_operand_offset: the 32 vectors
-  // of one iteration and one k-step are 1 KB in a row, 16 bytes per lane
-  const uint16_t* PBh = PB + (size_t)bh * gate_operand_vectors(n_other) * D + 8 * lane;
+  // pooled vectors of the other side, fp16, in the layout of gate_operand_offset: eight channels
+  // of the 32 vectors of one iteration are 512 bytes in a row, 16 bytes per lane
+  const uint16_t* PBh = PB + (size_t)bh * gate_operand_vectors(n_other) * D + 256 * q + 8 * l16;
 
-  // The B operand of one iteration is 32 pooled vectors: lane (l32, hf) supplies channels
-  // 16s + 8hf .. +7 of vector o0 + l32 for k-step s. It is fetched a whole iteration ahead
-  // (two register sets that swap roles); to make room the block's row tiles are taken two at
-  // a time, so only 32 accumulator registers are live. Vectors past the end of the last group
+  // The B operand of one iteration is 32 pooled vectors, two column tiles of 16: lane (l16, q) supplies
+  // channels 32s + 8q .. +7 of vectors o0 + l16 and o0 + 16 + l16 for k-step s. Its registers are
+  // reloaded for the next iteration as soon as their last product is issued. The block's row tiles are taken
+  // four at a time (a pass), so only 32 accumulator registers are live. Vectors past the end of the last group
   // are padding: they only feed output columns that are never stored.
-  constexpr int TP = MT < 2 ? MT : 2;
-  auto load_vectors = [&](u32x4 (&dstv)[KS], int o0) __attribute__((always_inline)) {
-    const uint16_t* p = PBh + (size_t)(o0 / 32) * KS * 512;
+  constexpr int TP = 4;
+  u32x4 bv[KS][2];
+  auto load_vectors = [&](int s, int o0) __attribute__((always_inline)) {
+    const uint16_t* p = PBh + (size_t)(o0 / 32) * KS * 1024 + 1024 * s;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) dstv[s] = *reinterpret_cast<const u32x4*>(p + 512 * s);
+    for (int c = 0; c < 2; ++c) bv[s][c] = *reinterpret_cast<const u32x4*>(p + 128 * c);
   };
-  auto iteration = [&](const u32x4 (&bv)[KS], u32x4 (&bnext)[KS], int o0) __attribute__((always_inline)) {
-    if (o0 + 32 * NW < n_other) load_vectors(bnext, o0 + 32 * NW);
+  // The A operand (rows) is read from LDS half a k-step ahead: two of the four row tiles of a pass.
+  u32x4 av[2][2];
+  auto load_a = [&](int set, int half_step) __attribute__((always_inline)) {   // half_step: (pass * KS + k-step) * 2 + half
+    const int s = half_step / 2 % KS, tile = half_step / 2 / KS * TP + half_step % 2 * 2;
+    const u32x4* p = arow + ((4 * s + q) ^ akey) + tile * (16 * CPR);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) av[set][t] = p[t * 16 * CPR];
+  };
+  auto iteration = [&](int o0, auto morec) __attribute__((always_inline)) {
+    constexpr bool more = decltype(morec)::value != 0;
+    const int j = o0 + lane % 32;       // the column that this lane decides or stores
     float s_val = 0.f, db_val = 0.f;
     if constexpr (GATE) {
-      const int m = o0 + l32 < n_other ? o0 + l32 : n_other - 1;
+      const int m = j < n_other ? j : n_other - 1;
       s_val = Spool[((size_t)bh * n_blocks_x + xb) * n_other + m];
       db_val = DBt[((size_t)bh * n_other + m) * n_blocks_x + xb];
     }
-    asm volatile("" ::: "memory");      // the A operand is re-read every iteration: no hoisting into registers
-    // every accumulator of a lane belongs to column o0 + l32; its rows are spread over the
-    // registers, the row tiles and the two half-waves
-    float dv4[4] = {0.f, 0.f, 0.f, 0.f};       // four partial sums: no long chain of dependent adds
+    // every accumulator of a lane belongs to column l16 of its tile; the rows are spread over the
+    // registers, the row tiles and the four quarters of the wave
+    float dv[2][2] = {{0.f, 0.f}, {0.f, 0.f}};     // two partial sums per column tile: no long chain of dependent adds
 #pragma unroll
     for (int t0 = 0; t0 < MT; t0 += TP) {
-      floatx16 acc[TP];
-#pragma unroll
-      for (int t = 0; t < TP; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+      floatx4 acc[TP][2];
 #pragma unroll
       for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int t = 0; t < TP; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(RSA_DEV_A(t0 + t, s), __builtin_bit_cast(halfx8, bv[s]), acc[t], 0, 0, 0);
+        for (int half = 0; half < 2; ++half) {
+          const int hs = (t0 / TP * KS + s) * 2 + half;
+          asm volatile("" ::: "memory");      // the A operand is re-read every iteration: no hoisting into registers
+          load_a((hs + 1) % 2, (hs + 1) % (MT / TP * KS * 2));
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              floatx4 c0 = acc[2 * half + t][c];
+              if (s == 0) c0 = floatx4{0.f, 0.f, 0.f, 0.f};
+              acc[2 * half + t][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, av[hs % 2][t]),
+                                                                            __builtin_bit_cast(halfx8, bv[s][c]), c0, 0, 0, 0);
+            }
+          if constexpr (more) {
+            if (t0 + TP == MT && half == 1) load_vectors(s, o0 + 32 * NW);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
       for (int t = 0; t < TP; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) dv4[r % 4] += fabsf(acc[t][r]);
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dv[c][r % 2] += fabsf(acc[t][c][r]);
     }
-    float dv = (dv4[0] + dv4[1]) + (dv4[2] + dv4[3]);
-    dv += __shfl_xor(dv, 32);
+    // odd quarters finish the second column tile, even ones the first: lane l holds column l % 32
+    const float d0 = dv[0][0] + dv[0][1], d1 = dv[1][0] + dv[1][1];
+    float d = (q & 1 ? d1 : d0) + __shfl_xor(q & 1 ? d0 : d1, 16);
+    d += __shfl_xor(d, 32);
     if constexpr (GATE) {
-      const bool pred = o0 + l32 < n_other && fabsf(s_val) > dv * outscale + db_val;
+      const bool pred = j < n_other && fabsf(s_val) > d * outscale + db_val;
       const unsigned long long word = __ballot(pred);
       if (lane == 0) Mc_bits[((size_t)bh * n_blocks_x + xb) * dm.w + o0 / 32] = (uint32_t)word;
     } else {
-      if (hf == 0 && o0 + l32 < n_other) orow[o0 + l32] = dv * outscale;
+      if (lane < 32 && j < n_other) orow[j] = d * outscale;
     }
   };
-  u32x4 b0[KS], b1[KS];
-  if (32 * wave < n_other) load_vectors(b0, 32 * wave);
-  for (int o0 = 32 * wave; o0 < n_other; o0 += 64 * NW) {
-    iteration(b0, b1, o0);
-    if (o0 + 32 * NW < n_other) iteration(b1, b0, o0 + 32 * NW);
+  int o0 = 32 * wave;
+  if (o0 < n_other) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) load_vectors(s, o0);
+    load_a(0, 0);
+    for (; o0 + 32 * NW < n_other; o0 += 32 * NW) iteration(o0, std::integral_constant<int, 1>{});
+    iteration(o0, std::integral_constant<int, 0>{});
   }
 }
 
