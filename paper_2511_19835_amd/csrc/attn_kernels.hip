@@ -135,15 +135,16 @@ __device__ __forceinline__ float column_sum(float v) {
 // Matrix products as inline asm, because only there the accumulator can be held to its place: the compiler gives this
 // instruction a destination of its own, and the accumulators then wander through the registers and into scratch. Its hazards
 // are ours in return: an accumulator is used by the next product at the earliest four products on (the matrix pipe needs 16
-// cycles for each), and before any other use stands settle_products. Operands come from LDS reads (waited for) and from the
-// phase before (a barrier away).
+// cycles, four wait states, for each), and before any other use stands settle_products. Operands come from LDS reads (waited
+// for) and from the phase before (a barrier away). tests/test_product_waits.py holds the compiler's output to all three.
 __device__ __forceinline__ void mfma_add(floatx4& c, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 __device__ __forceinline__ void mfma_first(floatx4& c, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
-// The products into c[][] are complete (an XDL result of 4 passes may be read by the vector ALU some ten wait states on).
+// The products into c[][] are complete (a result of four passes may be touched by another instruction eight wait states on:
+// NOPS, and four for each product that followed).
 template <int NOPS, int N>
 __device__ __forceinline__ void settle_products(floatx4 (&c)[N][2]) {
   asm volatile("s_nop %0" ::"n"(NOPS - 1) : "memory");
@@ -951,14 +952,17 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     };
     {
       const int kv_count = kvc_cur;
-      // (the first scores taken are those of tiles 0 and 1, whose last products four others followed where there are more tiles)
+      // (the first scores taken are those of tiles 0 and 1, whose last products four others followed where there are more tiles;
+      // those of the other tiles are taken far enough down the line)
       settle_products<(C::KT > 2 ? 1 : 8)>(sacc);
       // accumulator register r of key tile t is key part*KVS + 32(t/2) + 8(t%2) + r + key_row(4*g4) of the block
       // (rare, like the branch below: out of line, the path that every step takes has no jump over it)
       if (__builtin_expect(kv_count < BLK, 0)) {
         // (constants against one lane-dependent bound: compared the other way round, the key numbers are 32 registers that
         // the compiler keeps through the whole loop)
-        const int valid = kv_count - (ST % C::SPB) * KVS - key_row(4 * g4);
+        int valid = kv_count - (ST % C::SPB) * KVS - key_row(4 * g4);
+        // (here the compiler takes the tiles in any order: the last products are waited for ahead of the first comparison)
+        asm volatile("s_nop 7" : "+v"(valid));
 #pragma unroll
         for (int t = 0; t < C::KT; ++t)
 #pragma unroll
