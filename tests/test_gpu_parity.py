@@ -300,6 +300,45 @@ def test_reference_moves_at_any_step(gpu, d, block, rise):
             np.testing.assert_allclose(lse[0, h].numpy(), np.log(np.exp(S - top[:, None]).sum(axis=1)) + top, rtol=2e-5, atol=2e-3)
 
 
+@pytest.mark.parametrize("rise", ["below", "1", "2", "last", "every"])
+@pytest.mark.parametrize("half", [0, 1])
+@pytest.mark.parametrize("d,block", [(128, 64), (128, 128), (64, 64), (64, 128)])
+def test_reference_moves_for_one_half_of_the_rows(gpu, d, block, half, rise):
+    """A lane holds two query rows, 16 apart, each with a reference and a sum of its own. Here only one of them leaves the
+    window: scores 200 binades below zero at every key, 50 above from one step on, or 50 more at every one of the first
+    six. Without a new reference the first and the last of these leave the range of fp32; a factor that belongs to the other
+    row shows in all of them. The other rows never see the channel that does this."""
+    import parity
+    from oracle import rsa_oracle as ro
+    cfg = LayerConfig("rise_half", 1, 2, d, (1, 1, 6 * block - 3), block - 5, block, 0.0)
+    Qb, Kb, Vb = (x.copy() for x in synth.make_inputs(cfg, 48))
+    step = np.arange(cfg.t_total) // (block // 2)
+    if rise == "below":
+        binades = np.full(cfg.t_total, -200.0)
+    elif rise == "every":
+        binades = 50.0 * np.minimum(step, 6)
+    else:
+        binades = 50.0 * (step >= (int(step[-1]) if rise == "last" else int(rise)))
+    levels = (binades * np.sqrt(d) / np.log2(np.e) / 8.0).astype(np.float32)
+    token = np.arange(cfg.t_total)
+    row = np.where(token < cfg.t_video, token, token - cfg.t_video) % 32
+    Qb[..., 0] = np.where(row // 16 == half, 0x4100, 0).astype(np.uint16)         # 8.0 and 0
+    Kb[..., 0] = (levels.view(np.uint32) >> 16).astype(np.uint16)
+    Q, K, V = (gpu.bits_to_device(x) for x in (Qb, Kb, Vb))
+    for workspace, lists in ((False, True), (True, True), (True, False)):
+        O, lse = _attend_to_all(gpu, cfg, Q, K, V, workspace, lists)
+        for h in range(cfg.heads):
+            q, k, v = (ro.bf16_bits_to_f64(x[0, h]) for x in (Qb, Kb, Vb))
+            want = ro.dense_attention(q, k, v, 1 / np.sqrt(d))
+            for part in (row // 16 == half, row // 16 != half):
+                err = (O[0, h].numpy() - want)[part]
+                assert np.abs(err).max() <= parity.OUT_MAX_ABS
+                assert np.linalg.norm(err) / np.linalg.norm(want[part]) <= parity.OUT_REL_L2
+            S = q @ k.T / np.sqrt(d)
+            top = S.max(axis=1)
+            np.testing.assert_allclose(lse[0, h].numpy(), np.log(np.exp(S - top[:, None]).sum(axis=1)) + top, rtol=2e-5, atol=2e-3)
+
+
 def test_attention_without_a_workspace(gpu):
     """ws = NULL is legal without RSA_COMPENSATE: the rows are then launched in index order."""
     _run_and_compare(gpu, EDGE["d128_b64_text"], seed=15, flags=1, attn_workspace=False)
