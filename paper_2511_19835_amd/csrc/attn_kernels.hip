@@ -744,9 +744,12 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // step opens a new key block (its list entry came in during V(s-1)) follows from the parity of s. A group whose last step this
     // is requests the tile of its last list entry once more, into a stage nobody reads again.
     constexpr int REQ = OPEN + kStepPieces, TASKS = do_qk ? REQ + MLOADS : 0;
-    constexpr int TPS = (TASKS + LAST - 1) / LAST;    // tasks per slot
-    // (requests of the four waves meet in the CU's one address unit, 16 cycles for each: with room for it, one in two or three slots)
-    constexpr int GAP = TPS > 1 || !do_qk ? 1 : (LAST - REQ) / MLOADS > 3 ? 3 : (LAST - REQ) / MLOADS;
+    // Requests of the four waves meet in the CU's one address unit, 16 cycles for each: with room for it, one in two or three
+    // slots behind the addresses. Where slots are fewer than that (blocks of 64, d = 64), all tasks spread evenly over the phase:
+    // two to a slot from its start leave its end bare (us, attention, packed and spread: d = 128, blocks of 64, 24 heads of 1182
+    // blocks 6826 and 6687, all of 317 4437 and 4259, 4 of 128, lists of 13, 41.0 and 40.5; d = 64, blocks of 64, all of 64 81.2 and 79.3).
+    constexpr bool FEW = !do_qk || TASKS > LAST || (LAST - REQ) / MLOADS < 2;
+    constexpr int GAP = FEW ? 1 : (LAST - REQ) / MLOADS > 3 ? 3 : (LAST - REQ) / MLOADS;
     constexpr int WB = W / 2;                         // operands are waited for WB at a time
     Tile nt = {};
     // The wave that feeds the matrix pipe goes first wherever the two waves of a SIMD compete for an
@@ -793,8 +796,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
       product(IntC<i % 2>{});
       if constexpr (TASKS > 0) {
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (GAP < 2) {
-          static_for<TPS * i, TPS * (i + 1)>(task);
+        if constexpr (FEW) {
+          static_for<TASKS * i / LAST, TASKS * (i + 1) / LAST>(task);
         } else if constexpr (i < REQ) {
           task(ic);
         } else {
