@@ -23,9 +23,12 @@
 // the same two phases without loads of tiles, 16 x 16 x 32 sustains 1600 TFLOP/s and 32 x 32 x 16 1470 (2308 and 2206
 // cycles a step at 1.72 and 1.50 GHz; products alone from registers 2050 and 1785). The price is the vector ALU's: beside
 // products of 16 x 16 it issues two instructions in 16 cycles, so that the softmax phase is now the longer of the two,
-// and requests are all made in the MFMA phase. Against the larger instruction, us: 24 heads of 931 blocks, lists of 94, layer
-// 16 970 and 15 830; 40 of 591 11 040 and 10 650; 24 of 159, lists of 16, 633 and 607, all blocks 4040 and 3720; d = 64, 24 of 160
-// 794 and 758; blocks of 64, 24 of 1182 equal, all of 380 blocks 6300 and 6090.
+// and requests are all made in the MFMA phase. Against the larger instruction, us, the attention entry point, both forms in turn
+// (two figures: two boxes): 24 heads of 931 blocks, lists of 94, 14 790, 14 710 and 14 360, 14 080; 3 heads 1904 and 1783; 40 of 591
+// 9865 and 9469; 24 of 159, lists of 16, 479 and 452, all blocks 4099 and 3747; d = 64, 2 x 12 of 160, lists of 40, 715 and 675;
+// blocks of 64, 24 of 1182 7065 and 6878, all of 380 6282 and 5861. Where power is not the bound the larger one is the
+// faster: half a round of blocks of 64 (1 head of 512, lists of 52) 102.7 and 106.9; where the fabric is (24 of 931, full mask
+// rule) a loop of launches takes 21 060, 20 700, 20 870 and 21 450, 21 200, 20 900, four launches on their own 21 600 and 20 900.
 //
 // A step of a group is two phases, separated by workgroup barriers: an MFMA phase (the P V
 // product of the previous step, then K Q^T of this one: matrix instructions, their LDS operand
@@ -53,11 +56,8 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-#ifndef RSA_NSTAGE
-#define RSA_NSTAGE 2
-#endif
-constexpr int KSTAGES = RSA_NSTAGE;  // LDS ring depth of the K tiles of a group
-constexpr int VSTAGES = 3;           // ... of its V^T tiles, which are read one phase later than the K tile of the same step
+constexpr int KSTAGES = 2;          // LDS ring depth of the K tiles of a group (the loop is unrolled over it)
+constexpr int VSTAGES = 3;          // ... of its V^T tiles, which are read one phase later than the K tile of the same step
 #ifndef RSA_MWIN
 #define RSA_MWIN 4
 #endif
@@ -91,7 +91,7 @@ struct AttnCfg {
   static constexpr int GROUP = KSTAGES * KBUF + VSTAGES * VBUF;   // 16-byte chunks of one group: [K stages | V^T stages]
   static_assert(!VH || SPB * PDT == DT, "a half of the channels for each step of a block");
   static_assert(KINST % NW == 0 && VINST % NW == 0, "loads must split evenly over the waves");
-  static_assert(KSTAGES == 2 && NGRP * GROUP * 16 <= 160 * 1024, "the rings of all groups must fit the LDS of a CU");
+  static_assert(NGRP * GROUP * 16 <= 160 * 1024, "the rings of all groups must fit the LDS of a CU");
   static_assert(SPB == 2, "the main loop is unrolled twice: over the K stages and over the steps of a key block");
   static_assert(NGRP % 2 == 0 && BLK % KVS == 0, "groups pair up on the SIMDs; a block is a whole number of steps");
 };
@@ -197,14 +197,14 @@ struct SchedArgs {
 };
 
 // HALVES (blocks of 64): a V^T row of a key block is 128 bytes, one line, and the 32 keys of a step are half of it. Taken
-// step by step every line is asked for twice, and a step in the sparse layers waits 430 cycles for its tiles (24 heads of
+// step by step every line is asked for twice, and a step in the sparse layers waited 430 cycles for its tiles (24 heads of
 // 1182 blocks at d = 128: 1.23e9 requests of the L2, 55 GB through the fabric at 6 TB/s). So the two P V products of a
 // block take all its 64 keys and half of the channels each, one step later: M(s) multiplies the probabilities of the
 // block before with the half s % 2 of its V^T rows, whole lines. Probabilities of the block's first step are kept aside (pbn)
 // while the second product of the block before still needs pb, and an item's output is complete, and written, in the second
-// step of the next. Attention of that layer 9320 -> 7090 us, 24 heads of 318 blocks 609 -> 577. Not for RSA_DENSE, where
-// the groups of a CU walk in step and the L1 serves the second half (318 blocks: 4640 -> 4717), nor at d = 64, where the
-// softmax hides the requests and the moves do not (24 heads of 1182: 4712 -> 4840). The bits of the output are those of the
+// step of the next. Attention of that layer 8150 -> 6780 us, 24 heads of 317 blocks 559 -> 538. Not for RSA_DENSE, where
+// the groups of a CU walk in step and the L1 serves the second half (317 blocks: 4313 -> 4457), nor at d = 64, where the
+// softmax hides the requests and the moves do not (24 heads of 1182: 4297 -> 4458). The bits of the output are those of the
 // step-by-step form as long as the softmax reference stays at 0; where it moves, it is rounded up to a whole number here,
 // so that probabilities that wait can follow it in their exponents (below 2^-126 they become 0).
 template <int D, int BLK, bool HALVES>
@@ -446,8 +446,9 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
 
   // Q as the B operand of S^T = K Q^T, resident in registers; the next item's rows come into registers of their own, a
   // step ahead: they come from HBM, and asked for behind the last K Q^T, with nothing but a softmax before their use, they kept
-  // both groups waiting for some 5000 cycles of every item (24 heads of 931 blocks, lists of 94: 14642 us and 14532; 591 blocks,
-  // lists of 60: 9828 and 9755; shorter lists 0.2 %; where the power limit or the fabric bounds the kernel, equal). Rows past
+  // both groups waiting for some 5000 cycles of every item (with products of 32 x 32 x 16: 24 heads of 931 blocks, lists of 94, 14642 us
+  // and 14532; 591 blocks, lists of 60: 9828 and 9755; shorter lists 0.2 %; where the power limit or the fabric bounds the kernel,
+  // equal). Rows past
   // the end of a ragged block repeat its last row: the number of loads in flight is the same for every wave, and the waits
   // below count on it.
   bf16x8 qreg[C::KS][2], qnext[C::KS][2];      // (k-step, query tile)
@@ -478,8 +479,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // running state starts over for the next item. R_n and C_n are requested with the next
   // query rows: lane j holds elements CV*j .. CV*j+CV-1 of C_n, and every
   // lane reads the 64 it needs from LDS, 16 bytes at a time and all of a half of the channels before the first is used (one
-  // word at a time through the crossbar, eight before a wait: 506.6 us and 501.8 with it as it is, 24 heads of 159 blocks,
-  // lists of 16; 15366 and 15247 with 931 and 94) -- no memory latency is left in here.
+  // word at a time through the crossbar, eight before a wait: with products of 32 x 32 x 16 506.6 us and 501.8 with it as it is,
+  // 24 heads of 159 blocks, lists of 16; 15366 and 15247 with 931 and 94) -- no memory latency is left in here.
   constexpr int CV = D / 64;
   float done_comp[CV], next_comp[CV];            // of the item whose output is to be written; of the current one
 #pragma unroll
@@ -551,8 +552,8 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // half of the channels at a time is turned through LDS: the V^T stage whose tile was read in the MFMA phase just ended is
   // free here (its next tile is requested in the one to come), and a wave uses only the 1 KB pieces that its own requests
   // fill, so no other wave can get in the way. 16-byte chunk c of row r lies at chunk c ^ row_key(r).
-  // (24 heads of 159 blocks, lists of 16: layer 684 -> 680 us; 2 x 12 heads of 160, d = 64: 860 -> 848; 24 heads of
-  // 1182 blocks of 64: 11164 -> 11090; the longer the lists the less: 24 heads of 931, lists of 94: 17295 -> 17277.)
+  // (With products of 32 x 32 x 16: 24 heads of 159 blocks, lists of 16, layer 684 -> 680 us; 2 x 12 heads of 160, d = 64, 860 -> 848;
+  // 24 heads of 1182 blocks of 64 11164 -> 11090; the longer the lists the less: 24 heads of 931, lists of 94, 17295 -> 17277.)
   constexpr int ROWB = D;                          // bytes of half a row
   constexpr int RCH = ROWB / 16, RPC = 1024 / ROWB;   // chunks of half a row, rows per piece
   static_assert(VOFF == 1 && C::VPW * 1024 == 32 * ROWB, "a wave's own pieces of a V^T stage hold half of its 32 rows");
@@ -689,7 +690,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
   // of step s. A slot takes one A operand (16 bytes per lane of the V^T or K tile) with the B operands of both query
   // tiles, which change places from slot to slot, so that every instruction shares an operand with the one before it. The A
   // operand is read from LDS W slots ahead of its MFMAs into a ring of W registers, so that LDS latency stays behind MFMAs
-  // that already have their operands; the first W operands of a phase are read at the end of the
+  // that already have their operands; the first W operands of a phase are read at the start of the
   // softmax phase before it. The order is pinned slot by slot.
   constexpr int NPV = C::PPC * C::PDT, NQK = C::KS * C::KT, NSLOT = NPV + NQK;
   constexpr int W = MWIN;
@@ -705,7 +706,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     const int pc = slot / C::PDT, dt = slot % C::PDT;
     ring[slot % W] = __builtin_bit_cast(bf16x8, vcur[pc][dt * 16 * C::VCPR]);
   };
-  // the operands of the first W slots, at the end of a softmax phase
+  // the operands of the first W slots of the next MFMA phase
   auto read_ahead = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < W; ++j) read_v_operand(j);

@@ -24,8 +24,8 @@ __host__ __device__ __forceinline__ int make_span(int first, int len, bool parti
 __host__ __device__ __forceinline__ int span_first(int span) { return span & 4095; }
 __host__ __device__ __forceinline__ int span_len(int span) { return ((span >> 12) & 4095) + 1; }
 
-// Floats of a piece buffer: the accumulators of BLK rows as the waves hold them ([wave][16-register
-// quarter][lane][4]), then the row sums, then the softmax references (binades).
+// Floats of a piece buffer: the accumulators of BLK rows ([wave of 32 rows][eight channels][half of them][row][channel], the order
+// in which merge_kernel reads them), then the row sums, then the softmax references (binades).
 __host__ __device__ __forceinline__ size_t piece_floats(int d, int blk) { return (size_t)blk * d + 2 * (size_t)blk; }
 
 constexpr int kQueues = 8;                     // one queue of items per XCD
@@ -34,7 +34,8 @@ constexpr int kMaxCross = kQueues - 1;         // dense rows cut over all queues
 constexpr int kMaxTurns = 64;                  // sets of heads that are worked on one after the other
 constexpr int kTailDense = 128;                // dense rows of a queue that may be cut (more: dealt whole, ahead of the others)
 // Rows are cut only where an uneven last round would cost something: below this many rounds of items. (At 24 rounds
-// it still takes 1.4 % off the layer; at 44 the most it could take off is 1.1 % of the attention, for 70 MB of buffers.)
+// it took 1.4 % off the layer, with products of 32 x 32 x 16; at 44 the most it could take off is 1.1 % of the attention, for
+// 70 MB of buffers.)
 constexpr int kSplitRounds = 32;
 
 // Whether the `left` equally long rows of `len` key blocks that a last round has for the slots of a queue are cut when the
@@ -43,10 +44,12 @@ constexpr int kSplitRounds = 32;
 // and go through fp32 buffers. That costs the time of 9 key blocks of 128, of 15 of 64, 20 at d = 128, where a group asks the
 // L2 for the most bytes per product; twice to four times that once more than half of the slots have a row, and too much above
 // five eighths (at d = 128 with blocks of 64 above a third).
-// Measured from 0.05 to 0.9 of the slots, none to twenty rounds before, 1 to 40 heads, lists of a tenth, a fifth and half
-// of the blocks, smooth and random inputs (5600 pairs; us, whole and cut, the merging launch included). d = 128, blocks of
-// 128: 12 rows of 17 key blocks for 64 slots 57 and 48; 13 of 39 (after a full round) 252 and 211; 20 of 14 (after one) 106
-// and 112; 57 of 77 275 and 331. Blocks of 64: 26 rows of 104 for 128 slots 156 and 85; 40 of 20 47 and 54; 78 of 105 175 and 304.
+// The lines were drawn with products of 32 x 32 x 16, from 0.05 to 0.9 of the slots, none to twenty rounds before, 1 to 40 heads,
+// lists of a tenth, a fifth and half of the blocks, smooth and random inputs (5600 pairs). With the present ones, lists of half
+// the blocks, us, whole and cut, the merging launch included: d = 128, blocks of 128: 12 rows of 17 key blocks for 64 slots 55.7
+// and 45.0; 13 of 39 (after a full round) 233 and 188; 20 of 14 (after one) 101.2 and 99.6; 57 of 77 242 and 268. Blocks of 64: 26 rows
+// of 104 for 128 slots 172 and 80; 40 of 20 47.8 and 46.2 (left whole); 78 of 105 176 and 192. d = 64: 12 of 17 44.9 and 36.9, blocks
+// of 64, 40 of 20 36.8 and 39.0.
 struct CutRule {
   int most_left;            // thirty-seconds of the slots
   int least_saved;          // quarters of a key block, up to that many rows
@@ -86,11 +89,11 @@ struct DealArgs {
 // of the same head find each other's tiles in the XCD's L2. Limited by the Infinity Cache (256 MB): the tiles that miss the L2
 // should come from there, and the K rows and V^T tiles of all heads at work have to share it. At d = 128 with blocks of 64,
 // which ask for the most bytes per product, a little over that still pays.
-// Measured, attention in us, one head and as chosen: blocks of 128, 24 heads of 159 blocks 493 and 481, with the full mask
-// rule 1376 and 1260; 40 of 591 (39 MB a head) 9879 and 9737 (eight heads: 9 to 30 more); 24 of 931 (61 MB) 14 930 and 14 910
-// (four: 100 more), full rule 20 750 and 20 190 (one box of three: equal). Blocks of 64: 24 of 318 572 and 559, full rule 1706
-// and 1180; 24 of 1182 (39 MB) at sparsity 0.7 21 400 and 19 980; 24 of 1860 (61 MB) 21 640 and 19 010 (two: 21 250). d = 64,
-// bound by its softmax: 24 of 160 728 and 725, 24 of 591 3864 and 3814, blocks of 64, 24 of 318 369 and 365.
+// Measured, attention in us at sparsity 0.9, one head and as chosen: blocks of 128, 24 heads of 159 blocks 467 and 454, with the
+// full mask rule 1454 and 1232; 40 of 591 (39 MB a head) 9549 and 9472 (eight heads: 9599); 24 of 931 (61 MB) 14 460 and 14 400
+// (four: 14 560), full rule 21 640 and 21 410. Blocks of 64: 24 of 317 557 and 543, full rule 1795
+// and 1292; 24 of 1182 (39 MB) at sparsity 0.7 20 610 and 19 350; 24 of 1857 (61 MB) 17 970 and 16 930 (two: 17 070). d = 64,
+// bound by its softmax: 24 of 159 302 and 297, 24 of 591 3619 and 3569, blocks of 64, 24 of 317 356 and 346.
 inline int heads_at_once(const Dims& dm) {
   const int bh = dm.batch * dm.heads, least = (bh + kMaxTurns - 1) / kMaxTurns;
   const long long head_bytes = 4LL * dm.t * dm.d, most = (dm.d == 128 && dm.blk == 64 ? 250LL : 200LL) * 1000000;
@@ -111,7 +114,7 @@ inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   s.heads_at_once = heads_at_once(dm);
   // A queue of a sixteenth over the average ends that much later, and still gains where tiles bound the kernel (full mask rule,
   // heads of 5 % more or less key blocks, 24 of 366 blocks: 4386 us by eighths, 4020 by whole heads, 4250 by load); at d = 64 the
-  // softmax does (24 of 591: 6200, 6560 and 6190).
+  // softmax does (24 of 591: 6200, 6560 and 6190; all with products of 32 x 32 x 16).
   s.most_share = dm.d == 64 ? 65 : 68;
   s.slots = (n_wg / 8) * ngrp;
   s.rows_per_bh = dense_all ? dm.m : dm.n;
@@ -120,8 +123,10 @@ inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   s.n_dense = bh * s.dense_per_bh;
   s.n_items = s.n_dense + bh * s.rows_per_bh;
   // An item costs its key blocks and the switch from one query block to the next: about 15 000 cycles where
-  // a block of 128 keys takes 6 000 (two steps of both groups) and one of 64 keys 2 600. A piece also writes and
-  // reads its accumulators in fp32; below a few blocks it is not worth either.
+  // a block of 128 keys took 6 000 (two steps of both groups) and one of 64 keys 2 600, stamped with products of 32 x 32 x 16 and
+  // before the query rows were requested a step ahead. (By the times of lists of 47 to 591 blocks, 24 heads of 931 and of 1182, it
+  // is now 1 to 2 blocks of 128 and 6 of 64.) A piece also writes and reads its accumulators in fp32; below a few blocks it is
+  // not worth either.
   s.switch_cost = dm.blk == 128 ? 3 : 6;
   s.min_piece = 4;
   const long long longest = (long long)bh * ((s.rows_per_bh + kQueues - 1) / kQueues) + (s.n_dense + kQueues - 1) / kQueues;
@@ -133,12 +138,13 @@ inline SchedShape sched_shape(const Dims& dm, int flags, int n_wg, int ngrp) {
   // round puts them out of step, and their groups on CUs that others use: worth it while few slots would have a row of
   // that round -- fewest at d = 128 with blocks of 64, where a group asks the L2 for the most bytes per product -- and,
   // where it is the only round, while the pieces are long (a slot's share of the key blocks) or very few slots have one.
-  // Measured over last rounds of 1/16 to 9/10 of the slots, none to two rounds before, 1 to 24 heads (us, whole and cut):
-  // d = 128, blocks of 128: 3 heads of 85 blocks, 31 rows for 64 slots 213 and 190; of 106, 39 rows 279 and 317; 8 of 28,
-  // 28 rows 82 and 91; 24 of 159, 477 rows 4152 and 4070; 24 of 33, 99 rows 214 and 238. Blocks of 64: 3 of 128, 48 rows for
-  // 128 slots 181 and 138; of 149, 55 rows 207 and 237; 8 of 160, 160 rows 516 and 423; 24 of 56, 168 rows 197 and 216.
-  // d = 64, blocks of 128: 2 of 128, 32 rows 237 and 167; 24 of 33, 99 rows 143 and 148; 24 of 8, 24 rows 28 and 35; blocks of
-  // 64: 8 of 64, 64 rows 83 and 72; 24 of 66, 198 rows 165 and 185.
+  // The lines were drawn with products of 32 x 32 x 16, over last rounds of 1/16 to 9/10 of the slots, none to two rounds before, 1 to
+  // 24 heads; with the present ones cutting pays further than they go ("left": whole by the rule, though slower). Us, whole and cut:
+  // d = 128, blocks of 128: 3 heads of 85 blocks, 31 rows for 64 slots 205 and 169 (left); of 106, 39 rows 255 and 249 (left); 8 of
+  // 28, 28 rows 76.4 and 77.3; 24 of 159, 477 rows 3853 and 3723; 24 of 33, 99 rows 193 and 203. Blocks of 64: 3 of 128, 48 rows for
+  // 128 slots 184 and 116; of 149, 55 rows 214 and 183 (left); 8 of 160, 160 rows 494 and 379; 24 of 56, 168 rows 186 and 168 (left).
+  // d = 64, blocks of 128: 2 of 128, 32 rows 237 and 150; 24 of 33, 99 rows 136 and 133 (left); 24 of 8, 24 rows 26 and 33; blocks of
+  // 64: 8 of 64, 64 rows 79 and 65; 24 of 66, 198 rows 157 and 148 (left).
   bool whole = false;
   if (dense_all) {
     const int rows = s.n_items / kQueues, last = rows % s.slots;

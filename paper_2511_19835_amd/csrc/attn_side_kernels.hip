@@ -705,8 +705,8 @@ __global__ __launch_bounds__(256) void compensation_schedule_kernel(Dims dm, Att
 // Latency is all there is to it (a few dozen megabytes at most, out of the L2 or the Infinity Cache): one
 // workgroup per piece buffer and 32 channels, of which those with the first piece of a row do its work (the
 // pieces of a row are consecutive) and one per cross row and 32 channels (a run of pieces in every queue); four
-// pieces are on their way at a time. A wave holds 32 query rows in the layout of the attention kernel's
-// accumulators, so that pieces are read as they were written, 1 KB per instruction.
+// pieces are on their way at a time. A wave holds 32 query rows in the layout of 32 x 32 accumulators, a row and four
+// channels to a lane, which is the order that the attention kernel writes its pieces in: read 1 KB per instruction.
 template <int D, int BLK>
 __global__ __launch_bounds__(64 * (BLK / 32)) void merge_kernel(Dims dm, AttnArgs a, DealArgs da) {
   constexpr int NT = 64 * (BLK / 32);

@@ -21,10 +21,10 @@
 // deviation_long_kernel instead (below). What bounds it is the latency of its operands beside matrix work at the clock
 // that power leaves: products of 16 x 16 x 32 (less power than 32 x 32 x 16), and one register set for the pooled operand, reloaded
 // as it is used up, so that four waves fit a SIMD (two sets, a whole iteration ahead, three waves: 219 and 225 us where
-// one takes 208 and 211). Against products of 32 x 32 x 16 with two sets, key side and query side, us: 24 heads of 516 blocks 224 -> 208
-// and 229 -> 211, 24 of 159 45 -> 44 and 40 -> 39, d = 64 24.4 -> 24.1 and 20.4 -> 19.5; 24 of 317 blocks of 64 equal (67 -> 66 and 66 ->
-// 70, the runs differ by 3). The pooled operand is rounded to
-// fp16 as well; accumulation is fp32. fp16 rather than bf16 because both operands are O(1)
+// one takes 208 and 211). Against products of 32 x 32 x 16 with two sets, key side and query side, us, medians of three runs of either in
+// turn: 24 heads of 516 blocks 226 -> 216 and 235 -> 219, 24 of 159 46 -> 43 and 40 -> 39, d = 64 23.0 -> 21.5 and
+// 19.7 -> 18.2; blocks of 64, 24 of 317 76 -> 69 and 77 -> 76, 24 of 512 157 -> 141 and 167 -> 165, 1 of 1182 32 -> 28 and
+// 33 -> 31. The pooled operand is rounded to fp16 as well; accumulation is fp32. fp16 rather than bf16 because both operands are O(1)
 // quantities whose 2^-12 relative rounding leaves DA / DB within 2e-4 relative of fp64
 // arithmetic (bf16 operands: up to 1.5e-3, wider than the 1e-3 band in which the gate may
 // differ); the MFMA rate is the same. Conversions saturate at the largest finite half.
