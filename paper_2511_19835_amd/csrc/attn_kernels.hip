@@ -27,7 +27,7 @@
 // (two figures: two boxes): 24 heads of 931 blocks, lists of 94, 14 790, 14 710 and 14 360, 14 080; 3 heads 1904 and 1783; 40 of 591
 // 9865 and 9469; 24 of 159, lists of 16, 479 and 452, all blocks 4099 and 3747; d = 64, 2 x 12 of 160, lists of 40, 715 and 675;
 // blocks of 64, 24 of 1182 7065 and 6878, all of 380 6282 and 5861. Where power is not the bound the larger one is the
-// faster: half a round of blocks of 64 (1 head of 512, lists of 52) 102.7 and 106.9; where the fabric is (24 of 931, full mask
+// faster: half a round of blocks of 64 (1 head of 512, lists of 52) 102.3 and 106.6; where the fabric is (24 of 931, full mask
 // rule) a loop of launches takes 21 060, 20 700, 20 870 and 21 450, 21 200, 20 900, four launches on their own 21 600 and 20 900.
 //
 // A step of a group is two phases, separated by workgroup barriers: an MFMA phase (the P V
@@ -913,7 +913,11 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
     // The scores go through in a line, the two query tiles together: multiplied and taken from the reference, two places on
     // to the exponential, two further on to the sum and the conversion. Beside the other group's products the vector
     // ALU takes two instructions (one exponential) for each of them, and an instruction whose operand has only just been asked
-    // for takes as long as two that wait for nothing (left to the compiler, which chained them: 150 cycles more).
+    // for takes as long as two that wait for nothing (left to the compiler, which chained them: 150 cycles more). With the 16
+    // scores of a lane that a step of a block of 64 has, and the products of d = 128 beside them, the compiler's own order is the
+    // better one (us, attention, in a line and its own: 4 heads of 128 blocks, lists of 13, 40.6 and 40.1; 4 of 19, lists of 8, 29.1
+    // and 28.7; 24 of 1182 6685 and 6664; d = 64, 24 of 317 346.6 and 349.1, all of 64 blocks 79.3 and 80.1).
+    constexpr bool IN_LINE = C::KT > 2 || D == 64;
     auto probabilities = [&]() __attribute__((always_inline)) {
       constexpr int NE = 16 * C::PC, LAG = 2;
       float x[NE], p[NE];
@@ -942,7 +946,7 @@ __global__ __launch_bounds__(512, 1) void attn_kernel(Dims dm, AttnArgs a, Sched
             }
           }
         }
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (IN_LINE) __builtin_amdgcn_sched_barrier(0);
       });
 #pragma unroll
       for (int j = 0; j < C::PC; ++j)
